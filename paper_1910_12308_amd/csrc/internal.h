@@ -105,6 +105,7 @@ hipError_t launch_dequantize(const uint8_t *codes, const float *key, uint64_t d,
 // random streams.  A null array means: node = slot, H steps, the launch's common event.
 struct LocalSlots {
     const uint32_t *nodes = nullptr, *steps = nullptr, *events = nullptr;
+    uint32_t max_steps = 0;         // host: largest entry of `steps` (with steps only)
 };
 
 // Local steps, diagonal quadratics, for `count` slots.

@@ -2,16 +2,16 @@
 // Each step draws `batch` rows uniformly with replacement and uses
 //   g~ = (m / batch) A_B^T (A_B w - b_B),
 // an unbiased estimate of grad f_i (the paper's requirement on g~_i, Section 2).
-// The work per step is two thin matrix-vector products over `batch` rows of A (about one
-// flop per byte), so one workgroup per node streams those rows twice: waves take the
-// row dot products (wave reduction), then every thread updates its own float4 columns.
-// That form is bound by what one compute unit can pull through its cache.  Small swarms take the
-// split form instead (lsq_split_kernel): a node's columns are cut into slices of 512, one workgroup
-// per slice, which keeps its rows of A in registers for both products and its slice of w across all H
-// steps; per step the workgroups of a node exchange only their partial residuals (batch floats each)
-// through device memory, each word tagged with the launch and step it belongs to, so a reader simply
-// waits until the word it needs carries the right tag (no counters, no fences, nothing to reset).  In a batch of Algorithm 1 steps the
-// workgroup then runs the interaction on its slice, which is exactly one gossip tile.
+// The work per step is two thin matrix-vector products over `batch` rows of A (about one flop per byte).
+// Small swarms (at most 256 slices of 512 columns in all, so that the workgroups are resident together) take the
+// split form (lsq_split_kernel): one workgroup per slice, which keeps its rows of A in registers for both products
+// and its slice of w across all H steps; per step the workgroups of a node exchange only their partial residuals
+// (batch floats each) through device memory, each word tagged with the launch and step it belongs to, so a reader
+// simply waits until the word it needs carries the right tag (no counters, no fences, nothing to reset).  In a
+// batch of Algorithm 1 steps the workgroup then runs the interaction on its slice, which is exactly one gossip tile.
+// All other swarms take the wide form (lsq_wide_kernel), whose workgroups exchange their residuals between launches.
+#include <algorithm>
+
 #include "interact_tile.hpp"
 #include "internal.h"
 #include "objectives.h"
@@ -19,63 +19,176 @@
 
 namespace swarm {
 
-constexpr int LB = 1024;
+// ---- wide form -------------------------------------------------------------------------------------
+// Any number of nodes and columns: a node's columns are cut into blocks of 1024 (one float4 per thread), and
+// `slices` workgroups of a node share its blocks.  A residual needs the whole row, so a step ends where all of a
+// node's workgroups have stored their partial residuals, i.e. at the end of a launch: launch k applies the update of
+// step k - 1 to the workgroup's columns and takes the partial residuals of step k on them, H + 1 launches for H
+// steps.  With one slice per node (WHOLE) nothing leaves the workgroup and one launch runs all steps.
+// Bound by memory: the rows of a step are read twice, once for the residuals and, when these are known, once for the
+// update, and are too many to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
+// per thread.  16 nodes x 65544 columns, batch 64, 2 steps: 190 us = 1.07 GB of rows at 5.6 TB/s, against 1.96 ms for
+// one workgroup of 1024 threads per node, which left 240 of 256 compute units idle.  Measured without effect: groups
+// of nodes whose rows fit the last-level cache (more launches cost more than the hits give), non-temporal loads
+// for the second read, the nodes in reverse order in every other launch.
+constexpr int WB = 256;                           // threads per workgroup
+constexpr uint64_t WIDE_BLOCK = 4 * WB;           // columns a workgroup handles at a time
+constexpr uint32_t WIDE_GROUPS = 2048;            // workgroups a launch is cut into where the columns allow it
+constexpr uint32_t WIDE_WHOLE_NODES = 256;        // nodes from which one workgroup each fills the chip
+constexpr uint32_t WIDE_MAX_SLICES = 256;         // every workgroup adds up its node's partial residuals
 
-__global__ __launch_bounds__(LB) void local_lsq_kernel(const float *__restrict__ base, float *__restrict__ W,
-                                                       const float *__restrict__ A, const float *__restrict__ b,
-                                                       const LocalSlots slots, uint64_t d, uint32_t H,
-                                                       float lr, uint32_t m_rows, uint32_t batch, uint64_t seed,
-                                                       uint32_t event) {
-    __shared__ uint32_t rows[LSQ_MAX_BATCH];
+struct LsqWideArgs {
+    const float *base;        // n x d models the steps start from
+    float *W;                 // n x d live copies
+    const float *A, *b;
+    LocalSlots slots;
+    float *part;              // [step parity][slot][slice][LSQ_MAX_BATCH] partial residuals
+    uint64_t d, seed, part_parity;
+    uint32_t H, m_rows, batch, event, slices;
+    float lr;
+};
+
+// The wave's sums of R per-lane values, by halving: a lane gives half of its values to the lane a power of two
+// away and keeps the other half, so that about R exchanges (not 6 R) leave the total of value `lane % R` in the lane.
+template <int N, int R>
+__device__ __forceinline__ void halve(float v[R], uint32_t lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float keep = (lane & N) ? v[i + N] : v[i], give = (lane & N) ? v[i] : v[i + N];
+        v[i] = keep + __shfl_xor(give, N);
+    }
+    if constexpr (N > 1) halve<N / 2, R>(v, lane);
+}
+template <int R>
+__device__ __forceinline__ float wave_totals(float v[R], uint32_t lane) {
+    halve<R / 2, R>(v, lane);
+    float t = v[0];
+#pragma unroll
+    for (int off = R; off < 64; off *= 2) t += __shfl_xor(t, off);
+    return t;
+}
+
+template <int THREADS, bool WHOLE>
+__global__ __launch_bounds__(THREADS, 4) void lsq_wide_kernel(const LsqWideArgs sa, const uint32_t launch) {
+    __shared__ uint32_t rows[2][LSQ_MAX_BATCH];
     __shared__ float resid[LSQ_MAX_BATCH];
-    const uint32_t node = slots.nodes ? slots.nodes[blockIdx.x] : blockIdx.x;
-    if (slots.steps) H = slots.steps[blockIdx.x];
-    if (slots.events) event = slots.events[blockIdx.x];
-    const float *An = A + (uint64_t)node * m_rows * d;
-    const float *bn = b + (uint64_t)node * m_rows;
-    float *wrow = W + (uint64_t)node * d;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const float step = lr * ((float)m_rows / (float)batch);
-    for (uint32_t q = 0; q < H; ++q) {
-        const float *src = q == 0 ? base + (uint64_t)node * d : wrow;
+    __shared__ float sums[THREADS / 64][LSQ_MAX_BATCH];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, slice = blockIdx.x, slot = blockIdx.y;
+    const uint32_t node = sa.slots.nodes ? sa.slots.nodes[slot] : slot;
+    const uint32_t H = sa.slots.steps ? sa.slots.steps[slot] : sa.H, event = sa.slots.events ? sa.slots.events[slot] : sa.event;
+    if (!WHOLE && launch > H) return;
+    constexpr uint64_t BLOCK = 4 * THREADS;
+    constexpr int R = 16;                         // rows of A a thread requests at a time
+    const uint64_t d = sa.d;
+    const float *An = sa.A + (uint64_t)node * sa.m_rows * d, *bn = sa.b + (uint64_t)node * sa.m_rows;
+    const float *base = sa.base + (uint64_t)node * d;
+    float *wrow = sa.W + (uint64_t)node * d;
+    const float step = sa.lr * ((float)sa.m_rows / (float)sa.batch);
+    const uint32_t batch = sa.batch;
+    const uint64_t own = (d + BLOCK * sa.slices - 1 - BLOCK * slice) / (BLOCK * sa.slices);       // blocks of this slice
+
+    auto draw_rows = [&](uint32_t q) {
         if (threadIdx.x < batch) {
-            const Words4 r = stream(seed, TAG_BATCH, q, node, event, threadIdx.x >> 2);
+            const Words4 r = stream(sa.seed, TAG_BATCH, q, node, event, threadIdx.x >> 2);
             const uint32_t word = (threadIdx.x & 3u) == 0 ? r.w0 : (threadIdx.x & 3u) == 1 ? r.w1
                                   : (threadIdx.x & 3u) == 2 ? r.w2 : r.w3;
-            rows[threadIdx.x] = scaled_index(word, m_rows);
+            rows[q & 1u][threadIdx.x] = scaled_index(word, sa.m_rows);
         }
-        __syncthreads();
-        for (uint32_t s = wave; s < batch; s += LB / 64) {
-            const float *arow = An + (uint64_t)rows[s] * d;
-            float acc = 0.f;
-            for (uint64_t k = 4ull * lane; k < d; k += 256) {
-                const f4 av = *(const f4 *)(arow + k), wv = *(const f4 *)(src + k);
-                acc = fmaf(av.x, wv.x, acc); acc = fmaf(av.y, wv.y, acc);
-                acc = fmaf(av.z, wv.z, acc); acc = fmaf(av.w, wv.w, acc);
+    };
+    // this thread's float4 of rows [s0, s0 + R) of step q's batch, issued back to back (a batch is a multiple of 4)
+    auto fetch = [&](uint32_t q, uint32_t s0, uint64_t col, f4 a[R]) {
+#pragma unroll
+        for (int r = 0; r < R; r += 4) {
+            if (s0 + r < batch) {
+#pragma unroll
+                for (int i = r; i < r + 4; ++i) {
+                    const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)rows[q & 1u][s0 + i]);
+                    a[i] = *(const f4 *)(An + (uint64_t)row * d + col);
+                }
+            } else {
+#pragma unroll
+                for (int i = r; i < r + 4; ++i) a[i] = f4{0.f, 0.f, 0.f, 0.f};
             }
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-            if (lane == 0) resid[s] = acc - bn[rows[s]];
+        }
+    };
+    if (WHOLE && threadIdx.x < LSQ_MAX_BATCH) resid[threadIdx.x] = 0.f;      // stays zero past the batch
+    for (uint32_t k = WHOLE ? 0 : launch; k <= (WHOLE ? H : launch); ++k) {       // update of step k - 1, residuals of step k
+        const bool update = k > 0, residuals = k < H;
+        if (!WHOLE && update) draw_rows(k - 1);
+        if (residuals) draw_rows(k);
+        if (!WHOLE && update && lane < batch) {
+            const float *p = sa.part + (uint64_t)((k - 1) & 1u) * sa.part_parity + (uint64_t)slot * sa.slices * LSQ_MAX_BATCH + lane;
+            float t = 0.f;
+            for (uint32_t sl = wave; sl < sa.slices; sl += THREADS / 64) t += p[(uint64_t)sl * LSQ_MAX_BATCH];
+            sums[wave][lane] = t;
         }
         __syncthreads();
-        for (uint64_t k = 4ull * threadIdx.x; k < d; k += 4ull * LB) {
-            f4 g = {0.f, 0.f, 0.f, 0.f};
-            for (uint32_t s = 0; s < batch; ++s) {
-                const f4 av = *(const f4 *)(An + (uint64_t)rows[s] * d + k);
-                const float r = resid[s];
-                g.x = fmaf(av.x, r, g.x); g.y = fmaf(av.y, r, g.y);
-                g.z = fmaf(av.z, r, g.z); g.w = fmaf(av.w, r, g.w);
+        if (!WHOLE && update) {
+            if (threadIdx.x < LSQ_MAX_BATCH) {
+                float t = 0.f;
+                if (threadIdx.x < batch) {
+#pragma unroll
+                    for (int w = 0; w < THREADS / 64; ++w) t += sums[w][threadIdx.x];
+                    t -= bn[rows[(k - 1) & 1u][threadIdx.x]];
+                }
+                resid[threadIdx.x] = t;
             }
-            f4 wv = *(const f4 *)(src + k);
-            wv.x = fmaf(-step, g.x, wv.x); wv.y = fmaf(-step, g.y, wv.y);
-            wv.z = fmaf(-step, g.z, wv.z); wv.w = fmaf(-step, g.w, wv.w);
-            *(f4 *)(wrow + k) = wv;
+            __syncthreads();
         }
-        __threadfence_block();
+        const float *src = k <= 1 ? base : wrow;
+        if (update) {
+            for (uint64_t i = own; i-- > 0;) {    // backwards: the blocks read last are the ones still in cache
+                const uint64_t col = (slice + i * sa.slices) * BLOCK + 4ull * threadIdx.x;
+                if (col < d) {
+                    f4 w = *(const f4 *)(src + col), g = {0.f, 0.f, 0.f, 0.f};
+                    for (uint32_t s0 = 0; s0 < batch; s0 += R) {
+                        f4 a[R];
+                        fetch(k - 1, s0, col, a);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const float rr = resid[s0 + r];           // zero past the batch
+                            g.x = fmaf(a[r].x, rr, g.x); g.y = fmaf(a[r].y, rr, g.y);
+                            g.z = fmaf(a[r].z, rr, g.z); g.w = fmaf(a[r].w, rr, g.w);
+                        }
+                    }
+                    w.x = fmaf(-step, g.x, w.x); w.y = fmaf(-step, g.y, w.y);
+                    w.z = fmaf(-step, g.z, w.z); w.w = fmaf(-step, g.w, w.w);
+                    *(f4 *)(wrow + col) = w;
+                }
+            }
+            src = wrow;                           // every thread reads back only what it has written
+        }
+        if (!residuals) return;
+        for (uint32_t s0 = 0; s0 < batch; s0 += R) {
+            float acc[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = 0.f;
+            for (uint64_t i = 0; i < own; ++i) {
+                const uint64_t col = (slice + i * sa.slices) * BLOCK + 4ull * threadIdx.x;
+                if (col < d) {
+                    f4 a[R];
+                    fetch(k, s0, col, a);
+                    const f4 w = *(const f4 *)(src + col);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        acc[r] = fmaf(a[r].x, w.x, acc[r]); acc[r] = fmaf(a[r].y, w.y, acc[r]);
+                        acc[r] = fmaf(a[r].z, w.z, acc[r]); acc[r] = fmaf(a[r].w, w.w, acc[r]);
+                    }
+                }
+            }
+            const float total = wave_totals<R>(acc, lane);
+            if (lane < R) sums[wave][s0 + lane] = total;
+        }
         __syncthreads();
+        if (threadIdx.x < batch) {
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < THREADS / 64; ++w) t += sums[w][threadIdx.x];
+            if (WHOLE) resid[threadIdx.x] = t - bn[rows[k & 1u][threadIdx.x]];
+            else sa.part[(uint64_t)(k & 1u) * sa.part_parity + ((uint64_t)slot * sa.slices + slice) * LSQ_MAX_BATCH + threadIdx.x] = t;
+        }
+        if (WHOLE) __syncthreads();
     }
-    if (H == 0)
-        for (uint64_t k = 4ull * threadIdx.x; k < d; k += 4ull * LB)
-            *(f4 *)(wrow + k) = *(const f4 *)(base + (uint64_t)node * d + k);
 }
 
 // ---- split form ------------------------------------------------------------------------------------
@@ -246,12 +359,28 @@ __global__ __launch_bounds__(SW * 64) void lsq_split_kernel(const LsqSplitArgs s
     if (INTERACT) interact_tile<BITS, 3>(ia, sd, slice, lane, wA - hA, wB - hB);
 }
 
-bool lsq_split_fits(uint64_t d, uint32_t n) { return ((d + SLICE - 1) / SLICE) * n <= 256; }
+bool lsq_split_fits(uint64_t d, uint32_t n) { return ((d + SLICE - 1) / SLICE) * n <= LSQ_MAX_RESIDENT; }
+
+// Slices per node of the wide form, from the swarm's shape alone: the order in which a node's residuals are summed
+// must not depend on how many nodes take steps together (a batch of Algorithm 1 equals its single steps bit for bit).
+// From 256 nodes on one workgroup each fills the chip and spares the exchange (600 x 4096, batch 16, 2 steps:
+// 126 us with 2 slices, 98 with one); below, as many slices as make 2048 workgroups, every slice with as many blocks.
+static uint32_t wide_slices(uint64_t d, uint32_t n) {
+    if (n >= WIDE_WHOLE_NODES) return 1;
+    const uint64_t blocks = (d + WIDE_BLOCK - 1) / WIDE_BLOCK;
+    const uint64_t most = std::min<uint64_t>({blocks, WIDE_MAX_SLICES, WIDE_GROUPS / n});
+    const uint64_t each = (blocks + most - 1) / most;
+    return (uint32_t)((blocks + each - 1) / each);
+}
 
 hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n) {
-    if (!lsq_split_fits(d, n)) return hipSuccess;
-    const uint64_t slices = (d + SLICE - 1) / SLICE;
     hipError_t e;
+    if (!lsq_split_fits(d, n)) {
+        o.wide_slices = wide_slices(d, n);
+        o.wide_rows = (uint64_t)n * o.wide_slices;
+        return hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH);
+    }
+    const uint64_t slices = (d + SLICE - 1) / SLICE;
     o.part_bytes = sizeof(unsigned long long) * n * 2 * slices * LSQ_MAX_BATCH;
     if ((e = hipMalloc((void **)&o.part, o.part_bytes)) != hipSuccess) return e;
     o.launches = 0;
@@ -277,6 +406,16 @@ static hipError_t split_args(LsqSplitArgs &sa, const float *base, float *W, LsqO
     return hipSuccess;
 }
 
+static void launch_wide(const LsqWideArgs &wa, uint32_t count, uint32_t max_steps, hipStream_t st) {
+    if (wa.slices == 1) {
+        if (wa.d <= 4 * WB) lsq_wide_kernel<WB, true><<<dim3(1, count, 1), WB, 0, st>>>(wa, 0);
+        else if (wa.d <= 64 * WB) lsq_wide_kernel<2 * WB, true><<<dim3(1, count, 1), 2 * WB, 0, st>>>(wa, 0);
+        else lsq_wide_kernel<4 * WB, true><<<dim3(1, count, 1), 4 * WB, 0, st>>>(wa, 0);
+        return;
+    }
+    for (uint32_t k = 0; k <= max_steps; ++k) lsq_wide_kernel<WB, false><<<dim3(wa.slices, count, 1), WB, 0, st>>>(wa, k);
+}
+
 hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const LocalSlots &slots,
                             DeviceCounters *counters, uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed,
                             uint32_t event, hipStream_t st) {
@@ -287,7 +426,9 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
         if (e != hipSuccess) return e;
         lsq_split_kernel<0, false><<<dim3(sa.slices, count, 1), SW * 64, 0, st>>>(sa, InteractArgs{});
     } else {
-        local_lsq_kernel<<<count, LB, 0, st>>>(base, W, o.A, o.b, slots, d, H, lr, o.m_rows, o.batch, seed, event);
+        LsqWideArgs wa{base, W, o.A, o.b, slots, o.wide_part, d, seed, o.wide_rows * LSQ_MAX_BATCH,
+                       H, o.m_rows, o.batch, event, o.wide_slices, lr};
+        launch_wide(wa, count, slots.steps ? slots.max_steps : H, st);
     }
     return hipGetLastError();
 }
@@ -314,6 +455,7 @@ hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc
 
 void free_lsq(LsqObjective &o) {
     if (o.part) (void)hipFree(o.part);
+    if (o.wide_part) (void)hipFree(o.wide_part);
     o = LsqObjective{};
 }
 

@@ -13,10 +13,15 @@ struct LsqObjective {
     const float *b = nullptr;    // n x m_rows
     uint32_t m_rows = 0, batch = 0;
     // split form (small swarms): tagged partial residuals exchanged between the workgroups of a node
-    // (owned; null when the single-workgroup form is used)
+    // (owned; null when the wide form is used)
     unsigned long long *part = nullptr;
     size_t part_bytes = 0;
     uint32_t launches = 0;          // launches of the split form so far (24 bits, tags the exchanged words)
+    // wide form (all other swarms): partial residuals, two steps' worth of wide_rows x LSQ_MAX_BATCH (owned),
+    // wide_rows = nodes x wide_slices
+    float *wide_part = nullptr;
+    uint64_t wide_rows = 0;
+    uint32_t wide_slices = 0;
 };
 
 struct MlpObjective {

@@ -196,9 +196,8 @@ uint32_t draw_steps(const swarm_config &c, uint32_t node, uint32_t event) {
 }
 
 // Step counts of this event on the device, one word per slot of the launch (slot k = node ids[k], or
-// node k when ids is null), or null when the number of steps is constant.
-swarm_status upload_steps(swarm_t h, uint32_t event, const uint32_t *ids, uint32_t count, const uint32_t **steps_dev) {
-    *steps_dev = nullptr;
+// node k when ids is null); nothing to do when the number of steps is constant.
+swarm_status upload_steps(swarm_t h, uint32_t event, const uint32_t *ids, uint32_t count, LocalSlots *slots) {
     if (h->cfg.steps_law == SWARM_STEPS_CONSTANT) return SWARM_OK;
     uint8_t *slot = nullptr;
     unsigned slot_index = 0;
@@ -207,7 +206,8 @@ swarm_status upload_steps(swarm_t h, uint32_t event, const uint32_t *ids, uint32
     for (uint32_t k = 0; k < count; ++k) dst[k] = draw_steps(h->cfg, ids ? ids[k] : k, event);
     SWARM_HIP(h, hipMemcpyAsync(h->steps_dev, slot, sizeof(uint32_t) * count, hipMemcpyHostToDevice, h->stream));
     SWARM_HIP(h, hipEventRecord(h->desc_free[slot_index], h->stream));
-    *steps_dev = h->steps_dev;
+    slots->steps = h->steps_dev;
+    slots->max_steps = *std::max_element(dst, dst + count);
     return SWARM_OK;
 }
 
@@ -240,7 +240,7 @@ swarm_status run_local_steps(swarm_t h, const float *base, const uint32_t *ids, 
         return fail(h, SWARM_ESTATE, "the MLP objective takes a constant number of local steps");
     LocalSlots slots;
     slots.nodes = nodes_dev;
-    SWARM_TRY(upload_steps(h, event, ids, count, &slots.steps));
+    SWARM_TRY(upload_steps(h, event, ids, count, &slots));
     return launch_local(h, base, slots, count, event);
 }
 
@@ -874,7 +874,10 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
             if (with_steps && !steps_inside) {
                 LocalSlots slots;
                 slots.nodes = ids_dev + off;
-                slots.steps = c.steps_law == SWARM_STEPS_CONSTANT ? nullptr : ids_dev + h->seq_cap + off;
+                if (c.steps_law != SWARM_STEPS_CONSTANT) {
+                    slots.steps = ids_dev + h->seq_cap + off;
+                    slots.max_steps = *std::max_element(steps + off, steps + off + width);
+                }
                 slots.events = ids_dev + 2 * (size_t)h->seq_cap + off;
                 SWARM_TRY(launch_local(h, h->Xhat, slots, width, 0));
             }

@@ -1,0 +1,52 @@
+"""Kernels at the edges of the size ranges their dispatch rules cut, against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle.objectives import LeastSquares
+from helpers import TOL_GEMM, assert_close, make_both
+
+pytestmark = pytest.mark.gpu
+
+
+def lsq_swarm(gpu, n, d, m, batch, H, geometric, seed):
+    A, b, _ = wl.least_squares_data(n, d, m, seed)
+    edges = wl.complete_graph(n) if n < 16 else wl.random_regular_graph(n, 4, 0)
+    g, c = make_both(gpu, n, d, edges, 8, 2.0 ** -6, H, 0.05, 0, seed=seed, geometric=geometric)
+    c.objective = LeastSquares(A, b, batch)
+    g.set_objective_lsq(torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(), m, batch)
+    gen = np.random.Generator(np.random.PCG64(seed))
+    c.X[:] = gen.standard_normal((n, d)).astype(np.float32)
+    g.write_models(gpu.COMM, c.X)
+    return g, c
+
+
+# n x ceil(d / 512) > 256: several workgroups share a node below 256 nodes (blocks of 1024 columns, one or more per
+# slice, ragged or a whole number), one workgroup takes a node from there on (256, 512 or 1024 threads)
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", [
+    (129, 1024, 8, 4, 2, False), (129, 1032, 8, 20, 3, False), (40, 4096, 40, 64, 1, False), (9, 8 * 2051, 33, 16, 2, True),
+    (2, 8 * 33001, 17, 12, 2, False), (255, 8 * 1300, 6, 32, 2, False),
+    (257, 512, 9, 4, 3, True), (256, 1032, 8, 36, 2, False), (260, 16384 + 8, 5, 16, 2, False)])
+def test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric):
+    g, c = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)
+    nodes = sorted({n - 1, 0, n // 2}, reverse=True)
+    for node in nodes:
+        c.local_steps([node])
+    g.local_steps(nodes)
+    some = g.read_models(gpu.LIVE)[nodes]
+    assert_close(some, c.W[nodes], TOL_GEMM, "steps of a few nodes")
+    g.write_models(gpu.COMM, c.X)                          # clears the pending marks, same round: same draws
+    g.local_steps()
+    assert np.array_equal(g.read_models(gpu.LIVE)[nodes], some)        # the same sums whatever the launch carries
+
+
+def test_wide_least_squares_batched_algorithm1_equals_single_steps(gpu):
+    n, d = 9, 8 * 2051
+    pair = [lsq_swarm(gpu, n, d, 33, 16, 2, True, seed=4)[0] for _ in range(2)]
+    pairs, _ = pair[0].run_sequential(24)
+    for i, j in pairs:
+        assert pair[1].sample_pair() == (i, j)
+        pair[1].interact(i, j)
+    for which in (gpu.COMM, gpu.SNAP):
+        assert np.array_equal(pair[0].read_models(which), pair[1].read_models(which))
