@@ -5,6 +5,10 @@
 // coordinates 8g+2p, 8g+2p+1), i.e. the float4 of two neighbouring lanes: the even lane draws for
 // the group in the tile's first half, the odd lane for the one in the second half, and they swap
 // the halves they do not need -- one generator call per lane and step for 8 normals.
+// With noise the kernels that take five steps in registers are bound by vector instructions, not by memory: a step
+// issues 101 of them per lane (33 for the generator, 4 for the exchange, 40 for the four Box-Muller pairs, 24 for the
+// update).  It was 121 before the generator's three-input exclusive-ors and the exchange folded into the selects:
+// 32 nodes x 6 875 000, H = 5, 8-bit codes: 744 -> 704 us per one-pass round.
 #pragma once
 #include "gossip_common.hpp"
 
@@ -40,22 +44,17 @@ template <bool NOISE>
 __device__ __forceinline__ void diag_steps(f4 &wA, f4 &wB, const f4 aA, const f4 aB, const f4 cA, const f4 cB,
                                            uint32_t node, uint64_t tile, uint32_t lane, uint32_t H, float lr,
                                            float sigma, uint64_t seed, uint32_t event) {
-    const bool odd = lane & 1u;
-    const uint64_t group = tile * (TILE / 8) + (lane >> 1) + (odd ? 32u : 0u);
+    const uint64_t group = tile * (TILE / 8) + (lane >> 1) + ((lane & 1u) ? 32u : 0u);
     const float scale = -1.3862943611198906f * sigma * sigma;     // -2 ln 2 sigma^2
     for (uint32_t q = 0; q < H; ++q) {
         f4 nA = {0.f, 0.f, 0.f, 0.f}, nB = nA;
         if (NOISE) {
-            const Words4 w = stream(seed, TAG_NOISE, q, node, event, group);
-            // even lane: words 0,1 of its own call (first half) and of the neighbour's (second half);
-            // odd lane: words 2,3 of the neighbour's call (first half) and of its own (second half).
-            const uint32_t r0 = swap_with_neighbour(odd ? w.w0 : w.w2);
-            const uint32_t r1 = swap_with_neighbour(odd ? w.w1 : w.w3);
+            const LaneRandom w = pair_words(stream(seed, TAG_NOISE, q, node, event, group));
             float z0, z1, z2, z3, z4, z5, z6, z7;
-            box_muller16(odd ? r0 : w.w0, scale, z0, z1);
-            box_muller16(odd ? r1 : w.w1, scale, z2, z3);
-            box_muller16(odd ? w.w2 : r0, scale, z4, z5);
-            box_muller16(odd ? w.w3 : r1, scale, z6, z7);
+            box_muller16(w.a0, scale, z0, z1);
+            box_muller16(w.a1, scale, z2, z3);
+            box_muller16(w.b0, scale, z4, z5);
+            box_muller16(w.b1, scale, z6, z7);
             nA = f4{z0, z1, z2, z3};
             nB = f4{z4, z5, z6, z7};
         }

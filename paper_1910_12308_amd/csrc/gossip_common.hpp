@@ -33,10 +33,6 @@ __device__ __forceinline__ f4 ldg_nt(const float *row, uint32_t off) {
 __device__ __forceinline__ void stg_nt(float *row, uint32_t off, f4 v) {
     __builtin_nontemporal_store(v, (SWARM_GLOBAL f4 *)at_bytes(uniform(row), 4u * off));
 }
-__device__ __forceinline__ uint32_t swap_with_neighbour(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
-}
-
 // Packed code of one float4 (4 coordinates, 4*BITS bits, coordinate m at bit m*BITS).
 template <int BITS> struct CodeWord;
 template <> struct CodeWord<2>  { typedef uint8_t  type; };
@@ -65,23 +61,35 @@ __device__ __forceinline__ void store_tile_code(uint8_t *tile_codes, uint32_t f,
     __builtin_nontemporal_store((Word)c, (SWARM_GLOBAL Word *)at_bytes(uniform(tile_codes), f * (BITS / 2)));
 }
 
-// The two random words of the float4 this lane holds in the tile's first half (lo*)
-// and second half (hi*), for one row.
+// The words of the float4 this lane holds in the tile's first half (a*) and second half (b*), from one generator
+// call per lane: the even lane of a lane pair has called for the pair's group in the first half, the odd lane for its
+// group in the second.  The even lane keeps words 0, 1 of its call and takes words 0, 1 of its neighbour's for the
+// second half; the odd lane takes words 2, 3 of its neighbour's for the first half and keeps its own words 2, 3.
+// A select whose one operand comes from the neighbouring lane is a single instruction: 4 for the exchange
+// (the compiler's form of it takes 8).  The wait covers the distance a cross-lane operand has to keep from the
+// instruction that writes it, which the compiler does not see into.
 struct LaneRandom { uint32_t a0, a1, b0, b1; };
+
+__device__ __forceinline__ LaneRandom pair_words(const Words4 w) {
+    LaneRandom o;
+    asm("s_mov_b32 vcc_lo, 0x55555555\n\t"
+        "s_mov_b32 vcc_hi, 0x55555555\n\t"
+        "s_nop 1\n\t"
+        "v_cndmask_b32_dpp %0, %6, %4, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %1, %7, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_not_b64 vcc, vcc\n\t"
+        "v_cndmask_b32_dpp %2, %4, %6, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %3, %5, %7, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=&v"(o.a0), "=&v"(o.a1), "=&v"(o.b0), "=&v"(o.b1)
+        : "v"(w.w0), "v"(w.w1), "v"(w.w2), "v"(w.w3)
+        : "vcc", "scc");
+    return o;
+}
 
 __device__ __forceinline__ LaneRandom row_random(uint64_t seed, uint32_t node, uint32_t event,
                                                  uint64_t tile, uint32_t lane) {
-    const bool odd = lane & 1u;
-    const uint64_t group = tile * (TILE / 8) + (lane >> 1) + (odd ? 32u : 0u);
-    const Words4 w = stream(seed, TAG_SR, 0, node, event, group);
-    // even lane keeps words 0,1 of group A and needs words 0,1 of group B (made by the odd lane);
-    // odd lane keeps words 2,3 of group B and needs words 2,3 of group A (made by the even lane).
-    const uint32_t r0 = swap_with_neighbour(odd ? w.w0 : w.w2);
-    const uint32_t r1 = swap_with_neighbour(odd ? w.w1 : w.w3);
-    LaneRandom out;
-    out.a0 = odd ? r0 : w.w0;  out.a1 = odd ? r1 : w.w1;
-    out.b0 = odd ? w.w2 : r0;  out.b1 = odd ? w.w3 : r1;
-    return out;
+    const uint64_t group = tile * (TILE / 8) + (lane >> 1) + ((lane & 1u) ? 32u : 0u);
+    return pair_words(stream(seed, TAG_SR, 0, node, event, group));
 }
 
 template <int BITS>

@@ -13,14 +13,25 @@ enum : uint32_t { TAG_SR = 1, TAG_NOISE = 2, TAG_MATCH = 3, TAG_PICK = 4, TAG_BA
 
 struct Words4 { uint32_t w0, w1, w2, w3; };
 
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+#endif
+
 __host__ __device__ __forceinline__ Words4 philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0,
                                                          uint32_t c1, uint32_t c2, uint32_t c3) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+#if defined(__HIP_DEVICE_COMPILE__)
+        // One three-input instruction instead of two: 16 of the 30 exclusive-ors a lane issues per call, with a
+        // common node, tag and key.  (The first rounds mix in words common to the wave, whose part is scalar.)
+        const uint32_t n0 = r < 2 ? (uint32_t)(p1 >> 32) ^ c1 ^ k0 : xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = r < 3 ? (uint32_t)(p0 >> 32) ^ c3 ^ k1 : xor3((uint32_t)(p0 >> 32), c3, k1);
+#else
         const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
         const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+#endif
         c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }

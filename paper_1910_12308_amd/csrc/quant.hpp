@@ -19,6 +19,13 @@ __device__ __forceinline__ float lattice_coord(float x, float inv_eps, bool &cla
     return fminf(fmaxf(t, -LATTICE_CLAMP), LATTICE_CLAMP);
 }
 
+// (int)floor(t) in one instruction, for a finite t inside the int32 range (the compiler makes two of it).
+__device__ __forceinline__ int floor_to_int(float t) {
+    int z;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(z) : "v"(t));
+    return z;
+}
+
 // z = floor(t) + [r16 + 1/2 < frac(t) 2^16]: P(up) is within 2^-17 of frac(t).
 // The comparison is taken as r16 < frac(t) 2^16 - 1/2 with one fused multiply-add, whose rounding cannot
 // change the decision: the scaling is a power of two; for frac(t) 2^16 >= 1/2 the difference keeps the
@@ -29,7 +36,7 @@ __device__ __forceinline__ int stochastic_round(float x, float inv_eps, uint32_t
     const float t = lattice_coord(x, inv_eps, clamped);
     const float frac = __builtin_amdgcn_fractf(t);
     const int up = (float)r16 < fmaf(frac, 65536.0f, -0.5f);
-    return (int)floorf(t) + up;
+    return floor_to_int(t) + up;
 }
 
 // Lattice cell of the key (round to nearest, ties to even).
