@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "interact_run.hpp"
 #include "internal.h"
 #include "objectives.h"
 #include "philox.hpp"
@@ -813,18 +814,38 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
     const bool steps_inside = with_steps && h->kind == OBJ_DIAG && c.codec == SWARM_CODEC_FIXED;
     // small least-squares models: one workgroup runs an initiator's steps and then its interaction
     const bool lsq_inside = with_steps && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.part != nullptr;
+    // everything per-coordinate and the models of a tile fit local memory: one launch takes the whole run.  It reads
+    // and writes every node's model once, whether or not the run touches it, and 12 to 16 B per interaction-coordinate
+    // instead of 32 and two codes, so it needs enough interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 32 interactions
+    // 226 us with one launch per level, 234 in one launch; 48: 328 and 294; 256: 1636 and 920.  Interactions that do not
+    // depend on one another at all (one level) have nothing to keep.
+    const bool run_inside = (!with_steps || steps_inside) && c.codec == SWARM_CODEC_FIXED && c.n <= RUN_MAX_NODES;
     const uint64_t tiles = (c.d + PREFIX_TILE - 1) / PREFIX_TILE;
     const GossipArgs a = gossip_args(h, 0, 0);
     uint32_t total_launches = 0;
     SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
-    std::vector<uint32_t> level_of, last_level(c.n), order, level_start;
-    for (uint32_t done = 0; done < count;) {
+    uint32_t done = 0;
+    auto finish_chunk = [&](uint32_t m, uint32_t levels) {
+        total_launches += levels;
+        h->interactions += m;
+        if (c.codec == SWARM_CODEC_PREFIX) {
+            h->bits_communicated += (uint64_t)m * 2ull * (c.d * 4 + 64ull * tiles);
+            h->prefix_tile_reads += (uint64_t)m * tiles;
+        } else {
+            h->bits_communicated += (uint64_t)m * 2ull * c.d * (c.bits ? c.bits : 32);
+        }
+        done += m;
+    };
+    std::vector<uint32_t> level_of, last_level(c.n), order, level_start, touched(c.n), turns;
+    while (done < count) {
         const uint32_t m = std::min(count - done, SEQ_CHUNK);
         SWARM_TRY(ensure_sequence_buffers(h, m));
         // 1. the pairs Algorithm 1 draws next, and the earliest launch each interaction can join: one
         //    after the last launch that touches either of its nodes (interactions on disjoint nodes commute).
         level_of.assign(m, 0);
         std::fill(last_level.begin(), last_level.end(), 0u);
+        std::fill(touched.begin(), touched.end(), 0u);
+        turns.resize(m);
         std::vector<SeqDesc> drawn(m);
         uint32_t levels = 0;
         for (uint32_t t = 0; t < m; ++t) {
@@ -840,6 +861,8 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
             const uint32_t level = std::max(last_level[i], last_level[j]) + 1;
             last_level[i] = last_level[j] = level;
             level_of[t] = level - 1;
+            turns[t] = touched[i]++;
+            turns[t] |= touched[j]++ << 16;
             levels = std::max(levels, level);
             if (pairs_host) { pairs_host[2 * (size_t)(done + t)] = i; pairs_host[2 * (size_t)(done + t) + 1] = j; }
         }
@@ -849,6 +872,30 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
         for (uint32_t l = 0; l < levels; ++l) level_start[l + 1] += level_start[l];
         order.assign(level_start.begin(), level_start.end() - 1);
         SWARM_HIP(h, hipEventSynchronize(h->seq_free));
+        if (run_inside && levels > 1 && 4 * (uint64_t)m >= 3 * (uint64_t)c.n) {
+            RunDesc *run = (RunDesc *)h->seq_host;
+            constexpr uint32_t NEVER = ~0u;
+            std::vector<uint32_t> led(c.n, NEVER);        // the interaction that touched a node last, if it was the node's own
+            for (uint32_t t = 0; t < m; ++t) {
+                SeqDesc &s = drawn[t];
+                if ((turns[t] & 0xFFFFu) + 1 == touched[s.ni]) s.flags |= RUN_LAST_OF_I;
+                if ((turns[t] >> 16) + 1 == touched[s.nj]) s.flags |= RUN_LAST_OF_J;
+                if (led[s.ni] != NEVER) {
+                    s.flags |= RUN_SNAPSHOT_IS_MODEL;
+                    drawn[led[s.ni]].flags |= RUN_SNAPSHOT_SHORT;
+                }
+                led[s.ni] = t;
+                led[s.nj] = NEVER;
+            }
+            for (uint32_t t = 0; t < m; ++t)
+                run[order[level_of[t]]++] = RunDesc{drawn[t].ni | drawn[t].nj << 16, drawn[t].event, drawn[t].flags, turns[t]};
+            SWARM_HIP(h, hipMemcpyAsync(h->seq_dev, run, (size_t)m * sizeof(RunDesc), hipMemcpyHostToDevice, h->stream));
+            SWARM_HIP(h, hipEventRecord(h->seq_free, h->stream));
+            SWARM_HIP(h, launch_interact_run(a, c.bits, (const RunDesc *)h->seq_dev, m, steps_inside ? &h->diag : nullptr, c.lr,
+                                             h->stream));
+            finish_chunk(m, levels);
+            continue;
+        }
         SeqDesc *descs = (SeqDesc *)h->seq_host;
         uint32_t *ids = (uint32_t *)(h->seq_host + (size_t)h->seq_cap * sizeof(SeqDesc));
         uint32_t *steps = ids + h->seq_cap, *events = steps + h->seq_cap;
@@ -887,15 +934,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
                 SWARM_HIP(h, launch_interact(a, c.bits, descs_dev + off, SeqDesc{}, width, steps_inside ? &h->diag : nullptr,
                                              c.lr, h->stream));
         }
-        total_launches += levels;
-        h->interactions += m;
-        if (c.codec == SWARM_CODEC_PREFIX) {
-            h->bits_communicated += (uint64_t)m * 2ull * (c.d * 4 + 64ull * tiles);
-            h->prefix_tile_reads += (uint64_t)m * tiles;
-        } else {
-            h->bits_communicated += (uint64_t)m * 2ull * c.d * (c.bits ? c.bits : 32);
-        }
-        done += m;
+        finish_chunk(m, levels);
     }
     SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 1));
     h->timed_gossip += 1;

@@ -50,3 +50,54 @@ def test_wide_least_squares_batched_algorithm1_equals_single_steps(gpu):
         pair[1].interact(i, j)
     for which in (gpu.COMM, gpu.SNAP):
         assert np.array_equal(pair[0].read_models(which), pair[1].read_models(which))
+
+
+def diag_swarm(gpu, n, d, bits, H, sigma, seed, geometric=False, objective=True):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    a = torch.rand(n, d, generator=gen, device="cuda") + 0.5
+    c = torch.randn(n, d, generator=gen, device="cuda")
+    s = gpu.Swarm(n, d, wl.complete_graph(n), bits, {0: 1.0, 4: 0.5}.get(bits, 2.0 ** -4), H, 0.1, 0, seed,
+                  steps_law=gpu.GEOMETRIC if geometric else gpu.CONSTANT)
+    if objective:
+        s.set_objective_diag(a, c, sigma)
+    X = torch.randn(n, d, generator=gen, device="cuda")
+    s.models_view(gpu.COMM).copy_(X)
+    s.models_view(gpu.SNAP).copy_(X + 0.01 * c)
+    if not objective:
+        s.models_view(gpu.LIVE).copy_(X - 0.02 * c)
+        s.mark_pending()
+    return s
+
+
+# runs of Algorithm 1 in one launch (4, 8 and 16 waves per tile; the most nodes local memory holds) and, with one node
+# more, in one launch per level: both equal one call per interaction, bit for bit
+@pytest.mark.parametrize("n,d,bits,H,sigma,geometric,objective", [
+    (2, 8, 8, 1, 0.1, False, True), (3, 520, 2, 2, 0.05, True, True), (19, 504, 4, 3, 0.1, False, True),
+    (20, 1032, 16, 2, 0.0, False, True), (39, 8, 8, 5, 0.1, True, True), (40, 2056, 8, 1, 0.1, False, True),
+    (78, 1544, 4, 2, 0.1, False, True), (79, 1544, 4, 2, 0.1, False, True), (40, 520, 0, 2, 0.1, False, True),
+    (20, 520, 8, 0, 0.0, False, False), (5, 1544, 0, 0, 0.0, False, False)])
+def test_run_of_algorithm1_in_one_launch(gpu, n, d, bits, H, sigma, geometric, objective):
+    one, run = (diag_swarm(gpu, n, d, bits, H, sigma, 3, geometric, objective) for _ in range(2))
+    count = 3 * n + 1
+    pairs, launches = run.run_sequential(count)
+    assert 1 < launches <= count
+    for i, j in pairs:
+        assert one.sample_pair() == (i, j)
+        one.interact(i, j)
+    for which in (gpu.COMM, gpu.SNAP):
+        assert np.array_equal(run.read_models(which), one.read_models(which))
+    if bits:
+        for node in range(n):
+            assert np.array_equal(run.read_codes(node), one.read_codes(node))
+    assert run.counters(raise_on_range=False) == one.counters(raise_on_range=False)
+
+
+def test_run_of_algorithm1_longer_than_one_upload(gpu):
+    """32768 interactions are described per upload: a longer run goes on from where the upload before it ended."""
+    whole, parts = (diag_swarm(gpu, 2, 16, 8, 1, 0.1, 6) for _ in range(2))
+    whole.run_sequential(33000)
+    for _ in range(11):
+        parts.run_sequential(3000)
+    for which in (gpu.COMM, gpu.SNAP):
+        assert np.array_equal(whole.read_models(which), parts.read_models(which))
+    assert np.array_equal(whole.read_codes(1), parts.read_codes(1)) and whole.counters() == parts.counters()
