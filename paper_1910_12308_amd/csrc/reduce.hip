@@ -13,6 +13,7 @@ namespace swarm {
 
 constexpr int RB = 256;
 
+template <int THREADS>
 __device__ __forceinline__ double block_sum(double v, double *lds) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     const int wave = threadIdx.x >> 6;
@@ -20,10 +21,16 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
-        for (int w = 0; w < RB / 64; ++w) s += lds[w];
+        for (int w = 0; w < THREADS / 64; ++w) s += lds[w];
     return s;   // valid in thread 0
 }
 
+constexpr uint32_t ROWS = 2;          // rows a thread of the potential requests at a time
+
+// Bound by memory (4 B per node-coordinate).  16 x 25 557 032 with its sum of 24 959 partials: 306 us = 5.7 TB/s, from
+// 364 us with cached loads of one row at a time and 256 threads that took the partials one by one (39 us of it);
+// 256 x 8.4 M 1.34 ms from 1.51.  Requests of 4, 8 or 16 rows are no faster there and up to a third slower where the
+// matrix sits in the last-level cache (64 x 2^20: 45 us with 2 rows, 61 with 16).
 // Each thread owns one float4 of columns and walks down the n rows.  With y = x - x_0
 // (shift by the first row) Gamma_k = sum y^2 - (sum y)^2 / n.
 __global__ __launch_bounds__(RB) void potential_kernel(const float *__restrict__ X, uint32_t n, uint64_t d,
@@ -34,13 +41,21 @@ __global__ __launch_bounds__(RB) void potential_kernel(const float *__restrict__
     if (f * 4 < d) {
         const f4 x0 = *(const f4 *)(X + f * 4);
         double s1[4] = {0, 0, 0, 0}, s2[4] = {0, 0, 0, 0};
-        for (uint32_t i = 1; i < n; ++i) {
-            const f4 x = *(const f4 *)(X + (uint64_t)i * d + f * 4);
+        auto add = [&](const f4 x) {
             const double y[4] = {(double)x.x - (double)x0.x, (double)x.y - (double)x0.y,
                                  (double)x.z - (double)x0.z, (double)x.w - (double)x0.w};
 #pragma unroll
             for (int m = 0; m < 4; ++m) { s1[m] += y[m]; s2[m] += y[m] * y[m]; }
+        };
+        uint32_t i = 1;
+        for (; i + ROWS <= n; i += ROWS) {
+            f4 x[ROWS];
+#pragma unroll
+            for (uint32_t r = 0; r < ROWS; ++r) x[r] = ldg_nt(X + (uint64_t)(i + r) * d + f * 4);
+#pragma unroll
+            for (uint32_t r = 0; r < ROWS; ++r) add(x[r]);
         }
+        for (; i < n; ++i) add(ldg_nt(X + (uint64_t)i * d + f * 4));
         const double inv_n = 1.0 / (double)n;
 #pragma unroll
         for (int m = 0; m < 4; ++m) gam += s2[m] - s1[m] * s1[m] * inv_n;
@@ -49,16 +64,24 @@ __global__ __launch_bounds__(RB) void potential_kernel(const float *__restrict__
                                      (float)((double)x0.z + s1[2] * inv_n), (float)((double)x0.w + s1[3] * inv_n)};
         }
     }
-    const double s = block_sum(gam, lds);
+    const double s = block_sum<RB>(gam, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(RB) void sum_partials_kernel(const double *__restrict__ partials, uint32_t count,
+// One workgroup adds up the partial sums in a fixed order: thread t takes t, t + SB, ... of them, eight at a time.
+constexpr int SB = 1024;
+__global__ __launch_bounds__(SB) void sum_partials_kernel(const double *__restrict__ partials, uint32_t count,
                                                           double *__restrict__ out) {
-    __shared__ double lds[RB / 64];
+    __shared__ double lds[SB / 64];
     double v = 0.0;
-    for (uint32_t i = threadIdx.x; i < count; i += RB) v += partials[i];
-    const double s = block_sum(v, lds);
+    for (uint32_t i = threadIdx.x; i < count; i += 8 * SB) {
+        double p[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) p[k] = i + k * SB < count ? partials[i + k * SB] : 0.0;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) v += p[k];
+    }
+    const double s = block_sum<SB>(v, lds);
     if (threadIdx.x == 0) *out = s;
 }
 
@@ -104,7 +127,7 @@ uint32_t potential_partials(uint64_t d) { return (uint32_t)((d / 4 + RB - 1) / R
 hipError_t launch_potential(const float *X, uint32_t n, uint64_t d, float *mu, double *partials,
                             uint32_t npartials, double *gamma_out, hipStream_t st) {
     potential_kernel<<<npartials, RB, 0, st>>>(X, n, d, mu, partials);
-    sum_partials_kernel<<<1, RB, 0, st>>>(partials, npartials, gamma_out);
+    sum_partials_kernel<<<1, SB, 0, st>>>(partials, npartials, gamma_out);
     return hipGetLastError();
 }
 
