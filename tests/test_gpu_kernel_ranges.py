@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as wl
-from oracle.objectives import LeastSquares
+from oracle.objectives import LeastSquares, MixtureMLP
 from helpers import TOL_GEMM, assert_close, make_both
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +101,34 @@ def test_run_of_algorithm1_longer_than_one_upload(gpu):
     for which in (gpu.COMM, gpu.SNAP):
         assert np.array_equal(whole.read_models(which), parts.read_models(which))
     assert np.array_equal(whole.read_codes(1), parts.read_codes(1)) and whole.counters() == parts.counters()
+
+
+# tiles of 64 x 64 (batch up to 64; over 128 in float32), 128 x 64 and, from 512 (updates: 256) tiles on, 128 x 128,
+# each with whole and ragged edges; the hidden bias rides in the backward product only when one tile holds the batch
+@pytest.mark.parametrize("arithmetic", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [
+    (3, 32, 32, 32, 32), (3, 64, 96, 160, 64), (2, 96, 352, 64, 96), (2, 160, 128, 32, 128), (2, 64, 224, 96, 160),
+    (2, 32, 160, 32, 192), (130, 32, 512, 32, 128), (65, 32, 544, 544, 32)])
+def test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, arithmetic):
+    d = n_hid * n_in + n_hid + n_out * n_hid + n_out
+    means, cdf = wl.mixture_data(n, n_in, n_out, 1)
+    edges = wl.complete_graph(n) if n < 16 else wl.random_regular_graph(n, 4, 0)
+    g, c = make_both(gpu, n, d, edges, 8, 2.0 ** -10, 2, 0.05, 0, seed=n)
+    c.objective = MixtureMLP(n_in, n_hid, n_out, means, cdf, 0.5, batch)
+    g.set_objective_mlp(n_in, n_hid, n_out, torch.from_numpy(means).cuda(), torch.from_numpy(cdf).cuda(), 0.5, batch)
+    g.set_mlp_arithmetic(gpu.MLP_BF16X3 if arithmetic == "bf16x3" else gpu.MLP_FP32)
+    gen = np.random.Generator(np.random.PCG64(n))
+    c.X[:] = (0.1 * gen.standard_normal((n, d))).astype(np.float32)
+    g.write_models(gpu.COMM, c.X)
+    nodes = sorted({0, n // 2, n - 1})
+    c.local_steps(nodes)
+    g.local_steps()
+    W, want = g.read_models(gpu.LIVE)[nodes].astype(np.float64), c.W[nodes]
+    # A hidden unit whose pre-activation is within rounding of zero for some sample may be on for one side and off for the
+    # other.  That moves an entry of its row of W1 (or b1) by eta / batch |sum_o dlogits_o W2_o| |x|, at most
+    # eta / batch * 2 max|W2| * max(1, max|x|), features are within 4.9 sigma of a mean; everything else is compared as is.
+    w2 = np.abs(c.X[:, n_hid * n_in + n_hid:-n_out]).max()
+    kink = 2 * 0.05 / batch * 2 * w2 * (np.abs(means).max() + 4.9 * 0.5)
+    off = np.abs(W - want) > TOL_GEMM * np.maximum(1.0, np.abs(want))
+    assert not off[:, n_hid * n_in + n_hid:].any() and off.mean() < 1e-3
+    assert np.abs(W - want)[off].max(initial=0.0) <= kink
