@@ -355,11 +355,11 @@ def sequential_report(torch, swarm, s, cfg, batch, steps, warmup, compare_single
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "ms_per_interaction": m["times"]["gossip_ms"] / max(1, m["interactions"])}
     else:
-        # least squares: 2 * H * batch rows of A per interaction dominate (read twice per step), plus the rows of the pair
-        per_i = cfg["H"] * 2 * cfg["batch"] * d * 4 + 28.0 * d + 16.0 * d
+        # least squares: H * batch rows of A per interaction, read once (the models stay on chip between interactions)
+        per_i = cfg["H"] * cfg["batch"] * d * 4
         achieved = per_i * m["interactions"] / m["dt"] / 1e9
-        rep["roofline"] = {"kernel": "lsq_split_kernel (an initiator's local steps and its interaction in one launch; latency-bound: "
-                                     "a few dozen workgroups per launch, one exchange between them per local step)",
+        rep["roofline"] = {"kernel": "lsq_run_kernel (a call's interactions, local steps included, in one launch; latency-bound: "
+                                     "one exchange between a few dozen workgroups per local step)",
                            "bound": "hbm", "bytes_per_interaction": per_i, "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS}
     if compare_single:

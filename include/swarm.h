@@ -224,7 +224,8 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j);
  * so each interaction joins the earliest kernel launch after the last one that touches either of its
  * nodes, and a launch carries all its interactions as grid rows; no per-interaction host work or
  * copy remains.  Where everything is per-coordinate (fixed-width codes; diagonal objective, or no steps inside the
- * library) and n <= 78, the launches are merged into one, which keeps the models on chip between interactions.  For the diagonal objective (fixed-width codes) the initiator's local steps are
+ * library) and n <= 78, and for small least-squares swarms, the launches are merged into one, which keeps the
+ * models on chip between interactions.  For the diagonal objective (fixed-width codes) the initiator's local steps are
  * taken inside the interaction kernel and the live copy W is neither written nor read (it keeps its
  * old contents); for the other objectives they are one more launch per group.
  * pairs_host: receives the 2*count node ids (initiator, responder) in the order of Algorithm 1, or

@@ -20,13 +20,6 @@
 
 namespace swarm {
 
-// Descriptor k, or one of no consequence past the end.  Written before the launch and never by it: a scalar load.
-__device__ __forceinline__ RunDesc run_desc(const RunArgs &ra, uint32_t k) {
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    const u4 v = ((const __attribute__((address_space(4))) u4 *)ra.descs)[k < ra.count ? k : 0u];
-    return RunDesc{first_lane(v.x), first_lane(v.y), first_lane(v.z), first_lane(v.w)};
-}
-
 // LOCAL: 0 = the pending update is W_i - Xhat_i where the descriptor says so; 1 / 2 = local steps of the diagonal
 // objective in registers, with / without gradient noise.  RW: waves per workgroup.
 template <int BITS, int LOCAL, int RW>
@@ -61,7 +54,7 @@ __global__ __launch_bounds__(RW * 64, 4) void interact_run_kernel(const RunArgs 
     // Interactions k = wave, wave + RW, ...: no branch of this loop depends on the lane except around global stores, so
     // the wave stays together whatever the compiler makes of it.  What does not depend on the interactions before --
     // the next descriptor, its objective data, the random words -- is requested or computed ahead of the wait.
-    RunDesc next = run_desc(ra, wave);
+    RunDesc next = run_desc(ra.descs, wave, ra.count);
     f4 aA = zero, aB = zero, cA = zero, cB = zero;
     auto fetch_objective = [&](uint32_t node) {
         const uint64_t at = (uint64_t)node * a.d + t.base;
@@ -71,7 +64,7 @@ __global__ __launch_bounds__(RW * 64, 4) void interact_run_kernel(const RunArgs 
     if (LOCAL && wave < ra.count) fetch_objective(next.nodes & 0xFFFFu);
     for (uint32_t k = wave; k < ra.count; k += RW) {
         const RunDesc rd = next;
-        next = run_desc(ra, k + RW);
+        next = run_desc(ra.descs, k + RW, ra.count);
         const uint32_t event = rd.event, flags = rd.flags, turn = rd.turn, ni = rd.nodes & 0xFFFFu, nj = rd.nodes >> 16;
         const uint64_t at = (uint64_t)ni * a.d + t.base;
         LaneRandom ni_words{}, nj_words{};

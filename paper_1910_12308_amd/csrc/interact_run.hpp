@@ -1,4 +1,4 @@
-// A run of Algorithm 1 in one launch (interact_run.hip): what the host hands over.
+// A run of Algorithm 1 in one launch (interact_run.hip, lsq_run.hip): what the host hands over.
 #pragma once
 #include "internal.h"
 #include "objectives.h"
@@ -14,7 +14,17 @@ struct RunDesc {
 constexpr uint32_t RUN_LAST_OF_I = 2u, RUN_LAST_OF_J = 4u;        // no later interaction of the run touches the node
 constexpr uint32_t RUN_SNAPSHOT_IS_MODEL = 8u;    // the node's interaction before this one was its own: Xhat_i = X_i
 constexpr uint32_t RUN_SNAPSHOT_SHORT = 16u;      // so is the next one that touches it: nobody reads the snapshot
+constexpr uint32_t RUN_LAST_LED = 32u;            // no later interaction of the run is the initiator's own
 constexpr uint32_t RUN_MAX_NODES = 78;            // 2 KiB of local memory per node, 160 KiB per compute unit
+
+#if defined(__HIPCC__)
+// Descriptor k, or one of no consequence past the end.  Written before the launch and never by it: a scalar load.
+__device__ __forceinline__ RunDesc run_desc(const RunDesc *descs, uint32_t k, uint32_t count) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const u4 v = ((const __attribute__((address_space(4))) u4 *)descs)[k < count ? k : 0u];
+    return RunDesc{first_lane(v.x), first_lane(v.y), first_lane(v.z), first_lane(v.w)};
+}
+#endif
 
 struct RunArgs {
     GossipArgs g;
@@ -27,5 +37,12 @@ struct RunArgs {
 // local: take the initiators' local steps of this diagonal objective in registers, or null.
 hipError_t launch_interact_run(const GossipArgs &g, uint32_t bits, const RunDesc *descs_dev, uint32_t count,
                                const DiagObjective *local, float lr, hipStream_t st);
+
+// The same for small least-squares swarms (those whose objective has words to exchange, LsqObjective::run_part), steps
+// included: descs_dev, or the single interaction `one` when it is null.  total_steps: of all interactions together.
+hipError_t launch_lsq_run(const GossipArgs &g, uint32_t bits, const RunDesc *descs_dev, RunDesc one, uint32_t count,
+                          uint32_t total_steps, LsqObjective &o, float lr, hipStream_t st);
+bool lsq_run_fits(uint64_t d, uint32_t n, uint32_t batch);
+size_t lsq_run_bytes(uint64_t d, uint32_t batch);
 
 }  // namespace swarm

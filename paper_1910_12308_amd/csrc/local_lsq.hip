@@ -12,8 +12,10 @@
 // All other swarms take the wide form (lsq_wide_kernel), whose workgroups exchange their residuals between launches.
 #include <algorithm>
 
+#include "interact_run.hpp"
 #include "interact_tile.hpp"
 #include "internal.h"
+#include "lsq_wave.hpp"
 #include "objectives.h"
 #include "philox.hpp"
 
@@ -47,26 +49,6 @@ struct LsqWideArgs {
     uint32_t H, m_rows, batch, event, slices;
     float lr;
 };
-
-// The wave's sums of R per-lane values, by halving: a lane gives half of its values to the lane a power of two
-// away and keeps the other half, so that about R exchanges (not 6 R) leave the total of value `lane % R` in the lane.
-template <int N, int R>
-__device__ __forceinline__ void halve(float v[R], uint32_t lane) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float keep = (lane & N) ? v[i + N] : v[i], give = (lane & N) ? v[i] : v[i + N];
-        v[i] = keep + __shfl_xor(give, N);
-    }
-    if constexpr (N > 1) halve<N / 2, R>(v, lane);
-}
-template <int R>
-__device__ __forceinline__ float wave_totals(float v[R], uint32_t lane) {
-    halve<R / 2, R>(v, lane);
-    float t = v[0];
-#pragma unroll
-    for (int off = R; off < 64; off *= 2) t += __shfl_xor(t, off);
-    return t;
-}
 
 template <int THREADS, bool WHOLE>
 __global__ __launch_bounds__(THREADS, 4) void lsq_wide_kernel(const LsqWideArgs sa, const uint32_t launch) {
@@ -384,7 +366,11 @@ hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n) {
     o.part_bytes = sizeof(unsigned long long) * n * 2 * slices * LSQ_MAX_BATCH;
     if ((e = hipMalloc((void **)&o.part, o.part_bytes)) != hipSuccess) return e;
     o.launches = 0;
-    return hipMemset(o.part, 0xFF, o.part_bytes);      // no word carries the tag of a launch yet
+    if ((e = hipMemset(o.part, 0xFF, o.part_bytes)) != hipSuccess) return e;      // no word carries the tag of a launch yet
+    if (!lsq_run_fits(d, n, o.batch)) return hipSuccess;
+    o.run_part_bytes = lsq_run_bytes(d, o.batch);
+    if ((e = hipMalloc((void **)&o.run_part, o.run_part_bytes)) != hipSuccess) return e;
+    return hipMemset(o.run_part, 0xFF, o.run_part_bytes);
 }
 
 // Launches are numbered so that the words one launch exchanges cannot be taken for another's; when the
@@ -455,6 +441,7 @@ hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc
 
 void free_lsq(LsqObjective &o) {
     if (o.part) (void)hipFree(o.part);
+    if (o.run_part) (void)hipFree(o.run_part);
     if (o.wide_part) (void)hipFree(o.wide_part);
     o = LsqObjective{};
 }

@@ -17,6 +17,11 @@ struct LsqObjective {
     unsigned long long *part = nullptr;
     size_t part_bytes = 0;
     uint32_t launches = 0;          // launches of the split form so far (24 bits, tags the exchanged words)
+    // runs of Algorithm 1 in one launch: words its waves exchange (owned; null when the swarm does not fit that form) and
+    // the tag of the next step
+    unsigned long long *run_part = nullptr;
+    size_t run_part_bytes = 0;
+    uint32_t run_tag = 0;
     // wide form (all other swarms): partial residuals, two steps' worth of wide_rows x LSQ_MAX_BATCH (owned),
     // wide_rows = nodes x wide_slices
     float *wide_part = nullptr;

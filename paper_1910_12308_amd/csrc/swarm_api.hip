@@ -750,7 +750,17 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j) {
         if (rc != SWARM_OK) return rc;
     }
     bool has_delta = h->pending[i] != 0;
-    if (c.H > 0 && h->kind != OBJ_NONE) {
+    const GossipArgs a = gossip_args(h, (uint32_t)h->interactions, 0);
+    const bool lsq_run = c.H > 0 && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.run_part;
+    if (lsq_run) {                               // steps and interaction in one launch, the one a run of them takes
+        const uint32_t steps = draw_steps(c, i, (uint32_t)h->interactions);
+        const RunDesc one{i | j << 16, (uint32_t)h->interactions,
+                          SEQ_HAS_DELTA | RUN_LAST_OF_I | RUN_LAST_OF_J | RUN_LAST_LED | steps << 8, 0u};
+        SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
+        SWARM_HIP(h, launch_lsq_run(a, c.bits, nullptr, one, 1, steps, h->lsq, c.lr, h->stream));
+        SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 1));
+        h->timed_gossip += 1;
+    } else if (c.H > 0 && h->kind != OBJ_NONE) {
         SWARM_TRY(upload_nodes(h, &i, 1));
         SWARM_TRY(record_timing(h, h->ev_local, h->timed_local, 0));
         SWARM_TRY(run_local_steps(h, h->Xhat, &i, h->nodes_dev, 1, (uint32_t)h->interactions));
@@ -758,13 +768,14 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j) {
         h->timed_local += 1;
         has_delta = true;
     }
-    const GossipArgs a = gossip_args(h, (uint32_t)h->interactions, 0);
-    SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
-    const SeqDesc one{i, j, (uint32_t)h->interactions, has_delta ? SEQ_HAS_DELTA : 0u};
-    if (c.codec == SWARM_CODEC_PREFIX) SWARM_HIP(h, launch_prefix_interact(a, nullptr, one, 1, h->stream));
-    else SWARM_HIP(h, launch_interact(a, c.bits, nullptr, one, 1, nullptr, c.lr, h->stream));
-    SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 1));
-    h->timed_gossip += 1;
+    if (!lsq_run) {
+        SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
+        const SeqDesc one{i, j, (uint32_t)h->interactions, has_delta ? SEQ_HAS_DELTA : 0u};
+        if (c.codec == SWARM_CODEC_PREFIX) SWARM_HIP(h, launch_prefix_interact(a, nullptr, one, 1, h->stream));
+        else SWARM_HIP(h, launch_interact(a, c.bits, nullptr, one, 1, nullptr, c.lr, h->stream));
+        SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 1));
+        h->timed_gossip += 1;
+    }
     h->pending[i] = 0;
     h->interactions += 1;
     if (c.codec == SWARM_CODEC_PREFIX) {     // read by prefixes, average written back with as many bits
@@ -814,6 +825,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
     const bool steps_inside = with_steps && h->kind == OBJ_DIAG && c.codec == SWARM_CODEC_FIXED;
     // small least-squares models: one workgroup runs an initiator's steps and then its interaction
     const bool lsq_inside = with_steps && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.part != nullptr;
+    const bool lsq_run = lsq_inside && h->lsq.run_part;       // and where they fit, the whole run in one launch
     // everything per-coordinate and the models of a tile fit local memory: one launch takes the whole run.  It reads
     // and writes every node's model once, whether or not the run touches it, and 12 to 16 B per interaction-coordinate
     // instead of 32 and two codes, so it needs enough interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 32 interactions
@@ -872,10 +884,12 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
         for (uint32_t l = 0; l < levels; ++l) level_start[l + 1] += level_start[l];
         order.assign(level_start.begin(), level_start.end() - 1);
         SWARM_HIP(h, hipEventSynchronize(h->seq_free));
-        if (run_inside && levels > 1 && 4 * (uint64_t)m >= 3 * (uint64_t)c.n) {
+        if (lsq_run || (run_inside && levels > 1 && 4 * (uint64_t)m >= 3 * (uint64_t)c.n)) {
             RunDesc *run = (RunDesc *)h->seq_host;
             constexpr uint32_t NEVER = ~0u;
             std::vector<uint32_t> led(c.n, NEVER);        // the interaction that touched a node last, if it was the node's own
+            std::vector<uint32_t> last_led(c.n, NEVER);
+            uint32_t total_steps = 0;
             for (uint32_t t = 0; t < m; ++t) {
                 SeqDesc &s = drawn[t];
                 if ((turns[t] & 0xFFFFu) + 1 == touched[s.ni]) s.flags |= RUN_LAST_OF_I;
@@ -884,15 +898,20 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
                     s.flags |= RUN_SNAPSHOT_IS_MODEL;
                     drawn[led[s.ni]].flags |= RUN_SNAPSHOT_SHORT;
                 }
-                led[s.ni] = t;
+                led[s.ni] = last_led[s.ni] = t;
                 led[s.nj] = NEVER;
+                total_steps += s.flags >> 8;
             }
+            for (const uint32_t t : last_led) if (t != NEVER) drawn[t].flags |= RUN_LAST_LED;
             for (uint32_t t = 0; t < m; ++t)
                 run[order[level_of[t]]++] = RunDesc{drawn[t].ni | drawn[t].nj << 16, drawn[t].event, drawn[t].flags, turns[t]};
             SWARM_HIP(h, hipMemcpyAsync(h->seq_dev, run, (size_t)m * sizeof(RunDesc), hipMemcpyHostToDevice, h->stream));
             SWARM_HIP(h, hipEventRecord(h->seq_free, h->stream));
-            SWARM_HIP(h, launch_interact_run(a, c.bits, (const RunDesc *)h->seq_dev, m, steps_inside ? &h->diag : nullptr, c.lr,
-                                             h->stream));
+            if (lsq_run)
+                SWARM_HIP(h, launch_lsq_run(a, c.bits, (const RunDesc *)h->seq_dev, RunDesc{}, m, total_steps, h->lsq, c.lr, h->stream));
+            else
+                SWARM_HIP(h, launch_interact_run(a, c.bits, (const RunDesc *)h->seq_dev, m, steps_inside ? &h->diag : nullptr, c.lr,
+                                                 h->stream));
             finish_chunk(m, levels);
             continue;
         }

@@ -132,3 +132,50 @@ def test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, arithmetic):
     off = np.abs(W - want) > TOL_GEMM * np.maximum(1.0, np.abs(want))
     assert not off[:, n_hid * n_in + n_hid:].any() and off.mean() < 1e-3
     assert np.abs(W - want)[off].max(initial=0.0) <= kink
+
+
+# small least-squares swarms: a run of Algorithm 1 in one launch (up to 64 nodes, 64 groups of 128 columns, batch 32 and
+# 2048 words exchanged per step); beyond each of these limits the form with a launch per level
+@pytest.mark.parametrize("n,d,m,batch,H,bits,geometric", [
+    (2, 8, 5, 4, 1, 8, False), (3, 136, 20, 12, 3, 2, True), (8, 1032, 30, 16, 2, 4, False), (5, 2600, 40, 20, 2, 16, True),
+    (4, 8192, 16, 32, 1, 8, False), (64, 512, 9, 32, 2, 0, False), (65, 512, 9, 32, 2, 8, False), (5, 1024, 70, 36, 2, 8, False),
+    (4, 8200, 16, 16, 1, 8, False)])
+def test_least_squares_run_in_one_launch(gpu, n, d, m, batch, H, bits, geometric):
+    A, b, _ = wl.least_squares_data(n, d, m, 2)
+    edges = wl.complete_graph(n) if n < 16 else wl.random_regular_graph(n, 4, 0)
+    eps = 2.0 ** -6 if bits > 2 else 0.5
+    gen = np.random.Generator(np.random.PCG64(n))
+    X = (gen.standard_normal((1, d)) + 0.05 * gen.standard_normal((n, d))).astype(np.float32)
+    pair = []
+    for _ in range(2):
+        g, c = make_both(gpu, n, d, edges, bits, eps, H, 0.05, 0, seed=9, geometric=geometric)
+        g.set_objective_lsq(torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(), m, batch)
+        g.write_models(gpu.COMM, X)
+        g.write_models(gpu.SNAP, X + np.float32(0.01))
+        pair.append(g)
+    run, one = pair
+    c.objective = LeastSquares(A, b, batch)
+    c.X[:], c.Xhat[:] = X, X + np.float32(0.01)
+    # the first interaction against the oracle: same state, so codes are the same bits
+    i, j = c.step_sequential()
+    pairs, _ = run.run_sequential(1)
+    assert tuple(pairs[0]) == (i, j)
+    assert_close(run.read_models(gpu.COMM), c.X, TOL_GEMM, "X after one interaction")
+    assert_close(run.read_models(gpu.SNAP), c.Xhat, TOL_GEMM, "snapshots after one interaction")
+    assert_close(run.read_models(gpu.LIVE)[i], c.W[i], TOL_GEMM, "W_i after one interaction")
+    if bits:
+        for node in (i, j):
+            assert np.array_equal(run.read_codes(node), c.ring[0][node])
+    # the rest of the run against one call per interaction
+    one.interact(i, j)
+    for t in (3 * n, 2):
+        pairs, _ = run.run_sequential(t)
+        for i, j in pairs:
+            assert one.sample_pair() == (i, j)
+            one.interact(i, j)
+    for which in (gpu.COMM, gpu.SNAP, gpu.LIVE):
+        assert np.array_equal(run.read_models(which), one.read_models(which))
+    if bits:
+        for node in range(n):
+            assert np.array_equal(run.read_codes(node), one.read_codes(node))
+    assert run.counters(raise_on_range=False) == one.counters(raise_on_range=False)
