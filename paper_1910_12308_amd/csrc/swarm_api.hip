@@ -23,6 +23,16 @@ using namespace swarm;
 namespace {
 
 constexpr int DESC_SLOTS = 4;   // pinned staging slots for per-round metadata
+// Rounds of at most so many waves read their descriptors there: a read over the bus by every wave costs less than a copy
+// ahead of the kernels (one round and a wait: 8 nodes x 8888 30.4 -> 23.2 us, 64 x 30 000 36.0 -> 30.9), until there are
+// too many of them (64 x 65 536, 8192 waves, back to back: 32.8 -> 33.4).
+constexpr uint64_t DESC_IN_PLACE_WAVES = 4096;
+// Graphs of at most so many edges are matched on the host: 128 generator calls and a sort of as many words take 4 us,
+// less than enqueueing the matching kernel and waiting for its event, which set the period of small rounds (back to back,
+// 8 nodes x 8888, 16 edges: 17.2 -> 9.3 us; 16 x 4096, 120 edges: 18.4 -> 11.0; 64 x 8888, 128 edges: 18.8 -> 17.9).  The
+// kernel runs a round ahead and beside the round's kernels, so for more edges a single round is sooner done with it
+// (31 x 4096, 465 edges, one round and a wait: 28.6 us, 37.8 on the host).
+constexpr uint32_t HOST_MATCH_EDGES = 128;
 constexpr uint32_t SEQ_CHUNK = 1u << 15;                              // interactions of Algorithm 1 staged per upload
 constexpr size_t SEQ_ENTRY_BYTES = sizeof(swarm::SeqDesc) + 3 * sizeof(uint32_t);
 
@@ -58,6 +68,7 @@ struct swarm_ctx {
 
     // pinned host staging
     uint8_t *desc_host[DESC_SLOTS] = {nullptr, nullptr, nullptr, nullptr};
+    uint8_t *desc_mapped[DESC_SLOTS] = {nullptr, nullptr, nullptr, nullptr};     // the same as the device sees it
     hipEvent_t desc_free[DESC_SLOTS] = {nullptr, nullptr, nullptr, nullptr};
     unsigned desc_next = 0;
     uint32_t *match_host = nullptr;              // counts[2] | pairs | singles
@@ -65,6 +76,7 @@ struct swarm_ctx {
     hipStream_t match_stream = nullptr;          // the matching runs beside the round kernels, not between them
     hipEvent_t match_ready = nullptr;            // the matching of round match_round has reached match_host
     uint64_t match_round = ~0ull;
+    std::vector<uint8_t> match_taken;            // scratch of the matching on the host
     double *scalar_host = nullptr;
 
     size_t off_pairs = 0, off_singles = 0, desc_bytes = 0;
@@ -351,6 +363,7 @@ swarm_status swarm_init(const swarm_config *cfg, const float *x0_dev, void *hip_
         SWARM_HIP(h, hipMalloc((void **)&h->gamma_dev, sizeof(double)));
         for (int s = 0; s < DESC_SLOTS; ++s) {
             SWARM_HIP(h, hipHostMalloc((void **)&h->desc_host[s], h->desc_bytes, hipHostMallocDefault));
+            SWARM_HIP(h, hipHostGetDevicePointer((void **)&h->desc_mapped[s], h->desc_host[s], 0));
             SWARM_HIP(h, hipEventCreateWithFlags(&h->desc_free[s], hipEventDisableTiming));
             SWARM_HIP(h, hipEventRecord(h->desc_free[s], h->stream));
         }
@@ -527,8 +540,36 @@ static swarm_status enqueue_matching(swarm_t h, uint64_t round) {
     return SWARM_OK;
 }
 
+// The same matching on the host: a greedy scan by increasing (random word, edge index).
+static void match_on_host(swarm_t h) {
+    const swarm_config &c = h->cfg;
+    uint64_t order[HOST_MATCH_EDGES + 1];
+    for (uint32_t e = 0; e < c.n_edges; ++e)
+        order[e] = (uint64_t)stream(c.seed, TAG_MATCH, 0, e, (uint32_t)h->round, 0).w0 << 32 | e;
+    std::sort(order, order + c.n_edges);
+    std::vector<uint8_t> &taken = h->match_taken;
+    taken.assign(c.n + c.n_edges, 0);            // nodes, then edges
+    for (uint32_t k = 0; k < c.n_edges; ++k) {
+        const uint32_t e = (uint32_t)order[k], u = h->edges[2 * e], v = h->edges[2 * e + 1];
+        if (!taken[u] && !taken[v]) taken[u] = taken[v] = taken[c.n + e] = 1;
+    }
+    uint32_t np = 0, ns = 0, *pairs = h->match_host + 2, *singles = pairs + 2 * (c.n / 2);
+    for (uint32_t e = 0; e < c.n_edges; ++e)
+        if (taken[c.n + e]) { pairs[2 * np] = h->edges[2 * e]; pairs[2 * np + 1] = h->edges[2 * e + 1]; ++np; }
+    for (uint32_t u = 0; u < c.n; ++u) if (!taken[u]) singles[ns++] = u;
+    h->match_host[0] = np;
+    h->match_host[1] = ns;
+}
+
 static swarm_status sample_matching_device(swarm_t h, uint32_t *npairs, uint32_t *nsingles) {
     const swarm_config &c = h->cfg;
+    if (c.n_edges <= HOST_MATCH_EDGES) {
+        if (h->match_round != h->round) match_on_host(h);
+        h->match_round = h->round;
+        *npairs = h->match_host[0];
+        *nsingles = h->match_host[1];
+        return SWARM_OK;
+    }
     if (h->match_round != h->round) SWARM_TRY(enqueue_matching(h, h->round));
     SWARM_HIP(h, hipEventSynchronize(h->match_ready));
     *npairs = h->match_host[0];
@@ -613,7 +654,7 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         singles.assign(h->match_host + 2 + 2 * (n / 2), h->match_host + 2 + 2 * (n / 2) + nsingles);
         // The next round's matching goes into the stream now, ahead of this round's long kernels, so
         // that the next call finds it ready without waiting for them (match_host was copied out above).
-        SWARM_TRY(enqueue_matching(h, h->round + 1));
+        if (c.n_edges > HOST_MATCH_EDGES) SWARM_TRY(enqueue_matching(h, h->round + 1));
     }
     std::vector<uint8_t> stale(n, 0);
     if (stale_host) {
@@ -645,9 +686,12 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
     const int group_mode[3] = {delta_mode == 2 ? 2 : 0, 1, 3};
 
     // Per-round metadata: one descriptor per pair (nodes, staleness, pending flags) and the unmatched
-    // nodes, staged in pinned memory and copied with one transfer.  (Carrying them in the kernel arguments
+    // nodes, staged in pinned memory and copied with one transfer, or, in a small round, read from there by its kernels.  (Carrying them in the kernel arguments
     // of small rounds instead was measured: the copy costs the step nothing, a second source of descriptors
     // costs the kernels 0.5 to 2 %.)
+    const uint8_t *descs = h->desc_dev;
+    bool in_place = false;
+    unsigned used_slot = 0;
     {
         uint8_t *slot = nullptr;
         unsigned slot_index = 0;
@@ -660,11 +704,19 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         for (uint32_t k = 0; k < nsingles; ++k)
             sg[k] = singles[k] | (fused ? draw_steps(c, singles[k], (uint32_t)h->round) << 16 : 0u) |
                     (h->pending[singles[k]] ? SINGLE_PENDING : 0u);
-        SWARM_HIP(h, hipMemcpyAsync(h->desc_dev, slot, h->desc_bytes, hipMemcpyHostToDevice, h->stream));
-        SWARM_HIP(h, hipEventRecord(h->desc_free[slot_index], h->stream));
+        in_place = (uint64_t)(npairs + nsingles) * ((c.d + PREFIX_TILE - 1) / PREFIX_TILE) <= DESC_IN_PLACE_WAVES;
+        if (in_place) {
+            descs = h->desc_mapped[slot_index];
+            used_slot = slot_index;
+        } else {
+            SWARM_HIP(h, hipMemcpyAsync(h->desc_dev, slot, h->desc_bytes, hipMemcpyHostToDevice, h->stream));
+            SWARM_HIP(h, hipEventRecord(h->desc_free[slot_index], h->stream));
+        }
     }
 
     GossipArgs a = gossip_args(h, (uint32_t)h->round, (uint32_t)(h->round % (c.stale_max + 1)));
+    a.pairs = (const PairDesc *)(descs + h->off_pairs);
+    a.singles = (const uint32_t *)(descs + h->off_singles);
     SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
     const bool inplace = c.apply_mode == SWARM_APPLY_INPLACE;
     if (c.codec == SWARM_CODEC_PREFIX) {
@@ -715,6 +767,7 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         SWARM_HIP(h, launch_scale_close(h->eps_slots_dev, h->scale_state_dev, a.slot_now, a.ring_depth, c.bits, npairs,
                                         h->stream));
 
+    if (in_place) SWARM_HIP(h, hipEventRecord(h->desc_free[used_slot], h->stream));      // its kernels are the slot's readers
     std::fill(h->pending.begin(), h->pending.end(), 0);
     h->round += 1;
     h->interactions += npairs;

@@ -179,3 +179,36 @@ def test_least_squares_run_in_one_launch(gpu, n, d, m, batch, H, bits, geometric
         for node in range(n):
             assert np.array_equal(run.read_codes(node), one.read_codes(node))
     assert run.counters(raise_on_range=False) == one.counters(raise_on_range=False)
+
+
+@pytest.mark.parametrize("n_edges", [1, 127, 128, 129])
+def test_matching_on_the_host_and_on_the_device(gpu, n_edges):
+    """Up to 128 edges are matched on the host, more on the device."""
+    edges = np.random.Generator(np.random.PCG64(n_edges)).permutation(wl.complete_graph(20))[:n_edges]
+    g, c = make_both(gpu, 20, 64, edges, 8, 1.0, 0, 0.0, 0, seed=5)
+    for _ in range(6):
+        want = c.sample_matching()
+        assert np.array_equal(g.sample_matching(), want.astype(np.uint32))
+        g.gossip_round()
+        c.gossip_round(want)
+        assert g.counters()["interactions"] == c.interactions
+
+
+@pytest.mark.parametrize("d", [504, 512 * 60, 512 * 140])
+def test_rounds_enqueued_without_waiting(gpu, d):
+    """Small rounds read their descriptors from the staging slots, larger ones from a copy: many rounds in flight give what
+    the same rounds give one at a time."""
+    n = 64
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    a, c = torch.rand(n, d, generator=gen, device="cuda") + 0.5, torch.randn(n, d, generator=gen, device="cuda")
+    swarms = [gpu.Swarm(n, d, wl.random_regular_graph(n, 4, 0), 8, 2.0 ** -4, 2, 0.1, 1, 3) for _ in range(2)]
+    for s in swarms:
+        s.set_objective_diag(a, c, 0.1)
+        s.models_view(gpu.COMM).copy_(c)
+    for _ in range(40):
+        swarms[0].round_fused(stale=swarms[0].sample_stale())
+    for _ in range(40):
+        swarms[1].round_fused(stale=swarms[1].sample_stale())
+        torch.cuda.synchronize()
+    assert torch.equal(swarms[0].models_view(gpu.COMM), swarms[1].models_view(gpu.COMM))
+    assert swarms[0].counters() == swarms[1].counters()
