@@ -1,17 +1,17 @@
 // A run of Algorithm 1 in one launch, for objectives and updates that are per-coordinate: an interaction reads and
 // writes only its own coordinate of the two models, the initiator's snapshot and (with local steps inside) the
-// initiator's objective data, so every 512-coordinate tile of the matrix can go through all interactions of the
-// run on its own.  One workgroup per tile keeps the tile of all n models in local memory (2 KiB per node) from the
-// first interaction to the last; its waves take the interactions in turn, in an order in which every interaction comes
+// initiator's objective data, so every tile of 256 or 512 coordinates can go through all interactions of the
+// run on its own.  One workgroup per tile keeps the tile of all n models in local memory (1 or 2 KiB per node) from
+// the first interaction to the last; its waves take the interactions in turn, in an order in which every interaction comes
 // after the earlier ones that touch its nodes, and a wave waits for those by the number of interactions each of its two
 // nodes has been through.  (Same arithmetic as interact_tile, same results bit for bit.)
 // An interaction reads what is not in local memory -- a_i, c_i and, unless the initiator's last interaction was its
 // own, the snapshot -- and writes the snapshot unless the next interaction of the node writes it again.
-// Bound by vector instructions (about 520 per interaction and tile at H = 3) and by how many interactions can run side
-// by side: 64 nodes x 2^20, H = 3, 8-bit codes, 256 interactions on a complete graph take 920 us, against 1636 us for 28
-// launches that moved 34 B per interaction-coordinate at 5.6 TB/s; 16 nodes x 300 000, 200 interactions 353 us
-// against 1511; 8 nodes x 8888, 64 interactions 79 us against 249.  (Without the requests ahead of the wait and the
-// skipped snapshots: 1046 us.)
+// Bound by vector instructions (about 520 per interaction and 512 coordinates at H = 3) and by the chain of dependent
+// interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 256 interactions on a complete graph take 780 us, against 1636 us for 28
+// launches that moved 34 B per interaction-coordinate at 5.6 TB/s; 16 nodes x 300 000, 200 interactions 302 us
+// against 1511; 8 nodes x 8888, 64 interactions 55 us against 249.  (Steps on the way, the first: nothing requested ahead of
+// the wait, every snapshot read and written 1046 us; non-temporal accesses to objective data and snapshots, 512-coordinate tiles 902.)
 // The wait always ends: the waves of a workgroup are resident together, and the earliest interaction that is not
 // finished waits for none.
 #include "diag_steps.hpp"
@@ -20,31 +20,88 @@
 
 namespace swarm {
 
+// The generator's words of an interaction: two per float4 of the lane, for the initiator's row and for the responder's.
+// F = 2: a call per row, shared by a lane pair as everywhere (pair_words).  F = 1: a lane pair has one group of 8
+// coordinates; the even lane calls for the initiator's row, the odd lane for the responder's, and the same exchange
+// leaves each lane with its words of both.
+template <int F>
+struct RowWords { uint32_t i[F][2], j[F][2]; };
+template <int F>
+__device__ __forceinline__ RowWords<F> row_words(uint64_t seed, uint32_t ni, uint32_t nj, uint32_t event, uint64_t tile, uint32_t lane) {
+    if constexpr (F == 2) {
+        const LaneRandom wi = row_random(seed, ni, event, tile, lane), wj = row_random(seed, nj, event, tile, lane);
+        return RowWords<F>{{{wi.a0, wi.a1}, {wi.b0, wi.b1}}, {{wj.a0, wj.a1}, {wj.b0, wj.b1}}};
+    } else {
+        const LaneRandom w = pair_words(stream(seed, TAG_SR, 0, (lane & 1u) ? nj : ni, event, tile * 32 + (lane >> 1)));
+        return RowWords<F>{{{w.a0, w.a1}}, {{w.b0, w.b1}}};
+    }
+}
+
+// What a run reads again: objective data and snapshots, of which all tiles under way together stay in cache.
+__device__ __forceinline__ f4 ldg(const float *row, uint32_t off) { return *(SWARM_GLOBAL const f4 *)at_bytes(uniform(row), 4u * off); }
+__device__ __forceinline__ void stg(float *row, uint32_t off, f4 v) { *(SWARM_GLOBAL f4 *)at_bytes(uniform(row), 4u * off) = v; }
+
+// H local steps of the lane's F float4 (diag_steps).  F = 1: the even lane of a pair draws for step q, the odd lane for
+// step q + 1, and the exchange leaves each lane with its words of both steps.
+template <bool NOISE, int F>
+__device__ __forceinline__ void run_steps(f4 w[F], const f4 a[F], const f4 c[F], uint32_t node, uint64_t tile, uint32_t lane,
+                                          uint32_t H, float lr, float sigma, uint64_t seed, uint32_t event) {
+    if constexpr (F == 2) {
+        diag_steps<NOISE>(w[0], w[1], a[0], a[1], c[0], c[1], node, tile, lane, H, lr, sigma, seed, event);
+    } else {
+        const float scale = -1.3862943611198906f * sigma * sigma;     // -2 ln 2 sigma^2
+        for (uint32_t q = 0; q < H; q += 2) {
+            f4 n0 = {0.f, 0.f, 0.f, 0.f}, n1 = n0;
+            if (NOISE) {
+                const LaneRandom r = pair_words(stream(seed, TAG_NOISE, q + (lane & 1u), node, event, tile * 32 + (lane >> 1)));
+                float z0, z1, z2, z3;
+                box_muller16(r.a0, scale, z0, z1);
+                box_muller16(r.a1, scale, z2, z3);
+                n0 = f4{z0, z1, z2, z3};
+                box_muller16(r.b0, scale, z0, z1);
+                box_muller16(r.b1, scale, z2, z3);
+                n1 = f4{z0, z1, z2, z3};
+            }
+            w[0] = diag_update(w[0], a[0], c[0], n0, lr);
+            if (q + 1 < H) w[0] = diag_update(w[0], a[0], c[0], n1, lr);
+        }
+    }
+}
+
 // LOCAL: 0 = the pending update is W_i - Xhat_i where the descriptor says so; 1 / 2 = local steps of the diagonal
-// objective in registers, with / without gradient noise.  RW: waves per workgroup.
-template <int BITS, int LOCAL, int RW>
-__global__ __launch_bounds__(RW * 64, 4) void interact_run_kernel(const RunArgs ra) {
-    extern __shared__ f4 rows[];                  // n x TILE floats
+// objective in registers, with / without gradient noise.  RW: waves per workgroup.  F: float4 per lane, a tile has 256 F
+// coordinates.
+template <int BITS, int LOCAL, int RW, int F>
+__global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(const RunArgs ra) {
+    constexpr uint32_t COORDS = 256 * F, ROW = 64 * F;           // of a tile: coordinates, float4
+    extern __shared__ f4 rows[];                  // n x COORDS floats
     __shared__ uint32_t done[RUN_MAX_NODES];      // interactions each node has been through
     const GossipArgs &a = ra.g;
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t tile = blockIdx.x;
-    const TilePos t = tile_pos<false>(tile, lane, a.d);
-    static_assert(RW * 64 >= RUN_MAX_NODES, "one thread per node");
-    if (threadIdx.x < a.n) done[threadIdx.x] = 0;
-    for (uint32_t u0 = wave; u0 < a.n; u0 += 4 * RW) {          // four rows in flight per wave
-        f4 v[4][2];
+    const uint64_t tile = blockIdx.x, base = tile * COORDS;
+    bool in[F];
+    uint32_t from[F], to[F];                      // coordinates of the tile: loaded from (past the row end: its last float4), stored to
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float *x = a.X + (uint64_t)min(u0 + i * RW, a.n - 1) * a.d + t.base;
-            v[i][0] = ldg_nt(x, t.oA);
-            v[i][1] = ldg_nt(x, t.oB);
+    for (int f = 0; f < F; ++f) {
+        to[f] = 4u * lane + 256u * f;
+        in[f] = base + to[f] < a.d;
+        from[f] = in[f] ? to[f] : (uint32_t)(a.d - 4 - base);
+    }
+    for (uint32_t u = threadIdx.x; u < a.n; u += RW * 64) done[u] = 0;
+    constexpr int AT_ONCE = 8 / F;                // rows in flight per wave
+    for (uint32_t u0 = wave; u0 < a.n; u0 += AT_ONCE * RW) {
+        f4 v[AT_ONCE][F];
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i) {
+            const float *x = a.X + (uint64_t)min(u0 + i * RW, a.n - 1) * a.d + base;
+#pragma unroll
+            for (int f = 0; f < F; ++f) v[i][f] = ldg_nt(x, from[f]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < AT_ONCE; ++i)
             if (u0 + i * RW < a.n) {
-                rows[(u0 + i * RW) * (TILE / 4) + lane] = v[i][0];
-                rows[(u0 + i * RW) * (TILE / 4) + lane + 64] = v[i][1];
+#pragma unroll
+                for (int f = 0; f < F; ++f) rows[(u0 + i * RW) * ROW + lane + 64 * f] = v[i][f];
             }
     }
     __syncthreads();
@@ -55,79 +112,82 @@ __global__ __launch_bounds__(RW * 64, 4) void interact_run_kernel(const RunArgs 
     // the wave stays together whatever the compiler makes of it.  What does not depend on the interactions before --
     // the next descriptor, its objective data, the random words -- is requested or computed ahead of the wait.
     RunDesc next = run_desc(ra.descs, wave, ra.count);
-    f4 aA = zero, aB = zero, cA = zero, cB = zero;
+    f4 oa[F] = {}, oc[F] = {};
     auto fetch_objective = [&](uint32_t node) {
-        const uint64_t at = (uint64_t)node * a.d + t.base;
-        aA = ldg_nt(ra.A + at, t.oA); aB = ldg_nt(ra.A + at, t.oB);
-        cA = ldg_nt(ra.C + at, t.oA); cB = ldg_nt(ra.C + at, t.oB);
+        const uint64_t at = (uint64_t)node * a.d + base;
+#pragma unroll
+        for (int f = 0; f < F; ++f) { oa[f] = ldg(ra.A + at, from[f]); oc[f] = ldg(ra.C + at, from[f]); }
     };
     if (LOCAL && wave < ra.count) fetch_objective(next.nodes & 0xFFFFu);
     for (uint32_t k = wave; k < ra.count; k += RW) {
         const RunDesc rd = next;
         next = run_desc(ra.descs, k + RW, ra.count);
         const uint32_t event = rd.event, flags = rd.flags, turn = rd.turn, ni = rd.nodes & 0xFFFFu, nj = rd.nodes >> 16;
-        const uint64_t at = (uint64_t)ni * a.d + t.base;
-        LaneRandom ni_words{}, nj_words{};
-        if (BITS > 0) {
-            ni_words = row_random(a.seed, ni, event, tile, lane);
-            nj_words = row_random(a.seed, nj, event, tile, lane);
-        }
+        const uint64_t at = (uint64_t)ni * a.d + base;
+        RowWords<F> words{};
+        if (BITS > 0) words = row_words<F>(a.seed, ni, nj, event, tile, lane);
         while ((first_lane(__hip_atomic_load(&done[ni], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) ^ (turn & 0xFFFFu)) |
                (first_lane(__hip_atomic_load(&done[nj], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) ^ (turn >> 16)))
             __builtin_amdgcn_s_sleep(1);
-        f4 *ri = rows + ni * (TILE / 4) + lane, *rj = rows + nj * (TILE / 4) + lane;
+        f4 *ri = rows + ni * ROW + lane, *rj = rows + nj * ROW + lane;
         float *hi = a.Xhat + at;
-        const f4 xiA = ri[0], xiB = ri[64], xjA = rj[0], xjB = rj[64];
-        f4 dA = zero, dB = zero;
+        f4 xi[F], xj[F], delta[F], average[F];
+#pragma unroll
+        for (int f = 0; f < F; ++f) { xi[f] = ri[64 * f]; xj[f] = rj[64 * f]; delta[f] = zero; }
         if (LOCAL || (flags & SEQ_HAS_DELTA)) {
-            f4 hA = xiA, hB = xiB;
-            if (!(flags & RUN_SNAPSHOT_IS_MODEL)) { hA = ldg_nt(hi, t.oA); hB = ldg_nt(hi, t.oB); }
-            f4 wA = hA, wB = hB;
+            f4 h[F], w[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) h[f] = xi[f];
+            if (!(flags & RUN_SNAPSHOT_IS_MODEL)) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) h[f] = ldg(hi, from[f]);
+            }
+#pragma unroll
+            for (int f = 0; f < F; ++f) w[f] = h[f];
             if (LOCAL) {
-                const f4 a0 = aA, a1 = aB, c0 = cA, c1 = cB;
+                f4 a0[F], c0[F];
+#pragma unroll
+                for (int f = 0; f < F; ++f) { a0[f] = oa[f]; c0[f] = oc[f]; }
                 if (k + RW < ra.count) fetch_objective(next.nodes & 0xFFFFu);
-                diag_steps<LOCAL == 1>(wA, wB, a0, a1, c0, c1, ni, tile, lane, (flags >> 8) & 0xFFu, ra.lr, ra.sigma, a.seed, event);
+                run_steps<LOCAL == 1, F>(w, a0, c0, ni, tile, lane, (flags >> 8) & 0xFFu, ra.lr, ra.sigma, a.seed, event);
             } else {
-                const float *wi = a.W + at;
-                wA = ldg_nt(wi, t.oA); wB = ldg_nt(wi, t.oB);
+#pragma unroll
+                for (int f = 0; f < F; ++f) w[f] = ldg_nt(a.W + at, from[f]);
             }
-            dA = wA - hA;
-            dB = wB - hB;
+#pragma unroll
+            for (int f = 0; f < F; ++f) delta[f] = w[f] - h[f];
         }
-        f4 avgA, avgB;
         if constexpr (BITS > 0) {
-            bool clampedA = false, clampedB = false;
-            int failsA = 0, failsB = 0;
-            int ziA[4], ziB[4], zjA[4], zjB[4];
-            const uint64_t ciA = round_float4<BITS>(xiA, ni_words.a0, ni_words.a1, a.inv_eps, ziA, clampedA);
-            const uint64_t ciB = round_float4<BITS>(xiB, ni_words.b0, ni_words.b1, a.inv_eps, ziB, clampedB);
-            const uint64_t cjA = round_float4<BITS>(xjA, nj_words.a0, nj_words.a1, a.inv_eps, zjA, clampedA);
-            const uint64_t cjB = round_float4<BITS>(xjB, nj_words.b0, nj_words.b1, a.inv_eps, zjB, clampedB);
             const float half_eps = 0.5f * a.eps;
-            avgA = averaged<BITS>(ziA, cjA, xiA, zero, a.inv_eps, half_eps, zjA, failsA, clampedA);
-            avgB = averaged<BITS>(ziB, cjB, xiB, zero, a.inv_eps, half_eps, zjB, failsB, clampedB);
-            if (flags & RUN_LAST_OF_I) {          // the register keeps the code of the node's last interaction
-                uint8_t *pub = ring_tile<BITS>(a, 0, ni, t);
-                if (t.inA) store_tile_code<BITS>(pub, t.cA / 4, ciA);
-                if (t.inB) store_tile_code<BITS>(pub, t.cB / 4, ciB);
+            uint64_t codes_i[F], codes_j[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                bool far = false;
+                int missed = 0, zi[4], zj[4];
+                codes_i[f] = round_float4<BITS>(xi[f], words.i[f][0], words.i[f][1], a.inv_eps, zi, far);
+                codes_j[f] = round_float4<BITS>(xj[f], words.j[f][0], words.j[f][1], a.inv_eps, zj, far);
+                average[f] = averaged<BITS>(zi, codes_j[f], xi[f], zero, a.inv_eps, half_eps, zj, missed, far);
+                fails += in[f] ? missed : 0;
+                clamped |= in[f] && far;
             }
-            if (flags & RUN_LAST_OF_J) {
-                uint8_t *pub = ring_tile<BITS>(a, 0, nj, t);
-                if (t.inA) store_tile_code<BITS>(pub, t.cA / 4, cjA);
-                if (t.inB) store_tile_code<BITS>(pub, t.cB / 4, cjB);
-            }
-            fails += (t.inA ? failsA : 0) + (t.inB ? failsB : 0);
-            clamped |= (t.inA && clampedA) || (t.inB && clampedB);
+            auto publish = [&](uint32_t node, const uint64_t codes[F]) {
+                uint8_t *pub = a.ring + (uint64_t)node * a.row_bytes + base * BITS / 8;
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    if (in[f]) store_tile_code<BITS>(pub, to[f] / 4, codes[f]);
+            };
+            if (flags & RUN_LAST_OF_I) publish(ni, codes_i);      // the register keeps the code of the node's last interaction
+            if (flags & RUN_LAST_OF_J) publish(nj, codes_j);
         } else {
-            avgA = 0.5f * (xiA + xjA);
-            avgB = 0.5f * (xiB + xjB);
+#pragma unroll
+            for (int f = 0; f < F; ++f) average[f] = 0.5f * (xi[f] + xj[f]);
         }
-        const f4 oA = avgA + dA, oB = avgB + dB;
-        ri[0] = oA; ri[64] = oB;
-        rj[0] = avgA; rj[64] = avgB;
-        if (!(flags & RUN_SNAPSHOT_SHORT)) {
-            if (t.inA) stg_nt(hi, t.cA, oA);
-            if (t.inB) stg_nt(hi, t.cB, oB);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const f4 o = average[f] + delta[f];
+            ri[64 * f] = o;
+            rj[64 * f] = average[f];
+            if (!(flags & RUN_SNAPSHOT_SHORT) && in[f]) stg(hi, to[f], o);
         }
         __hip_atomic_store(&done[ni], (turn & 0xFFFFu) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);   // every lane:
         __hip_atomic_store(&done[nj], (turn >> 16) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);       // no branch
@@ -136,21 +196,37 @@ __global__ __launch_bounds__(RW * 64, 4) void interact_run_kernel(const RunArgs 
     __syncthreads();
     for (uint32_t u = wave; u < a.n; u += RW)
         if (done[u] != 0) {
-            float *x = a.X + (uint64_t)u * a.d + t.base;
-            const f4 xA = rows[u * (TILE / 4) + lane], xB = rows[u * (TILE / 4) + lane + 64];
-            if (t.inA) stg_nt(x, t.cA, xA);
-            if (t.inB) stg_nt(x, t.cB, xB);
+            float *x = a.X + (uint64_t)u * a.d + base;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                if (in[f]) stg_nt(x, to[f], rows[u * ROW + lane + 64 * f]);
         }
 }
 
+template <int BITS, int LOCAL, int RW, int F>
+static void launch_tiles(const RunArgs &ra, hipStream_t st) {
+    const dim3 grid((unsigned)((ra.g.d + 256 * F - 1) / (256 * F)));
+    interact_run_kernel<BITS, LOCAL, RW, F><<<grid, RW * 64, (size_t)ra.g.n * 256 * F * sizeof(float), st>>>(ra);
+}
+
+// Waves per workgroup and size of its tile, by the number of nodes (how many interactions can run side by side, about n / 7,
+// and how much local memory a tile takes) and by whether there are tiles enough to fill the chip.  512-coordinate tiles
+// (F = 2) issue the fewest instructions, 256-coordinate ones leave room for more workgroups per compute unit and finish an
+// interaction sooner.  us per run, F = 2 with 2, 4, 8, 16 waves (n to 9, 19, 39, 78) and F = 1 with 4, 4, 8, 12:
+//   8 x 2^20, 128 interactions, H = 3       433   488       32 x 500 000, 256, H = 3            400   423
+//   8 x 8888, 64, H = 3                      90    55       64 x 2^20, 256, H = 3               989   942
+//   16 x 300 000, 200, geometric H = 5      356   302       64 x 4 000 000, 256, geometric 5   4442  3842
+constexpr uint64_t RUN_FEW_COORDS = 1u << 18;     // 512 tiles of 512
+
 template <int BITS, int LOCAL>
 static void launch_waves(const RunArgs &ra, hipStream_t st) {
-    const dim3 grid((unsigned)((ra.g.d + TILE - 1) / TILE));
-    const size_t lds = (size_t)ra.g.n * TILE * sizeof(float);
-    // as many waves as a compute unit holds at this register count, shared by the workgroups that its local memory holds
-    if (ra.g.n <= 19) interact_run_kernel<BITS, LOCAL, 4><<<grid, 4 * 64, lds, st>>>(ra);
-    else if (ra.g.n <= 39) interact_run_kernel<BITS, LOCAL, 8><<<grid, 8 * 64, lds, st>>>(ra);
-    else interact_run_kernel<BITS, LOCAL, 16><<<grid, 16 * 64, lds, st>>>(ra);
+    const uint32_t n = ra.g.n;
+    const bool few = ra.g.d < RUN_FEW_COORDS;
+    if (n <= 9 && !few) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
+    else if (n <= 19) launch_tiles<BITS, LOCAL, 4, 1>(ra, st);
+    else if (n <= 39 && !few) launch_tiles<BITS, LOCAL, 8, 2>(ra, st);
+    else if (n <= 39) launch_tiles<BITS, LOCAL, 8, 1>(ra, st);
+    else launch_tiles<BITS, LOCAL, 12, 1>(ra, st);
 }
 
 template <int BITS>
