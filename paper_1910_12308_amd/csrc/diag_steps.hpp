@@ -6,8 +6,8 @@
 // the group in the tile's first half, the odd lane for the one in the second half, and they swap
 // the halves they do not need -- one generator call per lane and step for 8 normals.
 // With noise the kernels that take five steps in registers are bound by vector instructions, not by memory: a step
-// issues 101 of them per lane (33 for the generator, 4 for the exchange, 40 for the four Box-Muller pairs, 24 for the
-// update).  It was 121 before the generator's three-input exclusive-ors and the exchange folded into the selects:
+// issues 104 of them per lane (33 for the generator, 4 for the exchange, 40 for the four Box-Muller pairs, 24 for the
+// update, 3 around them).  It was 121 before the generator's three-input exclusive-ors and the exchange folded into the selects:
 // 32 nodes x 6 875 000, H = 5, 8-bit codes: 744 -> 704 us per one-pass round.
 #pragma once
 #include "gossip_common.hpp"
