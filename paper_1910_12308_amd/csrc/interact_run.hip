@@ -216,12 +216,15 @@ static void launch_tiles(const RunArgs &ra, hipStream_t st) {
 //   8 x 2^20, 128 interactions, H = 3       433   488       32 x 500 000, 256, H = 3            400   423
 //   8 x 8888, 64, H = 3                      90    55       64 x 2^20, 256, H = 3               989   942
 //   16 x 300 000, 200, geometric H = 5      356   302       64 x 4 000 000, 256, geometric 5   4442  3842
-constexpr uint64_t RUN_FEW_COORDS = 1u << 18;     // 512 tiles of 512
+// Where the tiles become many enough, 128 interactions, F = 1 and F = 2:
+//   8 x 262 144   159   214     8 x 393 216   202   218     8 x 524 288   255   233
+//   31 x 131 072   74    77     31 x 196 608   95   112     31 x 262 144   125   118
+constexpr uint64_t few_coords(uint32_t n) { return n <= 9 ? 1u << 19 : 1u << 18; }
 
 template <int BITS, int LOCAL>
 static void launch_waves(const RunArgs &ra, hipStream_t st) {
     const uint32_t n = ra.g.n;
-    const bool few = ra.g.d < RUN_FEW_COORDS;
+    const bool few = ra.g.d < few_coords(n);
     if (n <= 9 && !few) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
     else if (n <= 19) launch_tiles<BITS, LOCAL, 4, 1>(ra, st);
     else if (n <= 39 && !few) launch_tiles<BITS, LOCAL, 8, 2>(ra, st);

@@ -69,12 +69,12 @@ def diag_swarm(gpu, n, d, bits, H, sigma, seed, geometric=False, objective=True)
     return s
 
 
-# runs of Algorithm 1 in one launch (2, 4, 8 and 12 waves per tile of 256 or, from 2^18 coordinates on, 512; the most nodes
+# runs of Algorithm 1 in one launch (2, 4, 8 and 12 waves per tile of 256 or, from 2^19 (up to 9 nodes) or 2^18 coordinates on, 512; the most nodes
 # local memory holds) and, with one node more, in one launch per level: all equal one call per interaction, bit for bit
 @pytest.mark.parametrize("n,d,bits,H,sigma,geometric,objective", [
     (2, 8, 8, 1, 0.1, False, True), (3, 520, 2, 2, 0.05, True, True), (19, 504, 4, 3, 0.1, False, True),
     (20, 1032, 16, 2, 0.0, False, True), (39, 8, 8, 5, 0.1, True, True), (40, 2056, 8, 1, 0.1, False, True),
-    (78, 1544, 4, 2, 0.1, False, True), (79, 1544, 4, 2, 0.1, False, True), (9, (1 << 18) + 8, 8, 3, 0.1, True, True),
+    (78, 1544, 4, 2, 0.1, False, True), (79, 1544, 4, 2, 0.1, False, True), (9, (1 << 19) + 8, 8, 3, 0.1, True, True),
     (10, (1 << 18) - 8, 8, 3, 0.1, False, True), (20, 1 << 18, 4, 2, 0.05, False, True), (39, (1 << 18) - 264, 8, 1, 0.1, False, True), (40, 520, 0, 2, 0.1, False, True),
     (20, 520, 8, 0, 0.0, False, False), (5, 1544, 0, 0, 0.0, False, False)])
 def test_run_of_algorithm1_in_one_launch(gpu, n, d, bits, H, sigma, geometric, objective):
