@@ -213,3 +213,30 @@ def test_rounds_enqueued_without_waiting(gpu, d):
         torch.cuda.synchronize()
     assert torch.equal(swarms[0].models_view(gpu.COMM), swarms[1].models_view(gpu.COMM))
     assert swarms[0].counters() == swarms[1].counters()
+
+
+# both reads stale, codes of 2 and 4 bits: one kernel up to three steps from 2^15 tiles on (8 nodes of 2^21 coordinates
+# are exactly as many), another below and for more steps
+@pytest.mark.parametrize("bits,H,d,inplace", [
+    (4, 3, 1 << 21, False), (4, 3, (1 << 21) - 2048, False), (4, 4, 1 << 21, False), (2, 3, (1 << 21) + 8, False),
+    (2, 4, 4104, False), (4, 3, 1 << 21, True), (2, 1, 1 << 21, True)])
+def test_one_pass_round_with_stale_reads_equals_steps_then_gossip(gpu, bits, H, d, inplace):
+    n, pairs = 8, [(0, 5), (1, 2), (3, 6), (4, 7)]
+    gen = torch.Generator(device="cuda").manual_seed(bits + H)
+    a, c = torch.rand(n, d, generator=gen, device="cuda") + 0.5, torch.randn(n, d, generator=gen, device="cuda")
+    X = [torch.randn(n, d, generator=gen, device="cuda") for _ in range(2)]
+    swarms = [gpu.Swarm(n, d, wl.complete_graph(n), bits, 0.5, H, 0.1, 1, 7,
+                        apply_mode=gpu.INPLACE if inplace else gpu.DEFERRED) for _ in range(2)]
+    for s in swarms:
+        s.set_objective_diag(a, c, 0.1)
+        s.models_view(gpu.COMM).copy_(X[0])
+        s.gossip_round(pairs)
+        s.models_view(gpu.COMM).copy_(X[1])
+    ones = np.ones(n, dtype=np.uint8)
+    swarms[0].round_fused(pairs, ones)
+    swarms[1].local_steps()
+    swarms[1].gossip_round(pairs, ones)
+    assert torch.equal(swarms[0].models_view(gpu.COMM), swarms[1].models_view(gpu.COMM))
+    for node in (0, 7):
+        assert np.array_equal(swarms[0].read_codes(node), swarms[1].read_codes(node))
+    assert swarms[0].counters(raise_on_range=False) == swarms[1].counters(raise_on_range=False)
