@@ -196,7 +196,7 @@ struct LsqSplitArgs {
     float lr;
 };
 
-// INTERACT: grid row = one step of Algorithm 1 (descriptor in ia.descs): steps from the initiator's snapshot,
+// INTERACT: grid row = one step of Algorithm 1 (descriptor in ia.descs or ia.one): steps from the initiator's snapshot,
 // then the interaction on this slice.  Otherwise grid row = one slot of sa.slots, steps from sa.base.
 template <int BITS, bool INTERACT>
 __global__ __launch_bounds__(SW * 64) void lsq_split_kernel(const LsqSplitArgs sa, const InteractArgs ia) {
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(SW * 64) void lsq_split_kernel(const LsqSplitArgs s
     uint32_t node, H = sa.H, event = sa.event;
     const float *base = sa.base;
     if (INTERACT) {
-        sd = ia.descs[slot];
+        sd = ia.descs ? ia.descs[slot] : ia.one;
         node = sd.ni; H = (sd.flags >> 8) & 0xFFu; event = sd.event;
         base = ia.g.Xhat;
     } else {
@@ -355,7 +355,7 @@ static uint32_t wide_slices(uint64_t d, uint32_t n) {
     return (uint32_t)((blocks + each - 1) / each);
 }
 
-hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n) {
+hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
     hipError_t e;
     if (!lsq_split_fits(d, n)) {
         o.wide_slices = wide_slices(d, n);
@@ -367,7 +367,7 @@ hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n) {
     if ((e = hipMalloc((void **)&o.part, o.part_bytes)) != hipSuccess) return e;
     o.launches = 0;
     if ((e = hipMemset(o.part, 0xFF, o.part_bytes)) != hipSuccess) return e;      // no word carries the tag of a launch yet
-    if (!lsq_run_fits(d, n, o.batch)) return hipSuccess;
+    if (!merge_runs) return hipSuccess;
     o.run_part_bytes = lsq_run_bytes(d, o.batch);
     if ((e = hipMalloc((void **)&o.run_part, o.run_part_bytes)) != hipSuccess) return e;
     return hipMemset(o.run_part, 0xFF, o.run_part_bytes);
@@ -419,14 +419,14 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
     return hipGetLastError();
 }
 
-hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, uint32_t count,
+hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, const SeqDesc &one, uint32_t count,
                                LsqObjective &o, float lr, hipStream_t st) {
     if (count == 0) return hipSuccess;
     if (!o.part) return hipErrorInvalidValue;
     LsqSplitArgs sa;
     const hipError_t e = split_args(sa, nullptr, const_cast<float *>(g.W), o, LocalSlots{}, g.counters, g.d, 0, lr, g.seed, 0, st);
     if (e != hipSuccess) return e;
-    const InteractArgs ia{g, descs_dev, SeqDesc{}, nullptr, nullptr, 0.f, lr};
+    const InteractArgs ia{g, descs_dev, one, nullptr, nullptr, 0.f, lr};
     const dim3 grid(sa.slices, count, 1);
     switch (bits) {
         case 0: lsq_split_kernel<0, true><<<grid, SW * 64, 0, st>>>(sa, ia); break;

@@ -11,6 +11,8 @@
 // its 2.5 us) and an update, two to four interactions run side by side.  8 nodes x 4096, batch 32, H = 2, 200
 // interactions: 0.98 ms, against 1.75 ms for 112 launches of one interaction per 8 workgroups and row; a single
 // interaction 12.6 us against 43.5 in two launches and a copy.  All workgroups on one die: no faster (1.01 ms).
+// Four waves per workgroup are room for four interactions side by side: graphs that let many more run at once keep a launch
+// per level (LSQ_RUN_WIDTH in swarm_api.hip).
 // All workgroups are resident together (at most 64), the earliest unfinished interaction waits for none, and every
 // wait is bounded, so that all waves end whatever happens to the others.
 #include <type_traits>

@@ -52,14 +52,16 @@ struct LocalSlots;
 struct DeviceCounters;
 struct SeqDesc;
 // Allocates the exchange buffers of the split form when ceil(d / 512) * n workgroups are few enough to be
-// resident together (they wait for one another inside the kernel).
-hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n);
+// resident together (they wait for one another inside the kernel), and with merge_runs also those of the form that takes
+// a run of Algorithm 1 in one launch (lsq_run_fits).
+hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs);
 hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const LocalSlots &slots,
                             DeviceCounters *counters, uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed,
                             uint32_t event, hipStream_t st);
 // Steps of Algorithm 1 on disjoint nodes in one kernel (split form only): each initiator's local steps
-// (count taken from its descriptor) from its snapshot, then its interaction.
-hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, uint32_t count,
+// (count taken from its descriptor) from its snapshot, then its interaction.  descs_dev, or the single interaction
+// `one` when it is null.
+hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, const SeqDesc &one, uint32_t count,
                                LsqObjective &o, float lr, hipStream_t st);
 void free_lsq(LsqObjective &o);
 

@@ -33,6 +33,12 @@ constexpr uint64_t DESC_IN_PLACE_WAVES = 4096;
 // kernel runs a round ahead and beside the round's kernels, so for more edges a single round is sooner done with it
 // (31 x 4096, 465 edges, one round and a wait: 28.6 us, 37.8 on the host).
 constexpr uint32_t HOST_MATCH_EDGES = 128;
+// Least-squares runs of Algorithm 1 are merged into one launch (lsq_run_kernel) on graphs where at most so many
+// interactions run side by side: the kernel has room for four, the form with a launch per level takes them all.  us per
+// run, by levels and merged, at side by side: batch 32, H = 2: 8 nodes x 8192, 256 interactions, 1.8: 2275 and 1426;
+// 24 x 4096, 1000, 4.7: 3175 and 2420; 32 x 512, 1000, 6.3: 2396 and 2202; 48 x 2048, 256, 9.1: 498 and 577;
+// 64 x 512, 256, 11.1: 393 and 574; batch 16, H = 5: 32 x 4096, 1000, 6.7: 3743 and 3310; 64 x 2048, 256, 11.6: 586 and 890.
+constexpr double LSQ_RUN_WIDTH = 7.0;
 constexpr uint32_t SEQ_CHUNK = 1u << 15;                              // interactions of Algorithm 1 staged per upload
 constexpr size_t SEQ_ENTRY_BYTES = sizeof(swarm::SeqDesc) + 3 * sizeof(uint32_t);
 
@@ -436,6 +442,25 @@ swarm_status swarm_set_objective_diag(swarm_t h, const float *a_dev, const float
     return SWARM_OK;
 }
 
+// How many interactions of Algorithm 1 can run side by side on the handle's graph: a run of 32 per node over its number of
+// dependency levels.  Of the graph alone (a fixed seed): every call on a handle has to take the same form of the
+// least-squares steps, whose residuals are summed in another order in each.
+static double interactions_side_by_side(swarm_t h) {
+    const uint32_t n = h->cfg.n, count = 32 * n;
+    std::vector<uint32_t> last(n, 0);
+    uint32_t levels = 1;
+    for (uint32_t t = 0; t < count; ++t) {
+        const Words4 w = stream(0, TAG_PICK, 0, 0, t, 0);
+        const uint32_t i = scaled_index(w.w0, n);
+        const std::vector<uint32_t> &nb = h->adj[i];
+        if (nb.empty()) continue;
+        const uint32_t j = nb[scaled_index(w.w1, (uint32_t)nb.size())];
+        last[i] = last[j] = std::max(last[i], last[j]) + 1;
+        levels = std::max(levels, last[i]);
+    }
+    return (double)count / levels;
+}
+
 swarm_status swarm_set_objective_lsq(swarm_t h, const float *A_dev, const float *b_dev, uint32_t m_rows,
                                      uint32_t batch) {
     if (!h) return SWARM_EINVAL;
@@ -444,7 +469,8 @@ swarm_status swarm_set_objective_lsq(swarm_t h, const float *A_dev, const float 
     free_lsq(h->lsq);
     h->lsq = LsqObjective{};
     h->lsq.A = A_dev; h->lsq.b = b_dev; h->lsq.m_rows = m_rows; h->lsq.batch = batch;
-    const hipError_t e = alloc_lsq(h->lsq, h->cfg.d, h->cfg.n);
+    const bool merge_runs = lsq_run_fits(h->cfg.d, h->cfg.n, batch) && interactions_side_by_side(h) <= LSQ_RUN_WIDTH;
+    const hipError_t e = alloc_lsq(h->lsq, h->cfg.d, h->cfg.n, merge_runs);
     if (e != hipSuccess) return fail(h, e == hipErrorOutOfMemory ? SWARM_ENOMEM : SWARM_EDEVICE,
                                      std::string("least-squares exchange buffers: ") + hipGetErrorString(e));
     h->kind = OBJ_LSQ;
@@ -804,13 +830,14 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j) {
     }
     bool has_delta = h->pending[i] != 0;
     const GossipArgs a = gossip_args(h, (uint32_t)h->interactions, 0);
-    const bool lsq_run = c.H > 0 && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.run_part;
-    if (lsq_run) {                               // steps and interaction in one launch, the one a run of them takes
-        const uint32_t steps = draw_steps(c, i, (uint32_t)h->interactions);
-        const RunDesc one{i | j << 16, (uint32_t)h->interactions,
-                          SEQ_HAS_DELTA | RUN_LAST_OF_I | RUN_LAST_OF_J | RUN_LAST_LED | steps << 8, 0u};
+    const bool lsq_inside = c.H > 0 && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.part;
+    if (lsq_inside) {                            // steps and interaction in one launch, in the form a run of them takes
+        const uint32_t event = (uint32_t)h->interactions, steps = draw_steps(c, i, event);
+        const RunDesc run{i | j << 16, event, SEQ_HAS_DELTA | RUN_LAST_OF_I | RUN_LAST_OF_J | RUN_LAST_LED | steps << 8, 0u};
+        const SeqDesc one{i, j, event, SEQ_HAS_DELTA | steps << 8};
         SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
-        SWARM_HIP(h, launch_lsq_run(a, c.bits, nullptr, one, 1, steps, h->lsq, c.lr, h->stream));
+        if (h->lsq.run_part) SWARM_HIP(h, launch_lsq_run(a, c.bits, nullptr, run, 1, steps, h->lsq, c.lr, h->stream));
+        else SWARM_HIP(h, launch_lsq_interact(a, c.bits, nullptr, one, 1, h->lsq, c.lr, h->stream));
         SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 1));
         h->timed_gossip += 1;
     } else if (c.H > 0 && h->kind != OBJ_NONE) {
@@ -821,7 +848,7 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j) {
         h->timed_local += 1;
         has_delta = true;
     }
-    if (!lsq_run) {
+    if (!lsq_inside) {
         SWARM_TRY(record_timing(h, h->ev_gossip, h->timed_gossip, 0));
         const SeqDesc one{i, j, (uint32_t)h->interactions, has_delta ? SEQ_HAS_DELTA : 0u};
         if (c.codec == SWARM_CODEC_PREFIX) SWARM_HIP(h, launch_prefix_interact(a, nullptr, one, 1, h->stream));
@@ -987,7 +1014,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
         for (uint32_t l = 0; l < levels; ++l) {
             const uint32_t off = level_start[l], width = level_start[l + 1] - off;
             if (lsq_inside) {
-                SWARM_HIP(h, launch_lsq_interact(a, c.bits, descs_dev + off, width, h->lsq, c.lr, h->stream));
+                SWARM_HIP(h, launch_lsq_interact(a, c.bits, descs_dev + off, SeqDesc{}, width, h->lsq, c.lr, h->stream));
                 continue;
             }
             if (with_steps && !steps_inside) {

@@ -1,0 +1,143 @@
+// Runs calls of libswarm.so on a stand-in for the HIP runtime that keeps device memory on the host and executes nothing, and
+// prints what the library asked of it: kernel launches by name, event records and waits, the status of each call.
+// The symbols below are found ahead of the real runtime's, which the library is linked against.  No GPU is touched.
+//   host_calls run      n d bits H batch graph count       swarm_run_sequential; batch 0: diagonal objective, else least squares
+//   host_calls interact n d bits H batch graph             swarm_interact(0, a neighbour)
+//   host_calls steps    n d bits H batch graph             swarm_local_steps(all)
+//   host_calls rounds   n d bits H fail count              `count` rounds of one pair; the launch numbered `fail` fails (0: none)
+// graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
+#include <cxxabi.h>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "swarm.h"
+
+namespace {
+struct Dim3 { uint32_t x, y, z; };
+bool logging = false;
+int launches = 0, fail_at = 0, last_error = 0;
+struct Call { Dim3 grid, block; size_t shared; void *stream; } pushed;
+std::map<const void *, std::string> &kernels() { static std::map<const void *, std::string> k; return k; }
+int event_number(const void *e) { return (int)(intptr_t)e; }
+}  // namespace
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *, void *, int *) {
+    int status;
+    char *text = abi::__cxa_demangle(name, nullptr, nullptr, &status);
+    std::string plain = status == 0 ? text : name;
+    std::free(text);
+    if (plain.rfind("void ", 0) == 0) plain.erase(0, 5);
+    kernels()[host] = plain.substr(plain.find("swarm::") + 7, plain.find('(') - plain.find("swarm::") - 7);
+}
+int __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t shared, void *stream) { pushed = Call{grid, block, shared, stream}; return 0; }
+int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shared, void **stream) {
+    *grid = pushed.grid; *block = pushed.block; *shared = pushed.shared; *stream = pushed.stream;
+    return 0;
+}
+int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3 block, void **, size_t shared, void *) {
+    if (!logging) return 0;
+    std::printf("launch %s grid %u %u block %u shared %zu\n", kernels()[kernel].c_str(), grid.x, grid.y, block.x, shared);
+    if (++launches == fail_at) last_error = 1;
+    return last_error;
+}
+int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
+const char *hipGetErrorString(int) { return "stand-in error"; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipMalloc(void **p, size_t n) { *p = std::calloc(n ? n : 1, 1); return *p ? 0 : 2; }
+int hipFree(void *p) { std::free(p); return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+int hipHostFree(void *p) { return hipFree(p); }
+int hipHostGetDevicePointer(void **d, void *p, unsigned) { *d = p; return 0; }
+int hipMemset(void *, int, size_t) { return 0; }
+int hipMemsetAsync(void *, int, size_t, void *) { return 0; }
+int hipMemcpy(void *, const void *, size_t, int) { return 0; }
+int hipMemcpyAsync(void *, const void *, size_t, int, void *) {
+    if (logging) std::printf("copy\n");
+    return 0;
+}
+int hipMemcpy2DAsync(void *, size_t, const void *, size_t, size_t, size_t, int, void *) { return 0; }
+int hipGetSymbolAddress(void **p, const void *) { static char symbol[64]; *p = symbol; return 0; }
+int hipStreamCreateWithFlags(void **s, unsigned) { *s = (void *)1; return 0; }
+int hipStreamDestroy(void *) { return 0; }
+int hipStreamSynchronize(void *) { return 0; }
+int hipEventCreateWithFlags(void **e, unsigned) { static intptr_t next = 0; *e = (void *)++next; return 0; }
+int hipEventCreate(void **e) { return hipEventCreateWithFlags(e, 0); }
+int hipEventDestroy(void *) { return 0; }
+int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0.f; return 0; }
+int hipEventRecord(void *e, void *) { if (logging) std::printf("record %d\n", event_number(e)); return 0; }
+int hipEventSynchronize(void *e) { if (logging) std::printf("wait %d\n", event_number(e)); return 0; }
+}
+
+namespace {
+std::vector<uint32_t> edges_of(const std::string &graph, uint32_t n) {
+    std::vector<uint32_t> e;
+    const uint32_t hubs = graph == "star" ? 1 : graph.rfind("hubs", 0) == 0 ? (uint32_t)std::atoi(graph.c_str() + 4) : 0;
+    for (uint32_t u = 0; u < n; ++u)
+        for (uint32_t v = u + 1; v < n; ++v) {
+            const bool next = v == u + 1, around = u == 0 && v == n - 1 && n > 2;
+            if (graph == "complete" || (graph == "path" && next) || (graph == "ring" && (next || around)) ||
+                (hubs && u < hubs && v >= hubs)) {
+                e.push_back(u);
+                e.push_back(v);
+            }
+        }
+    return e;
+}
+}  // namespace
+
+int main(int argc, char **argv) {
+    if (argc < 8) return 2;
+    const std::string call = argv[1];
+    const uint32_t batch = call == "rounds" ? 0u : (uint32_t)std::atoi(argv[6]);
+    const std::string graph = call == "rounds" ? "complete" : argv[7];
+    swarm_config c{};
+    c.n = (uint32_t)std::atoi(argv[2]);
+    c.d = std::strtoull(argv[3], nullptr, 10);
+    c.bits = (uint32_t)std::atoi(argv[4]);
+    c.H = (uint32_t)std::atoi(argv[5]);
+    const std::vector<uint32_t> edges = edges_of(graph, c.n);
+    c.edges = edges.data();
+    c.n_edges = (uint32_t)(edges.size() / 2);
+    c.eps = 0.5f;
+    c.lr = 0.1f;
+    c.seed = 1;
+    swarm_t h = nullptr;
+    const float *data = reinterpret_cast<const float *>(64);        // objective data: the host never reads them
+    if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
+    swarm_status rc = batch ? swarm_set_objective_lsq(h, data, data, 64, batch) : swarm_set_objective_diag(h, data, data, 0.1f);
+    if (rc != SWARM_OK) { std::printf("objective: %s\n", swarm_last_error(h)); return 1; }
+    float *snapshots = nullptr;
+    swarm_models_ptr(h, SWARM_MODELS_SNAP, &snapshots);              // created ahead of the log
+    logging = true;
+    if (call == "run") {
+        uint32_t reported = 0;
+        rc = swarm_run_sequential(h, (uint32_t)std::atoi(argv[8]), nullptr, &reported);
+        std::printf("reported %u\n", reported);
+    } else if (call == "interact") {
+        rc = swarm_interact(h, edges[0], edges[1]);
+    } else if (call == "steps") {
+        rc = swarm_local_steps(h, nullptr, 0);
+    } else if (call == "rounds") {
+        fail_at = std::atoi(argv[6]);
+        const uint32_t pair[2] = {0, 1};
+        for (int r = 0; r < std::atoi(argv[7]); ++r) {
+            rc = swarm_round_fused(h, pair, 1, nullptr);
+            std::printf("status %d\n", rc);
+        }
+    } else {
+        return 2;
+    }
+    logging = false;
+    std::printf("status %d\n", rc);
+    swarm_destroy(h);
+    return 0;
+}

@@ -135,11 +135,12 @@ def test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, arithmetic):
     assert np.abs(W - want)[off].max(initial=0.0) <= kink
 
 
-# small least-squares swarms: a run of Algorithm 1 in one launch (up to 64 nodes, 64 groups of 128 columns, batch 32 and
-# 2048 words exchanged per step); beyond each of these limits the form with a launch per level
+# small least-squares swarms: a run of Algorithm 1 in one launch (graphs that let at most seven interactions run side by
+# side, up to 64 groups of 128 columns, batch 32 and 2048 words exchanged per step: tests/test_host_calls.py); beyond each
+# of these limits (64 and 65 nodes of a 4-regular graph among them) the form with a launch per level
 @pytest.mark.parametrize("n,d,m,batch,H,bits,geometric", [
     (2, 8, 5, 4, 1, 8, False), (3, 136, 20, 12, 3, 2, True), (8, 1032, 30, 16, 2, 4, False), (5, 2600, 40, 20, 2, 16, True),
-    (4, 8192, 16, 32, 1, 8, False), (64, 512, 9, 32, 2, 0, False), (65, 512, 9, 32, 2, 8, False), (5, 1024, 70, 36, 2, 8, False),
+    (4, 8192, 16, 32, 1, 8, False), (24, 512, 9, 32, 2, 8, False), (64, 512, 9, 32, 2, 0, False), (65, 512, 9, 32, 2, 8, False), (5, 1024, 70, 36, 2, 8, False),
     (4, 8200, 16, 16, 1, 8, False)])
 def test_least_squares_run_in_one_launch(gpu, n, d, m, batch, H, bits, geometric):
     A, b, _ = wl.least_squares_data(n, d, m, 2)

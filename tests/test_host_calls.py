@@ -1,0 +1,47 @@
+"""Which kernels the library launches, and how it guards its staging memory: its host code on the CPU, with host_calls.cpp in
+place of the HIP runtime."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import paper_1910_12308_amd as swarm
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def host_calls(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_calls") / "host_calls")
+    package = os.path.dirname(swarm.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "host_calls.cpp"), "-o", exe, "-L", package, "-l:libswarm.so", "-Wl,-rpath," + package,
+                    "-Wl,--allow-shlib-undefined"], check=True)
+
+    def call(*args):
+        out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True)
+        assert out.returncode == 0, out.stdout + out.stderr
+        return out.stdout.splitlines()
+    return call
+
+
+def kernels(lines):
+    return [re.match(r"launch (\w+)", ln).group(1) for ln in lines if ln.startswith("launch")]
+
+
+# Least squares, runs of Algorithm 1: one launch on graphs where at most seven interactions run side by side (the kernel has
+# room for four), a launch per level otherwise and beyond 64 nodes, a batch of 32, 2048 words and 64 groups of 128 columns
+@pytest.mark.parametrize("n,d,batch,graph,merged", [
+    (8, 4096, 32, "complete", True), (16, 8192, 32, "complete", True), (32, 4096, 32, "complete", True),
+    (48, 2048, 32, "complete", False), (64, 2048, 16, "complete", False), (64, 512, 32, "ring", False),
+    (64, 512, 32, "star", True), (65, 512, 16, "star", False), (5, 1024, 36, "complete", False), (5, 8200, 16, "complete", False),
+    (2, 4104, 32, "complete", True), (2, 8192, 32, "complete", True), (2, 8200, 12, "complete", False)])
+def test_least_squares_runs(host_calls, n, d, batch, graph, merged):
+    run = host_calls("run", n, d, 8, 2, batch, graph, 40)
+    levels = int(next(ln for ln in run if ln.startswith("reported")).split()[1])
+    assert kernels(run) == (["lsq_run_kernel"] if merged else ["lsq_split_kernel"] * levels) and levels > 1
+    # a single interaction takes the same form, so that it gives the same sums
+    one = host_calls("interact", n, d, 8, 2, batch, graph)
+    assert kernels(one) == ["lsq_run_kernel" if merged else "lsq_split_kernel"] and run[-1] == one[-1] == "status 0"
