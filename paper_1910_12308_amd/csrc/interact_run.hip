@@ -14,6 +14,8 @@
 // the wait, every snapshot read and written 1046 us; non-temporal accesses to objective data and snapshots, 512-coordinate tiles 902.)
 // The wait always ends: the waves of a workgroup are resident together, and the earliest interaction that is not
 // finished waits for none.
+#include <algorithm>
+
 #include "diag_steps.hpp"
 #include "interact_run.hpp"
 #include "round_tile.hpp"
@@ -219,17 +221,51 @@ static void launch_tiles(const RunArgs &ra, hipStream_t st) {
 // Where the tiles become many enough, 128 interactions, F = 1 and F = 2:
 //   8 x 262 144   159   214     8 x 393 216   202   218     8 x 524 288   255   233
 //   31 x 131 072   74    77     31 x 196 608   95   112     31 x 262 144   125   118
+// The sizes between were measured against one launch per level only (10, 12, 15, 19, 20, 24, 39, 40, 48 and 78 nodes, complete
+// graphs, rings and paths: interact_run_pays), not against the other forms.
 constexpr uint64_t few_coords(uint32_t n) { return n <= 9 ? 1u << 19 : 1u << 18; }
+
+struct TileForm { uint32_t waves, f; };
+static TileForm tile_form(uint32_t n, uint64_t d) {
+    const bool few = d < few_coords(n);
+    if (n <= 9 && !few) return {2, 2};
+    if (n <= 19) return {4, 1};
+    if (n <= 39) return {8, few ? 1u : 2u};
+    return {12, 1};
+}
+
+// Whether one launch is sooner done with m interactions that form so many dependency levels than a launch per level.
+//  - It reads and writes every node's model once, whether or not the run touches it, and 12 to 16 B per
+//    interaction-coordinate instead of 32 and two codes, so it needs enough interactions: 64 nodes x 2^20, H = 3, 8-bit
+//    codes, 16 interactions 125 us with one launch per level, 135 in one launch; 24: 176 and 166; 32 nodes: 8 interactions
+//    77 and 98, 12: 102 and 97.  Interactions that do not depend on one another at all (one level) have nothing to keep.
+//  - Below 3 x 2^17 coordinates a level is all launch (5 us): one launch is sooner done whatever the graph (star of 64 nodes
+//    x 200 000, H = 3, 64 interactions: 443 and 235 us; x 400 000: 459 and 424; of 78 x 100 000, H = 20: 1128 and 358).
+//  - Above, only as many waves of a compute unit work as it has workgroups times interactions side by side; a level keeps
+//    them all busy.  In units of 256 coordinates that have to be 5 up to three local steps and 1.4 per step beyond (14
+//    suffice).  By levels and in one launch, hubs joined to all other nodes, about as many interactions as nodes:
+//      24 x 4 000 000, H = 10, 1 hub   750  1600    4 hubs  661  765    40 x 2^20, H = 3, 2 hubs   273  383    4 hubs  298  269
+//      48 x 4 000 000, H = 5, 1 hub   1364  3087    3 hubs 1225 1499    64 x 4 000 000, H = 20, 4 hubs  2631  3273
+//      31 x 2^20, H = 5, 1 hub         292   382    3 hubs  243  217    19 x 4 000 000, H = 20, 1 hub    883   971
+//    Complete graphs, rings and paths are wide enough up to H = 5 (64 x 4 000 000, H = 20, path, 64 interactions: 2611, 2273).
+bool interact_run_pays(uint64_t d, uint32_t n, uint32_t H, uint32_t m, uint32_t levels) {
+    if (n > RUN_MAX_NODES || levels <= 1 || 8 * (uint64_t)m < 3 * (uint64_t)n) return false;
+    if (d < 3u << 17) return true;
+    const TileForm form = tile_form(n, d);
+    const uint32_t by_memory = 160u / (n * form.f + 1), by_waves = (form.f == 2 ? 16u : 28u) / form.waves;
+    const double side_by_side = std::min((double)m / levels, (double)form.waves);
+    const double need = std::min(std::max(1.4 * H, 5.0), 14.0);
+    return form.f * std::min(by_memory, by_waves) * side_by_side >= need;
+}
 
 template <int BITS, int LOCAL>
 static void launch_waves(const RunArgs &ra, hipStream_t st) {
-    const uint32_t n = ra.g.n;
-    const bool few = ra.g.d < few_coords(n);
-    if (n <= 9 && !few) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
-    else if (n <= 19) launch_tiles<BITS, LOCAL, 4, 1>(ra, st);
-    else if (n <= 39 && !few) launch_tiles<BITS, LOCAL, 8, 2>(ra, st);
-    else if (n <= 39) launch_tiles<BITS, LOCAL, 8, 1>(ra, st);
-    else launch_tiles<BITS, LOCAL, 12, 1>(ra, st);
+    const TileForm form = tile_form(ra.g.n, ra.g.d);
+    if (form.waves == 2) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
+    else if (form.waves == 4) launch_tiles<BITS, LOCAL, 4, 1>(ra, st);
+    else if (form.waves == 12) launch_tiles<BITS, LOCAL, 12, 1>(ra, st);
+    else if (form.f == 2) launch_tiles<BITS, LOCAL, 8, 2>(ra, st);
+    else launch_tiles<BITS, LOCAL, 8, 1>(ra, st);
 }
 
 template <int BITS>

@@ -34,6 +34,8 @@ struct RunArgs {
     float sigma, lr;
 };
 
+// Whether launch_interact_run is sooner done than a launch per level (H: mean number of local steps, 0 without).
+bool interact_run_pays(uint64_t d, uint32_t n, uint32_t H, uint32_t m, uint32_t levels);
 // local: take the initiators' local steps of this diagonal objective in registers, or null.
 hipError_t launch_interact_run(const GossipArgs &g, uint32_t bits, const RunDesc *descs_dev, uint32_t count,
                                const DiagObjective *local, float lr, hipStream_t st);

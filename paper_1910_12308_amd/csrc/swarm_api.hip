@@ -906,12 +906,8 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
     // small least-squares models: one workgroup runs an initiator's steps and then its interaction
     const bool lsq_inside = with_steps && h->kind == OBJ_LSQ && c.codec == SWARM_CODEC_FIXED && h->lsq.part != nullptr;
     const bool lsq_run = lsq_inside && h->lsq.run_part;       // and where they fit, the whole run in one launch
-    // everything per-coordinate and the models of a tile fit local memory: one launch takes the whole run.  It reads
-    // and writes every node's model once, whether or not the run touches it, and 12 to 16 B per interaction-coordinate
-    // instead of 32 and two codes, so it needs enough interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 16 interactions
-    // 125 us with one launch per level, 135 in one launch; 24: 176 and 166; 32 nodes: 8 interactions 77 and 98, 12: 102 and
-    // 97.  Interactions that do not depend on one another at all (one level) have nothing to keep.
-    const bool run_inside = (!with_steps || steps_inside) && c.codec == SWARM_CODEC_FIXED && c.n <= RUN_MAX_NODES;
+    // everything per-coordinate and the models of a tile fit local memory: one launch takes the whole run where that pays
+    const bool run_inside = (!with_steps || steps_inside) && c.codec == SWARM_CODEC_FIXED;
     const uint64_t tiles = (c.d + PREFIX_TILE - 1) / PREFIX_TILE;
     const GossipArgs a = gossip_args(h, 0, 0);
     uint32_t total_launches = 0;
@@ -964,7 +960,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
         for (uint32_t l = 0; l < levels; ++l) level_start[l + 1] += level_start[l];
         order.assign(level_start.begin(), level_start.end() - 1);
         SWARM_HIP(h, hipEventSynchronize(h->seq_free));
-        if (lsq_run || (run_inside && levels > 1 && 8 * (uint64_t)m >= 3 * (uint64_t)c.n)) {
+        if (lsq_run || (run_inside && interact_run_pays(c.d, c.n, steps_inside ? c.H : 0u, m, levels))) {
             RunDesc *run = (RunDesc *)h->seq_host;
             constexpr uint32_t NEVER = ~0u;
             std::vector<uint32_t> led(c.n, NEVER);        // the interaction that touched a node last, if it was the node's own

@@ -45,3 +45,20 @@ def test_least_squares_runs(host_calls, n, d, batch, graph, merged):
     # a single interaction takes the same form, so that it gives the same sums
     one = host_calls("interact", n, d, 8, 2, batch, graph)
     assert kernels(one) == ["lsq_run_kernel" if merged else "lsq_split_kernel"] and run[-1] == one[-1] == "status 0"
+
+
+# Diagonal objective, runs of Algorithm 1: one launch where the run has enough interactions, or rows short enough, and, on
+# long rows, where enough of them run side by side for their local steps
+@pytest.mark.parametrize("n,d,H,graph,count,merged", [
+    (8, 8888, 3, "complete", 16, True), (64, 1 << 20, 3, "complete", 256, True), (64, 1 << 20, 3, "complete", 23, False),
+    (64, 1 << 20, 3, "ring", 32, True), (78, 1544, 3, "star", 60, True), (79, 1544, 3, "complete", 60, False),
+    (64, (3 << 17) - 8, 20, "star", 64, True), (64, 3 << 17, 3, "star", 64, False), (40, 1 << 20, 3, "hubs4", 200, True),
+    (40, 1 << 20, 3, "hubs2", 200, False), (24, 4_000_000, 10, "star", 24, False), (24, 4_000_000, 3, "complete", 64, True),
+    (31, 1 << 20, 5, "hubs3", 64, True), (20, 1 << 20, 3, "star", 40, False), (19, 1 << 20, 5, "star", 40, True),
+    (19, 4_000_000, 20, "star", 40, False), (9, 4_000_000, 5, "star", 16, True), (2, 1 << 20, 3, "path", 4, True),
+    (48, 4_000_000, 20, "hubs4", 200, False)])
+def test_diagonal_runs(host_calls, n, d, H, graph, count, merged):
+    run = host_calls("run", n, d, 8, H, 0, graph, count)
+    levels = int(next(ln for ln in run if ln.startswith("reported")).split()[1])
+    assert kernels(run) == (["interact_run_kernel"] if merged else ["interact_kernel"] * levels)
+    assert levels > 1 and run[-1] == "status 0"
