@@ -26,7 +26,8 @@ namespace swarm {
 // `slices` workgroups of a node share its blocks.  A residual needs the whole row, so a step ends where all of a
 // node's workgroups have stored their partial residuals, i.e. at the end of a launch: launch k applies the update of
 // step k - 1 to the workgroup's columns and takes the partial residuals of step k on them, H + 1 launches for H
-// steps.  With one slice per node (WHOLE) nothing leaves the workgroup and one launch runs all steps.
+// steps.  With one slice per node (WHOLE) nothing leaves the workgroup and one launch runs all steps, in blocks of 1024
+// to 4096 columns.
 // Bound by memory: the rows of a step are read twice, once for the residuals and, when these are known, once for the
 // update, and are too many to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
 // per thread.  16 nodes x 65544 columns, batch 64, 2 steps: 190 us = 1.07 GB of rows at 5.6 TB/s, against 1.96 ms for
@@ -36,7 +37,6 @@ namespace swarm {
 constexpr int WB = 256;                           // threads per workgroup
 constexpr uint64_t WIDE_BLOCK = 4 * WB;           // columns a workgroup handles at a time
 constexpr uint32_t WIDE_GROUPS = 2048;            // workgroups a launch is cut into where the columns allow it
-constexpr uint32_t WIDE_WHOLE_NODES = 256;        // nodes from which one workgroup each fills the chip
 constexpr uint32_t WIDE_MAX_SLICES = 256;         // every workgroup adds up its node's partial residuals
 
 struct LsqWideArgs {
@@ -170,6 +170,60 @@ __global__ __launch_bounds__(THREADS, 4) void lsq_wide_kernel(const LsqWideArgs 
             else sa.part[(uint64_t)(k & 1u) * sa.part_parity + ((uint64_t)slot * sa.slices + slice) * LSQ_MAX_BATCH + threadIdx.x] = t;
         }
         if (WHOLE) __syncthreads();
+    }
+}
+
+// ---- wide form, a wave per row -----------------------------------------------------------------------
+// One workgroup of 16 waves per node: a wave takes the products with whole rows of the batch, then every thread updates
+// float4 columns of its own.  Where it is the better form: lsq_by_rows.
+constexpr int ROW_THREADS = 1024;
+
+__global__ __launch_bounds__(ROW_THREADS) void lsq_rows_kernel(const LsqWideArgs sa) {
+    __shared__ uint32_t rows[LSQ_MAX_BATCH];
+    __shared__ float resid[LSQ_MAX_BATCH];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, slot = blockIdx.x, batch = sa.batch;
+    const uint32_t node = sa.slots.nodes ? sa.slots.nodes[slot] : slot;
+    const uint32_t H = sa.slots.steps ? sa.slots.steps[slot] : sa.H, event = sa.slots.events ? sa.slots.events[slot] : sa.event;
+    const uint64_t d = sa.d;
+    const float *An = sa.A + (uint64_t)node * sa.m_rows * d, *bn = sa.b + (uint64_t)node * sa.m_rows;
+    float *wrow = sa.W + (uint64_t)node * d;
+    const float step = sa.lr * ((float)sa.m_rows / (float)batch);
+    for (uint32_t q = 0; q < H; ++q) {
+        const float *src = q == 0 ? sa.base + (uint64_t)node * d : wrow;
+        if (threadIdx.x < batch) {
+            const Words4 r = stream(sa.seed, TAG_BATCH, q, node, event, threadIdx.x >> 2);
+            const uint32_t word = (threadIdx.x & 3u) == 0 ? r.w0 : (threadIdx.x & 3u) == 1 ? r.w1
+                                  : (threadIdx.x & 3u) == 2 ? r.w2 : r.w3;
+            rows[threadIdx.x] = scaled_index(word, sa.m_rows);
+        }
+        __syncthreads();
+        for (uint32_t s = wave; s < batch; s += ROW_THREADS / 64) {
+            const float *arow = An + (uint64_t)rows[s] * d;
+            float acc = 0.f;
+            for (uint64_t k = 4ull * lane; k < d; k += 256) {
+                const f4 av = *(const f4 *)(arow + k), wv = *(const f4 *)(src + k);
+                acc = fmaf(av.x, wv.x, acc); acc = fmaf(av.y, wv.y, acc);
+                acc = fmaf(av.z, wv.z, acc); acc = fmaf(av.w, wv.w, acc);
+            }
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+            if (lane == 0) resid[s] = acc - bn[rows[s]];
+        }
+        __syncthreads();
+        for (uint64_t k = 4ull * threadIdx.x; k < d; k += 4ull * ROW_THREADS) {
+            f4 g = {0.f, 0.f, 0.f, 0.f};
+            for (uint32_t s = 0; s < batch; ++s) {
+                const f4 av = *(const f4 *)(An + (uint64_t)rows[s] * d + k);
+                const float r = resid[s];
+                g.x = fmaf(av.x, r, g.x); g.y = fmaf(av.y, r, g.y);
+                g.z = fmaf(av.z, r, g.z); g.w = fmaf(av.w, r, g.w);
+            }
+            f4 wv = *(const f4 *)(src + k);
+            wv.x = fmaf(-step, g.x, wv.x); wv.y = fmaf(-step, g.y, wv.y);
+            wv.z = fmaf(-step, g.z, wv.z); wv.w = fmaf(-step, g.w, wv.w);
+            *(f4 *)(wrow + k) = wv;
+        }
+        __threadfence_block();
+        __syncthreads();
     }
 }
 
@@ -345,20 +399,37 @@ bool lsq_split_fits(uint64_t d, uint32_t n) { return ((d + SLICE - 1) / SLICE) *
 
 // Slices per node of the wide form, from the swarm's shape alone: the order in which a node's residuals are summed
 // must not depend on how many nodes take steps together (a batch of Algorithm 1 equals its single steps bit for bit).
-// From 256 nodes on one workgroup each fills the chip and spares the exchange (600 x 4096, batch 16, 2 steps:
-// 126 us with 2 slices, 98 with one); below, as many slices as make 2048 workgroups, every slice with as many blocks.
+// One workgroup per node spares the exchange and the launches between steps and is the better form where such workgroups
+// keep the chip busy: from 256 nodes on, from 128 up to 16384 columns, from 65 where its blocks of 2048 columns are one
+// block or two full ones.  Below, as many slices as make 2048 workgroups, every slice with as many blocks.  us for two
+// steps, with slices and with one workgroup:
+//   65 x 2048, batch 16     13.0    9.0     128 x 1032, batch 16    13.2    8.4     200 x 4096, batch 16    41.9   29.4
+//   80 x 4096, batch 64     64.8   51.6     128 x 4096, batch 64   102.5   64.8     255 x 2048, batch 64   103.7   60.2
+//   65 x 3072, batch 64     29.2   43.1     100 x 12288, batch 64  166.5  181.4     200 x 65536, batch 8     233    236
 static uint32_t wide_slices(uint64_t d, uint32_t n) {
-    if (n >= WIDE_WHOLE_NODES) return 1;
+    if (n >= 256 || (n >= 128 && d <= 16384) || (n > 64 && (d <= 2048 || (d > 3072 && d <= 4096)))) return 1;
     const uint64_t blocks = (d + WIDE_BLOCK - 1) / WIDE_BLOCK;
     const uint64_t most = std::min<uint64_t>({blocks, WIDE_MAX_SLICES, WIDE_GROUPS / n});
     const uint64_t each = (blocks + most - 1) / most;
     return (uint32_t)((blocks + each - 1) / each);
 }
 
+// Of the swarms with one workgroup per node, those for which a wave per row is the better form, as measured: a few more
+// nodes than compute units, and rows of exactly 16 KiB (their stride matters, not their length: 255 x 4104, batch 16, takes
+// 45.0 us with a wave per row and 38.2 in blocks).  us for two steps, a wave per row and blocks of columns:
+//   280 x 4096, batch 16   41.5   50.7     300 x 8192, batch 16   91.9  100.2     512 x 4096, batch 16   74.3   81.4
+//   300 x 4096, batch 64    167    197     300 x 8192, batch 64    374    380     255 x 4096, batch 64    136    152
+//   300 x 5000, batch 16   60.4   55.7     400 x 8192, batch 64    445    433     200 x 4096, batch 64    112    106
+static bool lsq_by_rows(uint64_t d, uint32_t n, uint32_t batch) {
+    if (n > 256 && n <= 384) return (d > 3072 && d <= 4096) || (d > 6144 && d <= 12288 && batch <= 32);
+    return n > 224 && n <= 512 && d == 4096;
+}
+
 hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
     hipError_t e;
     if (!lsq_split_fits(d, n)) {
         o.wide_slices = wide_slices(d, n);
+        o.by_rows = o.wide_slices == 1 && lsq_by_rows(d, n, o.batch);
         o.wide_rows = (uint64_t)n * o.wide_slices;
         return hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH);
     }
@@ -392,9 +463,14 @@ static hipError_t split_args(LsqSplitArgs &sa, const float *base, float *W, LsqO
     return hipSuccess;
 }
 
-static void launch_wide(const LsqWideArgs &wa, uint32_t count, uint32_t max_steps, hipStream_t st) {
+// Threads of the one workgroup per node, where there are far more than compute units: 1024 leave a compute unit one
+// workgroup at a time instead of two, so that more of its rows are still in cache for the second read (512 x 2048, batch 16,
+// two steps: 38.2 us with 512 threads, 31.2 with 1024; 1000 x 2048, three steps: 89.6 and 68.0).
+static void launch_wide(const LsqWideArgs &wa, uint32_t n, uint32_t count, uint32_t max_steps, hipStream_t st) {
     if (wa.slices == 1) {
-        if (wa.d <= 4 * WB) lsq_wide_kernel<WB, true><<<dim3(1, count, 1), WB, 0, st>>>(wa, 0);
+        const bool one_at_a_time = n >= 500 && wa.d >= 1536 && wa.d <= 3072;
+        if (one_at_a_time) lsq_wide_kernel<4 * WB, true><<<dim3(1, count, 1), 4 * WB, 0, st>>>(wa, 0);
+        else if (wa.d <= 4 * WB) lsq_wide_kernel<WB, true><<<dim3(1, count, 1), WB, 0, st>>>(wa, 0);
         else if (wa.d <= 64 * WB) lsq_wide_kernel<2 * WB, true><<<dim3(1, count, 1), 2 * WB, 0, st>>>(wa, 0);
         else lsq_wide_kernel<4 * WB, true><<<dim3(1, count, 1), 4 * WB, 0, st>>>(wa, 0);
         return;
@@ -414,7 +490,8 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
     } else {
         LsqWideArgs wa{base, W, o.A, o.b, slots, o.wide_part, d, seed, o.wide_rows * LSQ_MAX_BATCH,
                        H, o.m_rows, o.batch, event, o.wide_slices, lr};
-        launch_wide(wa, count, slots.steps ? slots.max_steps : H, st);
+        if (o.by_rows) lsq_rows_kernel<<<count, ROW_THREADS, 0, st>>>(wa);
+        else launch_wide(wa, (uint32_t)(o.wide_rows / o.wide_slices), count, slots.steps ? slots.max_steps : H, st);
     }
     return hipGetLastError();
 }

@@ -27,6 +27,7 @@ struct LsqObjective {
     float *wide_part = nullptr;
     uint64_t wide_rows = 0;
     uint32_t wide_slices = 0;
+    bool by_rows = false;           // wide form with a wave per row of the batch instead
 };
 
 struct MlpObjective {

@@ -22,12 +22,17 @@ def lsq_swarm(gpu, n, d, m, batch, H, geometric, seed):
     return g, c
 
 
-# n x ceil(d / 512) > 256: several workgroups share a node below 256 nodes (blocks of 1024 columns, one or more per
-# slice, ragged or a whole number), one workgroup takes a node from there on (256, 512 or 1024 threads)
+# n x ceil(d / 512) > 256: several workgroups share a node (blocks of 1024 columns, one or more per slice, ragged or a whole
+# number) or one takes a node alone: from 256 nodes on, from 128 up to 16384 columns, from 65 up to 2048 and from 3080 to
+# 4096 columns (256, 512 or 1024 threads, or a wave per row)
 @pytest.mark.parametrize("n,d,m,batch,H,geometric", [
     (129, 1024, 8, 4, 2, False), (129, 1032, 8, 20, 3, False), (40, 4096, 40, 64, 1, False), (9, 8 * 2051, 33, 16, 2, True),
     (2, 8 * 33001, 17, 12, 2, False), (255, 8 * 1300, 6, 32, 2, False),
-    (257, 512, 9, 4, 3, True), (256, 1032, 8, 36, 2, False), (260, 16384 + 8, 5, 16, 2, False)])
+    (257, 512, 9, 4, 3, True), (256, 1032, 8, 36, 2, False), (260, 16384 + 8, 5, 16, 2, False),
+    (65, 2048, 8, 12, 2, False), (65, 2056, 8, 16, 2, True), (65, 3080, 7, 20, 2, False), (127, 4104, 5, 16, 2, False),
+    (128, 16384, 4, 8, 2, False), (128, 16392, 4, 8, 2, False), (500, 1536, 4, 16, 2, False), (500, 3072, 4, 60, 2, True),
+    (257, 3080, 5, 64, 2, False), (384, 4096, 4, 16, 3, True), (300, 6152, 4, 32, 2, False), (260, 12288, 4, 12, 2, False),
+    (225, 4096, 5, 48, 2, False)])
 def test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric):
     g, c = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)
     nodes = sorted({n - 1, 0, n // 2}, reverse=True)

@@ -62,3 +62,24 @@ def test_diagonal_runs(host_calls, n, d, H, graph, count, merged):
     levels = int(next(ln for ln in run if ln.startswith("reported")).split()[1])
     assert kernels(run) == (["interact_run_kernel"] if merged else ["interact_kernel"] * levels)
     assert levels > 1 and run[-1] == "status 0"
+
+
+# Least-squares local steps of swarms too wide for the exchanging form: several workgroups per node and a launch more than
+# steps, or one workgroup per node and one launch
+@pytest.mark.parametrize("n,d,batch,kernel,threads,grid", [
+    (64, 4104, 32, "lsq_wide_kernel<256, false>", 256, "5 64"), (65, 2048, 16, "lsq_wide_kernel<512, true>", 512, "1 65"),
+    (65, 2056, 16, "lsq_wide_kernel<256, false>", 256, "3 65"), (100, 3080, 64, "lsq_wide_kernel<512, true>", 512, "1 100"),
+    (100, 4104, 64, "lsq_wide_kernel<256, false>", 256, "5 100"), (128, 16384, 16, "lsq_wide_kernel<512, true>", 512, "1 128"),
+    (128, 16392, 16, "lsq_wide_kernel<256, false>", 256, "9 128"), (255, 1032, 16, "lsq_wide_kernel<512, true>", 512, "1 255"),
+    (260, 1024, 16, "lsq_wide_kernel<256, true>", 256, "1 260"), (300, 16392, 16, "lsq_wide_kernel<1024, true>", 1024, "1 300"),
+    (499, 2048, 16, "lsq_wide_kernel<512, true>", 512, "1 499"), (500, 2048, 16, "lsq_wide_kernel<1024, true>", 1024, "1 500"),
+    (500, 3080, 16, "lsq_wide_kernel<512, true>", 512, "1 500"), (512, 4096, 16, "lsq_rows_kernel", 1024, "512 1"),
+    (513, 4096, 16, "lsq_wide_kernel<512, true>", 512, "1 513"), (300, 4096, 64, "lsq_rows_kernel", 1024, "300 1"),
+    (300, 8192, 32, "lsq_rows_kernel", 1024, "300 1"), (300, 8192, 36, "lsq_wide_kernel<512, true>", 512, "1 300"),
+    (256, 8192, 16, "lsq_wide_kernel<512, true>", 512, "1 256")])
+def test_wide_least_squares_steps(host_calls, n, d, batch, kernel, threads, grid):
+    H = 3
+    out = host_calls("steps", n, d, 8, H, batch, "ring")
+    slices = H + 1 if kernel.endswith("false>") else 1
+    assert [ln for ln in out if ln.startswith("launch")] == [f"launch {kernel} grid {grid} block {threads} shared 0"] * slices
+    assert out[-1] == "status 0"
