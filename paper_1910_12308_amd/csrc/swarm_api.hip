@@ -645,6 +645,25 @@ swarm_status swarm_sample_pair(swarm_t h, uint32_t *i, uint32_t *j) {
     return SWARM_OK;
 }
 
+// A staging slot that kernels read in place: however the round ends, the slot's event is recorded behind the kernels that
+// were enqueued, a refused launch among them or not.
+struct SlotReaders {
+    swarm_t h;
+    unsigned slot = 0;
+    bool reading = false;
+    swarm_status close() {
+        if (!reading) return SWARM_OK;
+        reading = false;
+        const hipError_t e = hipEventRecord(h->desc_free[slot], h->stream);
+        if (e != hipSuccess) (void)hipStreamSynchronize(h->stream);
+        SWARM_HIP(h, e);
+        return SWARM_OK;
+    }
+    ~SlotReaders() {
+        if (reading && hipEventRecord(h->desc_free[slot], h->stream) != hipSuccess) (void)hipStreamSynchronize(h->stream);
+    }
+};
+
 static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t npairs, const uint8_t *stale_host,
                                bool fused) {
     const swarm_config &c = h->cfg;
@@ -716,8 +735,7 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
     // of small rounds instead was measured: the copy costs the step nothing, a second source of descriptors
     // costs the kernels 0.5 to 2 %.)
     const uint8_t *descs = h->desc_dev;
-    bool in_place = false;
-    unsigned used_slot = 0;
+    SlotReaders readers{h};
     {
         uint8_t *slot = nullptr;
         unsigned slot_index = 0;
@@ -730,10 +748,10 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         for (uint32_t k = 0; k < nsingles; ++k)
             sg[k] = singles[k] | (fused ? draw_steps(c, singles[k], (uint32_t)h->round) << 16 : 0u) |
                     (h->pending[singles[k]] ? SINGLE_PENDING : 0u);
-        in_place = (uint64_t)(npairs + nsingles) * ((c.d + PREFIX_TILE - 1) / PREFIX_TILE) <= DESC_IN_PLACE_WAVES;
-        if (in_place) {
+        readers.reading = (uint64_t)(npairs + nsingles) * ((c.d + PREFIX_TILE - 1) / PREFIX_TILE) <= DESC_IN_PLACE_WAVES;
+        if (readers.reading) {
             descs = h->desc_mapped[slot_index];
-            used_slot = slot_index;
+            readers.slot = slot_index;
         } else {
             SWARM_HIP(h, hipMemcpyAsync(h->desc_dev, slot, h->desc_bytes, hipMemcpyHostToDevice, h->stream));
             SWARM_HIP(h, hipEventRecord(h->desc_free[slot_index], h->stream));
@@ -793,7 +811,7 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         SWARM_HIP(h, launch_scale_close(h->eps_slots_dev, h->scale_state_dev, a.slot_now, a.ring_depth, c.bits, npairs,
                                         h->stream));
 
-    if (in_place) SWARM_HIP(h, hipEventRecord(h->desc_free[used_slot], h->stream));      // its kernels are the slot's readers
+    SWARM_TRY(readers.close());
     std::fill(h->pending.begin(), h->pending.end(), 0);
     h->round += 1;
     h->interactions += npairs;

@@ -83,3 +83,18 @@ def test_wide_least_squares_steps(host_calls, n, d, batch, kernel, threads, grid
     slices = H + 1 if kernel.endswith("false>") else 1
     assert [ln for ln in out if ln.startswith("launch")] == [f"launch {kernel} grid {grid} block {threads} shared 0"] * slices
     assert out[-1] == "status 0"
+
+
+@pytest.mark.parametrize("fail", [0, 1, 2, 3, 4])
+def test_staging_slot_is_guarded_until_its_readers_are_done(host_calls, fail):
+    """Small rounds are described in a staging slot that their kernels read: the event that frees the slot is recorded behind
+    every launch, also where a launch of the round fails."""
+    out = host_calls("rounds", 8, 8888, 8, 2, fail, 3)
+    ends = [k for k, ln in enumerate(out) if ln.startswith("status")][:3]
+    assert [out[k] for k in ends] == ["status 3" if fail and (fail - 1) // 2 == r else "status 0" for r in range(3)]
+    for first, end in zip([0] + [k + 1 for k in ends], ends):
+        call = out[first:end]
+        slot = next(ln.split()[1] for ln in call if ln.startswith("wait"))
+        launches = [k for k, ln in enumerate(call) if ln.startswith("launch")]
+        assert launches and f"record {slot}" in call[launches[-1]:]
+        assert "copy" not in call
