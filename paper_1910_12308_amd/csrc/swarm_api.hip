@@ -24,9 +24,12 @@ namespace {
 
 constexpr int DESC_SLOTS = 4;   // pinned staging slots for per-round metadata
 // Rounds of at most so many waves read their descriptors there: a read over the bus by every wave costs less than a copy
-// ahead of the kernels (one round and a wait: 8 nodes x 8888 30.4 -> 23.2 us, 64 x 30 000 36.0 -> 30.9), until there are
-// too many of them (64 x 65 536, 8192 waves, back to back: 32.8 -> 33.4).
-constexpr uint64_t DESC_IN_PLACE_WAVES = 4096;
+// ahead of the kernels (one round and a wait: 8 nodes x 8888 30.4 -> 23.2 us, 64 x 30 000 36.0 -> 30.9, 256 x 8192 34.5 ->
+// 30.8).  Rounds one behind the other pay for it, as the copy of the next runs beside the kernels of this one: from 8192
+// waves on where the matching is taken on the host (64 x 65 536: 32.8 -> 33.4 us), from about 1300 where its kernel sets
+// the pace (copied and in place: 128 x 8192, 1200 waves, 20.2 and 20.3; 200 x 8192, 1800 waves, 21.0 and 21.7;
+// 256 x 8192, 2300 waves, 21.0 and 22.3; 512 x 4096, 2700 waves, 22.8 and 24.6).
+constexpr uint64_t DESC_IN_PLACE_WAVES = 4096, DESC_IN_PLACE_WAVES_MATCHED = 1280;
 // Graphs of at most so many edges are matched on the host: 128 generator calls and a sort of as many words take 4 us,
 // less than enqueueing the matching kernel and waiting for its event, which set the period of small rounds (back to back,
 // 8 nodes x 8888, 16 edges: 17.2 -> 9.3 us; 16 x 4096, 120 edges: 18.4 -> 11.0; 64 x 8888, 128 edges: 18.8 -> 17.9).  The
@@ -730,10 +733,8 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
     }
     const int group_mode[3] = {delta_mode == 2 ? 2 : 0, 1, 3};
 
-    // Per-round metadata: one descriptor per pair (nodes, staleness, pending flags) and the unmatched
-    // nodes, staged in pinned memory and copied with one transfer, or, in a small round, read from there by its kernels.  (Carrying them in the kernel arguments
-    // of small rounds instead was measured: the copy costs the step nothing, a second source of descriptors
-    // costs the kernels 0.5 to 2 %.)
+    // Per-round metadata: one descriptor per pair (nodes, staleness, pending flags) and the unmatched nodes, staged in pinned
+    // memory and copied with one transfer or, in a small round, read from there by its kernels.
     const uint8_t *descs = h->desc_dev;
     SlotReaders readers{h};
     {
@@ -748,7 +749,8 @@ static swarm_status round_impl(swarm_t h, const uint32_t *pairs_host, uint32_t n
         for (uint32_t k = 0; k < nsingles; ++k)
             sg[k] = singles[k] | (fused ? draw_steps(c, singles[k], (uint32_t)h->round) << 16 : 0u) |
                     (h->pending[singles[k]] ? SINGLE_PENDING : 0u);
-        readers.reading = (uint64_t)(npairs + nsingles) * ((c.d + PREFIX_TILE - 1) / PREFIX_TILE) <= DESC_IN_PLACE_WAVES;
+        readers.reading = (uint64_t)(npairs + nsingles) * ((c.d + PREFIX_TILE - 1) / PREFIX_TILE) <=
+                          (c.n_edges <= HOST_MATCH_EDGES ? DESC_IN_PLACE_WAVES : DESC_IN_PLACE_WAVES_MATCHED);
         if (readers.reading) {
             descs = h->desc_mapped[slot_index];
             readers.slot = slot_index;

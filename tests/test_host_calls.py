@@ -98,3 +98,12 @@ def test_staging_slot_is_guarded_until_its_readers_are_done(host_calls, fail):
         launches = [k for k, ln in enumerate(call) if ln.startswith("launch")]
         assert launches and f"record {slot}" in call[launches[-1]:]
         assert "copy" not in call
+
+
+# tiles of 512 coordinates x (pair + unmatched nodes) = waves of the round; the graphs are complete: 120 edges at 16 nodes,
+# 136 at 17
+@pytest.mark.parametrize("n,d,copied", [
+    (16, 512 * 273, False), (16, 512 * 274, True), (17, 512 * 80, False), (17, 512 * 81, True), (8, 8888, False)])
+def test_descriptors_are_copied_ahead_of_larger_rounds(host_calls, n, d, copied):
+    out = host_calls("rounds", n, d, 8, 2, 0, 1)
+    assert ("copy" in out) == copied and out[-1] == "status 0"
