@@ -12,6 +12,17 @@ TOL_ELEMENTWISE = 1e-6     # averaging and elementwise updates (float32 path vs 
 TOL_TWO_STAGE = 2 * TOL_ELEMENTWISE
 TOL_GEMM = 1e-4            # GEMM-based gradients
 
+# Runs of Algorithm 1 on complete graphs, 3 n + 1 interactions: n, d, bits, H, sigma, geometric, objective, one launch for the
+# run.  2, 4, 8 and 12 waves per tile of 256 or, from 2^19 (up to 9 nodes) or 2^18 coordinates on, 512; the most nodes
+# local memory holds and, with one node more, one launch per level.
+ALGORITHM1_RUNS = [
+    (2, 8, 8, 1, 0.1, False, True, True), (3, 520, 2, 2, 0.05, True, True, True), (19, 504, 4, 3, 0.1, False, True, True),
+    (20, 1032, 16, 2, 0.0, False, True, True), (39, 8, 8, 5, 0.1, True, True, True), (40, 2056, 8, 1, 0.1, False, True, True),
+    (78, 1544, 4, 2, 0.1, False, True, True), (79, 1544, 4, 2, 0.1, False, True, False),
+    (9, (1 << 19) + 8, 8, 3, 0.1, True, True, True), (10, (1 << 18) - 8, 8, 3, 0.1, False, True, True),
+    (20, 1 << 18, 4, 2, 0.05, False, True, True), (39, (1 << 18) - 264, 8, 1, 0.1, False, True, True),
+    (40, 520, 0, 2, 0.1, False, True, True), (20, 520, 8, 0, 0.0, False, False, True), (5, 1544, 0, 0, 0.0, False, False, True)]
+
 
 def close(gpu, cpu, tol):
     """|gpu - cpu| <= tol * max(1, |cpu|) elementwise (relative error is ill-defined near 0)."""

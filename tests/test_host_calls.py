@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 import paper_1910_12308_amd as swarm
+from helpers import ALGORITHM1_RUNS
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -45,6 +46,12 @@ def test_least_squares_runs(host_calls, n, d, batch, graph, merged):
     # a single interaction takes the same form, so that it gives the same sums
     one = host_calls("interact", n, d, 8, 2, batch, graph)
     assert kernels(one) == ["lsq_run_kernel" if merged else "lsq_split_kernel"] and run[-1] == one[-1] == "status 0"
+
+
+@pytest.mark.parametrize("n,d,bits,H,merged", [(r[0], r[1], r[2], r[3], r[7]) for r in ALGORITHM1_RUNS])
+def test_runs_of_the_gpu_tests_take_the_form_they_are_there_for(host_calls, n, d, bits, H, merged):
+    run = host_calls("run", n, d, bits, H, 0, "complete", 3 * n + 1)
+    assert set(kernels(run)) == {"interact_run_kernel" if merged else "interact_kernel"} and (len(kernels(run)) == 1) == merged
 
 
 # Diagonal objective, runs of Algorithm 1: one launch where the run has enough interactions, or rows short enough, and, on
