@@ -334,33 +334,34 @@ def sequential_report(torch, swarm, s, cfg, batch, steps, warmup, compare_single
     """Algorithm 1: `batch` interactions per swarm_run_sequential call (a step), and, beside it, the same
     number of interactions as one swarm_sample_pair + swarm_interact per interaction."""
     n, d, bits = cfg["n"], cfg["d"], cfg["bits"]
-    launches = []
+    levels = []
 
     def step():
-        launches.append(s.run_sequential(batch)[1])
+        levels.append(s.run_sequential(batch)[1])
 
     m = measure(torch, s, step, steps, warmup)
-    per_launch = m["interactions"] / max(1, sum(launches[-steps:]))
-    rep = {"step": f"swarm_run_sequential({batch}): Algorithm 1, interactions on disjoint nodes share a launch",
+    per_level = m["interactions"] / max(1, sum(levels[-steps:]))
+    rep = {"step": f"swarm_run_sequential({batch}): Algorithm 1, the interactions of a call in one launch, those on disjoint "
+                   "nodes side by side",
            "steps": steps, "ms_per_step": m["dt"] / steps * 1e3, "interactions_per_s": m["interactions"] / m["dt"],
-           "interactions_per_launch": per_launch}
+           "interactions_per_level": per_level}
     if cfg["objective"] == "diag":
-        # a call reads X, Xhat, a, c and writes X, Xhat and the codes of every node once; it is not bound by these bytes
-        # but by the vector instructions of its interactions
+        # a call reads X, Xhat, a, c and writes X, Xhat and the codes of every node once; the fraction of the HBM peak says
+        # little, as the call is bound by the vector instructions of its interactions
         per_call = n * d * (24.0 + bits / 8)
         seconds = m["times"]["gossip_ms"] * 1e-3
         achieved = per_call * steps / seconds / 1e9
         rep["roofline"] = {"kernel": "interact_run_kernel (Algorithm 1, the run of a call in one launch, models kept on chip)",
-                           "bound": "hbm", "bytes_per_call": per_call, "achieved": achieved, "peak": HBM_PEAK_GBS,
+                           "bound": "alu", "priced_against": "hbm", "bytes_per_call": per_call, "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "ms_per_interaction": m["times"]["gossip_ms"] / max(1, m["interactions"])}
     else:
         # least squares: H * batch rows of A per interaction, read once (the models stay on chip between interactions)
         per_i = cfg["H"] * cfg["batch"] * d * 4
         achieved = per_i * m["interactions"] / m["dt"] / 1e9
-        rep["roofline"] = {"kernel": "lsq_run_kernel (a call's interactions, local steps included, in one launch; latency-bound: "
+        rep["roofline"] = {"kernel": "lsq_run_kernel (a call's interactions, local steps included, in one launch; "
                                      "one exchange between a few dozen workgroups per local step)",
-                           "bound": "hbm", "bytes_per_interaction": per_i, "achieved": achieved, "peak": HBM_PEAK_GBS,
+                           "bound": "latency", "priced_against": "hbm", "bytes_per_interaction": per_i, "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS}
     if compare_single:
         def single():
@@ -507,7 +508,7 @@ def main():
                "warmup": args.warmup, "ms_per_step": rep["ms_per_step"], "higher_is_better": True, "scaling": "weak",
                "vs_baseline": None, "dtype": "f32", "data": "synthetic",
                "config": {"workload": workload + " -- Algorithm 1, fresh reads", "step": rep["step"],
-                          "interactions_per_launch": rep["interactions_per_launch"],
+                          "interactions_per_level": rep["interactions_per_level"],
                           **({"one_call_per_interaction": rep["one_call_per_interaction"]}
                              if "one_call_per_interaction" in rep else {})},
                "roofline": rep["roofline"]}

@@ -225,11 +225,13 @@ swarm_status swarm_interact(swarm_t h, uint32_t i, uint32_t j);
  * nodes, and a launch carries all its interactions as grid rows; no per-interaction host work or
  * copy remains.  Where everything is per-coordinate (fixed-width codes; diagonal objective, or no steps inside the
  * library) and n <= 78, and for small least-squares swarms, the launches are merged into one, which keeps the
- * models on chip between interactions.  For the diagonal objective (fixed-width codes) the initiator's local steps are
+ * models on chip between interactions, if the run has enough interactions and the graph does not keep them too far
+ * from (per-coordinate) or too far beyond (least squares) what such a launch runs side by side.  For the diagonal objective (fixed-width codes) the initiator's local steps are
  * taken inside the interaction kernel and the live copy W is neither written nor read (it keeps its
  * old contents); for the other objectives they are one more launch per group.
  * pairs_host: receives the 2*count node ids (initiator, responder) in the order of Algorithm 1, or
- * NULL.  launches: receives the number of such launches (merged or not), or NULL.  Same requirements as
+ * NULL.  launches: receives the number of such groups of interactions (one launch each unless they are merged), or
+ * NULL.  Same requirements as
  * swarm_interact. */
 swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_host, uint32_t *launches);
 

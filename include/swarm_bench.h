@@ -18,6 +18,9 @@ extern "C" {
  * the gossip pass of every swarm_gossip_round / swarm_round_fused / swarm_interact, every whole
  * swarm_run_sequential call and the kernels of every swarm_local_steps with HIP events on the
  * handle's stream (up to 1024 calls of each kind between resets; later calls are not recorded).
+ * swarm_interact books local steps that run in a launch of their own as a local call; where one launch
+ * takes the steps and the interaction (the one-pass round, runs of Algorithm 1, and swarm_interact on
+ * least-squares swarms of at most 256 slices of 512 columns, n ceil(d / 512) <= 256) all of it counts as gossip.
  * swarm_kernel_times synchronises and returns the summed device milliseconds and the number of
  * recorded calls since the last swarm_timing_reset. */
 swarm_status swarm_timing_reset(swarm_t h);

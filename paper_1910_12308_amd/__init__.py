@@ -247,7 +247,8 @@ class Swarm:
         self._check(self._lib.swarm_interact(self._h, int(i), int(j)))
 
     def run_sequential(self, count):
-        """The next `count` steps of Algorithm 1 in batched launches; returns (pairs, number of launches)."""
+        """The next `count` steps of Algorithm 1 in batched launches; returns (pairs, number of groups that
+        could run side by side: the launches, where they are not merged into one)."""
         pairs = np.zeros((int(count), 2), dtype=np.uint32)
         launches = ctypes.c_uint32()
         self._check(self._lib.swarm_run_sequential(self._h, int(count), pairs.ctypes.data_as(ctypes.c_void_p),

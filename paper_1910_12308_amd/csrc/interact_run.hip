@@ -7,7 +7,7 @@
 // nodes has been through.  (Same arithmetic as interact_tile, same results bit for bit.)
 // An interaction reads what is not in local memory -- a_i, c_i and, unless the initiator's last interaction was its
 // own, the snapshot -- and writes the snapshot unless the next interaction of the node writes it again.
-// Bound by vector instructions (about 520 per interaction and 512 coordinates at H = 3) and by the chain of dependent
+// Bound by vector instructions (408 counted per interaction and 256 coordinates at H = 3) and by the chain of dependent
 // interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 256 interactions on a complete graph take 780 us, against 1636 us for 28
 // launches that moved 34 B per interaction-coordinate at 5.6 TB/s; 16 nodes x 300 000, 200 interactions 302 us
 // against 1511; 8 nodes x 8888, 64 interactions 55 us against 249.  (Steps on the way, the first: nothing requested ahead of

@@ -728,13 +728,16 @@ static void gemm_tiled(GemmArgs g, uint32_t count, bool split, hipStream_t st) {
     else mlp_gemm_kernel<A_KC, B_KC, EPI, TM, TN><<<grid, 256, 0, st>>>(g);
 }
 
-// Tile of a product, by its shape alone.  Tiles of 128 x 128 read the fewest operand bytes and issue the fewest
+// Tile of a product, by its shape and, where that decides whether the tiles fill the chip, the number of nodes in the launch
+// (the order of every sum is the same in all of them).  Tiles of 128 x 128 read the fewest operand bytes and issue the fewest
 // instructions per product; smaller ones where they would be mostly padding or too few to fill the chip (two fit a
 // compute unit).  M is the batch in the forward and backward products:
 //  - up to 64 rows: 64 x 64.  32 nodes, 800-1504-480, batch 64, two steps (with the other small kernels of this file):
 //    937 -> 635 us in float32, 605 -> 488 in bf16 x 3; 8 nodes, 1024-4096-1024, batch 32: 1115 -> 679 and 682 -> 500;
 //  - 129 to 192 rows and the like, float32 only: three tiles of 64 rows instead of two of 128 (64 nodes, 736-1376-896,
-//    batch 160: 3259 -> 2770 us; bf16 x 3, bound by the weights it then reads three times, would go from 1801 to 1934);
+//    batch 160: 3259 -> 2770 us; bf16 x 3, bound by the weights it then reads three times, would go from 1801 to 1934).
+//    The same remainder above 192 rows, all rules together against 128 x 128 throughout: 32 nodes, 800-1504-480, batch 288
+//    2380 -> 1837, 320 2492 -> 1907; 16 nodes, 1024-4096-1024, batch 544 7350 -> 6544; 8 nodes, batch 1056 7417 -> 6231;
 //  - fewer than 512 tiles of 128 x 128: 128 x 64 (4 nodes, 1024-2048-512, batch 128: 648 -> 433 us and 371 -> 252).
 // The update products take 64 x 64 below 256 tiles (39 nodes, 96-256-64: 148 -> 121 us for the two steps); above, the
 // smaller tile's extra operand reads cost more than it brings (64 nodes, 1024-4096-1024: float32 +4 %, bf16 x 3 +17 %).

@@ -24,8 +24,8 @@ __host__ __device__ __forceinline__ Words4 philox4x32_10(uint32_t k0, uint32_t k
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
 #if defined(__HIP_DEVICE_COMPILE__)
-        // One three-input instruction instead of two: 16 of the 30 exclusive-ors a lane issues per call, with a
-        // common node, tag and key.  (The first rounds mix in words common to the wave, whose part is scalar.)
+        // One three-input instruction instead of two at 15 places: that many exclusive-ors fewer per lane and call.  (The
+        // first rounds mix in words common to the wave, whose part is scalar.)
         const uint32_t n0 = r < 2 ? (uint32_t)(p1 >> 32) ^ c1 ^ k0 : xor3((uint32_t)(p1 >> 32), c1, k0);
         const uint32_t n2 = r < 3 ? (uint32_t)(p0 >> 32) ^ c3 ^ k1 : xor3((uint32_t)(p0 >> 32), c3, k1);
 #else
