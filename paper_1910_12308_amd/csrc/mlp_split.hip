@@ -111,17 +111,19 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
     u4 *const rows = lds + 2 * STAGE + wave * 512;
     const uint32_t put = 8 * (lane >> 3) + ((lane & 7u) ^ (lane >> 4)), turn = (r32 >> 1) & 7u;
 
-    const Buffer act_buffer = buffer_at(act, ((uint64_t)(BLOCKS - 1) * slabs + turns) * 4096);
     const u4 *by_row = UPDATE ? g.by_row + slot * g.by_row_stride : act;
-    const Buffer rows_buffer = buffer_at(by_row, (uint64_t)slabs * FRAGS * 1024);
     struct Staged { u4 act[PER_WAVE], rows[UPDATE ? PER_WAVE : 1]; };
+    // Offsets are 32 bits: the slab moves the base, so that one block of samples has no limit (2^20 slabs of 4 KiB are reached by
+    // 33.5 M features; several blocks are taken where many workgroups read them, and memory ends long before 2^18 slabs).
     auto load_act = [&](uint32_t t, Staged &r) {
+        const Buffer act_buffer = buffer_at(act + (uint64_t)t * 4 * FRAGMENT, ((uint64_t)(BLOCKS - 1) * slabs + 1) * 4096);
+        const Buffer rows_buffer = buffer_at(by_row + (uint64_t)t * FRAGS * FRAGMENT, FRAGS * 1024);
 #pragma unroll
         for (int i = 0; i < PER_WAVE; ++i) {
             const uint32_t f = wave + WAVES * i;
             if (FRAGS % WAVES == 0 || f < FRAGS) {
-                r.act[i] = load16<0>(act_buffer, 16 * lane, ((f / 4 * slabs + t) * 4 + f % 4) * 1024);
-                if (UPDATE) r.rows[i] = load16<0>(rows_buffer, 16 * lane, (t * FRAGS + f) * 1024);
+                r.act[i] = load16<0>(act_buffer, 16 * lane, (f / 4 * slabs * 4 + f % 4) * 1024);
+                if (UPDATE) r.rows[i] = load16<0>(rows_buffer, 16 * lane, f * 1024);
             }
         }
     };

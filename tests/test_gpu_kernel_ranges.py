@@ -180,6 +180,31 @@ def test_mlp_forms_from_bf16_operands(gpu, n, n_in, n_hid, n_out, batch):
     assert torch.equal(s.models_view(gpu.LIVE)[some], whole[some])
 
 
+def test_mlp_contraction_of_more_than_4_gib_of_packed_features(gpu):
+    """2^20 + 1 slabs of 32 features and 4 KiB each, the weights of all but the last slab zero: a 32-bit byte offset would come
+    round to the first slab's features.  The update of W2 shows the hidden activations; against the float32 arithmetic, whose
+    addresses are others, at the bar of the products."""
+    n, n_in, n_hid, n_out, batch = 2, 32 * (2 ** 20 + 1), 32, 32, 32
+    d = n_hid * n_in + n_hid + n_out * n_hid + n_out
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    means = torch.randn(n_out, n_in, generator=gen, device="cuda")
+    cdf = (torch.arange(1, n_out + 1, device="cuda") / n_out).float().repeat(n, 1).contiguous()
+    s = gpu.Swarm(n, d, [[0, 1]], 8, 2.0 ** -10, 1, 0.05, 0, 1)
+    s.set_objective_mlp(n_in, n_hid, n_out, means, cdf, 0.1, batch)
+    X, W = s.models_view(gpu.COMM), s.models_view(gpu.LIVE)
+    W2 = slice(n_hid * n_in + n_hid, d - n_out)
+    for i in range(n):
+        X[i].zero_()
+        X[i, :n_hid * n_in].view(n_hid, n_in)[:, -32:].normal_(0.0, 0.2, generator=gen)
+        X[i, W2].normal_(0.0, 0.2, generator=gen)
+    step = []
+    for arithmetic in (gpu.MLP_FP32, gpu.MLP_BF16X3):
+        s.set_mlp_arithmetic(arithmetic)
+        s.local_steps()
+        step.append((W[:, W2] - X[:, W2]).double())
+    assert step[0].norm() > 1e-3 and (step[1] - step[0]).norm() < TOL_GEMM * step[0].norm()
+    s.close()
+
 
 # small least-squares swarms: a run of Algorithm 1 in one launch (graphs that let at most seven interactions run side by
 # side, up to 64 groups of 128 columns, batch 32 and 2048 words exchanged per step: tests/test_host_calls.py); beyond each
