@@ -237,9 +237,11 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     here[8 * r32 + piece(i)] = __builtin_bit_cast(u4, f4{mine[4 * i], mine[4 * i + 1], mine[4 * i + 2], mine[4 * i + 3]});
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes' words come next
                 const Buffer to = buffer_at(Out + (uint64_t)col * 32 * ldw + 32 * t, 128 * (uint64_t)ldw);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) back[i] = here[64 * i + (put ^ (4 * (i & 1)))];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // and make room for the next rows
                 if (live) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) store16(to, back[i], weight_bytes, 32 * i * ldw);
