@@ -44,7 +44,7 @@ struct ProductArgs {
     u4 *by_sample, *by_column;      // HIDDEN: activations packed over the columns; HIDDEN, BACK: over the samples
     uint64_t by_sample_stride, by_column_stride;
     uint16_t *mask;                 // HIDDEN writes, BACK reads: bit v of lane l of block (samples, columns): result v is positive
-    float *sums;                    // BACK, several chunks: column sums per slot and chunk
+    float *sums;                    // BACK, several chunks: column sums per slot and block of 32 samples
     // UPDATE: the gradient of the weights is the product of these, packed over the samples
     const u4 *by_row, *own;         // rows: contraction index of the product; its columns
     uint64_t by_row_stride, own_stride;
@@ -298,8 +298,7 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
 
     const uint64_t bias_at = node * g.d + g.bias + 32 * col + r32;
     const float bias = KIND != PRODUCT_BACK && split == 0 ? g.biases[bias_at] : 0.f;
-    constexpr int PARTS = BLOCKS <= 2 ? BLOCKS : (BLOCKS + 1) / 2, EACH = BLOCKS <= 2 ? 1 : 2;
-    float column_sum[PARTS] = {};
+    float column_sum[BLOCKS] = {};                                     // of each block, whatever the chunks: the same bits in all
 #pragma unroll
     for (int m = 0; m < BLOCKS; ++m) {
         const uint32_t block = chunk * BLOCKS + m;                     // of 32 samples
@@ -325,7 +324,7 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     out[v] = (bits >> v) & 1u ? acc[m][v] : 0.f;
-                    column_sum[m / EACH] += out[v];
+                    column_sum[m] += out[v];
                 }
             }
             u4 *by_column = g.by_column + slot * g.by_column_stride + fragments_at(col, g.sample_blocks, block);
@@ -350,14 +349,14 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
     if constexpr (KIND == PRODUCT_BACK) {
         float total = 0.f;
 #pragma unroll
-        for (int i = 0; i < PARTS; ++i) {
-            const float part = column_sum[i] + __shfl_xor(column_sum[i], 32);
-            total = i == 0 ? part : total + part;
+        for (int m = 0; m < BLOCKS; ++m) {
+            const uint32_t block = chunk * BLOCKS + m;
+            if (block >= g.sample_blocks) break;
+            const float part = column_sum[m] + __shfl_xor(column_sum[m], 32);
+            total = m == 0 ? part : total + part;
+            if (g.chunks > 1 && half == 0) g.sums[((uint64_t)slot * g.sample_blocks + block) * 32 * g.cols + 32 * col + r32] = part;
         }
-        if (half == 0) {
-            if (g.chunks == 1) g.W_out[bias_at] = fmaf(-g.lr, total, g.biases[bias_at]);
-            else g.sums[((uint64_t)slot * g.chunks + chunk) * 32 * g.cols + 32 * col + r32] = total;
-        }
+        if (g.chunks == 1 && half == 0) g.W_out[bias_at] = fmaf(-g.lr, total, g.biases[bias_at]);
     }
 }
 
@@ -631,46 +630,54 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const flo
     }
 }
 
-// b_dst = b_src - lr x the column sums that the chunks of a batch have left.
+// b_dst = b_src - lr x the column sums that the chunks of a batch have left, block by block in the order of one chunk.
 __global__ __launch_bounds__(256) void mlp_bias_of_chunks_kernel(const float *__restrict__ sums, const float *__restrict__ src,
                                                                  float *__restrict__ dst, const uint32_t *__restrict__ nodes,
-                                                                 uint32_t width, uint32_t chunks, uint64_t d, uint64_t bias_off,
+                                                                 uint32_t width, uint32_t blocks, uint64_t d, uint64_t bias_off,
                                                                  float lr) {
     const uint32_t slot = blockIdx.y, node = nodes ? nodes[slot] : slot, c = blockIdx.x * 256 + threadIdx.x;
     if (c >= width) return;
-    float sum = 0.f;
-    for (uint32_t k = 0; k < chunks; ++k) sum += sums[((uint64_t)slot * chunks + k) * width + c];
+    sums += (uint64_t)slot * blocks * width + c;
+    float sum = sums[0];
+#pragma unroll 8
+    for (uint32_t k = 1; k < blocks; ++k) sum += sums[(uint64_t)k * width];
     dst[(uint64_t)node * d + bias_off + c] = fmaf(-lr, sum, src[(uint64_t)node * d + bias_off + c]);
 }
 
-// How the products are cut.  A workgroup takes `blocks` x 32 samples (as many as fit: every chunk reads the weights again) of
-// four or eight blocks of 32 columns.  Where that leaves compute units without work, the logits' contraction, the longest with the
-// fewest columns, is split between workgroups, and then a workgroup takes fewer samples (4 nodes, 1024-2048-512, batch 128, two
-// steps: 330 us with neither, 207 so).  Updates go inside the products where these fill the chip, because on their own they are
-// cut by rows too (36 nodes, 608-1280-64, batch 128: 302 us apart as well as inside), or where all of it is a few slabs.
-// Everything here follows from the swarm's shape and not from how many nodes step, because splits and chunks decide the order of
-// sums.
+// How the products of a call are cut.  A workgroup takes `blocks` x 32 samples (as many as fit: every chunk reads the weights
+// again) of four or eight blocks of 32 columns.  Where that gives work to no more than half of the compute units, a workgroup takes
+// fewer samples (one node of 256, 1024-4096-1024, batch 128, two steps: 560 -> 279 us; 16 nodes of 736-1376-896, batch 160, on the
+// line: cut at fewer than 128 workgroups 420, at fewer than 256 469).  The logits' contraction, the longest with the fewest
+// columns, is split between workgroups too where the whole swarm leaves compute units without work (4 nodes, 1024-2048-512, batch
+// 128: 330 us with neither, 207 so).
+// Updates go inside the products where these have enough workgroups, because on their own they are cut by rows too, or where all
+// of it is a few slabs.  The lines, inside and apart: batch 32, 512-1024-64, 48 workgroups 103 and 110 us, 1024-4096-1024, 32: 208
+// and 193; batch 64, 800-1504-480, 96: 192 and 196, 48: 182 and 166; batch 96, 512-1024-64, 80: 137 and 147; batch 128 (eight waves
+// each), 1024-4096-1024, 128: 577 and 575, 96: 546 and 495.
+// All of it follows from how many nodes step but the splits, which decide the order of the logits' sums and therefore follow from
+// the swarm alone; the other choices leave every bit where it is.
 struct Plan {
     uint32_t whole, hidden, logits, back;       // blocks
     uint32_t splits;
     bool inside;                                // updates inside the products
 };
-static Plan plan_of(const MlpObjective &o) {
+static Plan plan_of(const MlpObjective &o, uint32_t count) {
     constexpr uint64_t FILL = 256;              // workgroups
+    constexpr uint32_t INSIDE[] = {48, 64, 64, 128};        // workgroups from which updates go inside, by blocks
     const uint32_t samples = o.batch / 32;
     Plan p{};
     p.whole = parts_of(samples, parts_of(samples, MOST_BLOCKS));
-    auto groups = [&](uint32_t columns) { return (uint64_t)parts_of(columns / 32, 4) * o.n_nodes; };
+    auto groups = [](uint32_t columns, uint32_t waves, uint32_t nodes) { return (uint64_t)parts_of(columns / 32, waves) * nodes; };
     auto cut = [&](uint32_t columns, uint32_t splits) {
         uint32_t blocks = p.whole;
-        while (blocks > 1 && groups(columns) * splits * parts_of(samples, blocks) < FILL) blocks = (blocks + 1) / 2;
+        while (blocks > 1 && groups(columns, 4, count) * splits * parts_of(samples, blocks) <= FILL / 2) blocks = (blocks + 1) / 2;
         return blocks;
     };
     p.hidden = cut(o.n_hid, 1);
-    p.splits = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({MOST_SPLITS, o.n_hid / 32 / 4, FILL / groups(o.n_out)}));
+    p.splits = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({MOST_SPLITS, o.n_hid / 32 / 4, FILL / groups(o.n_out, 4, o.n_nodes)}));
     p.logits = cut(o.n_out, p.splits);
     p.inside = p.whole == samples && updates_inside(samples) &&
-               (groups(o.n_hid) >= FILL * 3 / 4 || std::max(o.n_in, o.n_out) <= 128);
+               (groups(o.n_hid, product_waves(samples, true), count) >= INSIDE[samples - 1] || std::max(o.n_in, o.n_out) <= 128);
     p.back = p.inside ? p.whole : p.hidden;
     return p;
 }
@@ -701,7 +708,7 @@ hipError_t alloc_mlp_split(MlpObjective &o) {
     packed(s.dlogits_by_sample, rows, out);
     packed(s.dlogits_by_class, out, batch);
     packed(s.dpre_by_unit, hid, batch);
-    take(s.logits, sizeof(float) * plan_of(o).splits * n * o.batch * o.n_out);
+    take(s.logits, sizeof(float) * plan_of(o, o.n_nodes).splits * n * o.batch * o.n_out);
     take(s.sums, sizeof(float) * n * batch * o.n_hid);
     take(s.mask, sizeof(uint16_t) * n * batch * hid * 64);
     if (e != hipSuccess) {
@@ -768,7 +775,7 @@ hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjectiv
     const uint64_t x_s = packed_words(rows, I / 32), x_f = packed_words(I / 32, sb);
     const uint64_t hid_s = packed_words(rows, Hd / 32), hid_u = packed_words(Hd / 32, sb);
     const uint64_t dl_s = packed_words(rows, O / 32), dl_c = packed_words(O / 32, sb), split_stride = (uint64_t)o.n_nodes * Bt * O;
-    const Plan plan = plan_of(o);
+    const Plan plan = plan_of(o, count);
     auto product = [&](ProductArgs g, ProductKind kind, bool updating, uint32_t blocks, uint32_t contraction, uint32_t columns) {
         g.slabs = contraction / 32;
         g.cols = columns / 32;
@@ -828,7 +835,7 @@ hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjectiv
         product(g, PRODUCT_BACK, plan.inside, plan.back, O, Hd);
         if (!plan.inside) update(u, O, Hd);
         if (plan.back < sb)
-            mlp_bias_of_chunks_kernel<<<dim3(parts_of(Hd, 256), count), 256, 0, st>>>(ws.sums, src, W, nodes, Hd, parts_of(sb, plan.back), d, off_b1, lr);
+            mlp_bias_of_chunks_kernel<<<dim3(parts_of(Hd, 256), count), 256, 0, st>>>(ws.sums, src, W, nodes, Hd, sb, d, off_b1, lr);
         launch_mlp_bias(o.dlogits, src, W, nodes, O, Bt, count, d, off_b2, lr, st);
         // W1 <- W1 - eta dpre^T x
         u.a = ws.dpre_by_unit; u.a_stride = hid_u;

@@ -5,6 +5,7 @@
 //   host_calls interact n d bits H batch graph             swarm_interact(0, a neighbour)
 //   host_calls steps    n d bits H batch graph             swarm_local_steps(all)
 //   host_calls rounds   n d bits H fail count              `count` rounds of one pair; the launch numbered `fail` fails (0: none)
+//   host_calls mlp      n in hid out batch H nodes         swarm_local_steps(0 .. nodes - 1) of perceptrons, bf16x3 arithmetic
 // graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
 #include <cxxabi.h>
 #include <cstdio>
@@ -94,9 +95,40 @@ std::vector<uint32_t> edges_of(const std::string &graph, uint32_t n) {
 }
 }  // namespace
 
+static int perceptrons(char **argv) {
+    uint32_t v[7];                                                  // n, in, hid, out, batch, H, nodes
+    for (int k = 0; k < 7; ++k) v[k] = (uint32_t)std::strtoul(argv[2 + k], nullptr, 10);
+    const std::vector<uint32_t> edges = edges_of("ring", v[0]);
+    swarm_config c{};
+    c.n = v[0];
+    c.d = (uint64_t)v[2] * v[1] + v[2] + (uint64_t)v[3] * v[2] + v[3];
+    c.bits = 8;
+    c.H = v[5];
+    c.edges = edges.data();
+    c.n_edges = (uint32_t)(edges.size() / 2);
+    c.eps = 0.5f;
+    c.lr = 0.1f;
+    c.seed = 1;
+    swarm_t h = nullptr;
+    const float *data = reinterpret_cast<const float *>(64);        // the host never reads them
+    if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
+    swarm_status rc = swarm_set_objective_mlp(h, v[1], v[2], v[3], data, data, 0.5f, v[4]);
+    if (rc == SWARM_OK) rc = swarm_set_mlp_arithmetic(h, SWARM_MLP_BF16X3);
+    if (rc != SWARM_OK) { std::printf("objective: %s\nstatus %d\n", swarm_last_error(h), rc); swarm_destroy(h); return 0; }
+    std::vector<uint32_t> nodes(v[6]);
+    for (uint32_t k = 0; k < v[6]; ++k) nodes[k] = k;
+    logging = true;
+    rc = v[6] < v[0] ? swarm_local_steps(h, nodes.data(), v[6]) : swarm_local_steps(h, nullptr, 0);
+    logging = false;
+    std::printf("status %d\n", rc);
+    swarm_destroy(h);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 8) return 2;
     const std::string call = argv[1];
+    if (call == "mlp") return argc < 9 ? 2 : perceptrons(argv);
     const uint32_t batch = call == "rounds" ? 0u : (uint32_t)std::atoi(argv[6]);
     const std::string graph = call == "rounds" ? "complete" : argv[7];
     swarm_config c{};

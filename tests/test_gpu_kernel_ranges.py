@@ -180,6 +180,13 @@ def test_mlp_forms_from_bf16_operands(gpu, n, n_in, n_hid, n_out, batch):
     assert torch.equal(s.models_view(gpu.LIVE)[some], whole[some])
 
 
+# Batches in chunks (tests/test_host_calls.py: which): five blocks of 32 samples per workgroup, 4 + 3, 5 + 4, 4 + 4 + 3, the
+# backward product apart from the update; the few nodes of the second call take other chunks, and the same bits
+@pytest.mark.parametrize("batch", [160, 224, 288, 352])
+def test_mlp_products_in_chunks(gpu, batch):
+    test_mlp_forms_from_bf16_operands(gpu, 64, 32, 512, 32, batch)
+
+
 def test_mlp_contraction_of_more_than_4_gib_of_packed_features(gpu):
     """2^20 + 1 slabs of 32 features and 4 KiB each, the weights of all but the last slab zero: a 32-bit byte offset would come
     round to the first slab's features.  The update of W2 shows the hidden activations; against the float32 arithmetic, whose

@@ -114,3 +114,33 @@ def test_staging_slot_is_guarded_until_its_readers_are_done(host_calls, fail):
 def test_descriptors_are_copied_ahead_of_larger_rounds(host_calls, n, d, copied):
     out = host_calls("rounds", n, d, 8, 2, 0, 1)
     assert ("copy" in out) == copied and out[-1] == "status 0"
+
+
+# Perceptrons, bf16x3 products, one step of `count` of the n nodes: blocks of 32 samples per workgroup and workgroups (dies in
+# turn) of the hidden, logits and backward products, the latter with the update of W2 inside or apart.  What a workgroup takes
+# follows from the nodes that step: one node of a swarm that fills the chip would leave it idle in the whole swarm's form.
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,count,hidden,logits,back,inside", [
+    (256, 1024, 4096, 1024, 128, 256, (4, 8192), (4, 2048), (4, 4096), True),
+    (256, 1024, 4096, 1024, 128, 8, (4, 256), (1, 256), (4, 128), True),
+    (256, 1024, 4096, 1024, 128, 7, (4, 224), (1, 224), (4, 224), False),
+    (256, 1024, 4096, 1024, 128, 1, (1, 128), (1, 32), (1, 128), False),
+    (32, 800, 1504, 480, 64, 32, (2, 384), (2, 256), (2, 384), True),
+    (32, 800, 1504, 480, 64, 5, (1, 120), (1, 80), (1, 120), False),
+    (64, 736, 1376, 896, 160, 12, (5, 136), (3, 168), (5, 136), False),
+    (64, 736, 1376, 896, 160, 1, (1, 56), (1, 40), (1, 56), False),
+    (100, 96, 224, 64, 32, 1, (1, 8), (1, 8), (1, 8), True),
+    (64, 32, 512, 32, 160, 64, (5, 256), (5, 256), (5, 256), False),
+    (64, 32, 512, 32, 224, 64, (4, 512), (4, 512), (4, 512), False),
+    (64, 32, 512, 32, 288, 64, (5, 512), (5, 512), (5, 512), False),
+    (64, 32, 512, 32, 352, 64, (4, 768), (4, 768), (4, 768), False),
+    (64, 32, 512, 32, 352, 9, (2, 216), (2, 216), (2, 216), False)])
+def test_perceptron_products(host_calls, n, n_in, n_hid, n_out, batch, count, hidden, logits, back, inside):
+    out = host_calls("mlp", n, n_in, n_hid, n_out, batch, 1, count)
+    products = [ln for ln in out if "mlp_product_kernel" in ln]
+    threads = 512 if inside and batch == 128 else 256
+    assert products == [
+        f"launch mlp_product_kernel<{hidden[0]}, true, 0, false> grid {hidden[1]} 1 block 256 shared 0",
+        f"launch mlp_product_kernel<{logits[0]}, true, 1, false> grid {logits[1]} 1 block 256 shared 0",
+        f"launch mlp_product_kernel<{back[0]}, false, 2, {str(inside).lower()}> grid {back[1]} 1 block {threads} shared 0"]
+    assert sum("update" in k for k in kernels(out)) == (1 if inside else 2)
+    assert kernels(out).count("mlp_bias_of_chunks_kernel") == (back[0] < batch // 32) and out[-1] == "status 0"
