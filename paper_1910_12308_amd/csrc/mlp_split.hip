@@ -26,6 +26,10 @@ namespace swarm {
 enum ProductKind { PRODUCT_HIDDEN = 0, PRODUCT_LOGITS = 1, PRODUCT_BACK = 2 };
 constexpr uint32_t MOST_BLOCKS = 5;              // blocks of 32 samples that one workgroup of a product takes at most
 constexpr uint32_t MOST_SPLITS = 8;              // of the logits' contraction
+// Updates of long batches: fewer tiles of 128 x 128 weights are taken as 64 x 64 (us for two steps, 64 x 64 throughout and this rule:
+// 4 nodes, 1024-2048-512, batch 512 386 and 337; 64 nodes, 736-1376-896, batch 192 1858 and 1643; 128 x 128 throughout leaves one
+// workgroup to each of 8 nodes, 64-128-32, batch 1024: 178 and 131).
+constexpr uint32_t SMALL_TILES = 256;
 
 struct ProductArgs {
     const u4 *act;                  // activations, rows = samples, packed over the contraction index; per slot
@@ -444,52 +448,77 @@ __global__ __launch_bounds__(256, 2) void mlp_update_kernel(const UpdateArgs g) 
     if (r < last) step(r, std::integral_constant<int, 0>{});
 }
 
-// The same for any number of samples: a workgroup takes 128 x 128 weights, a wave 64 x 64, both operands from cache.
+// The same for any number of samples: a wave takes B x B blocks of 32 x 32 weights, a workgroup of 2 x 2 waves, both operands from
+// cache, DEPTH half slabs on their way; the weights are requested behind the first of these.  Bound by the latency of these
+// requests until the waves are many, by memory then.  us for two steps, with nothing requested ahead and tiles of 128 x 128, and so:
+// 16 nodes, 800-1504-480, batch 288 550 and 528, one of them 280 and 155; 4 nodes, 1024-2048-512, batch 512 393 and 337; 8 nodes,
+// 256-512-64, batch 4096 1697 and 755.
+template <int B>
 __global__ __launch_bounds__(256, 2) void mlp_update_long_kernel(const UpdateArgs g) {
+    constexpr int DEPTH = B == 1 ? 4 : 2;
     const uint32_t lane = threadIdx.x & 63u, half = lane >> 5, r32 = lane & 31u, wave = wave_of_group();
     bool valid;
     const uint32_t q = place_of(blockIdx.x, g.groups, valid);
     if (!valid) return;
     const uint32_t per_slot = g.groups_n * g.parts, slot = q / per_slot, blocks = g.sample_blocks;
     const uint32_t node = g.nodes ? g.nodes[slot] : slot, ldw = g.ldw;
-    const uint32_t row0 = q % per_slot / g.groups_n * 4 + (wave >> 1) * 2, col0 = q % g.groups_n * 4 + (wave & 1u) * 2;
+    const uint32_t row0 = q % per_slot / g.groups_n * 2 * B + (wave >> 1) * B, col0 = q % g.groups_n * 2 * B + (wave & 1u) * B;
     if (row0 >= g.rows || col0 >= g.cols) return;
-    const u4 *a[2], *b[2];
+    Buffer a[B], b[B];
 #pragma unroll
-    for (uint32_t i = 0; i < 2; ++i) {
-        a[i] = g.a + slot * g.a_stride + fragments_at(min(row0 + i, g.rows - 1), blocks, 0);
-        b[i] = g.b + slot * g.b_stride + fragments_at(min(col0 + i, g.cols - 1), blocks, 0);
+    for (uint32_t i = 0; i < B; ++i) {
+        a[i] = buffer_at(g.a + slot * g.a_stride + fragments_at(min(row0 + i, g.rows - 1), blocks, 0), (uint64_t)blocks * 4096);
+        b[i] = buffer_at(g.b + slot * g.b_stride + fragments_at(min(col0 + i, g.cols - 1), blocks, 0), (uint64_t)blocks * 4096);
     }
-    f16v sum[2][2];
+    const uint64_t from = node * g.d + g.weights + (uint64_t)row0 * 32 * ldw + 32 * col0;
+    const uint32_t lane_bytes = 4 * (4 * half * ldw + r32);
+    auto inside = [&](uint32_t i, uint32_t j) { return B == 1 || (row0 + i < g.rows && col0 + j < g.cols); };
+
+    f16v sum[B][B];
+    float w[B][B][16];
+    struct Operands { u4 x[B][2], y[B][2]; } staged[DEPTH];
+    const uint32_t halves = 2 * blocks;
+    auto load = [&](uint32_t h, Operands &o) {     // half slab h, past the end the last one again
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sum[i / 2][i % 2] = cleared();
-    for (uint32_t f = 0; f < 4 * blocks; f += 2) {
-        u4 x[2][2], y[2][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < B; ++i)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                x[i][p] = a[i][(f + p) * FRAGMENT + lane];
-                y[i][p] = b[i][(f + p) * FRAGMENT + lane];
+                o.x[i][p] = load16<0>(a[i], 16 * lane, (2 * min(h, halves - 1) + p) * 1024);
+                o.y[i][p] = load16<0>(b[i], 16 * lane, (2 * min(h, halves - 1) + p) * 1024);
             }
+    };
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (uint32_t i = 0; i < DEPTH; ++i) load(i, staged[i]);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) add_products<false>(x[i][0], x[i][1], y[j][0], y[j][1], sum[i][j]);
-    }
-    const uint32_t lane_bytes = 4 * (4 * half * ldw + r32);
+    for (uint32_t i = 0; i < B; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            if (row0 + i >= g.rows || col0 + j >= g.cols) continue;
-            const uint64_t at = node * g.d + g.weights + (uint64_t)(row0 + i) * 32 * ldw + 32 * (col0 + j);
-            float w[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) w[v] = __builtin_nontemporal_load(at_bytes(uniform(g.src + at + (uint64_t)row_of(v, 0) * ldw), lane_bytes));
+        for (uint32_t j = 0; j < B; ++j) {
+            sum[i][j] = cleared();
+            if (!inside(i, j)) continue;
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                __builtin_nontemporal_store(fmaf(-g.lr, sum[i][j][v], w[v]), at_bytes(uniform(g.dst + at + (uint64_t)row_of(v, 0) * ldw), lane_bytes));
+                w[i][j][v] = __builtin_nontemporal_load(at_bytes(uniform(g.src + from + (uint64_t)(32 * i + row_of(v, 0)) * ldw + 32 * j), lane_bytes));
+        }
+    for (uint32_t h = 0; h < halves; h += DEPTH)
+#pragma unroll
+        for (uint32_t k = 0; k < DEPTH; ++k) {
+            if (DEPTH > 2 && h + k >= halves) break;                  // there are two halves to a slab
+            const Operands o = staged[k];
+            load(h + k + DEPTH, staged[k]);
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+#pragma unroll
+                for (int j = 0; j < B; ++j) add_products<false>(o.x[i][0], o.x[i][1], o.y[j][0], o.y[j][1], sum[i][j]);
+        }
+#pragma unroll
+    for (uint32_t i = 0; i < B; ++i)
+#pragma unroll
+        for (uint32_t j = 0; j < B; ++j) {
+            if (!inside(i, j)) continue;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                __builtin_nontemporal_store(fmaf(-g.lr, sum[i][j][v], w[i][j][v]),
+                                            at_bytes(uniform(g.dst + from + (uint64_t)(32 * i + row_of(v, 0)) * ldw + 32 * j), lane_bytes));
         }
 }
 
@@ -754,7 +783,19 @@ static void launch_product(const ProductArgs &g, ProductKind kind, bool update, 
         default: product_kind<5>(g, kind, update, count, st); break;
     }
 }
-static void launch_update(const UpdateArgs &g, hipStream_t st) {
+static void launch_update(UpdateArgs g, uint32_t count, hipStream_t st) {
+    if (g.sample_blocks > MOST_BLOCKS) {
+        const bool small = parts_of(g.rows, 4) * parts_of(g.cols, 4) * count < SMALL_TILES;
+        g.groups_n = parts_of(g.cols, small ? 2 : 4);
+        g.parts = parts_of(g.rows, small ? 2 : 4);
+        g.groups = g.groups_n * g.parts * count;
+        if (small) mlp_update_long_kernel<1><<<whole_turns(g.groups), 256, 0, st>>>(g);
+        else mlp_update_long_kernel<2><<<whole_turns(g.groups), 256, 0, st>>>(g);
+        return;
+    }
+    g.groups_n = parts_of(g.cols, 4);
+    g.parts = std::max(1u, std::min(1024 / (count * g.groups_n), g.rows / 2));
+    g.groups = g.groups_n * g.parts * count;
     const uint32_t grid = whole_turns(g.groups);
     switch (g.sample_blocks) {
         case 1: mlp_update_kernel<1><<<grid, 256, 0, st>>>(g); break;
@@ -762,7 +803,7 @@ static void launch_update(const UpdateArgs &g, hipStream_t st) {
         case 3: mlp_update_kernel<3><<<grid, 256, 0, st>>>(g); break;
         case 4: mlp_update_kernel<4><<<grid, 256, 0, st>>>(g); break;
         case 5: mlp_update_kernel<5><<<grid, 256, 0, st>>>(g); break;
-        default: mlp_update_long_kernel<<<grid, 256, 0, st>>>(g); break;
+        default: break;
     }
 }
 
@@ -787,10 +828,7 @@ hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjectiv
     auto update = [&](UpdateArgs g, uint32_t n_rows, uint32_t n_cols) {
         g.rows = n_rows / 32;
         g.cols = n_cols / 32;
-        g.groups_n = parts_of(g.cols, 4);
-        g.parts = sb > MOST_BLOCKS ? parts_of(g.rows, 4) : std::max(1u, std::min(1024 / (count * g.groups_n), g.rows / 2));
-        g.groups = g.groups_n * g.parts * count;
-        launch_update(g, st);
+        launch_update(g, count, st);
     };
     auto draw_batch = [&](uint32_t q) {
         // as many features per workgroup as still leave enough workgroups

@@ -144,3 +144,16 @@ def test_perceptron_products(host_calls, n, n_in, n_hid, n_out, batch, count, hi
         f"launch mlp_product_kernel<{back[0]}, false, 2, {str(inside).lower()}> grid {back[1]} 1 block {threads} shared 0"]
     assert sum("update" in k for k in kernels(out)) == (1 if inside else 2)
     assert kernels(out).count("mlp_bias_of_chunks_kernel") == (back[0] < batch // 32) and out[-1] == "status 0"
+
+
+# Updates of the weights, bf16x3: up to 160 samples down the rows of the matrix, more by tiles of 128 x 128 weights or, where these
+# are fewer than 256, of 64 x 64
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,count,w2,w1", [
+    (40, 128, 640, 96, 160, 40, ("mlp_update_kernel<5>", 200), ("mlp_update_kernel<5>", 400)),
+    (64, 32, 512, 32, 192, 64, ("mlp_update_long_kernel<2>", 256), ("mlp_update_long_kernel<2>", 256)),
+    (64, 32, 512, 32, 192, 63, ("mlp_update_long_kernel<1>", 504), ("mlp_update_long_kernel<1>", 504)),
+    (65, 128, 512, 160, 224, 65, ("mlp_update_long_kernel<2>", 520), ("mlp_update_long_kernel<2>", 264)),
+    (8, 64, 128, 32, 1024, 8, ("mlp_update_long_kernel<1>", 16), ("mlp_update_long_kernel<1>", 16))])
+def test_perceptron_updates(host_calls, n, n_in, n_hid, n_out, batch, count, w2, w1):
+    out = host_calls("mlp", n, n_in, n_hid, n_out, batch, 1, count)
+    assert [ln for ln in out if "update" in ln] == [f"launch {k} grid {g} 1 block 256 shared 0" for k, g in (w2, w1)]
