@@ -434,7 +434,9 @@ __global__ __launch_bounds__(256, 3) void mlp_float_update_kernel(const FloatUpd
 
 static void launch_float_update(FloatUpdateArgs g, uint32_t batch, uint32_t count, hipStream_t st) {
     g.groups_n = parts_of(g.cols, 4);
-    g.parts = std::max(1u, std::min(1024 / (count * g.groups_n), g.rows / 2));
+    // up to 1024 workgroups a block of rows each, else two or more (us for two steps of one node, two or more throughout and so:
+    // 608-1280-64, batch 128 234 and 227; 800-1504-480, batch 64 210 and 203; 39 nodes, 96-256-64, batch 128 124 and 120)
+    g.parts = (uint64_t)count * g.groups_n * g.rows <= 1024 ? g.rows : std::max(1u, std::min(1024 / (count * g.groups_n), g.rows / 2));
     g.groups = g.groups_n * g.parts * count;
     const uint32_t grid = whole_turns(g.groups);
     switch (batch / 32) {

@@ -6,6 +6,7 @@
 //   host_calls steps    n d bits H batch graph             swarm_local_steps(all)
 //   host_calls rounds   n d bits H fail count              `count` rounds of one pair; the launch numbered `fail` fails (0: none)
 //   host_calls mlp      n in hid out batch H nodes         swarm_local_steps(0 .. nodes - 1) of perceptrons, bf16x3 arithmetic
+//   host_calls mlp_fp32 n in hid out batch H nodes         the same in float32
 // graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
 #include <cxxabi.h>
 #include <cstdio>
@@ -95,7 +96,7 @@ std::vector<uint32_t> edges_of(const std::string &graph, uint32_t n) {
 }
 }  // namespace
 
-static int perceptrons(char **argv) {
+static int perceptrons(char **argv, uint32_t arithmetic) {
     uint32_t v[7];                                                  // n, in, hid, out, batch, H, nodes
     for (int k = 0; k < 7; ++k) v[k] = (uint32_t)std::strtoul(argv[2 + k], nullptr, 10);
     const std::vector<uint32_t> edges = edges_of("ring", v[0]);
@@ -113,7 +114,7 @@ static int perceptrons(char **argv) {
     const float *data = reinterpret_cast<const float *>(64);        // the host never reads them
     if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
     swarm_status rc = swarm_set_objective_mlp(h, v[1], v[2], v[3], data, data, 0.5f, v[4]);
-    if (rc == SWARM_OK) rc = swarm_set_mlp_arithmetic(h, SWARM_MLP_BF16X3);
+    if (rc == SWARM_OK) rc = swarm_set_mlp_arithmetic(h, arithmetic);
     if (rc != SWARM_OK) { std::printf("objective: %s\nstatus %d\n", swarm_last_error(h), rc); swarm_destroy(h); return 0; }
     std::vector<uint32_t> nodes(v[6]);
     for (uint32_t k = 0; k < v[6]; ++k) nodes[k] = k;
@@ -128,7 +129,8 @@ static int perceptrons(char **argv) {
 int main(int argc, char **argv) {
     if (argc < 8) return 2;
     const std::string call = argv[1];
-    if (call == "mlp") return argc < 9 ? 2 : perceptrons(argv);
+    if (call == "mlp") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_BF16X3);
+    if (call == "mlp_fp32") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_FP32);
     const uint32_t batch = call == "rounds" ? 0u : (uint32_t)std::atoi(argv[6]);
     const std::string graph = call == "rounds" ? "complete" : argv[7];
     swarm_config c{};

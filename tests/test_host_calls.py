@@ -157,3 +157,14 @@ def test_perceptron_products(host_calls, n, n_in, n_hid, n_out, batch, count, hi
 def test_perceptron_updates(host_calls, n, n_in, n_hid, n_out, batch, count, w2, w1):
     out = host_calls("mlp", n, n_in, n_hid, n_out, batch, 1, count)
     assert [ln for ln in out if "update" in ln] == [f"launch {k} grid {g} 1 block 256 shared 0" for k, g in (w2, w1)]
+
+
+# Updates of the weights in float32, up to 128 samples: a block of 32 rows per workgroup while there are at most 1024, two or more
+# otherwise
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,count,w2,w1", [
+    (36, 608, 1280, 64, 128, 1, 24, 200), (36, 608, 1280, 64, 128, 5, 104, 1000), (36, 608, 1280, 64, 128, 6, 120, 600),
+    (2, 32, 32, 32, 32, 2, 8, 8), (256, 1024, 4096, 1024, 128, 256, 8192, 2048)])
+def test_perceptron_updates_in_float32(host_calls, n, n_in, n_hid, n_out, batch, count, w2, w1):
+    out = host_calls("mlp_fp32", n, n_in, n_hid, n_out, batch, 1, count)
+    assert [ln for ln in out if "update" in ln] == [
+        f"launch mlp_float_update_kernel<{batch // 32}> grid {g} 1 block 256 shared 0" for g in (w2, w1)]
