@@ -158,8 +158,9 @@ swarm_status swarm_set_objective_mlp(swarm_t h, uint32_t n_in, uint32_t n_hid, u
  * bf16 matrix cores, float32 accumulation; the dropped terms are below 2^-16 |a b| per product, well
  * inside the 1e-4 bound of the GEMM-based gradients, and the local steps run at the speed of their
  * memory traffic instead of the float32 matrix rate.  Models, logits and updates stay float32 in
- * memory, activations lie there as these pairs.  BF16X3 allocates workspace of its own for all n nodes.
- * Call after swarm_set_objective_mlp (SWARM_ESTATE otherwise). */
+ * memory, activations lie there as these pairs.  BF16X3 allocates workspace of its own, for all n nodes
+ * or, where that finds no room, for fewer, which then step in groups with the same results; FP32 gives it
+ * back and waits for the device to do so.  Call after swarm_set_objective_mlp (SWARM_ESTATE otherwise). */
 enum { SWARM_MLP_FP32 = 0, SWARM_MLP_BF16X3 = 1 };
 swarm_status swarm_set_mlp_arithmetic(swarm_t h, uint32_t arithmetic);
 

@@ -13,6 +13,7 @@
 //    8 nodes, 1024-4096-1024, batch 32     478 -> 382      64 nodes, 736-1376-896, batch 160  1693 -> 1340
 //    4 nodes, 1024-2048-512, batch 128     255 -> 207      16 nodes, 800-1504-480, batch 288   704 -> 622
 #include <algorithm>
+#include <new>
 #include <type_traits>
 
 #include "internal.h"
@@ -119,6 +120,8 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
     struct Staged { u4 act[PER_WAVE], rows[UPDATE ? PER_WAVE : 1]; };
     // Offsets are 32 bits: the slab moves the base, so that one block of samples has no limit (2^20 slabs of 4 KiB are reached by
     // 33.5 M features; several blocks are taken where many workgroups read them, and memory ends long before 2^18 slabs).
+    // Blocks past the batch read its last one and are dropped.
+    const uint32_t last_block = g.sample_blocks - 1 - chunk * BLOCKS;
     auto load_act = [&](uint32_t t, Staged &r) {
         const Buffer act_buffer = buffer_at(act + (uint64_t)t * 4 * FRAGMENT, ((uint64_t)(BLOCKS - 1) * slabs + 1) * 4096);
         const Buffer rows_buffer = buffer_at(by_row + (uint64_t)t * FRAGS * FRAGMENT, FRAGS * 1024);
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
         for (int i = 0; i < PER_WAVE; ++i) {
             const uint32_t f = wave + WAVES * i;
             if (FRAGS % WAVES == 0 || f < FRAGS) {
-                r.act[i] = load16<0>(act_buffer, 16 * lane, (f / 4 * slabs * 4 + f % 4) * 1024);
+                r.act[i] = load16<0>(act_buffer, 16 * lane, (min(f / 4, last_block) * slabs * 4 + f % 4) * 1024);
                 if (UPDATE) r.rows[i] = load16<0>(rows_buffer, 16 * lane, f * 1024);
             }
         }
@@ -526,13 +529,14 @@ __global__ __launch_bounds__(256, 2) void mlp_update_long_kernel(const UpdateArg
 // searches the label of its own sample.
 constexpr uint32_t BATCH_TILES = 4;
 __global__ __launch_bounds__(256) void mlp_packed_batch_kernel(const float *__restrict__ means, const float *__restrict__ cdf,
-                                                               const uint32_t *__restrict__ nodes, const uint32_t *__restrict__ events,
+                                                               const uint32_t *__restrict__ nodes, uint32_t first_node,
+                                                               const uint32_t *__restrict__ events,
                                                                uint32_t *__restrict__ labels, u4 *__restrict__ by_sample,
                                                                u4 *__restrict__ by_feature, uint64_t by_sample_stride,
                                                                uint64_t by_feature_stride, uint32_t n_in, uint32_t n_out, uint32_t batch,
                                                                uint32_t per_group, float sigma, uint64_t seed, uint32_t event, uint32_t q) {
     __shared__ __attribute__((aligned(16))) float tiles[BATCH_TILES][32 * TILE_LD];
-    const uint32_t slot = blockIdx.z, node = nodes ? nodes[slot] : slot;
+    const uint32_t slot = blockIdx.z, node = nodes ? nodes[slot] : first_node + slot;
     if (events) event = events[slot];
     const uint32_t row = threadIdx.x >> 3, s = blockIdx.y * 32 + row, at = 4 * (threadIdx.x & 7u);
     const uint32_t first = blockIdx.x * per_group, last = min(first + per_group, n_in / 32);
@@ -726,48 +730,81 @@ static Plan plan_of(const MlpObjective &o, uint32_t count) {
     return p;
 }
 
-// Workspace for all nodes: packed operands, logits (for every split) and their gradient, signs of the hidden units, column sums.
+// Workspace of the nodes that step together: packed operands, logits for every split, signs of the hidden units, column sums.
 struct MlpSplitSpace {
+    uint32_t nodes;
+    void *own;                                  // what does not fit into the float32 steps' activations
     u4 *x_by_sample, *x_by_feature[2], *hid_by_sample, *hid_by_unit, *dlogits_by_sample, *dlogits_by_class, *dpre_by_unit;
     float *logits, *sums;
     uint16_t *mask;
 };
 
+// Where the workspace of s.nodes nodes lies: in x, hid and dhid, which hold the float32 steps' activations and which these steps do
+// not use otherwise, as far as it fits, the rest from s.own on.  Returns the bytes of the rest.
+static uint64_t lay_out(const MlpObjective &o, MlpSplitSpace &s) {
+    const uint64_t in = o.n_in, hid = o.n_hid, out = o.n_out, batch = o.batch, value = sizeof(float);
+    const Plan all = plan_of(o, o.n_nodes), one = plan_of(o, 1);
+    struct Area { uintptr_t at; uint64_t left; };
+    Area areas[] = {{(uintptr_t)o.x, value * o.n_nodes * batch * in}, {(uintptr_t)o.hid, value * o.n_nodes * batch * hid},
+                    {(uintptr_t)o.dhid, value * o.n_nodes * batch * hid}};
+    uint64_t rest = 0;
+    auto take = [&](auto &p, uint64_t bytes_of_node) {
+        const uint64_t bytes = (bytes_of_node * s.nodes + 255) / 256 * 256;
+        uintptr_t at = (uintptr_t)s.own + rest;
+        bool fits = false;
+        for (Area &a : areas) {
+            fits = bytes <= a.left;
+            if (!fits) continue;
+            at = a.at;
+            a.at += bytes;
+            a.left -= bytes;
+            break;
+        }
+        if (!fits) rest += bytes;
+        p = (std::remove_reference_t<decltype(p)>)at;
+    };
+    take(s.x_by_sample, value * batch * in);             // hi and lo are as large as the value
+    take(s.hid_by_sample, value * batch * hid);
+    take(s.dpre_by_unit, value * batch * hid);
+    take(s.hid_by_unit, value * batch * hid);
+    take(s.x_by_feature[0], value * batch * in);
+    s.x_by_feature[1] = s.x_by_feature[0];
+    if (all.inside) take(s.x_by_feature[1], value * batch * in);         // updates inside meet the next step's features
+    take(s.dlogits_by_sample, value * batch * out);
+    take(s.dlogits_by_class, value * batch * out);
+    take(s.logits, value * all.splits * batch * out);
+    if (one.back < batch / 32) take(s.sums, value * (batch / 32) * hid); // few nodes have the most chunks
+    take(s.mask, sizeof(uint16_t) * (batch / 32) * (hid / 32) * 64);
+    return rest;
+}
+
+// For all nodes, or, where memory is short, for as many as find room: the others step after them.
 hipError_t alloc_mlp_split(MlpObjective &o) {
     if (o.split) return hipSuccess;
-    o.split = new MlpSplitSpace{};
-    MlpSplitSpace &s = *o.split;
-    const uint64_t n = o.n_nodes, in = o.n_in / 32, hid = o.n_hid / 32, out = o.n_out / 32, batch = o.batch / 32;
-    const uint64_t rows = batch + MOST_BLOCKS - 1;       // a last chunk reads, and drops, what lies behind the batch
-    hipError_t e = hipSuccess;
-    auto take = [&](auto &p, uint64_t bytes) {
-        if (e == hipSuccess) e = hipMalloc((void **)&p, bytes);
-    };
-    auto packed = [&](u4 *&p, uint64_t row_blocks, uint64_t slabs) { take(p, n * packed_words(row_blocks, slabs) * sizeof(u4)); };
-    packed(s.x_by_sample, rows, in);
-    packed(s.x_by_feature[0], in, batch);
-    packed(s.x_by_feature[1], in, batch);
-    packed(s.hid_by_sample, rows, hid);
-    packed(s.hid_by_unit, hid, batch);
-    packed(s.dlogits_by_sample, rows, out);
-    packed(s.dlogits_by_class, out, batch);
-    packed(s.dpre_by_unit, hid, batch);
-    take(s.logits, sizeof(float) * plan_of(o, o.n_nodes).splits * n * o.batch * o.n_out);
-    take(s.sums, sizeof(float) * n * batch * o.n_hid);
-    take(s.mask, sizeof(uint16_t) * n * batch * hid * 64);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();                          // reported here, not by the next launch
-        free_mlp_split(o);
+    MlpSplitSpace *s = new (std::nothrow) MlpSplitSpace{};
+    if (!s) return hipErrorOutOfMemory;
+    hipError_t e = hipErrorOutOfMemory;
+    for (uint32_t nodes = o.n_nodes; nodes > 0 && e == hipErrorOutOfMemory; nodes /= 2) {
+        s->nodes = nodes;
+        const uint64_t bytes = lay_out(o, *s);
+        e = bytes > 0 ? hipMalloc(&s->own, bytes) : hipSuccess;
+        if (e != hipSuccess) {
+            (void)hipGetLastError();                      // reported here, not by the next launch
+            s->own = nullptr;
+        }
     }
-    return e;
+    if (e != hipSuccess) {
+        delete s;
+        return e;
+    }
+    (void)lay_out(o, *s);
+    o.split = s;
+    return hipSuccess;
 }
 
 void free_mlp_split(MlpObjective &o) {
     if (!o.split) return;
-    const MlpSplitSpace &s = *o.split;
-    void *p[] = {s.x_by_sample, s.x_by_feature[0], s.x_by_feature[1], s.hid_by_sample, s.hid_by_unit, s.dlogits_by_sample,
-                 s.dlogits_by_class, s.dpre_by_unit, s.logits, s.sums, s.mask};
-    for (void *q : p) if (q) (void)hipFree(q);
+    if (o.split->own) (void)hipFree(o.split->own);
     delete o.split;
     o.split = nullptr;
 }
@@ -822,15 +859,16 @@ static void launch_update(UpdateArgs g, uint32_t count, hipStream_t st) {
     }
 }
 
-hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots, uint32_t count,
-                                  uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
+// Steps of up to ws.nodes nodes; base, W: the models of node 0, or of `first_node`, the first slot's, where slots are not named.
+static void launch_steps(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots, uint32_t first_node, uint32_t count,
+                         uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
     const MlpSplitSpace &ws = *o.split;
     const uint32_t *nodes = slots.nodes;
-    const uint32_t I = o.n_in, Hd = o.n_hid, O = o.n_out, Bt = o.batch, sb = Bt / 32, rows = sb + MOST_BLOCKS - 1;
+    const uint32_t I = o.n_in, Hd = o.n_hid, O = o.n_out, Bt = o.batch, sb = Bt / 32;
     const uint64_t off_b1 = (uint64_t)Hd * I, off_w2 = off_b1 + Hd, off_b2 = off_w2 + (uint64_t)O * Hd;
-    const uint64_t x_s = packed_words(rows, I / 32), x_f = packed_words(I / 32, sb);
-    const uint64_t hid_s = packed_words(rows, Hd / 32), hid_u = packed_words(Hd / 32, sb);
-    const uint64_t dl_s = packed_words(rows, O / 32), dl_c = packed_words(O / 32, sb), split_stride = (uint64_t)o.n_nodes * Bt * O;
+    const uint64_t x_s = packed_words(sb, I / 32), x_f = packed_words(I / 32, sb);
+    const uint64_t hid_s = packed_words(sb, Hd / 32), hid_u = packed_words(Hd / 32, sb);
+    const uint64_t dl_s = packed_words(sb, O / 32), dl_c = packed_words(O / 32, sb), split_stride = (uint64_t)ws.nodes * Bt * O;
     const Plan plan = plan_of(o, count);
     auto product = [&](ProductArgs g, ProductKind kind, bool updating, uint32_t blocks, uint32_t contraction, uint32_t columns) {
         g.slabs = contraction / 32;
@@ -849,7 +887,7 @@ hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjectiv
         // as many features per workgroup as still leave enough workgroups
         const uint32_t tiles = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(BATCH_TILES, (uint64_t)I / 32 * sb * count / 512));
         mlp_packed_batch_kernel<<<dim3(parts_of(I / 32, tiles), sb, count), 256, 0, st>>>(
-            o.means, o.cdf, nodes, slots.events, o.labels, ws.x_by_sample, ws.x_by_feature[q & 1], x_s, x_f, I, O, Bt, tiles, o.data_sigma,
+            o.means, o.cdf, nodes, first_node, slots.events, o.labels, ws.x_by_sample, ws.x_by_feature[q & 1], x_s, x_f, I, O, Bt, tiles, o.data_sigma,
             seed, event, q);
     };
     for (uint32_t q = 0; q < H; ++q) {
@@ -902,6 +940,18 @@ hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjectiv
             first.by_row = u.b; first.by_row_stride = u.b_stride; first.own = u.a; first.own_stride = u.a_stride;
             product(first, PRODUCT_HIDDEN, true, plan.whole, I, Hd);
         }
+    }
+}
+
+hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots, uint32_t count,
+                                  uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
+    const uint32_t each = parts_of(count, parts_of(count, o.split->nodes));
+    for (uint32_t first = 0; first < count; first += each) {
+        LocalSlots part;
+        if (slots.nodes) part.nodes = slots.nodes + first;
+        if (slots.events) part.events = slots.events + first;
+        const uint64_t skipped = slots.nodes ? 0 : first * d;
+        launch_steps(base + skipped, W + skipped, o, part, first, std::min(each, count - first), d, H, lr, seed, event, st);
     }
     return hipGetLastError();
 }

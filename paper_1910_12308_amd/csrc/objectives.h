@@ -36,12 +36,13 @@ struct MlpObjective {
     const float *means = nullptr;   // n_out x n_in
     const float *cdf = nullptr;     // n x n_out
     float data_sigma = 0.f;
-    // workspace for all nodes (owned): inputs, labels, hidden activations, logits gradient, hidden gradient
+    // workspace for all nodes (owned): inputs, labels, hidden activations, logits gradient, hidden gradient; the bf16x3 steps keep
+    // packed operands in x, hid and dhid
     float *x = nullptr, *hid = nullptr, *dlogits = nullptr, *dhid = nullptr;
     uint32_t *labels = nullptr;
     uint32_t n_nodes = 0;
     bool bf16x3 = false;            // products as three bf16 products per term instead of float32 matrix instructions
-    MlpSplitSpace *split = nullptr; // their workspace (owned), there once they have been chosen
+    MlpSplitSpace *split = nullptr; // their workspace (owned), there while they are chosen
 };
 
 // Whole round in one pass (local steps + quantized gossip) for the diagonal objective; bits in {2,4,8,16}.
@@ -73,7 +74,8 @@ void free_mlp(MlpObjective &o);
 hipError_t launch_local_mlp(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots,
                             uint32_t count, uint32_t n, uint64_t d, uint32_t H, float lr, uint64_t seed,
                             uint32_t event, hipStream_t st);
-// The same with bf16x3 products; alloc_mlp_split is called when they are chosen and does nothing a second time.
+// The same with bf16x3 products; alloc_mlp_split is called when they are chosen and does nothing a second time, free_mlp_split when
+// they no longer are.
 hipError_t alloc_mlp_split(MlpObjective &o);
 void free_mlp_split(MlpObjective &o);
 hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots, uint32_t count,

@@ -509,6 +509,8 @@ swarm_status swarm_set_mlp_arithmetic(swarm_t h, uint32_t arithmetic) {
         const hipError_t e = alloc_mlp_split(h->mlp);
         if (e != hipSuccess) return fail(h, e == hipErrorOutOfMemory ? SWARM_ENOMEM : SWARM_EDEVICE,
                                          std::string("mlp workspace: ") + hipGetErrorString(e));
+    } else {
+        free_mlp_split(h->mlp);
     }
     h->mlp.bf16x3 = arithmetic == SWARM_MLP_BF16X3;
     return SWARM_OK;

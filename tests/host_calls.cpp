@@ -7,6 +7,8 @@
 //   host_calls rounds   n d bits H fail count              `count` rounds of one pair; the launch numbered `fail` fails (0: none)
 //   host_calls mlp      n in hid out batch H nodes         swarm_local_steps(0 .. nodes - 1) of perceptrons, bf16x3 arithmetic
 //   host_calls mlp_fp32 n in hid out batch H nodes         the same in float32
+//   host_calls mlp_room n in hid out batch H nodes room    as mlp, with `room` bytes of device memory left for the arithmetic; and
+//                                                          device memory with the objective, the arithmetic, and back in float32
 // graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
 #include <cxxabi.h>
 #include <cstdio>
@@ -23,6 +25,8 @@ namespace {
 struct Dim3 { uint32_t x, y, z; };
 bool logging = false;
 int launches = 0, fail_at = 0, last_error = 0;
+size_t in_use = 0, memory = ~(size_t)0;                            // device memory
+std::map<void *, size_t> &allocations() { static std::map<void *, size_t> a; return a; }
 struct Call { Dim3 grid, block; size_t shared; void *stream; } pushed;
 std::map<const void *, std::string> &kernels() { static std::map<const void *, std::string> k; return k; }
 int event_number(const void *e) { return (int)(intptr_t)e; }
@@ -54,10 +58,18 @@ int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3 block, void **, size_t s
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int) { return "stand-in error"; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
-int hipMalloc(void **p, size_t n) { *p = std::calloc(n ? n : 1, 1); return *p ? 0 : 2; }
-int hipFree(void *p) { std::free(p); return 0; }
-int hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
-int hipHostFree(void *p) { return hipFree(p); }
+int hipHostMalloc(void **p, size_t n, unsigned) { *p = std::calloc(n ? n : 1, 1); return *p ? 0 : 2; }
+int hipHostFree(void *p) { std::free(p); return 0; }
+int hipMalloc(void **p, size_t n) {
+    if (n > memory - in_use || hipHostMalloc(p, n, 0)) { last_error = 2; return 2; }
+    in_use += allocations()[*p] = n;
+    return 0;
+}
+int hipFree(void *p) {
+    in_use -= allocations()[p];
+    allocations().erase(p);
+    return hipHostFree(p);
+}
 int hipHostGetDevicePointer(void **d, void *p, unsigned) { *d = p; return 0; }
 int hipMemset(void *, int, size_t) { return 0; }
 int hipMemsetAsync(void *, int, size_t, void *) { return 0; }
@@ -96,7 +108,7 @@ std::vector<uint32_t> edges_of(const std::string &graph, uint32_t n) {
 }
 }  // namespace
 
-static int perceptrons(char **argv, uint32_t arithmetic) {
+static int perceptrons(char **argv, uint32_t arithmetic, const char *room) {
     uint32_t v[7];                                                  // n, in, hid, out, batch, H, nodes
     for (int k = 0; k < 7; ++k) v[k] = (uint32_t)std::strtoul(argv[2 + k], nullptr, 10);
     const std::vector<uint32_t> edges = edges_of("ring", v[0]);
@@ -114,7 +126,11 @@ static int perceptrons(char **argv, uint32_t arithmetic) {
     const float *data = reinterpret_cast<const float *>(64);        // the host never reads them
     if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
     swarm_status rc = swarm_set_objective_mlp(h, v[1], v[2], v[3], data, data, 0.5f, v[4]);
+    const size_t objective = in_use;
+    if (room) memory = in_use + std::strtoull(room, nullptr, 10);
     if (rc == SWARM_OK) rc = swarm_set_mlp_arithmetic(h, arithmetic);
+    const size_t chosen = in_use;
+    memory = ~(size_t)0;
     if (rc != SWARM_OK) { std::printf("objective: %s\nstatus %d\n", swarm_last_error(h), rc); swarm_destroy(h); return 0; }
     std::vector<uint32_t> nodes(v[6]);
     for (uint32_t k = 0; k < v[6]; ++k) nodes[k] = k;
@@ -122,6 +138,10 @@ static int perceptrons(char **argv, uint32_t arithmetic) {
     rc = v[6] < v[0] ? swarm_local_steps(h, nodes.data(), v[6]) : swarm_local_steps(h, nullptr, 0);
     logging = false;
     std::printf("status %d\n", rc);
+    if (room) {
+        rc = swarm_set_mlp_arithmetic(h, SWARM_MLP_FP32);
+        std::printf("memory %zu %zu %zu\nstatus %d\n", objective, chosen, in_use, rc);
+    }
     swarm_destroy(h);
     return 0;
 }
@@ -129,8 +149,9 @@ static int perceptrons(char **argv, uint32_t arithmetic) {
 int main(int argc, char **argv) {
     if (argc < 8) return 2;
     const std::string call = argv[1];
-    if (call == "mlp") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_BF16X3);
-    if (call == "mlp_fp32") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_FP32);
+    if (call == "mlp") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_BF16X3, nullptr);
+    if (call == "mlp_room") return argc < 10 ? 2 : perceptrons(argv, SWARM_MLP_BF16X3, argv[9]);
+    if (call == "mlp_fp32") return argc < 9 ? 2 : perceptrons(argv, SWARM_MLP_FP32, nullptr);
     const uint32_t batch = call == "rounds" ? 0u : (uint32_t)std::atoi(argv[6]);
     const std::string graph = call == "rounds" ? "complete" : argv[7];
     swarm_config c{};

@@ -189,6 +189,43 @@ def test_mlp_products_in_chunks(gpu, n, n_in, n_hid, n_out, batch):
     test_mlp_forms_from_bf16_operands(gpu, n, n_in, n_hid, n_out, batch)
 
 
+def test_bf16x3_steps_where_memory_is_short(gpu):
+    """With too little memory for the workspace of all nodes they step in groups: the same bits."""
+    n, n_in, n_hid, n_out, batch = 45, 256, 1024, 256, 1024         # 500 MiB of workspace
+    d = n_hid * n_in + n_hid + n_out * n_hid + n_out
+    means, cdf = wl.mixture_data(n, n_in, n_out, 1)
+    means, cdf = torch.from_numpy(means).cuda(), torch.from_numpy(cdf).cuda()
+
+    def steps(leave):
+        s = gpu.Swarm(n, d, wl.random_regular_graph(n, 4, 0), 8, 2.0 ** -10, 2, 0.05, 0, n)
+        s.set_objective_mlp(n_in, n_hid, n_out, means, cdf, 0.5, batch)
+        X, W = s.models_view(gpu.COMM), s.models_view(gpu.LIVE)
+        X.copy_(torch.randn(n, d, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").mul_(0.1))
+        torch.cuda.empty_cache()
+        taken, free = [], torch.cuda.mem_get_info()[0]
+        while leave and free - leave > 4 << 20:
+            taken.append(torch.empty(min(free - leave, 16 << 30), dtype=torch.uint8, device="cuda"))
+            free = torch.cuda.mem_get_info()[0]
+        s.set_mlp_arithmetic(gpu.MLP_BF16X3)
+        used = free - torch.cuda.mem_get_info()[0]
+        s.local_steps()
+        torch.cuda.synchronize()
+        del taken
+        torch.cuda.empty_cache()
+        return W.clone(), used, s
+
+    whole, used, s = steps(None)
+    short, used_short, s_short = steps(160 << 20)
+    assert used > 400 << 20 and used_short <= 160 << 20
+    assert torch.equal(short, whole)
+    some = [44, 3]                                                   # fewer than a group, by a list
+    s.local_steps(some)
+    s_short.local_steps(some)
+    assert torch.equal(s.models_view(gpu.LIVE)[some], s_short.models_view(gpu.LIVE)[some])
+    s.close()
+    s_short.close()
+
+
 def test_mlp_contraction_of_more_than_4_gib_of_packed_features(gpu):
     """2^20 + 1 slabs of 32 features and 4 KiB each, the weights of all but the last slab zero: a 32-bit byte offset would come
     round to the first slab's features.  The update of W2 shows the hidden activations; against the float32 arithmetic, whose

@@ -168,3 +168,32 @@ def test_perceptron_updates_in_float32(host_calls, n, n_in, n_hid, n_out, batch,
     out = host_calls("mlp_fp32", n, n_in, n_hid, n_out, batch, 1, count)
     assert [ln for ln in out if "update" in ln] == [
         f"launch mlp_float_update_kernel<{batch // 32}> grid {g} 1 block 256 shared 0" for g in (w2, w1)]
+
+
+def room_calls(host_calls, *args):
+    out = host_calls("mlp_room", *args)
+    assert out[-1] == "status 0" and out[-3] == "status 0", out[-3:]
+    return kernels(out), [int(v) for v in out[-2].split()[1:]]
+
+
+# The memory that bf16x3 takes besides the float32 steps' activations: per node the hidden activations and twice the features once
+# more (updates inside the products; once, apart), the logits' gradient twice and the logits as often as they are split, all of the
+# size of float32 activations, signs, and column sums where a call takes its batch in chunks.  Going back to float32 frees it.
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,features,splits,sums", [
+    (256, 1024, 4096, 1024, 128, 2, 1, True), (32, 800, 1504, 480, 64, 2, 2, True), (64, 736, 1376, 896, 160, 1, 1, True),
+    (100, 96, 224, 64, 32, 2, 1, False)])
+def test_memory_of_the_bf16x3_arithmetic(host_calls, n, n_in, n_hid, n_out, batch, features, splits, sums):
+    _, (objective, chosen, back) = room_calls(host_calls, n, n_in, n_hid, n_out, batch, 1, n, 1 << 50)
+    rest = n * batch * (4 * (n_hid + features * n_in + (2 + splits) * n_out) + n_hid // 8 + (n_hid // 8 if sums else 0))
+    assert chosen - objective == rest and back == objective
+
+
+# With no room at all a few nodes step at a time, in the float32 steps' activations; nodes follow one another in every kernel
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,count,groups", [
+    (256, 1024, 4096, 1024, 128, 256, 4), (256, 1024, 4096, 1024, 128, 100, 2), (32, 800, 1504, 480, 64, 32, 4),
+    (33, 800, 1504, 480, 64, 33, 5), (64, 96, 96, 1024, 32, 64, 32), (64, 736, 1376, 896, 160, 64, 4)])
+def test_bf16x3_steps_where_memory_is_short(host_calls, n, n_in, n_hid, n_out, batch, count, groups):
+    whole, _ = room_calls(host_calls, n, n_in, n_hid, n_out, batch, 2, count, 1 << 50)
+    short, (objective, chosen, back) = room_calls(host_calls, n, n_in, n_hid, n_out, batch, 2, count, 0)
+    assert chosen == back == objective
+    assert whole.count("mlp_packed_batch_kernel") == 2 and short.count("mlp_packed_batch_kernel") == 2 * groups
