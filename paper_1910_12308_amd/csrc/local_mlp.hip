@@ -8,9 +8,10 @@
 // Per step:  data (labels, features)  ->  hid = relu(x W1^T + b1)  ->  logits = hid W2^T + b2
 //   -> dlogits = (softmax - onehot)/batch -> dpre = (dlogits W2) * [hid > 0]
 //   -> W2 -= eta dlogits^T hid, b2 -= eta colsum(dlogits), W1 -= eta dpre^T x, b1 -= eta colsum(dpre).
-// The weight updates are fused into the epilogues of the two weight-gradient GEMMs, so
-// the gradients never reach memory; the hidden-layer bias update rides in the epilogue of the
-// backward GEMM (the tile holds the whole batch, so its column sums are the bias gradient).
+// The weight updates ride in the two weight-gradient products, so the gradients never reach memory: up to 128 samples
+// in mlp_float_update_kernel, which streams down the weight matrix, beyond in the epilogue of mlp_gemm_kernel.  The
+// hidden-layer bias update rides in the epilogue of the backward GEMM where one tile holds the whole batch, so that its
+// column sums are the bias gradient.
 //
 // Tiling: 4 waves per workgroup, each wave a quarter of the tile (64x64 = 2x2 MFMA blocks of 128x128); K is
 // consumed in slabs of 16 staged through LDS (double buffered, next slab prefetched into
@@ -52,18 +53,12 @@ struct GemmArgs {
     uint32_t tiles_n, tiles_m, groups;   // workgroups of the launch: tiles_n x tiles_m per slot, total = their product x slots
 };
 
-// Which tile a workgroup computes.  The hardware deals consecutive workgroup ids round-robin over the 8
-// dies (XCDs), each with its own L2; the tiles of one node share that node's activations (and nothing
-// with other nodes), so the ids are renumbered to put all tiles of a node on one die, one after the
-// other: die x takes the x-th eighth of the (node, tile) list.  Ids past the end of the list do nothing.
+// Which tile a workgroup computes, in the order of the dies (place_of): all tiles of a node on one die, one after the other.
 struct Tile { const float *A, *B, *aux, *colsum_src; float *C, *colsum_dst; uint32_t m0, n0; bool valid; };
 template <int TM, int TN>
 __device__ __forceinline__ Tile tile_of_id(const GemmArgs &g, uint32_t id) {
-    constexpr uint32_t DIES = 8;
-    const uint32_t chunk = (g.groups + DIES - 1) / DIES;
-    const uint32_t q = (id % DIES) * chunk + id / DIES;
     Tile t{};
-    t.valid = id / DIES < chunk && q < g.groups;
+    const uint32_t q = place_of(id, g.groups, t.valid);
     if (!t.valid) return t;
     const uint32_t per_slot = g.tiles_n * g.tiles_m, r = q % per_slot;
     const uint32_t slot = q / per_slot, node = g.nodes ? g.nodes[slot] : slot;
@@ -190,15 +185,13 @@ __device__ __forceinline__ void prefetch_aux_rest(const GemmArgs &g, const AuxPo
 
 // Accumulator layout of a 32x32 block (every 32x32 MFMA shape): register v of lane l holds row
 // 8*(v/4) + 4*(l/32) + v%4, column l%32.
-// LATE: the tile of the other matrix was not requested ahead of the K loop and is read here.
 // scratch: 64 NB floats of LDS that nothing else uses any more (column sums, when the tile asks for them).
-template <int EPI, int MB, int NB, bool LATE>
+template <int EPI, int MB, int NB>
 __device__ __forceinline__ void epilogue(const GemmArgs &g, const Tile &t, f16v acc[MB][NB], uint32_t wm, uint32_t wn,
                                          uint32_t half, uint32_t r32, bool full_tile, float pre[MB][NB][16], float *scratch) {
     float *C = t.C;
     const float *aux = t.aux;
     const uint32_t m0 = t.m0, n0 = t.n0;
-    if (LATE) prefetch_aux_rest<EPI, MB, NB>(g, AuxPos{aux, m0, n0, wm, wn, half, r32, full_tile}, 0, pre);
     float colsum[NB] = {};
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
@@ -330,7 +323,7 @@ __global__ __launch_bounds__(256, TM * TN > 64 * 64 ? 2 : 4) void mlp_gemm_kerne
     }
     prefetch_aux_rest<EPI, MB, NB>(g, aux_pos, 2 * slabs, pre);    // K shorter than the parts
 
-    epilogue<EPI, MB, NB, false>(g, t, acc, wm, wn, half, r32, full_tile, pre, lds_a[0]);
+    epilogue<EPI, MB, NB>(g, t, acc, wm, wn, half, r32, full_tile, pre, lds_a[0]);
 }
 
 // weights -= lr x (sum over the batch of a^T b) for batches of up to 128 samples (BLOCKS x 32; 160 take

@@ -113,8 +113,9 @@ def test_run_of_algorithm1_longer_than_one_upload(gpu):
     assert np.array_equal(whole.read_codes(1), parts.read_codes(1)) and whole.counters() == parts.counters()
 
 
-# tiles of 64 x 64 (batch up to 64; over 128 in float32), 128 x 64 and, from 512 (updates: 256) tiles on, 128 x 128,
-# each with whole and ragged edges; the hidden bias rides in the backward product only when one tile holds the batch
+# Products in float32 by tiles of 64 x 64 (batch up to 64, and over 128), 128 x 64 and, from 512 tiles on, 128 x 128, each with
+# whole and ragged edges; updates down the rows, over 128 samples by tiles of 64 x 64 (of 128 x 128: below).  The hidden bias rides
+# in the backward product only when one tile holds the batch.
 @pytest.mark.parametrize("arithmetic", ["fp32", "bf16x3"])
 @pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [
     (3, 32, 32, 32, 32), (3, 64, 96, 160, 64), (2, 96, 352, 64, 96), (2, 160, 128, 32, 128), (2, 64, 224, 96, 160),
@@ -157,9 +158,15 @@ def test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, arithmetic):
     assert np.abs(W - want)[off].max(initial=0.0) <= kink
 
 
+# Updates in float32 over 128 samples by tiles of 128 x 128, from 256 of them on: ragged, and whole beside ragged ones
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [(130, 32, 512, 32, 160), (65, 128, 512, 160, 160)])
+def test_mlp_float_updates_in_large_tiles(gpu, n, n_in, n_hid, n_out, batch):
+    test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, "fp32")
+
+
 # The bf16x3 steps in their forms: updates inside the products for 32 to 128 samples (eight waves per workgroup at 128) with whole
-# and ragged groups of columns and odd numbers of slabs, apart at 160, batches in chunks with a ragged last one; logits split 8 ways
-# and not at all; rows of the softmax beyond what its lanes hold.
+# and ragged groups of columns and odd numbers of slabs, apart at 160, batches in chunks of one block (several: below); logits split
+# 8 ways and not at all; rows of the softmax beyond what its lanes hold.
 @pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [
     (100, 96, 224, 64, 32), (50, 160, 512, 96, 64), (70, 64, 384, 32, 96), (26, 32, 1024, 160, 128), (40, 128, 640, 96, 160),
     (2, 64, 96, 64, 352), (3, 96, 1056, 544, 96), (2, 64, 96, 2144, 64)])

@@ -197,3 +197,13 @@ def test_bf16x3_steps_where_memory_is_short(host_calls, n, n_in, n_hid, n_out, b
     short, (objective, chosen, back) = room_calls(host_calls, n, n_in, n_hid, n_out, batch, 2, count, 0)
     assert chosen == back == objective
     assert whole.count("mlp_packed_batch_kernel") == 2 and short.count("mlp_packed_batch_kernel") == 2 * groups
+
+
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,count,w2,w1", [
+    (130, 32, 512, 32, 130, "128, 128> grid 520", "128, 128> grid 520"), (65, 128, 512, 160, 65, "128, 128> grid 520", "128, 128> grid 264"),
+    (65, 128, 512, 160, 63, "128, 128> grid 504", "64, 64> grid 1008"), (2, 64, 224, 96, 2, "64, 64> grid 16", "64, 64> grid 8")])
+def test_perceptron_updates_in_float32_tiles(host_calls, n, n_in, n_hid, n_out, count, w2, w1):
+    """Over 128 samples: tiles of 128 x 128 from 256 of them on."""
+    out = host_calls("mlp_fp32", n, n_in, n_hid, n_out, 160, 1, count)
+    assert [ln for ln in out if "mlp_gemm_kernel<false, false, 3" in ln] == [
+        f"launch mlp_gemm_kernel<false, false, 3, {g} 1 block 256 shared 0" for g in (w2, w1)]
