@@ -540,8 +540,8 @@ __global__ __launch_bounds__(256) void mlp_bias_kernel(const float *__restrict__
     dst[(uint64_t)node * d + bias_off + c] = fmaf(-lr, sum, src[(uint64_t)node * d + bias_off + c]);
 }
 
-void launch_mlp_bias(const float *G, const float *src, float *dst, const uint32_t *nodes, uint32_t width, uint32_t batch,
-                     uint32_t count, uint64_t d, uint64_t bias_off, float lr, hipStream_t st) {
+static void launch_mlp_bias(const float *G, const float *src, float *dst, const uint32_t *nodes, uint32_t width, uint32_t batch,
+                            uint32_t count, uint64_t d, uint64_t bias_off, float lr, hipStream_t st) {
     mlp_bias_kernel<<<dim3((width + 63) / 64, count), 256, 0, st>>>(G, src, dst, nodes, width, batch, d, bias_off, lr);
 }
 

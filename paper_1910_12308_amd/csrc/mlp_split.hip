@@ -49,7 +49,8 @@ struct ProductArgs {
     u4 *by_sample, *by_column;      // HIDDEN: activations packed over the columns; HIDDEN, BACK: over the samples
     uint64_t by_sample_stride, by_column_stride;
     uint16_t *mask;                 // HIDDEN writes, BACK reads: bit v of lane l of block (samples, columns): result v is positive
-    float *sums;                    // BACK, several chunks: column sums per slot and block of 32 samples
+    float *sums;                    // BACK, several chunks: column sums per slot and block of 32 samples, `sums_width` floats each
+    uint32_t sums_width;
     // UPDATE: the gradient of the weights is the product of these, packed over the samples
     const u4 *by_row, *own;         // rows: contraction index of the product; its columns
     uint64_t by_row_stride, own_stride;
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(64 * product_waves(BLOCKS, UPDATE), 2) void mlp_pro
             if (block >= g.sample_blocks) break;
             const float part = column_sum[m] + __shfl_xor(column_sum[m], 32);
             total = m == 0 ? part : total + part;
-            if (g.chunks > 1 && half == 0) g.sums[((uint64_t)slot * g.sample_blocks + block) * 32 * g.cols + 32 * col + r32] = part;
+            if (g.chunks > 1 && half == 0) g.sums[((uint64_t)slot * g.sample_blocks + block) * g.sums_width + 32 * col + r32] = part;
         }
         if (g.chunks == 1 && half == 0) g.W_out[bias_at] = fmaf(-g.lr, total, g.biases[bias_at]);
     }
@@ -555,20 +556,33 @@ __global__ __launch_bounds__(256) void mlp_packed_batch_kernel(const float *__re
                   by_feature + slot * by_feature_stride + fragments_at(first + i, batch / 32, blockIdx.y));
 }
 
-// logits -> (softmax - onehot(y)) / batch, and the same packed.  A workgroup of 16 waves takes 32 rows, a wave two of them; 128
-// columns at a time pass through local memory to be packed, every gridDim.z-th 128 in the same workgroup (where there are few
+struct SoftmaxArgs {
+    const float *logits;            // batch x classes per slot, for every split (split_stride floats apart)
+    const uint32_t *labels, *nodes;
+    u4 *by_sample, *by_column;      // the gradient, packed
+    uint64_t split_stride, by_sample_stride, by_column_stride;
+    // its column sums take a step of the bias when the batch is one block of 32 samples, and else go to `sums`
+    const float *src;               // models, `d` floats per node
+    float *dst, *sums;
+    uint64_t d, bias;               // bias: where in a node's model
+    uint32_t splits, n_out, batch, sums_width, sums_at;
+    float lr;
+};
+
+// logits -> (softmax - onehot(y)) / batch, packed, and its column sums.  A workgroup of 16 waves takes 32 rows, a wave two of them;
+// 128 columns at a time pass through local memory, every gridDim.z-th 128 in the same workgroup (where there are few
 // rows, several workgroups take the same sums, so that more of the chip packs).  Rows of up to 1024 entries stay in registers
 // between the passes (maximum, sum of exponentials, result), in groups of 256 that a short row
 // leaves out (48 nodes, 32 classes, batch 288: 22.4 -> 16.8 us).  The sums are those of mlp_softmax_grad_kernel (local_mlp.hip) in
 // its order: 256 partial sums of every 256th entry, 64 of them by halves at a time, the four results one after the other.
-__global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const float *__restrict__ logits, uint32_t splits,
-                                                                       uint64_t split_stride, float *__restrict__ dlogits,
-                                                                       const uint32_t *__restrict__ labels, u4 *__restrict__ by_sample,
-                                                                       u4 *__restrict__ by_column, uint64_t by_sample_stride,
-                                                                       uint64_t by_column_stride, uint32_t n_out, uint32_t batch) {
+__global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const SoftmaxArgs g) {
     __shared__ __attribute__((aligned(16))) float tiles[2][4][32 * TILE_LD];
     constexpr uint32_t HELD = 16;                  // of 64 entries
-    const uint32_t lane = threadIdx.x & 63u, wave = wave_of_group(), slot = blockIdx.y, blocks = n_out / 32;
+    const float *logits = g.logits;
+    const uint64_t split_stride = g.split_stride;
+    const uint32_t n_out = g.n_out, batch = g.batch, splits = g.splits;
+    const uint32_t lane = threadIdx.x & 63u, wave = wave_of_group(), slot = blockIdx.y, node = g.nodes ? g.nodes[slot] : slot;
+    const uint32_t blocks = n_out / 32, block = blockIdx.x, sample_blocks = gridDim.x;
     const float inv_b = 1.0f / (float)batch;
     float held[2][HELD], top[2], sum[2];
     uint32_t y[2];
@@ -581,9 +595,9 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const flo
     };
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const uint32_t row = blockIdx.x * 32 + 2 * wave + r;
+        const uint32_t row = block * 32 + 2 * wave + r;
         offset[r] = ((uint64_t)slot * batch + row) * n_out;
-        y[r] = labels[(uint64_t)slot * batch + row];
+        y[r] = g.labels[(uint64_t)slot * batch + row];
     }
     // entries past the row: exp(-inf) = 0.  In fours, of which rows of few classes fill one.
 #pragma unroll
@@ -650,15 +664,28 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const flo
                 const uint32_t col = c + 64 * i + lane;
                 if (col < n_out) {
                     const float out = (e[r][i] / sum[r] - (col == y[r] ? 1.f : 0.f)) * inv_b;
-                    dlogits[offset[r] + col] = out;
                     tiles[turn][2 * i + (lane >> 5)][(2 * wave + r) * TILE_LD + (lane & 31u)] = out;
                 }
             }
         __syncthreads();
-        const uint32_t mine = threadIdx.x >> 8, block = c / 32 + mine;
-        if (block < blocks)
-            pack_tile(tiles[turn][mine], threadIdx.x & 255u, by_sample + slot * by_sample_stride + fragments_at(blockIdx.x, blocks, block),
-                      by_column + slot * by_column_stride + fragments_at(block, batch / 32, blockIdx.x));
+        const uint32_t mine = wave / 4, column = c / 32 + mine;         // of 32 classes
+        if (column < blocks) {
+            const float *tile = tiles[turn][mine];
+            pack_tile(tile, threadIdx.x & 255u, g.by_sample + slot * g.by_sample_stride + fragments_at(block, blocks, column),
+                      g.by_column + slot * g.by_column_stride + fragments_at(column, sample_blocks, block));
+            if (wave % 4 == 0) {                  // half a wave's rows one after the other, then the halves
+                const float *at = tile + 16 * (lane >> 5) * TILE_LD + (lane & 31u);
+                float total = at[0];
+#pragma unroll
+                for (uint32_t r = 1; r < 16; ++r) total += at[r * TILE_LD];
+                total += __shfl_xor(total, 32);
+                const uint32_t col = 32 * column + lane;
+                if (lane < 32) {
+                    if (sample_blocks == 1) g.dst[node * g.d + g.bias + col] = fmaf(-g.lr, total, g.src[node * g.d + g.bias + col]);
+                    else g.sums[((uint64_t)slot * sample_blocks + block) * g.sums_width + g.sums_at + col] = total;
+                }
+            }
+        }
         turn ^= 1u;
     };
 #pragma unroll
@@ -678,18 +705,20 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const flo
     }
 }
 
-// b_dst = b_src - lr x the column sums that the chunks of a batch have left, block by block in the order of one chunk.
-__global__ __launch_bounds__(256) void mlp_bias_of_chunks_kernel(const float *__restrict__ sums, const float *__restrict__ src,
+// Biases take a step by the column sums that blocks of 32 samples have left, in the order of the blocks: columns [first, width) of
+// the hidden units' sums and, behind them, the classes'.
+__global__ __launch_bounds__(256) void mlp_bias_of_blocks_kernel(const float *__restrict__ sums, const float *__restrict__ src,
                                                                  float *__restrict__ dst, const uint32_t *__restrict__ nodes,
-                                                                 uint32_t width, uint32_t blocks, uint64_t d, uint64_t bias_off,
-                                                                 float lr) {
-    const uint32_t slot = blockIdx.y, node = nodes ? nodes[slot] : slot, c = blockIdx.x * 256 + threadIdx.x;
+                                                                 uint32_t first, uint32_t width, uint32_t n_hid, uint32_t blocks,
+                                                                 uint64_t d, uint64_t hidden_off, uint64_t class_off, float lr) {
+    const uint32_t slot = blockIdx.y, node = nodes ? nodes[slot] : slot, c = first + blockIdx.x * 256 + threadIdx.x;
     if (c >= width) return;
     sums += (uint64_t)slot * blocks * width + c;
     float sum = sums[0];
 #pragma unroll 8
     for (uint32_t k = 1; k < blocks; ++k) sum += sums[(uint64_t)k * width];
-    dst[(uint64_t)node * d + bias_off + c] = fmaf(-lr, sum, src[(uint64_t)node * d + bias_off + c]);
+    const uint64_t at = (uint64_t)node * d + (c < n_hid ? hidden_off + c : class_off + (c - n_hid));
+    dst[at] = fmaf(-lr, sum, src[at]);
 }
 
 // How the products of a call are cut.  A workgroup takes `blocks` x 32 samples (as many as fit: every chunk reads the weights
@@ -739,14 +768,14 @@ struct MlpSplitSpace {
     uint16_t *mask;
 };
 
-// Where the workspace of s.nodes nodes lies: in x, hid and dhid, which hold the float32 steps' activations and which these steps do
-// not use otherwise, as far as it fits, the rest from s.own on.  Returns the bytes of the rest.
+// Where the workspace of s.nodes nodes lies: in x, hid, dhid and dlogits, which hold the float32 steps' activations and which these
+// steps do not use otherwise, as far as it fits, the rest from s.own on.  Returns the bytes of the rest.
 static uint64_t lay_out(const MlpObjective &o, MlpSplitSpace &s) {
     const uint64_t in = o.n_in, hid = o.n_hid, out = o.n_out, batch = o.batch, value = sizeof(float);
-    const Plan all = plan_of(o, o.n_nodes), one = plan_of(o, 1);
+    const Plan all = plan_of(o, o.n_nodes);
     struct Area { uintptr_t at; uint64_t left; };
     Area areas[] = {{(uintptr_t)o.x, value * o.n_nodes * batch * in}, {(uintptr_t)o.hid, value * o.n_nodes * batch * hid},
-                    {(uintptr_t)o.dhid, value * o.n_nodes * batch * hid}};
+                    {(uintptr_t)o.dhid, value * o.n_nodes * batch * hid}, {(uintptr_t)o.dlogits, value * o.n_nodes * batch * out}};
     uint64_t rest = 0;
     auto take = [&](auto &p, uint64_t bytes_of_node) {
         const uint64_t bytes = (bytes_of_node * s.nodes + 255) / 256 * 256;
@@ -766,14 +795,14 @@ static uint64_t lay_out(const MlpObjective &o, MlpSplitSpace &s) {
     take(s.x_by_sample, value * batch * in);             // hi and lo are as large as the value
     take(s.hid_by_sample, value * batch * hid);
     take(s.dpre_by_unit, value * batch * hid);
+    take(s.dlogits_by_sample, value * batch * out);
     take(s.hid_by_unit, value * batch * hid);
     take(s.x_by_feature[0], value * batch * in);
     s.x_by_feature[1] = s.x_by_feature[0];
     if (all.inside) take(s.x_by_feature[1], value * batch * in);         // updates inside meet the next step's features
-    take(s.dlogits_by_sample, value * batch * out);
     take(s.dlogits_by_class, value * batch * out);
     take(s.logits, value * all.splits * batch * out);
-    if (one.back < batch / 32) take(s.sums, value * (batch / 32) * hid); // few nodes have the most chunks
+    if (batch > 32) take(s.sums, value * (batch / 32) * (hid + out));
     take(s.mask, sizeof(uint16_t) * (batch / 32) * (hid / 32) * 64);
     return rest;
 }
@@ -910,11 +939,13 @@ static void launch_steps(const float *base, float *W, const MlpObjective &o, con
         g.logits = ws.logits;
         product(g, PRODUCT_LOGITS, false, plan.logits, Hd, O);
         const uint32_t share = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(parts_of(O, 128), 256 / ((uint64_t)sb * count)));
-        mlp_packed_softmax_grad_kernel<<<dim3(sb, count, share), 1024, 0, st>>>(ws.logits, plan.splits, split_stride, o.dlogits, o.labels,
-                                                                                ws.dlogits_by_sample, ws.dlogits_by_class, dl_s, dl_c, O, Bt);
-        // dpre = (dlogits W2) * [hid > 0], and b1 <- b1 - eta colsum(dpre) when one chunk is the whole batch
+        mlp_packed_softmax_grad_kernel<<<dim3(sb, count, share), 1024, 0, st>>>(
+            SoftmaxArgs{ws.logits, o.labels, nodes, ws.dlogits_by_sample, ws.dlogits_by_class, split_stride, dl_s, dl_c, src, W, ws.sums, d,
+                        off_b2, plan.splits, O, Bt, Hd + O, Hd, lr});
+        // dpre = (dlogits W2) * [hid > 0], and b1 <- b1 - eta colsum(dpre) when one chunk is the whole batch (b2 <- b2 - eta colsum(dlogits)
+        // went with the softmax when that is one block)
         g.act = ws.dlogits_by_sample; g.act_stride = dl_s;
-        g.bias = off_b1; g.sums = ws.sums;
+        g.bias = off_b1; g.sums = ws.sums; g.sums_width = Hd + O;
         g.by_column = ws.dpre_by_unit; g.by_column_stride = hid_u;
         // W2 <- W2 - eta dlogits^T hid
         UpdateArgs u{};
@@ -925,9 +956,11 @@ static void launch_steps(const float *base, float *W, const MlpObjective &o, con
         g.by_row = u.a; g.by_row_stride = u.a_stride; g.own = u.b; g.own_stride = u.b_stride;
         product(g, PRODUCT_BACK, plan.inside, plan.back, O, Hd);
         if (!plan.inside) update(u, O, Hd);
-        if (plan.back < sb)
-            mlp_bias_of_chunks_kernel<<<dim3(parts_of(Hd, 256), count), 256, 0, st>>>(ws.sums, src, W, nodes, Hd, sb, d, off_b1, lr);
-        launch_mlp_bias(o.dlogits, src, W, nodes, O, Bt, count, d, off_b2, lr, st);
+        if (sb > 1) {
+            const uint32_t first_sum = plan.back < sb ? 0 : Hd;
+            mlp_bias_of_blocks_kernel<<<dim3(parts_of(Hd + O - first_sum, 256), count), 256, 0, st>>>(
+                ws.sums, src, W, nodes, first_sum, Hd + O, Hd, sb, d, off_b1, off_b2, lr);
+        }
         // W1 <- W1 - eta dpre^T x
         u.a = ws.dpre_by_unit; u.a_stride = hid_u;
         u.b = ws.x_by_feature[q & 1]; u.b_stride = x_f;

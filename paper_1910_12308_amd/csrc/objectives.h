@@ -37,7 +37,7 @@ struct MlpObjective {
     const float *cdf = nullptr;     // n x n_out
     float data_sigma = 0.f;
     // workspace for all nodes (owned): inputs, labels, hidden activations, logits gradient, hidden gradient; the bf16x3 steps keep
-    // packed operands in x, hid and dhid
+    // packed operands in x, hid, dhid and dlogits
     float *x = nullptr, *hid = nullptr, *dlogits = nullptr, *dhid = nullptr;
     uint32_t *labels = nullptr;
     uint32_t n_nodes = 0;
@@ -80,8 +80,5 @@ hipError_t alloc_mlp_split(MlpObjective &o);
 void free_mlp_split(MlpObjective &o);
 hipError_t launch_local_mlp_split(const float *base, float *W, const MlpObjective &o, const LocalSlots &slots, uint32_t count,
                                   uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st);
-// b_dst = b_src - lr x column sums of G (batch x width per slot).
-void launch_mlp_bias(const float *G, const float *src, float *dst, const uint32_t *nodes, uint32_t width, uint32_t batch,
-                     uint32_t count, uint64_t d, uint64_t bias_off, float lr, hipStream_t st);
 
 }  // namespace swarm

@@ -198,7 +198,7 @@ def test_mlp_products_in_chunks(gpu, n, n_in, n_hid, n_out, batch):
 
 def test_bf16x3_steps_where_memory_is_short(gpu):
     """With too little memory for the workspace of all nodes they step in groups: the same bits."""
-    n, n_in, n_hid, n_out, batch = 45, 256, 1024, 256, 1024         # 500 MiB of workspace
+    n, n_in, n_hid, n_out, batch = 45, 256, 1024, 256, 1024         # 360 MiB of workspace
     d = n_hid * n_in + n_hid + n_out * n_hid + n_out
     means, cdf = wl.mixture_data(n, n_in, n_out, 1)
     means, cdf = torch.from_numpy(means).cuda(), torch.from_numpy(cdf).cuda()
@@ -223,7 +223,7 @@ def test_bf16x3_steps_where_memory_is_short(gpu):
 
     whole, used, s = steps(None)
     short, used_short, s_short = steps(160 << 20)
-    assert used > 400 << 20 and used_short <= 160 << 20
+    assert used > 300 << 20 and used_short <= 160 << 20
     assert torch.equal(short, whole)
     some = [44, 3]                                                   # fewer than a group, by a list
     s.local_steps(some)
