@@ -730,7 +730,8 @@ __global__ __launch_bounds__(256) void mlp_bias_of_blocks_kernel(const float *__
 // Updates go inside the products where these have enough workgroups, because on their own they are cut by rows too, or where all
 // of it is a few slabs.  The lines, inside and apart: batch 32, 512-1024-64, 48 workgroups 103 and 110 us, 1024-4096-1024, 32: 208
 // and 193; batch 64, 800-1504-480, 96: 192 and 196, 48: 182 and 166; batch 96, 512-1024-64, 80: 137 and 147; batch 128 (eight waves
-// each), 1024-4096-1024, 128: 577 and 575, 96: 546 and 495.
+// each), 1024-4096-1024, 128: 577 and 575, 96: 546 and 495.  Few slabs, whatever the workgroups: 96-224-64, one node, batch 32 61 and
+// 68, batch 96 77 and 80; with the eight waves of batch 128 the other way round (128-512-128 110 and 90, 64-64-128 90 and 78).
 // All of it follows from how many nodes step but the splits, which decide the order of the logits' sums and therefore follow from
 // the swarm alone; the other choices leave every bit where it is.
 struct Plan {
@@ -754,7 +755,8 @@ static Plan plan_of(const MlpObjective &o, uint32_t count) {
     p.splits = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({MOST_SPLITS, o.n_hid / 32 / 4, FILL / groups(o.n_out, 4, o.n_nodes)}));
     p.logits = cut(o.n_out, p.splits);
     p.inside = p.whole == samples && updates_inside(samples) &&
-               (groups(o.n_hid, product_waves(samples, true), count) >= INSIDE[samples - 1] || std::max(o.n_in, o.n_out) <= 128);
+               (groups(o.n_hid, product_waves(samples, true), count) >= INSIDE[samples - 1] ||
+                (samples < 4 && std::max(o.n_in, o.n_out) <= 128));
     p.back = p.inside ? p.whole : p.hidden;
     return p;
 }

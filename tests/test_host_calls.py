@@ -129,6 +129,7 @@ def test_descriptors_are_copied_ahead_of_larger_rounds(host_calls, n, d, copied)
     (64, 736, 1376, 896, 160, 12, (5, 136), (3, 168), (5, 136), False),
     (64, 736, 1376, 896, 160, 1, (1, 56), (1, 40), (1, 56), False),
     (100, 96, 224, 64, 32, 1, (1, 8), (1, 8), (1, 8), True),
+    (100, 96, 224, 64, 96, 1, (1, 8), (1, 8), (3, 8), True), (100, 96, 224, 64, 128, 1, (1, 8), (1, 8), (1, 8), False),
     (64, 32, 512, 32, 160, 64, (5, 256), (5, 256), (5, 256), False),
     (64, 32, 512, 32, 224, 64, (4, 512), (4, 512), (4, 512), False),
     (64, 32, 512, 32, 288, 64, (5, 512), (5, 512), (5, 512), False),
