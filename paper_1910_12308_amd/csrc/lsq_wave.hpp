@@ -1,4 +1,4 @@
-// Sums over a wave of several values per lane (least-squares kernels).
+// Sums over a wave of several values per lane, and its largest value (least-squares and softmax kernels).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -58,6 +58,17 @@ template <int R, int TOP = R / 2>
 __device__ __forceinline__ float wave_totals(float v[R], uint32_t lane) {
     halve<R / 2, TOP>(v, lane);
     return total_from<2 * TOP>(v[0], lane);
+}
+
+// The largest value of the wave, in every lane.
+template <int S = 32>
+__device__ __forceinline__ float wave_maximum(float x) {
+    if constexpr (S == 0) return x;
+    else if constexpr (S >= 16) {
+        const uint32_t u = __float_as_uint(x);
+        const auto r = S == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return wave_maximum<S / 2>(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    } else return wave_maximum<S / 2>(fmaxf(x, across<S>(x)));
 }
 
 }  // namespace swarm

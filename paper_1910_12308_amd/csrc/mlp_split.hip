@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "lsq_wave.hpp"
 #include "mlp_batch.hpp"
 #include "mlp_common.hpp"
 #include "mlp_planes.hpp"
@@ -575,7 +576,11 @@ struct SoftmaxArgs {
 // between the passes (maximum, sum of exponentials, result), in groups of 256 that a short row
 // leaves out (48 nodes, 32 classes, batch 288: 22.4 -> 16.8 us).  The sums are those of mlp_softmax_grad_kernel (local_mlp.hip) in
 // its order: 256 partial sums of every 256th entry, 64 of them by halves at a time, the four results one after the other.
-__global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const SoftmaxArgs g) {
+// PER_SIMD: waves per SIMD, four for up to a workgroup per compute unit (73 registers), eight beyond: 31 x 1024 rows of 896
+// 87.1 and 75.1 us, 256 x 128 of 1024 99.9 and 84.7; 32 x 64 of 480 10.2 and 11.4, 8 x 32 of 864 9.8 and 11.5.  Exchanges
+// through local memory instead of between registers: 85.3, 101.0, 11.2 and 11.2.
+template <int PER_SIMD>
+__global__ __launch_bounds__(1024, PER_SIMD) void mlp_packed_softmax_grad_kernel(const SoftmaxArgs g) {
     __shared__ __attribute__((aligned(16))) float tiles[2][4][32 * TILE_LD];
     constexpr uint32_t HELD = 16;                  // of 64 entries
     const float *logits = g.logits;
@@ -633,8 +638,7 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const Sof
 #pragma unroll
         for (uint32_t i = 0; i < HELD; ++i) mx = fmaxf(mx, held[r][i]);
         for (uint32_t c = 64 * HELD; c + lane < n_out; c += 64) mx = fmaxf(mx, read(r, c));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        mx = wave_maximum(mx);
         top[r] = mx;
         float part[4] = {};
 #pragma unroll
@@ -650,9 +654,7 @@ __global__ __launch_bounds__(1024) void mlp_packed_softmax_grad_kernel(const Sof
             for (uint32_t i = 0; i < 4; ++i)
                 if (c + 64 * i + lane < n_out) part[i] += expf(read(r, c + 64 * i) - mx);
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) part[i] += __shfl_xor(part[i], off);
+        for (int i = 0; i < 4; ++i) part[i] = wave_totals<1, 32>(part + i, lane);
         sum[r] = ((part[0] + part[1]) + part[2]) + part[3];
     }
     uint32_t turn = 0;
@@ -941,7 +943,8 @@ static void launch_steps(const float *base, float *W, const MlpObjective &o, con
         g.logits = ws.logits;
         product(g, PRODUCT_LOGITS, false, plan.logits, Hd, O);
         const uint32_t share = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(parts_of(O, 128), 256 / ((uint64_t)sb * count)));
-        mlp_packed_softmax_grad_kernel<<<dim3(sb, count, share), 1024, 0, st>>>(
+        const auto softmax = (uint64_t)sb * count > 256 ? mlp_packed_softmax_grad_kernel<8> : mlp_packed_softmax_grad_kernel<4>;
+        softmax<<<dim3(sb, count, share), 1024, 0, st>>>(
             SoftmaxArgs{ws.logits, o.labels, nodes, ws.dlogits_by_sample, ws.dlogits_by_class, split_stride, dl_s, dl_c, src, W, ws.sums, d,
                         off_b2, plan.splits, O, Bt, Hd + O, Hd, lr});
         // dpre = (dlogits W2) * [hid > 0], and b1 <- b1 - eta colsum(dpre) when one chunk is the whole batch (b2 <- b2 - eta colsum(dlogits)

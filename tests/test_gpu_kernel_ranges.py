@@ -189,9 +189,11 @@ def test_mlp_forms_from_bf16_operands(gpu, n, n_in, n_hid, n_out, batch):
 
 # Batches in chunks (tests/test_host_calls.py: which): five blocks of 32 samples per workgroup, 4 + 3, 5 + 4, 4 + 4 + 3, the
 # backward product apart from the update; the few nodes of the second call take other chunks, and the same bits.  Updates of long
-# batches by tiles of 128 x 128, whole and ragged, and of 64 x 64 for few nodes.
+# batches by tiles of 128 x 128, whole and ragged, and of 64 x 64 for few nodes.  Softmax of more than 256 blocks of rows, up to 1024
+# classes and beyond.
 @pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [
-    (64, 32, 512, 32, 160), (64, 32, 512, 32, 224), (64, 32, 512, 32, 288), (64, 32, 512, 32, 352), (65, 128, 512, 160, 224)])
+    (64, 32, 512, 32, 160), (64, 32, 512, 32, 224), (64, 32, 512, 32, 288), (64, 32, 512, 32, 352), (65, 128, 512, 160, 224),
+    (33, 32, 32, 1120, 256)])
 def test_mlp_products_in_chunks(gpu, n, n_in, n_hid, n_out, batch):
     test_mlp_forms_from_bf16_operands(gpu, n, n_in, n_hid, n_out, batch)
 

@@ -163,6 +163,13 @@ def test_perceptron_updates(host_calls, n, n_in, n_hid, n_out, batch, count, w2,
     assert [ln for ln in out if "update" in ln] == [f"launch {k} grid {g} 1 block 256 shared 0" for k, g in (w2, w1)]
 
 
+@pytest.mark.parametrize("n,batch,count,waves", [(32, 256, 32, 4), (33, 256, 33, 8), (33, 256, 32, 4), (64, 160, 64, 8), (2, 32, 2, 4)])
+def test_perceptron_softmax(host_calls, n, batch, count, waves):
+    """bf16x3: eight waves per SIMD from more than 256 blocks of 32 rows on."""
+    out = host_calls("mlp", n, 32, 32, 1120, batch, 1, count)
+    assert sum(f"softmax_grad_kernel<{waves}> grid {batch // 32} {count} " in ln for ln in out) == 1
+
+
 # Updates of the weights in float32, up to 128 samples: a block of 32 rows per workgroup while there are at most 1024, two or more
 # otherwise
 @pytest.mark.parametrize("n,n_in,n_hid,n_out,batch,count,w2,w1", [
