@@ -38,11 +38,11 @@ __global__ __launch_bounds__(WAVES * 64) void fused_singles_kernel(const RoundAr
 //   4 000 000, H = 3             721   744   726   698     100 000, H = 3    30.5  29.9  30.0  31.1
 //   12 000 000, 2 bits, H = 3   2121  2187  2151  2051     300 000, H = 3    66.3  65.9  66.0  65.8
 //   4 000 000, H = 5             816   757   752   759     1 048 576, H = 1   190   190   190   187
-// With 8 bits the compiler's choice and five, the mean of two interleaved runs; six are between them, and from four steps on
-// or in shorter launches the choice is as good or better (16 nodes, 1 000 000, H = 4: 56.2, five 59.5).  With 16 bits
-// five and six gain nothing anywhere.
-//   16 000 000, H = 2           3159  3045     1 048 576, H = 2           206  200     9 nodes, 16 000 000, H = 2   441  419
-//   4 000 000, H = 3             783   739     1 048 576, H = 3           205  198     31 nodes, 1 000 000, H = 3   104  103
+// With 8 bits the compiler's choice and five, the best of four interleaved runs: 1 to 5 %; six are between them, and from four
+// steps on or in shorter launches the choice is as good or better (16 nodes, 1 000 000, H = 4: 56.2, five 59.5).  With 16
+// bits five and six gain nothing anywhere.
+//   16 000 000, H = 2           3097  3069     1 048 576, H = 2           204  202     9 nodes, 16 000 000, H = 2   434  423
+//   4 000 000, H = 3             779   739     1 048 576, H = 3           204  200     31 nodes, 1 000 000, H = 3   104  103
 static bool five_waves(uint32_t H, uint64_t tiles) { return H <= 3 && tiles >= 1u << 15; }
 
 template <int BITS, bool INPLACE, bool NOISE>

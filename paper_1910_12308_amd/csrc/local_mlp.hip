@@ -331,11 +331,13 @@ __global__ __launch_bounds__(256, TM * TN > 64 * 64 ? 2 : 4) void mlp_gemm_kerne
 // matrix, b its columns, both stored [sample][row or column].  A wave owns 32 columns of the matrix, whose operand stays in its
 // registers, and goes down the rows in blocks of 32; the rows' operand passes through local memory for the four waves.
 // Bound by the matrix cores.  As tiles with K = batch, eight slabs at batch 128, filling and draining each tile's pipeline lay
-// open (matrix cores busy 67 % of the time against 89 % in the forward products); here nothing restarts between row blocks (76 %).
-// 256 nodes, 1024 x 4096 weights, batch 128: 2.68 -> 2.45 ms, 2.07 for the matrix instructions alone; calls long enough to sit at
-// the power limit gain nothing (two steps of it 23.9 ms either way).  Whole calls, two steps, us: 32 nodes, 800-1504-480, batch 64
-// 653 -> 623; 23 nodes, 448-3840-224, batch 96 1059 -> 996; 36 nodes, 608-1280-64, batch 128 562 -> 537; 48 nodes, 1024-4096-1024,
-// batch 64 2978 -> 2923; 8 nodes at batch 32 the same.
+// open (matrix cores busy 67 % of the time against 89 % in the forward products); here nothing restarts between row blocks (79 %).
+// 256 nodes, 1024 x 4096 weights, batch 128: 2.66 -> 2.45 ms, 2.07 for the matrix instructions alone.  Whole calls, two steps, us:
+// that swarm, at the power limit, 24 380 -> 23 790 and 24 740 -> 24 420 in two runs; 32 nodes, 800-1504-480, batch 64 572 -> 537;
+// 23 nodes, 448-3840-224, batch 96 1035 -> 954; 36 nodes, 608-1280-64, batch 128 537 -> 508; 48 nodes, 1024-4096-1024, batch 64
+// 2901 -> 2817; 8 nodes at batch 32 the same.
+// Three workgroups per compute unit: with four blocks of samples that costs 12 bytes of scratch per lane; two without it take
+// as long (that swarm 2.42 and 2.46 ms for W1 and W2, 2.47 and 2.46 with two; 36 nodes, 608-1280-64: 84 and 14 us, 86 and 14).
 // The order of the products is that of mlp_gemm_kernel, so is every bit.
 struct FloatUpdateArgs {
     const float *a, *b, *src;       // src: models, `d` floats per node

@@ -34,7 +34,7 @@ constexpr int RUN_COLS = 128;                     // columns per workgroup
 constexpr int TEAMS = 4;                          // per workgroup, each with interactions of its own
 constexpr int CREW = 4;                           // waves of a team, each with rows of its own
 constexpr uint32_t RUN_LSQ_NODES = 64;            // 64 KiB of local memory
-constexpr uint32_t RUN_LSQ_WORDS = 2048;          // batch x workgroups: every wave reads so many words per step
+constexpr uint32_t RUN_LSQ_WORDS = 2048;          // batch x workgroups: a team reads so many words per step, each wave a quarter
 constexpr uint64_t WAIT_TICKS = 200000000ull;     // 2 s of the 100 MHz wall clock
 
 struct LsqRunArgs {
@@ -104,7 +104,9 @@ __global__ __launch_bounds__(TEAMS * CREW * 64, 1) void lsq_run_kernel(const Lsq
     const auto part = __builtin_amdgcn_make_buffer_rsrc((void *)ra.part, 0, (int)(TEAMS * 2 * NB * 8u * slots), 0x00020000);
     // Cycles from a wave's words to its first request.  us for 200 interactions of 8 nodes, H = 2, at 256 / 768 / 1280 / 1792 cycles:
     // batch 32, 4096 columns 657 / 599 / 595 / 622, 1024: 466 / 431 / 463 / 508, 8192: 868 / 794 / 784 / 808, 128 (alone): 362 / 386 / 444 / 495;
-    // batch 16, 2048: 426 / 380 / 429 / 479; 16 nodes x 8192, H = 1: 313 / 274 / 258 / 239.
+    // batch 16, 2048: 426 / 380 / 429 / 479; 16 nodes x 8192, H = 1: 313 / 274 / 258 / 239.  By workgroups alone: with 64 of them
+    // (1920 cycles) two steps at batch 32 pay for the single steps (8 nodes x 8192, H = 2: 780, 760 at 1280; 16 nodes, H = 1: 316 and
+    // 324 at batch 32, 230 and 248 at batch 16).
     const uint64_t pause = groups == 1 ? 0u : 640u + 20u * groups;
     const float step = ra.lr * ((float)ra.m_rows / (float)ra.batch);
 

@@ -8,10 +8,12 @@
 // hold a gradient's operand.  Features, hidden activations and the logits' gradient are packed by samples (for the products with
 // weights) and by columns (for the gradients of the weights), the hidden gradient by columns, all by the kernels that make them.
 // us for two steps, against one kernel per product that split both operands on the way into local memory:
-//   64 nodes, 1024-4096-1024, batch 128   3536 -> 3035     32 nodes, 800-1504-480, batch 64   476 -> 430
-//   48 nodes, 1024-4096-1024, batch 64    2221 -> 1917     36 nodes, 608-1280-64, batch 128   359 -> 302
-//    8 nodes, 1024-4096-1024, batch 32     478 -> 382      64 nodes, 736-1376-896, batch 160  1693 -> 1340
-//    4 nodes, 1024-2048-512, batch 128     255 -> 207      16 nodes, 800-1504-480, batch 288   704 -> 622
+//   64 nodes, 1024-4096-1024, batch 128   3576 -> 2979     32 nodes, 800-1504-480, batch 64   454 -> 398, one of them 139 -> 133
+//   48 nodes, 1024-4096-1024, batch 64    2244 -> 1897     36 nodes, 608-1280-64, batch 128   347 -> 285, one of them 138 -> 101
+//    8 nodes, 1024-4096-1024, batch 32     477 -> 382      64 nodes, 736-1376-896, batch 160  1616 -> 1221, one of them 218 -> 176
+//    4 nodes, 1024-2048-512, batch 128     247 -> 196      16 nodes, 800-1504-480, batch 288   653 -> 527, one of them 227 -> 146
+// Packing costs where a product is a slab or two deep and its operands are what moves: 31 nodes, 32-96-896, batch 1024 503 -> 527;
+// 31 nodes, 608-32-832, batch 32 113 -> 123.
 #include <algorithm>
 #include <new>
 #include <type_traits>
