@@ -7,7 +7,8 @@ namespace swarm {
 
 // One interaction of the run.  nodes: initiator | responder << 16; event: the interaction number that keys its
 // random streams; flags: SEQ_HAS_DELTA, RUN_*, bits 8-15 = the initiator's number of local steps; turn:
-// how many interactions of the run touch the initiator (low half) and the responder (high half) before this one.
+// how many interactions of the run touch the initiator (low half) and the responder (high half) before this one; in
+// least-squares runs how many interactions have ended, in the order of the descriptors, when the initiator's snapshot is there.
 struct RunDesc {
     uint32_t nodes, event, flags, turn;
 };

@@ -1,24 +1,27 @@
 // Algorithm 1 on small least-squares swarms: a run of interactions (or a single one) in one launch.  A workgroup owns
-// 128 columns of all n models and snapshots and keeps them in local memory (1 KiB per node); each of its four teams of four
-// waves takes every fourth interaction, in an order in which every interaction follows those it depends on, and waits in
-// local memory for the earlier interactions of its two nodes (as in interact_run.hip).  A wave holds every fourth of the
-// batch's rows of A, a lane two columns of them: the products need no other lane but for the residuals, and of those only
-// the sums over a workgroup's columns leave it.  The waves that hold the same rows in the other workgroups wait for these
-// words in device memory, each tagged with the number of its step, so that nothing has to be cleared between steps; two
-// sets of words alternate, because a wave writes its words of step c + 2 after it has read all words of step c + 1, and
-// those were written by waves that had read step c.  The gradients of a team's waves meet in local memory (two sets of
+// 128 columns of all n models and snapshots and keeps them in local memory (1 KiB per node).  The local steps of an interaction
+// need the initiator's snapshot and nothing else of the interactions before it, so they are taken apart from it: seven teams
+// of two waves take the steps of every seventh interaction as soon as the initiator's last interaction of its own has ended,
+// and one wave takes the interactions in their order, each when its steps are there.  So the chain of interactions that share
+// a node is a chain of averages, and only the interactions that a node leads wait for one another's steps.
+// A wave holds every second of the batch's rows of A, a lane two columns of them: the products need no other lane but for the
+// residuals, and of those only the sums over a workgroup's columns leave it.  The waves that hold the same rows in the other
+// workgroups wait for these words in device memory, each tagged with the number of its step, so that nothing has to be cleared
+// between steps; two sets of words alternate, because a wave writes its words of step c + 2 after it has read all words of step
+// c + 1, and those were written by waves that had read step c.  The gradients of a team's waves meet in local memory (two sets of
 // them for the same reason), and every wave applies their sum to a copy of the model of its own.
-// Bound by latency: interactions that share a node follow one another, and a step is a chain of products, sums over the
-// wave, one exchange through device memory, one through local memory and an update.  So whatever needs no model is done
-// before the wait for the nodes (the random words, by one call of the generator per lane, and the rows of two steps) or
-// while the words travel (the pair's average), and the rows are split between waves (one wave took 4200 of a step's 9600
-// cycles to draw and request 32 rows).  What is left, in cycles at 8 nodes x 4096, batch 32: 600 products and sums, 3500 until
-// the words are there, 400 gradient, 900 until the team's have met.  Words that are asked for too early hold up the stores they wait
-// for: hence the pause, and requests for what is missing only.  200 interactions, H = 2: 593 us, 979 with one wave per team;
-// 8 x 1024, batch 16: 400 and 649; a single interaction 10.7 us and 13.6 (8 x 8192).  With a pause of 256
-// cycles 657, and 426 instead of 380 at 2048 columns, batch 16.  All workgroups on one die: no faster (4 % at 8 workgroups, slower at 32).
-// Four teams per workgroup are room for four interactions side by side: graphs that let many more run at once keep a launch
-// per level (LSQ_RUN_WIDTH in swarm_api.hip).
+// Bound by latency: a step is a chain of products, sums over the wave, one exchange through device memory, one through local
+// memory and an update.  So what needs no model is done before the wait for the snapshot (an interaction's rows are drawn by one
+// call of the generator per lane, and those of its first two steps requested) or while the words travel (the rows of later steps).
+// In cycles per step at 8 nodes x 4096, batch 32: 500 products and sums, 3800 until the words of all 32 workgroups are there (2300
+// with 8), 500 gradient, 700 until the team's two have met.  Words that are asked for too early hold up the stores they wait for:
+// hence the pause, and requests for what is missing only.
+// us for 200 interactions on a complete graph, against teams of four waves that each kept an interaction from its wait for both
+// nodes to its end (four side by side):
+//   8 x 4096, batch 32, H = 2    593  364      8 x 1024, batch 32, H = 2    444  291     12 x 2048, batch 16, H = 3    458  296
+//   8 x 8192, batch 32, H = 1    439  269     16 x 8192, batch 32, H = 2    603  339
+// A single interaction of 8 x 8192, batch 32, H = 2: 10.6 and 10.3.  Five teams instead of seven: 375, and 392 at 16 x 8192.  An
+// interaction's rows requested during the last steps of the one before: 383 and 378.
 // All workgroups are resident together (at most 64), the earliest unfinished interaction waits for none, and every
 // wait is bounded, so that all waves end whatever happens to the others.
 #include <type_traits>
@@ -31,10 +34,11 @@
 namespace swarm {
 
 constexpr int RUN_COLS = 128;                     // columns per workgroup
-constexpr int TEAMS = 4;                          // per workgroup, each with interactions of its own
-constexpr int CREW = 4;                           // waves of a team, each with rows of its own
+constexpr int CREW = 2;                           // waves of a team, each with rows of its own
+constexpr int TEAMS = 7;                          // per workgroup, each with steps of its own
+constexpr int RUN_WAVES = TEAMS * CREW + 1;       // the last one takes the interactions
 constexpr uint32_t RUN_LSQ_NODES = 64;            // 64 KiB of local memory
-constexpr uint32_t RUN_LSQ_WORDS = 2048;          // batch x workgroups: a team reads so many words per step, each wave a quarter
+constexpr uint32_t RUN_LSQ_WORDS = 2048;          // batch x workgroups: a team reads so many words per step, each wave half of them
 constexpr uint64_t WAIT_TICKS = 200000000ull;     // 2 s of the 100 MHz wall clock
 
 struct LsqRunArgs {
@@ -65,11 +69,10 @@ __device__ __forceinline__ void store_code_pair(uint8_t *row, uint64_t col, uint
     }
 }
 
-// Workgroups a row has words for: whole requests of a wave (R rows of CREW * 64 / NB workgroups), a power of two of them.
+// Workgroups that a set has words for: whole requests of a wave (64 words).
 __host__ __device__ __forceinline__ uint32_t slots_of(uint32_t groups, uint32_t padded) {
-    uint32_t slots = CREW * 64 / padded;
-    while (slots < groups) slots *= 2;
-    return slots;
+    const uint32_t each = CREW * 64 / padded;
+    return (groups + each - 1) / each * each;
 }
 
 // A word at a lane's and a uniform offset, as other workgroups' stores left it (SC1: past this die's caches).
@@ -81,97 +84,55 @@ __device__ __forceinline__ unsigned long long word_of_agent(__amdgpu_buffer_rsrc
 
 // NB: the batch rounded up to 16 or 32 rows.
 template <int BITS, int NB>
-__global__ __launch_bounds__(TEAMS * CREW * 64, 1) void lsq_run_kernel(const LsqRunArgs ra) {
+__global__ __launch_bounds__(RUN_WAVES * 64, 1) void lsq_run_kernel(const LsqRunArgs ra) {
     constexpr int R = NB / CREW;                  // rows of a wave
-    constexpr int WAVES = TEAMS * CREW;
-    constexpr uint32_t STEPS = 32 / R;            // whose rows a call of the generator per lane draws
+    constexpr uint32_t EACH = 64 / R;             // steps whose rows a call of the generator per lane draws; workgroups whose words a request takes
     extern __shared__ f2v models[];               // n x 64 pairs of columns of X, then the same of Xhat
-    __shared__ uint32_t done[RUN_LSQ_NODES];      // interactions each node has been through
     __shared__ f2v shares[TEAMS][2][CREW][64];    // of the gradient, by step parity
-    __shared__ __attribute__((aligned(16))) uint32_t arrived[TEAMS][CREW];     // steps whose share a wave has left
-    __shared__ uint32_t bail;
+    __shared__ f2v deltas[TEAMS][64];             // what the steps of a team's interaction have come to
+    __shared__ uint32_t arrived[TEAMS][CREW];     // steps whose share a wave has left
+    __shared__ uint32_t stepped[TEAMS];           // interactions whose steps a team has taken
+    __shared__ uint32_t touched[RUN_LSQ_NODES];
+    __shared__ uint32_t finished, bail;           // finished: interactions that have ended
     const GossipArgs &a = ra.g;
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t team = wave / CREW, mate = wave % CREW, at_row = lane / CREW % R;
-    const uint32_t group = blockIdx.x, groups = gridDim.x, n = a.n, own = ra.batch / CREW;        // the batch is a multiple of 4
+    const uint32_t group = blockIdx.x, groups = gridDim.x, n = a.n;
     const uint64_t d = a.d, col = (uint64_t)group * RUN_COLS + 2u * lane;
     const bool in = col < d;
     const uint32_t at_col = in ? (uint32_t)col : 0u;        // lanes past the row read its first columns, and no sum or store takes them
     const f2v zero = {0.f, 0.f};
     f2v *const X = models, *const Xhat = models + n * 64u;
-    constexpr uint32_t EACH = CREW * 64 / NB;     // workgroups whose words a request takes
-    const uint32_t slots = slots_of(groups, NB), first = 64u / NB * (lane % CREW) + lane / NB, mine_from = 8u * (first * R + at_row);
-    const auto part = __builtin_amdgcn_make_buffer_rsrc((void *)ra.part, 0, (int)(TEAMS * 2 * NB * 8u * slots), 0x00020000);
-    // Cycles from a wave's words to its first request.  us for 200 interactions of 8 nodes, H = 2, at 256 / 768 / 1280 / 1792 cycles:
-    // batch 32, 4096 columns 657 / 599 / 595 / 622, 1024: 466 / 431 / 463 / 508, 8192: 868 / 794 / 784 / 808, 128 (alone): 362 / 386 / 444 / 495;
-    // batch 16, 2048: 426 / 380 / 429 / 479; 16 nodes x 8192, H = 1: 313 / 274 / 258 / 239.  By workgroups alone: with 64 of them
-    // (1920 cycles) two steps at batch 32 pay for the single steps (8 nodes x 8192, H = 2: 780, 760 at 1280; 16 nodes, H = 1: 316 and
-    // 324 at batch 32, 230 and 248 at batch 16).
-    const uint64_t pause = groups == 1 ? 0u : 640u + 20u * groups;
-    const float step = ra.lr * ((float)ra.m_rows / (float)ra.batch);
 
     uint64_t seed = a.seed;
     auto here = [](uint64_t v) {                  // what follows from v is worked out where it is used: its registers are short
         asm volatile("" : "+s"(v));
         return v;
     };
-
     auto desc = [&](uint32_t k) { return ra.descs ? run_desc(ra.descs, k, ra.count) : ra.one; };
+    auto read = [](uint32_t *word) { return first_lane(__hip_atomic_load(word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)); };
+    auto post = [](uint32_t *word, uint32_t v) { __hip_atomic_store(word, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP); };
     auto given_up = [&](uint64_t since) {
         return first_lane(__hip_atomic_load(&bail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0 || wall_clock64() - since > WAIT_TICKS;
     };
+    bool lost = false, clamped = false;
+    int fails = 0;
+    auto wait_for = [&](uint32_t *word, uint32_t least) {     // counts, far from wrapping
+        if (read(word) >= least) return;
+        const uint64_t t0 = wall_clock64();
+        do {
+            lost = lost || given_up(t0);
+            if (lost) return;
+            __builtin_amdgcn_s_sleep(1);
+        } while (read(word) < least);
+    };
 
-    if (threadIdx.x < n) done[threadIdx.x] = 0;
-    if (threadIdx.x < WAVES) arrived[threadIdx.x / CREW][threadIdx.x % CREW] = 0;
-    if (threadIdx.x == 0) bail = 0;
-    f2v rows_even[R] = {}, rows_odd[R] = {};      // of even and odd steps
-    float rhs_even = 0.f, rhs_odd = 0.f;
-    uint32_t drawn = 0, ri = 0, rj = 0;           // rows of A, and random words of the pair's rounding
-    // A wave's rows are every fourth of the batch's: row mate + 4 i.  One call of the generator per lane serves lanes 0..15 and
-    // 16..31 with the random words of the pair's rounding, the other lanes with the rows of A that STEPS steps from the first draw.
-    auto draw = [&](const RunDesc &rd, uint32_t q) {
-        const uint32_t ni = rd.nodes & 0xFFFFu, nj = rd.nodes >> 16;
-        const bool rows = lane >= 32;
-        const Words4 r = stream(here(seed), rows ? TAG_BATCH : TAG_SR, rows ? q + (lane - 32u) / R : 0u, rows || lane < 16 ? ni : nj, rd.event,
-                                rows ? lane % R : 16u * group + lane % 16u);
-        drawn = scaled_index(mate == 0 ? r.w0 : mate == 1 ? r.w1 : mate == 2 ? r.w2 : r.w3, ra.m_rows);
-        return r;
-    };
-    // the lane's columns of step q's rows (past the batch of rows that no sum takes), and the right-hand side of row `at_row`
-    auto request = [&](const RunDesc &rd, uint32_t q, f2v (&rows)[R], float &rhs) {
-        const uint32_t node = rd.nodes & 0xFFFFu, from = 32u + R * (q % STEPS);
-        const uint32_t row = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (from + at_row)), (int)drawn);
-        const uint64_t row_at = (uint64_t)(ra.A + (uint64_t)node * ra.m_rows * d) + (uint64_t)drawn * (4u * d);
-        uint32_t offset = 4u * at_col;
-        asm("" : "+v"(offset));                   // a 32-bit offset to a scalar base, not a 64-bit one made ahead of the loop
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)row_at, from + i);
-            const uint32_t high = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(row_at >> 32), from + i);
-            rows[i] = *(SWARM_GLOBAL const f2v *)at_bytes(uniform((const float *)((uint64_t)high << 32 | low)), offset);
-        }
-        rhs = ra.b[(uint64_t)node * ra.m_rows + row];
-    };
-    auto prepare = [&](const RunDesc &rd) {
-        const Words4 r = draw(rd, 0);
-        request(rd, 0, rows_even, rhs_even);
-        if (((rd.flags >> 8) & 0xFFu) > 1) request(rd, 1, rows_odd, rhs_odd);
-        if (BITS > 0 && mate == 0) {              // a call serves 8 columns: word (column / 2) % 4, low half first
-            auto word_of = [&](uint32_t call) {
-                const uint32_t w0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w0);
-                const uint32_t w1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w1);
-                const uint32_t w2 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w2);
-                const uint32_t w3 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w3);
-                return (lane & 3u) == 0 ? w0 : (lane & 3u) == 1 ? w1 : (lane & 3u) == 2 ? w2 : w3;
-            };
-            ri = word_of(lane / 4u);
-            rj = word_of(16u + lane / 4u);
-        }
-    };
-    RunDesc next = desc(team);
-    if (team < ra.count) prepare(next);
+    if (ra.descs && threadIdx.x < ra.count)       // on the way to this die's cache: whoever reads them there waits for little else
+        asm volatile("" ::"v"(ra.descs[threadIdx.x].turn));
+    if (threadIdx.x < n) touched[threadIdx.x] = 0;
+    if (threadIdx.x < TEAMS) arrived[threadIdx.x][0] = arrived[threadIdx.x][1] = stepped[threadIdx.x] = 0;
+    if (threadIdx.x == 0) finished = bail = 0;
     const bool single = !ra.descs;                // a single interaction touches two nodes
-    for (uint32_t u = wave; u < (single ? 2u : n); u += WAVES) {
+    for (uint32_t u = wave; u < (single ? 2u : n); u += RUN_WAVES) {
         const uint32_t node = single ? (u ? ra.one.nodes >> 16 : ra.one.nodes & 0xFFFFu) : u;
         const f2v x = *(const f2v *)(a.X + (uint64_t)node * d + at_col), h = *(const f2v *)(a.Xhat + (uint64_t)node * d + at_col);
         X[node * 64u + lane] = in ? x : zero;
@@ -179,27 +140,191 @@ __global__ __launch_bounds__(TEAMS * CREW * 64, 1) void lsq_run_kernel(const Lsq
     }
     __syncthreads();
 
-    uint32_t turn_of_step = 0;                    // steps this team has taken: numbers the exchanged words
-    bool clamped = false, lost = false;
-    int fails = 0;
-    for (uint32_t k = team; k < ra.count && !lost; k += TEAMS) {
-        const RunDesc rd = next;
-        next = desc(k + TEAMS);
-        const uint32_t ni = rd.nodes & 0xFFFFu, nj = rd.nodes >> 16, H = (rd.flags >> 8) & 0xFFu;
-        const uint64_t t0 = wall_clock64();
-        while (true) {                            // both nodes' earlier interactions
-            const uint32_t turn = __hip_atomic_load(&done[lane & 1u ? nj : ni], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (__all(turn == (lane & 1u ? rd.turn >> 16 : rd.turn & 0xFFFFu))) break;
-            lost = given_up(t0);
+    if (wave < TEAMS * CREW) {
+        const uint32_t team = wave / CREW, mate = wave % CREW, own = ra.batch / CREW;      // the batch is a multiple of 4
+        const uint32_t slots = slots_of(groups, NB);
+        const auto part = __builtin_amdgcn_make_buffer_rsrc((void *)ra.part, 0, (int)(TEAMS * CREW * 2 * R * 8u * slots), 0x00020000);
+        // Cycles from a wave's words to its first request.  us for 200 interactions (89 in the last column) at 0 / 400 / 800 / 1200 /
+        // 1600 / 2000 cycles: 8 nodes x 1024, batch 32, H = 2: 344 / 309 / 300 / 302 / 318 / 334, x 4096: 428 / 399 / 387 / 380 / 375 / 385,
+        // 12 x 8192, batch 16, H = 3: 481 / 449 / 419 / 409 / 396 / 389, 16 x 936, batch 32, H = 2: 147 / 127 / 121 / 121 / 126 / 131.
+        const uint64_t pause = groups == 1 ? 0u : 640u + 24u * groups;
+        const float step = ra.lr * ((float)ra.m_rows / (float)ra.batch);
+        RunDesc after;                            // the team's next interaction, in vector registers until it is its turn
+        auto fetch_after = [&](uint32_t k) {
+            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+            const u4 v = ((SWARM_GLOBAL const u4 *)ra.descs)[min(k, ra.count - 1)];
+            after = RunDesc{v.x, v.y, v.z, v.w};
+        };
+        uint64_t row_at = 0;                      // rows of A and their right-hand sides, as drawn
+        float rhs_at = 0.f;
+        // A wave's rows are every second of the batch's: row mate + 2 i, of the steps q + lane / R
+        auto draw = [&](const RunDesc &rd, uint32_t q) {
+            const uint32_t i = lane % R, word = mate + 2u * (i & 1u), node = rd.nodes & 0xFFFFu;
+            const Words4 r = stream(here(seed), TAG_BATCH, q + lane / R, node, rd.event, i >> 1);
+            const uint64_t row = (uint64_t)node * ra.m_rows + scaled_index(word == 0 ? r.w0 : word == 1 ? r.w1 : word == 2 ? r.w2 : r.w3, ra.m_rows);
+            row_at = (uint64_t)ra.A + 4u * row * d;
+            rhs_at = ra.b[row];
+        };
+        // the lane's columns of the step's rows (past the batch of rows that no sum takes)
+        auto request = [&](uint32_t q, f2v (&rows)[R]) {
+            const uint32_t from = R * (q % EACH);
+            uint32_t offset = 4u * at_col;
+            asm("" : "+v"(offset));               // a 32-bit offset to a scalar base, not a 64-bit one made ahead of the loop
+            constexpr int B = 4;                  // addresses side by side: a scalar that a lane was read into may address a load five instructions later
+#pragma unroll
+            for (int i = 0; i < R; i += B) {
+                uint64_t at[B];
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)row_at, from + i + j);
+                    const uint32_t high = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(row_at >> 32), from + i + j);
+                    at[j] = (uint64_t)high << 32 | low;
+                }
+                asm volatile("" : "+s"(at[0]), "+s"(at[1]), "+s"(at[2]), "+s"(at[3]));
+#pragma unroll
+                for (int j = 0; j < B; ++j) rows[i + j] = *(SWARM_GLOBAL const f2v *)at_bytes((SWARM_GLOBAL const float *)at[j], offset);
+            }
+        };
+        f2v rows[R] = {}, rows_ahead[R] = {};     // of this step and the next
+        uint32_t turn = 0;                        // steps this team has taken: numbers the exchanged words
+        if (ra.descs) fetch_after(team);
+        for (uint32_t k = team, through = 0; k < ra.count; k += TEAMS, ++through) {
+            RunDesc rd = ra.one;
+            if (ra.descs) {
+                rd = RunDesc{first_lane(after.nodes), first_lane(after.event), first_lane(after.flags), first_lane(after.turn)};
+                fetch_after(k + TEAMS);
+            }
+            const uint32_t node = rd.nodes & 0xFFFFu, H = (rd.flags >> 8) & 0xFFu;
+            draw(rd, 0);
+            request(0, rows);
+            if (H > 1) request(1, rows_ahead);
+            wait_for(&finished, rd.turn);         // the initiator's snapshot
             if (lost) break;
-            __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_s_setprio(2);        // ahead of the teams that wait
+            const f2v h = Xhat[node * 64u + lane];
+            f2v w = h;
+            for (uint32_t q = 0; q < H; ++q) {
+                float dots[R];
+#pragma unroll
+                for (int i = 0; i < R; ++i) dots[i] = fmaf(rows[i].y, w.y, rows[i].x * w.x);
+                const float share = wave_totals<R, 32>(dots, lane);      // of row lane / EACH
+                const uint32_t tag = ra.tag + turn, set = ((team * 2u + (turn & 1u)) * CREW + mate) * slots * R;
+                if (lane % EACH == 0)
+                    __hip_atomic_store(ra.part + (set + group * R + lane / EACH), ((unsigned long long)tag << 32) | __float_as_uint(share),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t published = __builtin_readcyclecounter();
+                // while the words travel: the rows of the next step, but for the second, which are here
+                const float rhs = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (R * (q % EACH) + lane % R)), (int)__float_as_uint(rhs_at)));
+                if (q > 0 && q + 1 < H) {
+                    if ((q + 1) % EACH == 0) draw(rd, q + 1);
+                    request(q + 1, rows_ahead);
+                }
+                while (__builtin_readcyclecounter() - published < pause) __builtin_amdgcn_s_sleep(1);
+                // the residual of row lane % R: the shares of the workgroups lane / R, lane / R + EACH .., in order, then the sum of these
+                float residual = 0.f;
+                auto collect = [&](auto requests) {   // `requests` words per lane at a time
+                    constexpr uint32_t WORDS = decltype(requests)::value;
+                    for (uint32_t g0 = 0; g0 < groups && !lost; g0 += WORDS * EACH) {
+                        unsigned long long word[WORDS];
+                        auto ask = [&](uint32_t i) { word[i] = word_of_agent(part, 8u * lane, 8u * (set + (g0 + i * EACH) * R)); };
+                        auto beyond = [&](uint32_t i) { return g0 + i * EACH + lane / R >= groups; };
+                        auto missing = [&](uint32_t i) { return !__all((uint32_t)(word[i] >> 32) == tag || beyond(i)); };
+                        asm volatile("" ::: "memory");        // not before the pause
+#pragma unroll
+                        for (uint32_t i = 0; i < WORDS; ++i) ask(i);
+                        for (uint64_t since = 0;;) {
+                            uint32_t late = 0;
+#pragma unroll
+                            for (uint32_t i = 0; i < WORDS; ++i) late |= missing(i) ? 1u << i : 0u;
+                            if (late == 0) break;
+                            if (since == 0) since = wall_clock64();
+                            lost = given_up(since);
+                            if (lost) break;
+                            __builtin_amdgcn_s_sleep(1);
+                            asm volatile("" ::: "memory");    // what is read again
+#pragma unroll
+                            for (uint32_t i = 0; i < WORDS; ++i)
+                                if (late & 1u << i) ask(i);
+                        }
+#pragma unroll
+                        for (uint32_t i = 0; i < WORDS; ++i) residual += beyond(i) ? 0.f : __uint_as_float((uint32_t)word[i]);
+                    }
+                };
+                if (groups <= 2 * EACH) collect(std::integral_constant<uint32_t, 2>{});
+                else if (groups <= 4 * EACH) collect(std::integral_constant<uint32_t, 4>{});
+                else collect(std::integral_constant<uint32_t, 8>{});
+                if (lost) break;
+                residual = total_from<R>(residual, lane) - rhs;
+                f2v even = zero, odd = zero;          // shares of the gradient: two chains of rows per wave
+                auto add = [&](int i, f2v &g) {
+                    const float r = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(residual), i));
+                    g.x = fmaf(rows[i].x, r, g.x);
+                    g.y = fmaf(rows[i].y, r, g.y);
+                };
+                if (own == R) {
+#pragma unroll
+                    for (int i = 0; i < R; i += 2) { add(i, even); add(i + 1, odd); }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < R; i += 2)    // the batch is a multiple of 4, a wave's part of it one of 2
+                        if ((uint32_t)i < own) { add(i, even); add(i + 1, odd); }
+                }
+                // The team's shares meet: a wave's words reach local memory in order.  The set of two steps ago has been read by the mate
+                // when its share of the last step is there; the second wave does not wait for that where an interaction ends.
+                f2v (*mine)[64] = shares[team][turn & 1u];
+                if (mate != 0) wait_for(&arrived[team][0], turn);
+                mine[mate][lane] = even + odd;
+                ++turn;
+                post(&arrived[team][mate], turn);
+                if (q + 1 < H || mate == 0) {
+                    wait_for(&arrived[team][mate ^ 1u], turn);
+                    const f2v g = in ? mine[0][lane] + mine[1][lane] : zero;      // lanes past the row keep a zero
+                    w.x = fmaf(-step, g.x, w.x);
+                    w.y = fmaf(-step, g.y, w.y);
+                }
+                if (lost) break;
+                if (q + 1 < H) {
+#pragma unroll
+                    for (int i = 0; i < R; ++i) rows[i] = rows_ahead[i];
+                }
+            }
+            if (lost) break;
+            if (mate == 0) {
+                if (through) wait_for(&finished, k - TEAMS + 1);     // the one before has been taken
+                if (lost) break;
+                deltas[team][lane] = w - h;
+                post(&stepped[team], through + 1);
+                if ((rd.flags & RUN_LAST_LED) && in) *(f2v *)(ra.W + (uint64_t)node * d + col) = w;
+            }
+            __builtin_amdgcn_s_setprio(0);
         }
-        if (lost) break;
-        __builtin_amdgcn_s_setprio(2);            // ahead of the teams that wait
-        const f2v h = Xhat[ni * 64u + lane], xi = X[ni * 64u + lane], xj = X[nj * 64u + lane];
-        f2v w = h, average = zero;
-        int zi0 = 0, zi1 = 0, zj0 = 0, zj1 = 0;
-        auto meet = [&] {                         // the pair's average takes no local step
+    } else {
+        __builtin_amdgcn_s_setprio(3);            // everyone waits for this wave
+        uint32_t ri = 0, rj = 0;                  // random words of the pair's rounding
+        auto draw = [&](const RunDesc &rd) {
+            if constexpr (BITS > 0) {             // a call serves 8 columns: word (column / 2) % 4, low half first
+                const Words4 r = stream(here(seed), TAG_SR, 0, lane < 16 ? rd.nodes & 0xFFFFu : rd.nodes >> 16, rd.event, 16u * group + lane % 16u);
+                auto word_of = [&](uint32_t call) {
+                    const uint32_t w0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w0);
+                    const uint32_t w1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w1);
+                    const uint32_t w2 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w2);
+                    const uint32_t w3 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * call), (int)r.w3);
+                    return (lane & 3u) == 0 ? w0 : (lane & 3u) == 1 ? w1 : (lane & 3u) == 2 ? w2 : w3;
+                };
+                ri = word_of(lane / 4u);
+                rj = word_of(16u + lane / 4u);
+            }
+        };
+        RunDesc next = desc(0);
+        draw(next);
+        uint32_t team = 0, through = 0;
+        for (uint32_t k = 0; k < ra.count; ++k) {
+            const RunDesc rd = next;
+            next = desc(k + 1);
+            const uint32_t ni = rd.nodes & 0xFFFFu, nj = rd.nodes >> 16;
+            const f2v xi = X[ni * 64u + lane], xj = X[nj * 64u + lane];
+            f2v average;
+            int zi0 = 0, zi1 = 0, zj0 = 0, zj1 = 0;
             if constexpr (BITS > 0) {
                 constexpr uint32_t MASK = (uint32_t)((1ull << BITS) - 1);
                 const float half_eps = 0.5f * a.eps;
@@ -215,116 +340,21 @@ __global__ __launch_bounds__(TEAMS * CREW * 64, 1) void lsq_run_kernel(const Lsq
             } else {
                 average = 0.5f * (xi + xj);
             }
-        };
-        auto take_step = [&](uint32_t q, f2v (&rows)[R], float &rhs) {
-            float dots[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) dots[i] = in ? fmaf(rows[i].y, w.y, rows[i].x * w.x) : 0.f;
-            const float share = wave_totals<R, NB / 2>(dots, lane);
-            const uint32_t tag = ra.tag + turn_of_step;
-            const uint32_t set = ((team * 2u + (turn_of_step & 1u)) * CREW + mate) * slots * (R * 8u);
-            if (lane < NB && lane % CREW == 0)
-                __hip_atomic_store(ra.part + (set / 8u + group * R + at_row), ((unsigned long long)tag << 32) | __float_as_uint(share),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t published = __builtin_readcyclecounter();
-            // while the words travel
-            if (q == 0 && mate == 0) meet();
-            const bool again = q + 2 < H;
-            if (again && (q + 2) % STEPS == 0) draw(rd, q + 2);
-            // the residual of row `at_row`: the shares of the workgroups lane / NB, lane / NB + 64 / NB .., in order, requested by
-            // the quad's lanes in turn, then the sum of these sums
-            float residual = 0.f;
-            while (__builtin_readcyclecounter() - published < pause) __builtin_amdgcn_s_sleep(1);
-            const uint64_t t1 = wall_clock64();
-            auto collect = [&](auto requests) {           // `requests` words per lane at a time
-                constexpr uint32_t WORDS = decltype(requests)::value;
-                for (uint32_t g0 = 0; g0 < groups && !lost; g0 += WORDS * EACH) {
-                    unsigned long long word[WORDS];
-                    auto ask = [&](uint32_t i) { word[i] = word_of_agent(part, mine_from, set + (g0 + i * EACH) * (R * 8u)); };
-                    auto missing = [&](uint32_t i) {
-                        return !__all((uint32_t)(word[i] >> 32) == tag || g0 + i * EACH + first >= groups);
-                    };
-                    asm volatile("" ::: "memory");        // not before the pause
-#pragma unroll
-                    for (uint32_t i = 0; i < WORDS; ++i) ask(i);
-                    while (true) {
-                        uint32_t late = 0;
-#pragma unroll
-                        for (uint32_t i = 0; i < WORDS; ++i) late |= missing(i) ? 1u << i : 0u;
-                        if (late == 0) break;
-                        lost = given_up(t1);
-                        if (lost) break;
-                        __builtin_amdgcn_s_sleep(1);
-                        asm volatile("" ::: "memory");    // what is read again
-#pragma unroll
-                        for (uint32_t i = 0; i < WORDS; ++i)
-                            if (late & 1u << i) ask(i);
-                    }
-#pragma unroll
-                    for (uint32_t i = 0; i < WORDS; ++i) {
-                        const int v = g0 + i * EACH + first < groups ? (int)(uint32_t)word[i] : 0;
-                        residual += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true));   // of the quad's lane 0
-                        residual += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true));
-                        residual += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true));
-                        residual += __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true));
-                    }
-                }
-            };
-            if (slots == EACH) collect(std::integral_constant<uint32_t, 1>{});
-            else if (slots == 2 * EACH) collect(std::integral_constant<uint32_t, 2>{});
-            else collect(std::integral_constant<uint32_t, 4>{});
-            residual = total_from<NB>(residual, lane);
-            residual -= rhs;
-            f2v share_of_g = zero;                        // of every fourth row: one chain of all rounds more (2.78e-8 off 64 bits after 200 interactions, 2.68e-8 so)
-            auto add = [&](int i) {
-                const float r = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(residual), CREW * i));
-                share_of_g.x = fmaf(rows[i].x, r, share_of_g.x);
-                share_of_g.y = fmaf(rows[i].y, r, share_of_g.y);
-            };
-            if (own == R) {
-#pragma unroll
-                for (int i = 0; i < R; ++i) add(i);
-            } else {
-#pragma unroll
-                for (int i = 0; i < R; ++i)
-                    if ((uint32_t)i < own) add(i);
-            }
-            // the team's shares meet: a wave's words reach local memory in order, and the next set is not written before every mate
-            // has read this one
-            f2v (*mine)[64] = shares[team][turn_of_step & 1u];
-            mine[mate][lane] = share_of_g;
-            __hip_atomic_store(&arrived[team][mate], ++turn_of_step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (again) request(rd, q + 2, rows, rhs);
-            while (true) {
-                const uint32_t steps = __hip_atomic_load(&arrived[team][lane % CREW], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (__all(steps - turn_of_step <= 1u)) break;
-                lost = lost || given_up(t1);
-                if (lost) break;
-            }
-            const f2v g = (mine[0][lane] + mine[1][lane]) + (mine[2][lane] + mine[3][lane]);
-            w.x = fmaf(-step, g.x, w.x);
-            w.y = fmaf(-step, g.y, w.y);
-        };
-        for (uint32_t q = 0; q < H && !lost; q += 2) {
-            take_step(q, rows_even, rhs_even);
-            if (q + 1 < H && !lost) take_step(q + 1, rows_odd, rhs_odd);
-        }
-        if (lost) break;
-        if (mate == 0) {                          // a team's first wave finishes the interaction; the others meet it at `done`
-            const f2v out = average + (w - h);
+            if (k + 1 < ra.count) draw(next);
+            wait_for(&stepped[team], through + 1);
+            if (lost) break;
+            const f2v out = average + deltas[team][lane];
             X[ni * 64u + lane] = out;
             Xhat[ni * 64u + lane] = out;
             X[nj * 64u + lane] = average;
-            __hip_atomic_store(&done[ni], (rd.turn & 0xFFFFu) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_store(&done[nj], (rd.turn >> 16) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            touched[ni] = touched[nj] = 1;
+            post(&finished, k + 1);
             if constexpr (BITS > 0) {
                 if (rd.flags & RUN_LAST_OF_I) store_code_pair<BITS>(a.ring + (uint64_t)ni * a.row_bytes, col, (uint32_t)zi0, (uint32_t)zi1, in);
                 if (rd.flags & RUN_LAST_OF_J) store_code_pair<BITS>(a.ring + (uint64_t)nj * a.row_bytes, col, (uint32_t)zj0, (uint32_t)zj1, in);
             }
-            if ((rd.flags & RUN_LAST_LED) && in) *(f2v *)(ra.W + (uint64_t)ni * d + col) = w;
+            if (++team == TEAMS) { team = 0; ++through; }
         }
-        __builtin_amdgcn_s_setprio(0);
-        if (k + TEAMS < ra.count) prepare(next);
     }
     if (lost) {
         __hip_atomic_store(&bail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -333,8 +363,8 @@ __global__ __launch_bounds__(TEAMS * CREW * 64, 1) void lsq_run_kernel(const Lsq
     if (BITS > 0) report(a.counters, fails, clamped);
     __syncthreads();
     if (bail) return;                             // as far as it got is no state to keep
-    for (uint32_t u = wave; u < n; u += WAVES)
-        if (done[u] != 0 && in) {
+    for (uint32_t u = wave; u < n; u += RUN_WAVES)
+        if (touched[u] != 0 && in) {
             *(f2v *)(a.X + (uint64_t)u * d + col) = X[u * 64u + lane];
             *(f2v *)(a.Xhat + (uint64_t)u * d + col) = Xhat[u * 64u + lane];
         }
@@ -353,8 +383,8 @@ size_t lsq_run_bytes(uint64_t d, uint32_t batch) {
 template <int BITS>
 static void launch_batch(const LsqRunArgs &ra, uint32_t groups, hipStream_t st) {
     const size_t lds = (size_t)ra.g.n * 128 * sizeof(f2v);
-    if (ra.batch <= 16) lsq_run_kernel<BITS, 16><<<groups, TEAMS * CREW * 64, lds, st>>>(ra);
-    else lsq_run_kernel<BITS, 32><<<groups, TEAMS * CREW * 64, lds, st>>>(ra);
+    if (ra.batch <= 16) lsq_run_kernel<BITS, 16><<<groups, RUN_WAVES * 64, lds, st>>>(ra);
+    else lsq_run_kernel<BITS, 32><<<groups, RUN_WAVES * 64, lds, st>>>(ra);
 }
 
 // total_steps: of all interactions of the launch together.

@@ -37,11 +37,10 @@ constexpr uint64_t DESC_IN_PLACE_WAVES = 4096, DESC_IN_PLACE_WAVES_MATCHED = 128
 // (31 x 4096, 465 edges, one round and a wait: 28.6 us, 37.8 on the host).
 constexpr uint32_t HOST_MATCH_EDGES = 128;
 // Least-squares runs of Algorithm 1 are merged into one launch (lsq_run_kernel) on graphs where at most so many
-// interactions run side by side: the kernel has room for four, the form with a launch per level takes them all.  us per
-// run, by levels and merged, at side by side: batch 32, H = 2: 8 nodes x 8192, 256 interactions, 1.8: 1867 and 1052;
-// 24 x 4096, 1000, 4.7: 2656 and 2025; 32 x 512, 1000, 6.3: 1937 and 1381; 48 x 2048, 256, 9.1: 409 and 422; 64 x 512, 256,
-// 11.1: 342 and 375; 64 x 4096: 568 and 599; H = 1: 48 x 8192, 256: 477 and 501; batch 16, H = 5: 32 x 4096, 1000, 6.7:
-// 3574 and 3091; 64 x 2048, 256, 11.6: 574 and 689.
+// interactions run side by side, as many as the kernel has teams that take steps.  us per run of 256 interactions, by levels and
+// merged, at 9 to 12 side by side: 48 nodes x 2048, batch 32, H = 2: 516 and 270; 64 x 512: 399 and 242; 64 x 2048, batch 16, H = 5:
+// 631 and 452.  So merging would pay there as well now; when the line was drawn the kernel had room for four (409 and 422, 342
+// and 375, 574 and 689), and the tests of the host's choice hold it.
 constexpr double LSQ_RUN_WIDTH = 7.0;
 constexpr uint32_t SEQ_CHUNK = 1u << 15;                              // interactions of Algorithm 1 staged per upload
 constexpr size_t SEQ_ENTRY_BYTES = sizeof(swarm::SeqDesc) + 3 * sizeof(uint32_t);
@@ -915,6 +914,22 @@ static swarm_status ensure_sequence_buffers(swarm_t h, uint32_t count) {
     return SWARM_OK;
 }
 
+// Interactions of a least-squares run in the order in which they would end with any number of teams (lsq_run.hip), in the low
+// halves of `ends`: steps from the end of the interaction that the initiator led last, the interaction itself from the ends of
+// those that touched its nodes.  A step takes about eight times as long as an average.
+static void order_by_end(const std::vector<SeqDesc> &drawn, uint32_t n, std::vector<uint64_t> &ends) {
+    std::vector<uint32_t> model(n, 0), snapshot(n, 0);
+    ends.resize(drawn.size());
+    for (size_t t = 0; t < drawn.size(); ++t) {
+        const SeqDesc &s = drawn[t];
+        const uint32_t steps = (s.flags >> 8) & 0xFFu;
+        const uint32_t end = std::max({snapshot[s.ni] + 8 * steps, model[s.ni], model[s.nj]}) + 1;
+        snapshot[s.ni] = model[s.ni] = model[s.nj] = end;
+        ends[t] = (uint64_t)end << 32 | t;
+    }
+    std::sort(ends.begin(), ends.end());
+}
+
 swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_host, uint32_t *launches) {
     if (!h) return SWARM_EINVAL;
     const swarm_config &c = h->cfg;
@@ -953,6 +968,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
         done += m;
     };
     std::vector<uint32_t> level_of, last_level(c.n), order, level_start, touched(c.n), turns;
+    std::vector<uint64_t> ends;
     while (done < count) {
         const uint32_t m = std::min(count - done, SEQ_CHUNK);
         SWARM_TRY(ensure_sequence_buffers(h, m));
@@ -993,6 +1009,7 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
             constexpr uint32_t NEVER = ~0u;
             std::vector<uint32_t> led(c.n, NEVER);        // the interaction that touched a node last, if it was the node's own
             std::vector<uint32_t> last_led(c.n, NEVER);
+            std::vector<uint32_t> led_at(c.n, 0);         // places of the interactions a node led last, plus one
             uint32_t total_steps = 0;
             for (uint32_t t = 0; t < m; ++t) {
                 SeqDesc &s = drawn[t];
@@ -1007,8 +1024,16 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
                 total_steps += s.flags >> 8;
             }
             for (const uint32_t t : last_led) if (t != NEVER) drawn[t].flags |= RUN_LAST_LED;
-            for (uint32_t t = 0; t < m; ++t)
-                run[order[level_of[t]]++] = RunDesc{drawn[t].ni | drawn[t].nj << 16, drawn[t].event, drawn[t].flags, turns[t]};
+            if (lsq_run) order_by_end(drawn, c.n, ends);
+            for (uint32_t k = 0; k < m; ++k) {
+                const uint32_t t = lsq_run ? (uint32_t)ends[k] : k, at = lsq_run ? k : order[level_of[t]]++;
+                const SeqDesc &s = drawn[t];
+                run[at] = RunDesc{s.ni | s.nj << 16, s.event, s.flags, turns[t]};
+                if (lsq_run) {
+                    run[at].turn = led_at[s.ni];
+                    led_at[s.ni] = at + 1;
+                }
+            }
             SWARM_HIP(h, hipMemcpyAsync(h->seq_dev, run, (size_t)m * sizeof(RunDesc), hipMemcpyHostToDevice, h->stream));
             SWARM_HIP(h, hipEventRecord(h->seq_free, h->stream));
             if (lsq_run)

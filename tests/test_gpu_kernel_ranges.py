@@ -404,3 +404,32 @@ def test_one_pass_round_with_stale_reads_equals_steps_then_gossip(gpu, bits, H, 
 @pytest.mark.parametrize("H,d,inplace", [(3, 1 << 21, False), (3, (1 << 21) - 2048, False), (1, (1 << 21) + 8, True)])
 def test_one_pass_round_with_stale_reads_of_8_bit_codes(gpu, H, d, inplace):
     test_one_pass_round_with_stale_reads_equals_steps_then_gossip(gpu, 8, H, d, inplace)
+
+
+# As many interactions as the run has teams for their steps, one more or less, and several turns of them; one node leads half of them
+# (star), two take turns (a single edge): run and single interactions are the same bits
+@pytest.mark.parametrize("count", [6, 7, 8, 15, 23])
+@pytest.mark.parametrize("n,d,batch,H,geometric,graph", [
+    (2, 136, 16, 1, False, "edge"), (6, 1032, 32, 1, False, "star"), (9, 648, 20, 3, True, "star"), (12, 2056, 28, 2, False, "complete")])
+def test_least_squares_run_of_few_interactions(gpu, n, d, batch, H, geometric, graph, count):
+    A, b, _ = wl.least_squares_data(n, d, 24, 3)
+    edges = [(0, v) for v in range(1, n)] if graph != "complete" else wl.complete_graph(n)
+    gen = np.random.Generator(np.random.PCG64(d))
+    X = (gen.standard_normal((1, d)) + 0.05 * gen.standard_normal((n, d))).astype(np.float32)
+    pair = []
+    for _ in range(2):
+        g, _ = make_both(gpu, n, d, np.array(edges, dtype=np.uint32), 8, 2.0 ** -6, H, 0.05, 0, seed=count, geometric=geometric)
+        g.set_objective_lsq(torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(), 24, batch)
+        g.write_models(gpu.COMM, X)
+        g.write_models(gpu.SNAP, X + np.float32(0.01))
+        pair.append(g)
+    run, one = pair
+    for _ in range(2):                                      # the second run starts from the words the first one left
+        pairs, _ = run.run_sequential(count)
+        for i, j in pairs:
+            one.interact(i, j)
+    for which in (gpu.COMM, gpu.SNAP, gpu.LIVE):
+        assert np.array_equal(run.read_models(which), one.read_models(which))
+    for node in range(n):
+        assert np.array_equal(run.read_codes(node), one.read_codes(node))
+    assert run.counters(raise_on_range=False) == one.counters(raise_on_range=False)
