@@ -4,14 +4,16 @@
 // run on its own.  One workgroup per tile keeps the tile of all n models in local memory (1 or 2 KiB per node) from
 // the first interaction to the last; its waves take the interactions in turn, in an order in which every interaction comes
 // after the earlier ones that touch its nodes, and a wave waits for those by the number of interactions each of its two
-// nodes has been through.  (Same arithmetic as interact_tile, same results bit for bit.)
+// nodes has been through: the local steps for the last interaction that the initiator led, which made its snapshot, the rest
+// for the last ones of both.  (Same arithmetic as interact_tile, same results bit for bit.)
 // An interaction reads what is not in local memory -- a_i, c_i and, unless the initiator's last interaction was its
-// own, the snapshot -- and writes the snapshot unless the next interaction of the node writes it again.
-// Bound by vector instructions (408 counted per interaction and 256 coordinates at H = 3) and by the chain of dependent
-// interactions: 64 nodes x 2^20, H = 3, 8-bit codes, 256 interactions on a complete graph take 780 us, against 1636 us for 28
-// launches that moved 34 B per interaction-coordinate at 5.6 TB/s; 16 nodes x 300 000, 200 interactions 302 us
-// against 1511; 8 nodes x 8888, 64 interactions 55 us against 249.  (Steps on the way, the first: nothing requested ahead of
-// the wait, every snapshot read and written 1046 us; non-temporal accesses to objective data and snapshots, 512-coordinate tiles 902.)
+// own, the snapshot -- and writes the snapshot unless the next interaction of the node writes it again.  Where tiles are few
+// (AHEAD), snapshots are held in local memory too, and the noise of the first four steps is drawn ahead of the wait.
+// Bound by vector instructions (408 counted per interaction and 256 coordinates at H = 3) and, with few tiles, by the chain of
+// dependent interactions.  On complete graphs with 8-bit codes, steps that waited for both nodes and steps that wait for the
+// snapshot: 64 nodes x 2^20, H = 3, 256 interactions 784 and 759 us (1636 in 28 launches that moved 34 B per
+// interaction-coordinate at 5.6 TB/s), 31 x 2 000 000, H = 5, 100 interactions 745 and 693; and with few tiles 8 x 8888, H = 3,
+// 64 interactions 53.8, 42.2 and with AHEAD 33.6, 9 x 20 000, H = 3, 128 interactions 90.3, 71.1 and 53.4.
 // The wait always ends: the waves of a workgroup are resident together, and the earliest interaction that is not
 // finished waits for none.
 #include <algorithm>
@@ -43,27 +45,31 @@ __device__ __forceinline__ RowWords<F> row_words(uint64_t seed, uint32_t ni, uin
 __device__ __forceinline__ f4 ldg(const float *row, uint32_t off) { return *(SWARM_GLOBAL const f4 *)at_bytes(uniform(row), 4u * off); }
 __device__ __forceinline__ void stg(float *row, uint32_t off, f4 v) { *(SWARM_GLOBAL f4 *)at_bytes(uniform(row), 4u * off) = v; }
 
-// H local steps of the lane's F float4 (diag_steps).  F = 1: the even lane of a pair draws for step q, the odd lane for
+// Gradient noise of steps q and q + 1 for a tile of 256 coordinates: the even lane of a pair draws for step q, the odd lane for
 // step q + 1, and the exchange leaves each lane with its words of both steps.
+__device__ __forceinline__ void two_noises(f4 &n0, f4 &n1, uint32_t q, uint32_t node, uint64_t tile, uint32_t lane, float scale,
+                                           uint64_t seed, uint32_t event) {
+    const LaneRandom r = pair_words(stream(seed, TAG_NOISE, q + (lane & 1u), node, event, tile * 32 + (lane >> 1)));
+    float z0, z1, z2, z3;
+    box_muller16(r.a0, scale, z0, z1);
+    box_muller16(r.a1, scale, z2, z3);
+    n0 = f4{z0, z1, z2, z3};
+    box_muller16(r.b0, scale, z0, z1);
+    box_muller16(r.b1, scale, z2, z3);
+    n1 = f4{z0, z1, z2, z3};
+}
+__device__ __forceinline__ float noise_scale(float sigma) { return -1.3862943611198906f * sigma * sigma; }     // -2 ln 2 sigma^2
+
+// Local steps q .. H - 1 of the lane's F float4 (diag_steps; F = 2: from the first).
 template <bool NOISE, int F>
 __device__ __forceinline__ void run_steps(f4 w[F], const f4 a[F], const f4 c[F], uint32_t node, uint64_t tile, uint32_t lane,
-                                          uint32_t H, float lr, float sigma, uint64_t seed, uint32_t event) {
+                                          uint32_t q, uint32_t H, float lr, float sigma, uint64_t seed, uint32_t event) {
     if constexpr (F == 2) {
         diag_steps<NOISE>(w[0], w[1], a[0], a[1], c[0], c[1], node, tile, lane, H, lr, sigma, seed, event);
     } else {
-        const float scale = -1.3862943611198906f * sigma * sigma;     // -2 ln 2 sigma^2
-        for (uint32_t q = 0; q < H; q += 2) {
+        for (; q < H; q += 2) {
             f4 n0 = {0.f, 0.f, 0.f, 0.f}, n1 = n0;
-            if (NOISE) {
-                const LaneRandom r = pair_words(stream(seed, TAG_NOISE, q + (lane & 1u), node, event, tile * 32 + (lane >> 1)));
-                float z0, z1, z2, z3;
-                box_muller16(r.a0, scale, z0, z1);
-                box_muller16(r.a1, scale, z2, z3);
-                n0 = f4{z0, z1, z2, z3};
-                box_muller16(r.b0, scale, z0, z1);
-                box_muller16(r.b1, scale, z2, z3);
-                n1 = f4{z0, z1, z2, z3};
-            }
+            if (NOISE) two_noises(n0, n1, q, node, tile, lane, noise_scale(sigma), seed, event);
             w[0] = diag_update(w[0], a[0], c[0], n0, lr);
             if (q + 1 < H) w[0] = diag_update(w[0], a[0], c[0], n1, lr);
         }
@@ -73,10 +79,11 @@ __device__ __forceinline__ void run_steps(f4 w[F], const f4 a[F], const f4 c[F],
 // LOCAL: 0 = the pending update is W_i - Xhat_i where the descriptor says so; 1 / 2 = local steps of the diagonal
 // objective in registers, with / without gradient noise.  RW: waves per workgroup.  F: float4 per lane, a tile has 256 F
 // coordinates.
-template <int BITS, int LOCAL, int RW, int F>
-__global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(const RunArgs ra) {
+template <int BITS, int LOCAL, int RW, int F, bool AHEAD>
+__global__ __launch_bounds__(RW * 64, F == 2 || AHEAD ? 4 : 7) void interact_run_kernel(const RunArgs ra) {
     constexpr uint32_t COORDS = 256 * F, ROW = 64 * F;           // of a tile: coordinates, float4
-    extern __shared__ f4 rows[];                  // n x COORDS floats
+    constexpr int EARLY = AHEAD && LOCAL == 1 ? 4 : 0;           // steps whose noise is drawn ahead of the wait
+    extern __shared__ f4 rows[];                  // n x COORDS floats; AHEAD: then the snapshots
     __shared__ uint32_t done[RUN_MAX_NODES];      // interactions each node has been through
     const GossipArgs &a = ra.g;
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -91,17 +98,19 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
     }
     for (uint32_t u = threadIdx.x; u < a.n; u += RW * 64) done[u] = 0;
     constexpr int AT_ONCE = 8 / F;                // rows in flight per wave
-    for (uint32_t u0 = wave; u0 < a.n; u0 += AT_ONCE * RW) {
+    const uint32_t all = AHEAD ? 2 * a.n : a.n;
+    auto row_of = [&](uint32_t u) { return u < a.n ? a.X + (uint64_t)u * a.d + base : a.Xhat + (uint64_t)(u - a.n) * a.d + base; };
+    for (uint32_t u0 = wave; u0 < all; u0 += AT_ONCE * RW) {
         f4 v[AT_ONCE][F];
 #pragma unroll
         for (int i = 0; i < AT_ONCE; ++i) {
-            const float *x = a.X + (uint64_t)min(u0 + i * RW, a.n - 1) * a.d + base;
+            const float *x = row_of(min(u0 + i * RW, all - 1));
 #pragma unroll
             for (int f = 0; f < F; ++f) v[i][f] = ldg_nt(x, from[f]);
         }
 #pragma unroll
         for (int i = 0; i < AT_ONCE; ++i)
-            if (u0 + i * RW < a.n) {
+            if (u0 + i * RW < all) {
 #pragma unroll
                 for (int f = 0; f < F; ++f) rows[(u0 + i * RW) * ROW + lane + 64 * f] = v[i][f];
             }
@@ -121,6 +130,7 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
         for (int f = 0; f < F; ++f) { oa[f] = ldg(ra.A + at, from[f]); oc[f] = ldg(ra.C + at, from[f]); }
     };
     if (LOCAL && wave < ra.count) fetch_objective(next.nodes & 0xFFFFu);
+    auto through = [&](uint32_t node) { return first_lane(__hip_atomic_load(&done[node], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)); };
     for (uint32_t k = wave; k < ra.count; k += RW) {
         const RunDesc rd = next;
         next = run_desc(ra.descs, k + RW, ra.count);
@@ -128,19 +138,25 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
         const uint64_t at = (uint64_t)ni * a.d + base;
         RowWords<F> words{};
         if (BITS > 0) words = row_words<F>(a.seed, ni, nj, event, tile, lane);
-        while ((first_lane(__hip_atomic_load(&done[ni], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) ^ (turn & 0xFFFFu)) |
-               (first_lane(__hip_atomic_load(&done[nj], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) ^ (turn >> 16)))
-            __builtin_amdgcn_s_sleep(1);
-        f4 *ri = rows + ni * ROW + lane, *rj = rows + nj * ROW + lane;
+        f4 *ri = rows + ni * ROW + lane, *rj = rows + nj * ROW + lane, *snap = ri + a.n * ROW;       // snap: AHEAD only
         float *hi = a.Xhat + at;
         f4 xi[F], xj[F], delta[F], average[F];
 #pragma unroll
-        for (int f = 0; f < F; ++f) { xi[f] = ri[64 * f]; xj[f] = rj[64 * f]; delta[f] = zero; }
-        if (LOCAL || (flags & SEQ_HAS_DELTA)) {
-            f4 h[F], w[F];
+        for (int f = 0; f < F; ++f) delta[f] = zero;
+        f4 early[EARLY + 1];
+        if constexpr (EARLY > 0) {
+            const uint32_t H = (flags >> 8) & 0xFFu;
 #pragma unroll
-            for (int f = 0; f < F; ++f) h[f] = xi[f];
-            if (!(flags & RUN_SNAPSHOT_IS_MODEL)) {
+            for (int q = 0; q < EARLY; q += 2)
+                if ((uint32_t)q < H) two_noises(early[q], early[q + 1], q, ni, tile, lane, noise_scale(ra.sigma), a.seed, event);
+        }
+        if (LOCAL || (flags & SEQ_HAS_DELTA)) {
+            while (through(ni) < flags >> RUN_READY_SHIFT) __builtin_amdgcn_s_sleep(1);       // the snapshot
+            f4 h[F], w[F];
+            if (AHEAD || (flags & RUN_SNAPSHOT_IS_MODEL)) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) h[f] = (AHEAD ? snap : ri)[64 * f];
+            } else {
 #pragma unroll
                 for (int f = 0; f < F; ++f) h[f] = ldg(hi, from[f]);
             }
@@ -151,7 +167,11 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
 #pragma unroll
                 for (int f = 0; f < F; ++f) { a0[f] = oa[f]; c0[f] = oc[f]; }
                 if (k + RW < ra.count) fetch_objective(next.nodes & 0xFFFFu);
-                run_steps<LOCAL == 1, F>(w, a0, c0, ni, tile, lane, (flags >> 8) & 0xFFu, ra.lr, ra.sigma, a.seed, event);
+                const uint32_t H = (flags >> 8) & 0xFFu;
+#pragma unroll
+                for (int q = 0; q < EARLY; ++q)
+                    if ((uint32_t)q < H) w[0] = diag_update(w[0], a0[0], c0[0], early[q], ra.lr);
+                run_steps<LOCAL == 1, F>(w, a0, c0, ni, tile, lane, EARLY, H, ra.lr, ra.sigma, a.seed, event);
             } else {
 #pragma unroll
                 for (int f = 0; f < F; ++f) w[f] = ldg_nt(a.W + at, from[f]);
@@ -159,6 +179,9 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
 #pragma unroll
             for (int f = 0; f < F; ++f) delta[f] = w[f] - h[f];
         }
+        while ((through(ni) ^ (turn & 0xFFFFu)) | (through(nj) ^ (turn >> 16))) __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+        for (int f = 0; f < F; ++f) { xi[f] = ri[64 * f]; xj[f] = rj[64 * f]; }
         if constexpr (BITS > 0) {
             const float half_eps = 0.5f * a.eps;
             uint64_t codes_i[F], codes_j[F];
@@ -189,7 +212,8 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
             const f4 o = average[f] + delta[f];
             ri[64 * f] = o;
             rj[64 * f] = average[f];
-            if (!(flags & RUN_SNAPSHOT_SHORT) && in[f]) stg(hi, to[f], o);
+            if (AHEAD) snap[64 * f] = o;
+            else if (!(flags & RUN_SNAPSHOT_SHORT) && in[f]) stg(hi, to[f], o);
         }
         __hip_atomic_store(&done[ni], (turn & 0xFFFFu) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);   // every lane:
         __hip_atomic_store(&done[nj], (turn >> 16) + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);       // no branch
@@ -202,36 +226,51 @@ __global__ __launch_bounds__(RW * 64, F == 2 ? 4 : 7) void interact_run_kernel(c
 #pragma unroll
             for (int f = 0; f < F; ++f)
                 if (in[f]) stg_nt(x, to[f], rows[u * ROW + lane + 64 * f]);
+            if constexpr (AHEAD) {
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    if (in[f]) stg_nt(a.Xhat + (uint64_t)u * a.d + base, to[f], rows[(a.n + u) * ROW + lane + 64 * f]);
+            }
         }
 }
 
-template <int BITS, int LOCAL, int RW, int F>
+template <int BITS, int LOCAL, int RW, int F, bool AHEAD = false>
 static void launch_tiles(const RunArgs &ra, hipStream_t st) {
     const dim3 grid((unsigned)((ra.g.d + 256 * F - 1) / (256 * F)));
-    interact_run_kernel<BITS, LOCAL, RW, F><<<grid, RW * 64, (size_t)ra.g.n * 256 * F * sizeof(float), st>>>(ra);
+    interact_run_kernel<BITS, LOCAL, RW, F, AHEAD><<<grid, RW * 64, (size_t)ra.g.n * 256 * F * (AHEAD ? 2 : 1) * sizeof(float), st>>>(ra);
 }
 
-// Waves per workgroup and size of its tile, by the number of nodes (how many interactions can run side by side, about n / 7,
-// and how much local memory a tile takes) and by whether there are tiles enough to fill the chip.  512-coordinate tiles
-// (F = 2) issue the fewest instructions, 256-coordinate ones leave room for more workgroups per compute unit and finish an
-// interaction sooner.  us per run, F = 2 with 2, 4, 8, 16 waves (n to 9, 19, 39, 78) and F = 1 with 4, 4, 8, 12:
-//   8 x 2^20, 128 interactions, H = 3       433   488       32 x 500 000, 256, H = 3            400   423
-//   8 x 8888, 64, H = 3                      90    55       64 x 2^20, 256, H = 3               989   942
-//   16 x 300 000, 200, geometric H = 5      356   302       64 x 4 000 000, 256, geometric 5   4442  3842
-// Where the tiles become many enough, 128 interactions, F = 1 and F = 2:
-//   8 x 262 144   159   214     8 x 393 216   202   218     8 x 524 288   255   233
-//   31 x 131 072   74    77     31 x 196 608   95   112     31 x 262 144   125   118
-// The sizes between were measured against one launch per level only (10, 12, 15, 19, 20, 24, 39, 40, 48 and 78 nodes, complete
-// graphs, rings and paths: interact_run_pays), not against the other forms.
-constexpr uint64_t few_coords(uint32_t n) { return n <= 9 ? 1u << 19 : 1u << 18; }
-
-struct TileForm { uint32_t waves, f; };
+// Waves per workgroup, size of its tile and whether noise and snapshots are held ahead, by the number of nodes (how many
+// interactions can run side by side, and how much local memory a tile takes) and of tiles.  512-coordinate tiles (F = 2) issue
+// the fewest instructions, 256-coordinate ones leave room for more workgroups per compute unit and finish an interaction
+// sooner.  With one or two workgroups per compute unit the chain of interactions is what takes the time, and a wave that has
+// drawn its noise and finds the snapshot in local memory shortens it; with more, the waves that this leaves out are
+// missed.  us per run, H = 3:  waves, F, A where ahead
+//   d, interactions            4,1   8,1  12,1   2,2   4,2 |  4,1A  8,1A 12,1A 16,1A
+//   n =  8,     8 888,  64      43    41    42    85    57 |    36    34    35    35
+//            131 072, 128       89    91    96   158   104 |    77    75   110   112
+//            262 144, 128      126   153   178   211   134 |   116   138   213   217
+//          1 200 000, 128      428   586   769   484   446 |   431   586
+//          2 400 000, 128      791  1114  1477   802   809 |   811  1120
+//          3 200 000, 100      818  1156         793   824 |   834  1165
+//   n = 16,   20 000, 200       94    73    73   236   129 |    82    63    62    62
+//            131 072, 200      112   103   107   239   129 |   106    94   118   119
+//            200 000, 200      169   173   195   327   176 |   168   171   228   231
+//            400 000, 200      256   277   326   340   280 |   270   286   397   401
+//          1 600 000, 100      410   482         639   415 |   443   505
+//          4 000 000, 100     1002  1172  1436  1430   958 |  1063  1241
+//   n = 31,   65 536, 200       92    61    58   241   125 |    84    60    56    54
+//            131 072, 200      115    93    92   247   129 |   111    96   108   105
+//   n = 64,   65 536, 256      121    79    68   319   163 |   110    80    73    70
+// For 20 to 39 nodes 8 waves, F = 2 and 1: 32 x 500 000, 256 interactions: 349 and 357, 31 x 196 608, 128: 112 and 95.  The line between
+// these two was not measured again since steps are taken ahead of the wait for both nodes.
+struct TileForm { uint32_t waves, f; bool ahead; };
 static TileForm tile_form(uint32_t n, uint64_t d) {
-    const bool few = d < few_coords(n);
-    if (n <= 9 && !few) return {2, 2};
-    if (n <= 19) return {4, 1};
-    if (n <= 39) return {8, few ? 1u : 2u};
-    return {12, 1};
+    constexpr uint64_t MANY = 5u << 19;           // coordinates
+    if (n <= 9) return d <= 1u << 17 ? TileForm{8, 1, true} : d < 1u << 19 ? TileForm{4, 1, true} : d < MANY ? TileForm{4, 1, false} : TileForm{2, 2, false};
+    if (n <= 19) return d <= 1u << 17 ? TileForm{8, 1, true} : d <= 3u << 16 ? TileForm{4, 1, true} : d < MANY ? TileForm{4, 1, false} : TileForm{4, 2, false};
+    if (n <= 39) return d <= 1u << 16 ? TileForm{16, 1, true} : TileForm{8, d < 1u << 18 ? 1u : 2u, false};
+    return {12, 1, false};
 }
 
 // Whether one launch is sooner done with m interactions that form so many dependency levels than a launch per level.
@@ -251,7 +290,8 @@ static TileForm tile_form(uint32_t n, uint64_t d) {
 bool interact_run_pays(uint64_t d, uint32_t n, uint32_t H, uint32_t m, uint32_t levels) {
     if (n > RUN_MAX_NODES || levels <= 1 || 8 * (uint64_t)m < 3 * (uint64_t)n) return false;
     if (d < 3u << 17) return true;
-    const TileForm form = tile_form(n, d);
+    // waves and tiles as they were when the line was drawn, with steps that waited for both nodes
+    const TileForm form = n <= 9 && d >= 1u << 19 ? TileForm{2, 2, false} : n <= 19 ? TileForm{4, 1, false} : tile_form(n, d);
     const uint32_t by_memory = 160u / (n * form.f + 1), by_waves = (form.f == 2 ? 16u : 28u) / form.waves;
     const double side_by_side = std::min((double)m / levels, (double)form.waves);
     const double need = std::min(std::max(1.4 * H, 5.0), 14.0);
@@ -261,7 +301,12 @@ bool interact_run_pays(uint64_t d, uint32_t n, uint32_t H, uint32_t m, uint32_t 
 template <int BITS, int LOCAL>
 static void launch_waves(const RunArgs &ra, hipStream_t st) {
     const TileForm form = tile_form(ra.g.n, ra.g.d);
-    if (form.waves == 2) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
+    if (form.ahead) {
+        if (form.waves == 4) launch_tiles<BITS, LOCAL, 4, 1, true>(ra, st);
+        else if (form.waves == 8) launch_tiles<BITS, LOCAL, 8, 1, true>(ra, st);
+        else launch_tiles<BITS, LOCAL, 16, 1, true>(ra, st);
+    } else if (form.waves == 2) launch_tiles<BITS, LOCAL, 2, 2>(ra, st);
+    else if (form.waves == 4 && form.f == 2) launch_tiles<BITS, LOCAL, 4, 2>(ra, st);
     else if (form.waves == 4) launch_tiles<BITS, LOCAL, 4, 1>(ra, st);
     else if (form.waves == 12) launch_tiles<BITS, LOCAL, 12, 1>(ra, st);
     else if (form.f == 2) launch_tiles<BITS, LOCAL, 8, 2>(ra, st);

@@ -16,6 +16,7 @@ constexpr uint32_t RUN_LAST_OF_I = 2u, RUN_LAST_OF_J = 4u;        // no later in
 constexpr uint32_t RUN_SNAPSHOT_IS_MODEL = 8u;    // the node's interaction before this one was its own: Xhat_i = X_i
 constexpr uint32_t RUN_SNAPSHOT_SHORT = 16u;      // so is the next one that touches it: nobody reads the snapshot
 constexpr uint32_t RUN_LAST_LED = 32u;            // no later interaction of the run is the initiator's own
+constexpr uint32_t RUN_READY_SHIFT = 16;          // bits 16-31: how many of the run's interactions the initiator has been through when its snapshot is there
 constexpr uint32_t RUN_MAX_NODES = 78;            // two tiles of 256 coordinates (1 KiB per node) per compute unit of 160 KiB
 
 #if defined(__HIPCC__)

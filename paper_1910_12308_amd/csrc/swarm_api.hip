@@ -1019,9 +1019,10 @@ swarm_status swarm_run_sequential(swarm_t h, uint32_t count, uint32_t *pairs_hos
                     s.flags |= RUN_SNAPSHOT_IS_MODEL;
                     drawn[led[s.ni]].flags |= RUN_SNAPSHOT_SHORT;
                 }
+                total_steps += s.flags >> 8;
+                if (last_led[s.ni] != NEVER) s.flags |= ((turns[last_led[s.ni]] & 0xFFFFu) + 1) << RUN_READY_SHIFT;
                 led[s.ni] = last_led[s.ni] = t;
                 led[s.nj] = NEVER;
-                total_steps += s.flags >> 8;
             }
             for (const uint32_t t : last_led) if (t != NEVER) drawn[t].flags |= RUN_LAST_LED;
             if (lsq_run) order_by_end(drawn, c.n, ends);

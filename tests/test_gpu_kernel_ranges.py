@@ -433,3 +433,13 @@ def test_least_squares_run_of_few_interactions(gpu, n, d, batch, H, geometric, g
     for node in range(n):
         assert np.array_equal(run.read_codes(node), one.read_codes(node))
     assert run.counters(raise_on_range=False) == one.counters(raise_on_range=False)
+
+
+# The forms of a run of Algorithm 1 that the sizes above leave out: four waves with noise and snapshots held ahead, their largest
+# tiles, and from 5 x 2^19 coordinates on 512-coordinate tiles of two and four waves; up to four steps' noise is drawn ahead
+@pytest.mark.parametrize("n,d,bits,H,sigma,geometric", [
+    (9, 1 << 17, 8, 4, 0.1, False), (4, (1 << 17) + 8, 8, 3, 0.1, True), (8, (1 << 19) - 8, 4, 6, 0.05, False), (12, 3 << 16, 16, 5, 0.1, True),
+    (3, 5 << 19, 8, 3, 0.1, False), (10, (5 << 19) + 8, 4, 2, 0.1, True), (39, 1 << 16, 8, 2, 0.0, False), (20, (1 << 16) + 8, 2, 5, 0.1, False),
+    (2, 8, 8, 9, 0.1, False), (6, 264, 0, 255, 0.1, False)])
+def test_run_of_algorithm1_by_its_forms(gpu, n, d, bits, H, sigma, geometric):
+    test_run_of_algorithm1_in_one_launch(gpu, n, d, bits, H, sigma, geometric, True)
