@@ -443,3 +443,25 @@ def test_least_squares_run_of_few_interactions(gpu, n, d, batch, H, geometric, g
     (2, 8, 8, 9, 0.1, False), (6, 264, 0, 255, 0.1, False)])
 def test_run_of_algorithm1_by_its_forms(gpu, n, d, bits, H, sigma, geometric):
     test_run_of_algorithm1_in_one_launch(gpu, n, d, bits, H, sigma, geometric, True)
+
+
+# Logits in float32 cut along the hidden units: 14 parts and a shorter one, parts as wide as the row of classes allows (two), the most
+# classes that are cut and more; tiles of 32 rows (batch 32 and 96), biases beside the updates.  The same bits whoever steps along.
+@pytest.mark.parametrize("n,n_in,n_hid,n_out,batch", [
+    (3, 64, 1056, 32, 32), (2, 96, 1120, 96, 96), (5, 32, 2080, 64, 128), (2, 32, 4096, 2048, 32), (2, 64, 2144, 2080, 64),
+    (4, 64, 672, 160, 160), (130, 64, 128, 32, 96), (2, 544, 64, 32, 64)])
+def test_mlp_logits_in_parts(gpu, n, n_in, n_hid, n_out, batch):
+    test_mlp_tiles(gpu, n, n_in, n_hid, n_out, batch, "fp32")
+    d = n_hid * n_in + n_hid + n_out * n_hid + n_out
+    means, cdf = wl.mixture_data(n, n_in, n_out, 1)
+    s = gpu.Swarm(n, d, wl.complete_graph(n) if n < 16 else wl.random_regular_graph(n, 4, 0), 8, 2.0 ** -10, 2, 0.05, 0, n)
+    s.set_objective_mlp(n_in, n_hid, n_out, torch.from_numpy(means).cuda(), torch.from_numpy(cdf).cuda(), 0.5, batch)
+    X, W = s.models_view(gpu.COMM), s.models_view(gpu.LIVE)
+    X.copy_(torch.randn(n, d, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").mul_(0.1))
+    s.local_steps()
+    whole = W.clone()
+    for some in ([n - 1], [n - 1, 0]):
+        W.zero_()
+        s.local_steps(some)
+        assert torch.equal(W[some], whole[some])
+    s.close()
