@@ -38,6 +38,10 @@ swarm_status swarm_stream_copy(void *dst_dev, const void *src_dev, uint64_t nbyt
 swarm_status swarm_stream_mix(void *dst_dev, const void *src_dev, uint64_t stream_bytes, uint32_t n_read,
                               uint32_t n_write, void *hip_stream);
 
+/* Test aid: how long the workgroups of a team that takes least-squares steps together wait for one another before one of them
+ * takes the rest by itself, in ticks of 10 ns (2000000 when the objective is set). */
+swarm_status swarm_lsq_patience(swarm_t h, uint64_t ticks);
+
 #ifdef __cplusplus
 }
 #endif

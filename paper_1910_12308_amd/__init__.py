@@ -29,7 +29,7 @@ EXPORTS = ["swarm_init", "swarm_destroy", "swarm_set_objective_diag", "swarm_set
            "swarm_read_models", "swarm_write_models", "swarm_models_ptr", "swarm_read_codes",
            "swarm_state_bytes", "swarm_save_state", "swarm_load_state",
            "swarm_potential", "swarm_potential_static", "swarm_pair_linf", "swarm_scale", "swarm_prefix_stats", "swarm_counters", "swarm_timing_reset", "swarm_kernel_times",
-           "swarm_stream_copy", "swarm_stream_mix", "swarm_last_error"]
+           "swarm_stream_copy", "swarm_stream_mix", "swarm_lsq_patience", "swarm_last_error"]
 
 
 class SwarmError(RuntimeError):
@@ -86,6 +86,7 @@ def load_library():
         "swarm_prefix_stats": [vp, vp, P(u64)],
         "swarm_counters": [vp, P(u64), P(u64), P(u64), P(u64)],
         "swarm_timing_reset": [vp],
+        "swarm_lsq_patience": [vp, u64],
         "swarm_stream_copy": [vp, vp, u64, vp],
         "swarm_stream_mix": [vp, vp, u64, u32, u32, vp],
         "swarm_kernel_times": [vp, P(ctypes.c_double), P(u32), P(ctypes.c_double), P(u32)],
@@ -331,6 +332,10 @@ class Swarm:
             self._check(rc)
         return dict(rounds=vals[0].value, interactions=vals[1].value, bits_communicated=vals[2].value,
                     decode_failures=vals[3].value, range_clamped=(rc == ERANGE))
+
+    def lsq_patience(self, ticks):
+        """Test aid: ticks of 10 ns that workgroups taking least-squares steps together wait for one another."""
+        self._check(self._lib.swarm_lsq_patience(self._h, ticks))
 
     def timing_reset(self):
         self._check(self._lib.swarm_timing_reset(self._h))

@@ -9,7 +9,9 @@
 // (batch floats each) through device memory, each word tagged with the launch and step it belongs to, so a reader
 // simply waits until the word it needs carries the right tag (no counters, no fences, nothing to reset).  In a
 // batch of Algorithm 1 steps the workgroup then runs the interaction on its slice, which is exactly one gossip tile.
-// All other swarms take the wide form (lsq_wide_kernel), whose workgroups exchange their residuals between launches.
+// Of all other swarms, many nodes take the wide form (lsq_wide_kernel) with one workgroup per node, fewer take steps by teams of
+// workgroups (lsq_team.hip) or, where not even one node's workgroups fit the chip or the steps update the models themselves, the wide
+// form with several per node, which exchange their residuals between launches.
 #include <algorithm>
 #include <type_traits>
 
@@ -467,6 +469,7 @@ hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
         o.wide_slices = wide_slices(d, n);
         o.by_rows = o.wide_slices == 1 && lsq_by_rows(d, n, o.batch);
         o.wide_rows = (uint64_t)n * o.wide_slices;
+        if (o.wide_slices > 1 && (e = alloc_lsq_teams(o, d, n)) != hipSuccess) return e;
         return hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH);
     }
     const uint64_t slices = (d + SLICE - 1) / SLICE;
@@ -523,6 +526,8 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
         const hipError_t e = split_args(sa, base, W, o, slots, counters, d, H, lr, seed, event, st);
         if (e != hipSuccess) return e;
         lsq_split_kernel<0, false><<<dim3(sa.slices, count, 1), SW * 64, 0, st>>>(sa, InteractArgs{});
+    } else if (o.teams && base != W) {
+        return launch_lsq_teams(base, W, o, slots, counters, count, d, H, lr, seed, event, st);
     } else {
         LsqWideArgs wa{base, W, o.A, o.b, slots, o.wide_part, d, seed, o.wide_rows * LSQ_MAX_BATCH,
                        H, o.m_rows, o.batch, event, o.wide_slices, lr};
@@ -556,6 +561,7 @@ void free_lsq(LsqObjective &o) {
     if (o.part) (void)hipFree(o.part);
     if (o.run_part) (void)hipFree(o.run_part);
     if (o.wide_part) (void)hipFree(o.wide_part);
+    free_lsq_teams(o);
     o = LsqObjective{};
 }
 

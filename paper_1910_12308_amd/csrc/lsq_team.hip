@@ -1,0 +1,455 @@
+// Local SGD steps for least-squares objectives whose swarm has too many columns for a workgroup per slice (local_lsq.hip), by
+// teams: the workgroups of a team take one node after the other, each on its own columns, and keep a step's rows of A in
+// registers from the residuals to the update, so that these are read once.  Between the two the team's partial residuals are
+// added: a workgroup publishes one word per row of the batch, the team's reducing workgroups add these up, in an order that the
+// number of columns alone decides, and publish the totals.  While a workgroup waits for them the next step's rows are on
+// their way to it, and other teams' workgroups share its compute unit.
+// A word carries the number of the step it belongs to beside the value, so a reader simply waits until the word it needs is there.
+// A team's numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too).
+// Workgroups wait for one another, so a launch has no more than fit the chip at once, and such launches of several swarms on one GPU
+// take turns (device_turn).  Where other work keeps some of a team's workgroups from starting, the first of the others that has waited
+// long enough takes the rest of the team's nodes by itself, with the same sums, and the others end.
+#include <algorithm>
+#include <mutex>
+
+#include "internal.h"
+#include "lsq_wave.hpp"
+#include "objectives.h"
+#include "philox.hpp"
+#include "uniform_address.hpp"
+
+namespace swarm {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned long long Word;                  // tag << 32 | float bits
+constexpr int TEAM_WAVES = 4;
+constexpr int TEAM_THREADS = 64 * TEAM_WAVES;
+constexpr uint32_t REDUCE_WORDS = 8;              // words a thread of a reducing workgroup asks for at a time
+constexpr uint32_t COPIES = 8;                    // of a step's totals, read by every eighth workgroup each: all of them ask for the same lines
+constexpr unsigned long long START_TICKS = 200000000ull;    // 2 s of the 100 MHz wall clock
+
+// Of a team.  tag: number of the next launch's first step.  claim: first number of the launch << 32 | steps whose totals are known to be
+// out, set by the workgroup that ends the team's part of the launch.  started: workgroups of the launch that have begun.
+struct LsqTeamHead {
+    unsigned long long claim;
+    uint32_t tag, started;
+    uint32_t pad[28];         // a line each
+};
+
+struct LsqTeamArgs {
+    const float *base, *A, *b;
+    float *W;
+    LocalSlots slots;
+    LsqTeamHead *heads;
+    Word *words, *totals;     // [team][parity; 2: of a workgroup by itself][slice][LSQ_MAX_BATCH], [team][..][COPIES][LSQ_MAX_BATCH]
+    float *models;            // [team][d] model of a workgroup by itself between two steps
+    DeviceCounters *counters;
+    uint64_t d, seed;
+    unsigned long long patience;     // ticks of the 100 MHz clock
+    uint32_t count, teams, slices, reducers, rows_each, H, m_rows, batch, event;
+    float lr;
+};
+
+struct TeamItem { uint32_t slot, q, H, node, event; };
+
+__device__ __forceinline__ void store_word(SWARM_GLOBAL Word *p, uint32_t tag, float v) {
+    __hip_atomic_store(p, ((Word)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ Word load_word(SWARM_GLOBAL const Word *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// ROWS rows of the batch per wave (s = wave ROWS .. wave ROWS + ROWS - 1) of COLS blocks of 256 columns; FULL: the batch has
+// 4 ROWS rows.
+// Bound by the exchange and memory together: a step of one team is its loads and then about 5 us until the totals are back, hidden
+// behind the loads of the other teams on the chip.  Hence as few registers as five workgroups per compute unit take (with four 16 nodes
+// x 65544 columns, batch 64, two steps take 140 us, with two buffers of rows and three workgroups 154), the first rows asked for
+// after the team's number (before, they delay it: 134), totals in copies (one for all: 190).  us for the steps of all nodes, before (rows
+// read twice, a launch per step) and now: 16 x 65544, batch 64, H = 2: 189 and 126 (4.3 TB/s of rows read once); 64 x 131072, 64, 1: 709
+// and 513; 9 x 131072, 64, 4: 432 and 285; 8 x 32768, 64, 2: 46.3 and 28.7; 31 x 16384, 32, 3: 68.5 and 34.7; 100 x 12288, 64, 2: 158 and 82;
+// 64 x 4104, 16, 1: 9.0 and 8.8; 16 x 16384, 16, 1: 8.8 and 7.7.  Error against 64 bits as before (3.6e-8).
+template <int ROWS, int COLS, bool FULL>
+__global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kernel(const LsqTeamArgs sa) {
+    __shared__ f4 gsum[2][TEAM_WAVES][64 * COLS];
+    __shared__ float red[2][TEAM_WAVES][LSQ_MAX_BATCH];
+    __shared__ float resid[2][LSQ_MAX_BATCH];
+    __shared__ uint32_t rows_of[2][LSQ_MAX_BATCH];
+    __shared__ uint32_t quit;                      // the step that was given up
+    __shared__ unsigned long long head_claim;
+    __shared__ uint32_t head_tag;
+    constexpr uint32_t WIDTH = 256 * COLS;
+    uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t batch = sa.batch, first_row = ROWS * wave, G = sa.slices, all = G + sa.reducers;
+    const uint64_t d = sa.d;
+    const float step = sa.lr * ((float)sa.m_rows / (float)batch);
+    // neighbours of a team on one die: workgroups go round the eight dies
+    const uint32_t die = blockIdx.x & 7u, spare = gridDim.x & 7u;
+    const uint32_t id = die * (gridDim.x >> 3) + min(die, spare) + (blockIdx.x >> 3);
+    const uint32_t team = id / all, member = id - team * all;
+    auto find = [&](TeamItem &it, uint32_t slot) {          // the next of the team's slots that takes steps
+        for (; slot < sa.count; slot += sa.teams) {
+            it.slot = slot; it.q = 0;
+            it.H = sa.slots.steps ? sa.slots.steps[slot] : sa.H;
+            it.node = sa.slots.nodes ? sa.slots.nodes[slot] : slot;
+            it.event = sa.slots.events ? sa.slots.events[slot] : sa.event;
+            if (it.H > 0) return true;
+        }
+        it.slot = slot;
+        return false;
+    };
+    auto advance = [&](TeamItem &it) { return ++it.q < it.H || find(it, it.slot + sa.teams); };
+    TeamItem it{};
+    if (!find(it, team)) return;
+    LsqTeamHead *head = sa.heads + team;
+    uint32_t first_tag = 0, tag = 0;
+    unsigned long long patience = sa.patience;
+    bool alone = false;
+    // A wave that has waited long enough: go on waiting where the totals are known to come, else end, one as the team's only workgroup.
+    auto give_up = [&](uint32_t with) {
+        const unsigned long long claim = __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)(claim >> 32) == first_tag && with - first_tag < (uint32_t)claim) return false;
+        quit = with;
+        return true;
+    };
+
+    auto drawn = [&](const TeamItem &it) {                  // lane s: row s of the batch
+        const Words4 r = stream(sa.seed, TAG_BATCH, it.q, it.node, it.event, lane >> 2);
+        const uint32_t word = (lane & 3u) == 0 ? r.w0 : (lane & 3u) == 1 ? r.w1 : (lane & 3u) == 2 ? r.w2 : r.w3;
+        return scaled_index(word, sa.m_rows);
+    };
+    // byte offsets into a row's slice, past the row's end those of its last columns
+    auto column = [&](uint32_t slice, int c) { return (uint64_t)slice * WIDTH + 256u * c + 4u * lane; };
+    auto offset = [&](uint32_t slice, int c) {
+        return 4u * (uint32_t)(min(column(slice, c), d - 4) - (uint64_t)slice * WIDTH);
+    };
+    auto load_model = [&](const float *from, uint32_t slice, f4 w[COLS]) {
+        SWARM_GLOBAL const float *p = uniform(from + (uint64_t)slice * WIDTH);
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) w[c] = *(SWARM_GLOBAL const f4 *)at_bytes(p, offset(slice, c));
+    };
+    auto store_model = [&](float *p, uint32_t slice, const f4 w[COLS]) {
+#pragma unroll
+        for (int c = 0; c < COLS; ++c)
+            if (wave == (uint32_t)c && column(slice, c) < d) *(f4 *)(p + column(slice, c)) = w[c];
+    };
+    auto fetch = [&](const TeamItem &it, uint32_t slice, uint32_t rows, f4 a[ROWS][COLS]) {
+        const float *An = sa.A + (uint64_t)it.node * sa.m_rows * d + (uint64_t)slice * WIDTH;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {          // past the batch its last row again, which is not used
+            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)rows, (int)(FULL ? first_row + r : min(first_row + r, batch - 1u)));
+            SWARM_GLOBAL const float *p = uniform(An + (uint64_t)row * d);
+#pragma unroll
+            for (int c = 0; c < COLS; ++c) a[r][c] = *(SWARM_GLOBAL const f4 *)at_bytes(p, offset(slice, c));
+        }
+    };
+    auto offered = [&](uint32_t parity) { return sa.words + ((uint64_t)team * 3 + parity) * G * LSQ_MAX_BATCH; };
+    auto summed = [&](uint32_t parity) { return sa.totals + ((uint64_t)team * 3 + parity) * COPIES * LSQ_MAX_BATCH; };
+    auto publish = [&](const f4 a[ROWS][COLS], const f4 w[COLS], uint32_t slice, Word *to, uint32_t with) {
+        constexpr int PART = ROWS > 8 ? 8 : ROWS, LANES = 64 / PART;          // rows summed together
+#pragma unroll
+        for (int p = 0; p < ROWS; p += PART) {
+            float dots[PART];
+#pragma unroll
+            for (int r = 0; r < PART; ++r) {
+                dots[r] = 0.f;
+#pragma unroll
+                for (int c = 0; c < COLS; ++c) {
+                    const f4 v = a[p + r][c];
+                    float acc = v.x * w[c].x;
+                    acc = fmaf(v.y, w[c].y, acc); acc = fmaf(v.z, w[c].z, acc); acc = fmaf(v.w, w[c].w, acc);
+                    dots[r] += column(slice, c) < d ? acc : 0.f;
+                }
+            }
+            const float total = wave_totals<PART, 32>(dots, lane);           // of row p + lane / LANES
+            const uint32_t s = first_row + p + lane / LANES;
+            if (lane % LANES == 0 && (FULL || s < batch)) store_word(at_bytes(uniform(to + (uint64_t)slice * LSQ_MAX_BATCH), 8u * s), with, total);
+        }
+    };
+    // The residuals into local memory, by one wave.
+    auto wait_total = [&](const Word *from, float b_of_row, uint32_t with, uint32_t parity) {     // lane s: the batch's row s
+        const unsigned long long t0 = wall_clock64();
+        Word word;
+        while (true) {
+            word = load_word(at_bytes(uniform(from), 8u * min(lane, batch - 1u)));
+            if (__all((uint32_t)(word >> 32) == with)) break;
+            if (wall_clock64() - t0 > patience && give_up(with)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        resid[parity][lane] = __uint_as_float((uint32_t)word) - b_of_row;
+    };
+    // rows [j * rows_each, ...) of the batch summed over the slices: a thread takes every (256 / rows_each)-th slice of one row
+    auto reduce = [&](uint32_t j, const Word *from, Word *to, uint32_t with, uint32_t parity) {
+        const uint32_t R = sa.rows_each, row = j * R + (threadIdx.x & (R - 1u)), own = min(row, batch - 1u), stride = TEAM_THREADS / R;
+        const unsigned long long t0 = wall_clock64();
+        float t = 0.f;
+        for (uint32_t g0 = threadIdx.x / R; __any(g0 < G); g0 += REDUCE_WORDS * stride) {
+            Word word[REDUCE_WORDS];
+            while (true) {
+                bool there = true;
+#pragma unroll
+                for (uint32_t i = 0; i < REDUCE_WORDS; ++i) word[i] = load_word(at_bytes(uniform(from), 8u * (min(g0 + i * stride, G - 1u) * LSQ_MAX_BATCH + own)));
+#pragma unroll
+                for (uint32_t i = 0; i < REDUCE_WORDS; ++i) there = there && (uint32_t)(word[i] >> 32) == with;
+                if (__all(there)) break;
+                if (wall_clock64() - t0 > patience && give_up(with)) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < REDUCE_WORDS; ++i)
+                if (g0 + i * stride < G) t += __uint_as_float((uint32_t)word[i]);
+        }
+        for (uint32_t off = R; off < 64; off *= 2) t += __shfl_xor(t, off);
+        if (lane < R) red[parity][wave][lane] = t;
+        __syncthreads();
+        if (quit == with) return false;
+        if (row < batch) {
+            const uint32_t r = threadIdx.x & (R - 1u);
+            float sum = red[parity][0][r];
+#pragma unroll
+            for (int w = 1; w < TEAM_WAVES; ++w) sum += red[parity][w][r];
+            for (uint32_t copy = threadIdx.x / R; copy < COPIES; copy += stride) store_word(at_bytes(uniform(to), 8u * (copy * LSQ_MAX_BATCH + row)), with, sum);
+        }
+        return true;
+    };
+    auto update = [&](const f4 a[ROWS][COLS], uint32_t from, uint32_t parity, f4 w[COLS]) {
+        const float residuals = resid[from][lane];
+        f4 g[COLS];
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) g[c] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if (FULL || first_row + r < batch) {
+                const float rr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(residuals), (int)(first_row + r)));
+#pragma unroll
+                for (int c = 0; c < COLS; ++c) {
+                    g[c].x = fmaf(a[r][c].x, rr, g[c].x); g[c].y = fmaf(a[r][c].y, rr, g[c].y);
+                    g[c].z = fmaf(a[r][c].z, rr, g[c].z); g[c].w = fmaf(a[r][c].w, rr, g[c].w);
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) gsum[parity][wave][64 * c + lane] = g[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) {
+            f4 t = gsum[parity][0][64 * c + lane];
+#pragma unroll
+            for (int v = 1; v < TEAM_WAVES; ++v) t = t + gsum[parity][v][64 * c + lane];
+            w[c].x = fmaf(-step, t.x, w[c].x); w[c].y = fmaf(-step, t.y, w[c].y);
+            w[c].z = fmaf(-step, t.z, w[c].z); w[c].w = fmaf(-step, t.w, w[c].w);
+        }
+    };
+
+    auto base_of = [&](uint32_t node) { return sa.base + (uint64_t)node * d; };
+    auto enter = [&] {                            // the team's numbers; false: the launch's part of the team has ended
+        if (threadIdx.x == 0) {
+            head_tag = __hip_atomic_load(&head->tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            head_claim = __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            atomicAdd(&head->started, 1u);        // has read them
+            quit = head_tag - 1u;
+        }
+        __syncthreads();
+        tag = first_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)head_tag);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(head_claim >> 32)) != first_tag;
+    };
+    if (member >= G) {
+        if (!enter()) return;
+        do {
+            if (!reduce(member - G, offered(tag & 1u), summed(tag & 1u), tag, tag & 1u)) { alone = true; break; }
+            ++tag;
+        } while (advance(it));
+    } else {
+        f4 a[ROWS][COLS], w[COLS];
+        float b_of_row;
+        auto begin = [&](uint32_t rows) {         // the step's rows on their way
+            if (it.q == 0) load_model(base_of(it.node), member, w);
+            fetch(it, member, rows, a);
+            b_of_row = sa.b[(uint64_t)it.node * sa.m_rows + rows];
+        };
+        if (false) return;
+        if (!enter()) return;
+        begin(drawn(it));
+        while (true) {
+            const uint32_t parity = tag & 1u;
+            asm volatile("" : "+v"(lane));        // what derives from it is worked out again, or the rows would not fit the registers
+            publish(a, w, member, offered(parity), tag);
+            TeamItem then = it;
+            const bool more = advance(then);
+            if (wave == 0) wait_total(summed(parity) + (member % COPIES) * LSQ_MAX_BATCH, b_of_row, tag, parity);
+            if (wave == 1 && more) rows_of[parity][lane] = drawn(then);      // the next step's, meanwhile
+            __syncthreads();
+            alone = quit == tag;
+            if (alone) break;
+            const uint32_t rows = rows_of[parity][lane];
+            update(a, parity, parity, w);
+            if (it.q + 1 == it.H) store_model(sa.W + (uint64_t)it.node * d, member, w);
+            ++tag;
+            if (!more) break;
+            it = then;
+            begin(rows);
+        }
+    }
+    // The end of the team's part: by its first workgroup, all others having published the last step, or by the first that gave up.
+    if (!alone && member != 0) return;
+    if (threadIdx.x == 0) {
+        const unsigned long long unclaimed = head_claim;
+        head_tag = atomicCAS(&head->claim, unclaimed, (unsigned long long)first_tag << 32 | (tag - first_tag)) == unclaimed;
+    }
+    __syncthreads();
+    if (!head_tag) return;
+    if (alone) {
+        patience = START_TICKS;                   // what it waits for it has stored itself
+        it.q = 0;
+        ++tag;                                    // `quit` holds the one that was given up
+        uint32_t parity = 0;
+        float *own = sa.models + (uint64_t)team * d;
+        for (bool more = true; more; more = advance(it), ++tag) {
+            f4 a[ROWS][COLS], w[COLS];
+            asm volatile("" : "+v"(lane));
+            const uint32_t rows = drawn(it);
+            const float b_of_row = sa.b[(uint64_t)it.node * sa.m_rows + rows];
+            const float *from = it.q ? own : base_of(it.node);
+            float *to = it.q + 1 == it.H ? sa.W + (uint64_t)it.node * d : own;
+            for (uint32_t g = 0; g < G; ++g) {
+                load_model(from, g, w);
+                fetch(it, g, rows, a);
+                publish(a, w, g, offered(2), tag);
+            }
+            for (uint32_t j = 0; j < sa.reducers; ++j, parity ^= 1u) (void)reduce(j, offered(2), summed(2), tag, parity);
+            if (wave == 0) wait_total(summed(2), b_of_row, tag, 0);
+            __syncthreads();
+            if (quit == tag) {
+                if (threadIdx.x == 0) atomicOr(&sa.counters->barrier_timeouts, 1u);
+                break;
+            }
+            for (uint32_t g = 0; g < G; ++g, parity ^= 1u) {
+                load_model(from, g, w);
+                fetch(it, g, rows, a);
+                update(a, 0, parity, w);
+                store_model(to, g, w);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // the next step reads what other waves have written
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {                   // the number may go on once no workgroup of this launch has yet to read it
+            const unsigned long long t0 = wall_clock64();
+            while (__hip_atomic_load(&head->started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
+                if (wall_clock64() - t0 > START_TICKS) { atomicOr(&sa.counters->barrier_timeouts, 1u); break; }
+                __builtin_amdgcn_s_sleep(64);
+            }
+        }
+    }
+    if (threadIdx.x == 0) {
+        atomicSub(&head->started, all);
+        __hip_atomic_store(&head->tag, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Rows of a workgroup: 64 KiB, 32 of batches of at most 16.  More teams than one, and workgroups of several of them on a
+// compute unit, keep memory busy while a team waits.
+static int team_rows(uint32_t batch) { return batch <= 8 ? 2 : batch <= 16 ? 4 : batch <= 32 ? 8 : 16; }
+typedef void (*TeamKernel)(const LsqTeamArgs);
+static TeamKernel team_kernel(uint32_t batch) {
+    switch (team_rows(batch)) {
+        case 2: return batch == 8 ? lsq_team_kernel<2, 4, true> : lsq_team_kernel<2, 4, false>;
+        case 4: return batch == 16 ? lsq_team_kernel<4, 2, true> : lsq_team_kernel<4, 2, false>;
+        case 8: return batch == 32 ? lsq_team_kernel<8, 2, true> : lsq_team_kernel<8, 2, false>;
+        default: return batch == 64 ? lsq_team_kernel<16, 1, true> : lsq_team_kernel<16, 1, false>;
+    }
+}
+
+// Launches of several swarms on one GPU one after the other: each waits for the last one, where there are several such swarms.
+namespace {
+struct DeviceTurn {
+    std::mutex mutex;
+    uint32_t swarms = 0;
+    hipEvent_t last = nullptr;                    // there while several swarms are
+    bool recorded = false;                        // `last` follows a launch
+};
+constexpr int MAX_DEVICES = 64;
+DeviceTurn device_turns[MAX_DEVICES];
+}  // namespace
+
+struct LsqTeams {
+    int device;
+    uint32_t most, slices, reducers, rows_each;   // most: teams whose workgroups fit the chip together
+    LsqTeamHead *heads;
+    Word *words, *totals;
+    float *models;
+};
+
+// o.teams stays null where not even one team fits.
+hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
+    int device = 0, units = 0, each = 0;
+    hipError_t e;
+    if ((e = hipGetDevice(&device)) != hipSuccess) return e;
+    if (device >= MAX_DEVICES) return hipSuccess;
+    if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device)) != hipSuccess) return e;
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&each, (const void *)team_kernel(o.batch), TEAM_THREADS, 0)) != hipSuccess) return e;
+    const uint64_t width = o.batch <= 8 ? 1024 : o.batch <= 32 ? 512 : 256, slices = (d + width - 1) / width;
+    uint32_t rows_each = 4;                       // rows a reducing workgroup adds: REDUCE_WORDS words per thread where four rows have no more
+    while (rows_each < o.batch && 2 * rows_each * slices <= REDUCE_WORDS * TEAM_THREADS) rows_each *= 2;
+    const uint32_t reducers = (o.batch + rows_each - 1) / rows_each;
+    const uint64_t most = std::min<uint64_t>((uint64_t)units * each / (slices + reducers), n);
+    if (most == 0) return hipSuccess;
+    LsqTeams t{};
+    t.device = device; t.most = (uint32_t)most; t.slices = (uint32_t)slices; t.reducers = reducers; t.rows_each = rows_each;
+    const uint64_t head_bytes = sizeof(LsqTeamHead) * most, words = most * 3 * slices * LSQ_MAX_BATCH, totals = most * 3 * COPIES * LSQ_MAX_BATCH;
+    const uint64_t exchange = head_bytes + sizeof(Word) * (words + totals);
+    if ((e = hipMalloc((void **)&t.heads, exchange + sizeof(float) * most * d)) != hipSuccess) return e;
+    t.words = (Word *)(t.heads + most);
+    t.totals = t.words + words;
+    t.models = (float *)(t.totals + totals);
+    // numbers begin at 0; no word carries one that is used soon, no claim one at all
+    if ((e = hipMemset(t.heads, 0xFF, exchange)) != hipSuccess || (e = hipMemset2D(&t.heads->tag, sizeof(LsqTeamHead), 0, 2 * sizeof(uint32_t), most)) != hipSuccess) {
+        (void)hipFree(t.heads);
+        return e;
+    }
+    DeviceTurn &turn = device_turns[device];
+    std::lock_guard<std::mutex> lock(turn.mutex);
+    if (turn.swarms == 1 && (e = hipEventCreateWithFlags(&turn.last, hipEventDisableTiming)) != hipSuccess) {
+        (void)hipFree(t.heads);
+        return e;
+    }
+    turn.swarms += 1;
+    o.teams = new LsqTeams(t);
+    return hipSuccess;
+}
+
+void free_lsq_teams(LsqObjective &o) {
+    if (!o.teams) return;
+    (void)hipFree(o.teams->heads);
+    DeviceTurn &turn = device_turns[o.teams->device];
+    std::lock_guard<std::mutex> lock(turn.mutex);
+    turn.swarms -= 1;
+    if (turn.swarms == 1) {
+        (void)hipEventDestroy(turn.last);
+        turn.last = nullptr; turn.recorded = false;
+    }
+    delete o.teams;
+    o.teams = nullptr;
+}
+
+hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, const LocalSlots &slots, DeviceCounters *counters,
+                            uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
+    const LsqTeams &t = *o.teams;
+    const uint32_t rounds = (count + t.most - 1) / t.most, teams = (count + rounds - 1) / rounds;
+    const LsqTeamArgs a{base, o.A, o.b, W, slots, t.heads, t.words, t.totals, t.models, counters, d, seed, o.patience,
+                        count, teams, t.slices, t.reducers, t.rows_each, H, o.m_rows, o.batch, event, lr};
+    DeviceTurn &turn = device_turns[t.device];
+    std::lock_guard<std::mutex> lock(turn.mutex);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipError_t e;
+    if (turn.swarms > 1 && (e = hipStreamIsCapturing(st, &capture)) != hipSuccess) return e;
+    const bool several = turn.swarms > 1 && capture == hipStreamCaptureStatusNone;
+    if (several && turn.recorded && (e = hipStreamWaitEvent(st, turn.last, 0)) != hipSuccess) return e;
+    team_kernel(o.batch)<<<teams * (t.slices + t.reducers), TEAM_THREADS, 0, st>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (several) {
+        if ((e = hipEventRecord(turn.last, st)) != hipSuccess) return e;
+        turn.recorded = true;
+    }
+    return hipSuccess;
+}
+
+}  // namespace swarm

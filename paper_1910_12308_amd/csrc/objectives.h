@@ -8,6 +8,7 @@ namespace swarm {
 struct DiagObjective { const float *a; const float *c; float sigma; };
 
 constexpr uint32_t LSQ_MAX_BATCH = 64;
+struct LsqTeams;
 struct LsqObjective {
     const float *A = nullptr;    // n x m_rows x d
     const float *b = nullptr;    // n x m_rows
@@ -28,6 +29,9 @@ struct LsqObjective {
     uint64_t wide_rows = 0;
     uint32_t wide_slices = 0;
     bool by_rows = false;           // wide form with a wave per row of the batch instead
+    // teams of workgroups (lsq_team.hip), where the wide form would cut a node's columns and its models and live copies differ
+    LsqTeams *teams = nullptr;
+    unsigned long long patience = 2000000;        // 100 MHz ticks a workgroup waits for the others of its team: 20 ms
 };
 
 struct MlpSplitSpace;
@@ -68,6 +72,10 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
 hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, const SeqDesc &one, uint32_t count,
                                LsqObjective &o, float lr, hipStream_t st);
 void free_lsq(LsqObjective &o);
+hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n);
+void free_lsq_teams(LsqObjective &o);
+hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, const LocalSlots &slots, DeviceCounters *counters,
+                            uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st);
 
 hipError_t alloc_mlp(MlpObjective &o, uint32_t n_nodes);
 void free_mlp(MlpObjective &o);

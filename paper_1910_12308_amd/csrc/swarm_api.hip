@@ -1413,6 +1413,12 @@ swarm_status swarm_timing_reset(swarm_t h) {
     return SWARM_OK;
 }
 
+swarm_status swarm_lsq_patience(swarm_t h, uint64_t ticks) {
+    if (!h) return SWARM_EINVAL;
+    h->lsq.patience = ticks;
+    return SWARM_OK;
+}
+
 swarm_status swarm_kernel_times(swarm_t h, double *gossip_ms, uint32_t *gossip_calls, double *local_ms,
                                 uint32_t *local_calls) {
     if (!h) return SWARM_EINVAL;

@@ -55,6 +55,60 @@ def test_split_least_squares_steps(gpu, n, d, m, batch, H, geometric):
     test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric)
 
 
+# Teams: two, four, eight or sixteen rows per wave of full and other batches, one, two and four blocks of columns, ragged slices; one node
+# after the other (64 nodes of 33 slices) and all at once; one and several reducing workgroups
+TEAM_STEPS = [(64, 8200, 5, 64, 2, False), (64, 8200, 5, 60, 2, True), (40, 16392, 6, 32, 2, False), (40, 16392, 6, 20, 2, False),
+              (64, 12296, 5, 16, 3, False), (33, 4104, 5, 12, 1, False), (64, 8200, 5, 8, 2, False), (35, 4104, 5, 4, 2, True), (2, 8 * 9001, 6, 64, 3, False), (9, 131072, 5, 32, 2, False)]
+
+
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", TEAM_STEPS)
+def test_least_squares_steps_by_teams(gpu, n, d, m, batch, H, geometric):
+    test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric)
+
+
+# Workgroups that do not wait: one takes what is left of a team's nodes by itself, the sums are the same bits, and the next launch
+# starts from the numbers this one has left
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", [(34, 8200, 5, 64, 3, False), (40, 8200, 6, 20, 2, True), (33, 4104, 5, 12, 2, False)])
+def test_least_squares_steps_by_teams_whose_workgroups_do_not_wait(gpu, n, d, m, batch, H, geometric):
+    g, _ = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)
+    h, _ = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)
+    X = g.read_models(gpu.COMM)
+    for ticks in (2000000, 0, 200, 2000, 2000000):
+        g.lsq_patience(ticks)
+        for s in (g, h):
+            s.write_models(gpu.COMM, X)
+            s.write_models(gpu.LIVE, np.full_like(X, np.nan))
+            s.local_steps()
+        assert np.array_equal(g.read_models(gpu.LIVE), h.read_models(gpu.LIVE)), ticks
+    g.counters()
+
+
+# Two swarms on streams of their own take turns, from two threads
+def test_least_squares_steps_by_teams_of_two_swarms_at_once(gpu):
+    import threading
+    swarms = [lsq_swarm(gpu, 16, 16392, 5, 64, 2, False, seed=s)[0] for s in (1, 2)]
+    want = []
+    for s in swarms:
+        s.local_steps()
+        want.append(s.read_models(gpu.LIVE))
+    X = [s.read_models(gpu.COMM) for s in swarms]
+    got = [None, None]
+
+    def work(k):
+        for _ in range(20):
+            swarms[k].write_models(gpu.COMM, X[k])
+            swarms[k].local_steps()
+        got[k] = swarms[k].read_models(gpu.LIVE)
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in (0, 1):
+        assert np.array_equal(got[k], want[k])
+        swarms[k].counters()
+
+
 def test_wide_least_squares_batched_algorithm1_equals_single_steps(gpu):
     n, d = 9, 8 * 2051
     pair = [lsq_swarm(gpu, n, d, 33, 16, 2, True, seed=4)[0] for _ in range(2)]
