@@ -378,14 +378,16 @@ struct LsqTeams {
     float *models;
 };
 
-// o.teams stays null where not even one team fits.
+// o.teams stays null where not even one team fits, or where the runtime cannot tell.
 hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     int device = 0, units = 0, each = 0;
+    if (hipGetDevice(&device) != hipSuccess || device >= MAX_DEVICES ||
+        hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&each, (const void *)team_kernel(o.batch), TEAM_THREADS, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
     hipError_t e;
-    if ((e = hipGetDevice(&device)) != hipSuccess) return e;
-    if (device >= MAX_DEVICES) return hipSuccess;
-    if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device)) != hipSuccess) return e;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&each, (const void *)team_kernel(o.batch), TEAM_THREADS, 0)) != hipSuccess) return e;
     const uint64_t width = o.batch <= 8 ? 1024 : o.batch <= 32 ? 512 : 256, slices = (d + width - 1) / width;
     uint32_t rows_each = 4;                       // rows a reducing workgroup adds: REDUCE_WORDS words per thread where four rows have no more
     while (rows_each < o.batch && 2 * rows_each * slices <= REDUCE_WORDS * TEAM_THREADS) rows_each *= 2;
