@@ -9,8 +9,8 @@
 // (batch floats each) through device memory, each word tagged with the launch and step it belongs to, so a reader
 // simply waits until the word it needs carries the right tag (no counters, no fences, nothing to reset).  In a
 // batch of Algorithm 1 steps the workgroup then runs the interaction on its slice, which is exactly one gossip tile.
-// Of all other swarms, many nodes take the wide form (lsq_wide_kernel) with one workgroup per node, fewer take steps by teams of
-// workgroups (lsq_team.hip) or, where not even one node's workgroups fit the chip or the steps update the models themselves, the wide
+// Of all other swarms, many nodes with few rows take the wide form (lsq_wide_kernel) with one workgroup per node, the rest steps by
+// teams of workgroups (lsq_team.hip) or, where not even one node's workgroups fit the chip or the steps update the models themselves, the wide
 // form with several per node, which exchange their residuals between launches.
 #include <algorithm>
 #include <type_traits>
@@ -32,7 +32,7 @@ namespace swarm {
 // steps.  With one slice per node (WHOLE) nothing leaves the workgroup and one launch runs all steps, in blocks of 1024
 // to 4096 columns.
 // Bound by memory: the rows of a step are read twice, once for the residuals and, when these are known, once for the
-// update, and are too many to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
+// update, and are too many for a workgroup to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
 // per thread.  16 nodes x 65544 columns, batch 64, 2 steps: 190 us = 1.07 GB of rows at 5.6 TB/s, against 1.96 ms for
 // one workgroup of 1024 threads per node, which left 240 of 256 compute units idle.  Measured without effect: groups
 // of nodes whose rows fit the last-level cache (more launches cost more than the hits give), non-temporal loads
@@ -463,13 +463,23 @@ static bool lsq_by_rows(uint64_t d, uint32_t n, uint32_t batch) {
     return n > 224 && n <= 512 && d == 4096;
 }
 
+// Of the swarms that would take one workgroup per node, those whose steps teams take (lsq_team.hip): where a step's rows are many
+// enough to outweigh the exchange.  us, one workgroup per node and teams:
+//   80 x 4096, batch 64, H = 2    50.5   27.7    200 x 8192, batch 32, H = 2    106   64.5    128 x 8192, batch 16, H = 1    18.5   19.1
+//   255 x 2048, batch 64, H = 2   59.1   41.1    300 x 16384, batch 16, H = 1   108   83.3    65 x 2048, batch 16, H = 2      8.8   11.0
+//   300 x 4096, batch 64, H = 2    171   81.2    260 x 65536, batch 16, H = 1   489    425    1000 x 2048, batch 16, H = 3    82.3   97.4
+//   300 x 16384, batch 64, H = 2   820    338    128 x 16384, batch 64, H = 2   320    152    200 x 4096, batch 16, H = 2    28.2   26.5
+static bool teams_pay(uint64_t d, uint32_t batch) {
+    return batch >= 64 ? d >= 2048 : batch >= 32 ? d >= 4096 : batch >= 16 && d >= 16384;
+}
+
 hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
     hipError_t e;
     if (!lsq_split_fits(d, n)) {
         o.wide_slices = wide_slices(d, n);
         o.by_rows = o.wide_slices == 1 && lsq_by_rows(d, n, o.batch);
         o.wide_rows = (uint64_t)n * o.wide_slices;
-        if (o.wide_slices > 1 && (e = alloc_lsq_teams(o, d, n)) != hipSuccess) return e;
+        if ((o.wide_slices > 1 || teams_pay(d, o.batch)) && (e = alloc_lsq_teams(o, d, n)) != hipSuccess) return e;
         return hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH);
     }
     const uint64_t slices = (d + SLICE - 1) / SLICE;

@@ -58,7 +58,8 @@ def test_split_least_squares_steps(gpu, n, d, m, batch, H, geometric):
 # Teams: two, four, eight or sixteen rows per wave of full and other batches, one, two and four blocks of columns, ragged slices; one node
 # after the other (64 nodes of 33 slices) and all at once; one and several reducing workgroups
 TEAM_STEPS = [(64, 8200, 5, 64, 2, False), (64, 8200, 5, 60, 2, True), (40, 16392, 6, 32, 2, False), (40, 16392, 6, 20, 2, False),
-              (64, 12296, 5, 16, 3, False), (33, 4104, 5, 12, 1, False), (64, 8200, 5, 8, 2, False), (35, 4104, 5, 4, 2, True), (2, 8 * 9001, 6, 64, 3, False), (9, 131072, 5, 32, 2, False)]
+              (64, 12296, 5, 16, 3, False), (33, 4104, 5, 12, 1, False), (64, 8200, 5, 8, 2, False), (35, 4104, 5, 4, 2, True), (2, 8 * 9001, 6, 64, 3, False), (9, 131072, 5, 32, 2, False), (66, 4096, 5, 32, 2, False),
+              (300, 2056, 5, 64, 2, True), (257, 16392, 4, 16, 2, False)]
 
 
 @pytest.mark.parametrize("n,d,m,batch,H,geometric", TEAM_STEPS)
