@@ -13,6 +13,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "lsq_team_end.hpp"
 #include "lsq_wave.hpp"
 #include "objectives.h"
 #include "philox.hpp"
@@ -73,6 +74,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     __shared__ float resid[2][LSQ_MAX_BATCH];
     __shared__ uint32_t rows_of[2][LSQ_MAX_BATCH];
     __shared__ uint32_t quit;                      // the step that was given up
+    __shared__ uint32_t took;                      // this workgroup's claim was the first
     __shared__ unsigned long long head_claim;
     __shared__ uint32_t head_tag;
     constexpr uint32_t WIDTH = 256 * COLS;
@@ -103,12 +105,18 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     uint32_t first_tag = 0, tag = 0;
     unsigned long long patience = sa.patience;
     bool alone = false;
-    // A wave that has waited long enough: go on waiting where the totals are known to come, else end, one as the team's only workgroup.
+    // A wave that has waited long enough for the step's words; false: it waits on.
     auto give_up = [&](uint32_t with) {
-        const unsigned long long claim = __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)(claim >> 32) == first_tag && with - first_tag < (uint32_t)claim) return false;
-        quit = with;
-        return true;
+        uint32_t then = 0;
+        if ((threadIdx.x & 63u) == 0) {
+            then = (uint32_t)out_of_patience(
+                first_tag, with - first_tag,
+                [&] { return __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                [&](TeamClaim there, TeamClaim mine) { return (TeamClaim)atomicCAS(&head->claim, there, mine); });
+            if (then != (uint32_t)TeamWait::GO_ON) quit = with;
+            if (then == (uint32_t)TeamWait::ALONE) took = 1;
+        }
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)then) != (uint32_t)TeamWait::GO_ON;
     };
 
     auto drawn = [&](const TeamItem &it) {                  // lane s: row s of the batch
@@ -247,6 +255,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             atomicAdd(&head->started, 1u);        // has read them
             quit = head_tag - 1u;
+            took = 0;
         }
         __syncthreads();
         tag = first_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)head_tag);
@@ -289,14 +298,16 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             begin(rows);
         }
     }
-    // The end of the team's part: by its first workgroup, all others having published the last step, or by the first that gave up.
-    if (!alone && member != 0) return;
-    if (threadIdx.x == 0) {
-        const unsigned long long unclaimed = head_claim;
-        head_tag = atomicCAS(&head->claim, unclaimed, (unsigned long long)first_tag << 32 | (tag - first_tag)) == unclaimed;
+    // The end of the team's part: by its first workgroup, all others having published the last step, or by the one that took the rest.
+    if (alone ? took == 0 : member != 0) return;
+    if (!alone) {
+        if (threadIdx.x == 0) {
+            const TeamClaim unclaimed = head_claim;
+            head_tag = atomicCAS(&head->claim, unclaimed, (TeamClaim)first_tag << 32 | (tag - first_tag)) == unclaimed;
+        }
+        __syncthreads();
+        if (!head_tag) return;
     }
-    __syncthreads();
-    if (!head_tag) return;
     if (alone) {
         patience = START_TICKS;                   // what it waits for it has stored itself
         it.q = 0;

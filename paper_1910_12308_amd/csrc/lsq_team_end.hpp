@@ -1,0 +1,34 @@
+// What a workgroup of a least-squares team (lsq_team.hip) does that has waited long enough for the others.  On plain integers and
+// with the accesses to the team's claim passed in, so that the model of a team on the host (tests/lsq_team_end.cpp) runs these lines.
+#pragma once
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define SWARM_TEAM_FN __host__ __device__ __forceinline__
+#else
+#define SWARM_TEAM_FN inline
+#endif
+
+namespace swarm {
+
+// Of a team's part of a launch: number of its first step << 32 | how many of its steps are left to all workgroups.  The one whose
+// claim is the first of the launch takes the others by itself.
+typedef unsigned long long TeamClaim;
+
+enum class TeamWait { GO_ON, END, ALONE };
+
+// At the launch's step `done`, all steps before it being known to come to their end.  load and swap (compare and exchange, which
+// returns what was there) reach the claim; it is another launch's until one of this launch is made.  So that no step falls between two workgroups, leaving and
+// claiming are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.
+template <class Load, class Swap>
+SWARM_TEAM_FN TeamWait out_of_patience(uint32_t first, uint32_t done, Load load, Swap swap) {
+    TeamClaim there = load();
+    if ((uint32_t)(there >> 32) != first) {
+        const TeamClaim before = swap(there, (TeamClaim)first << 32 | done);
+        if (before == there) return TeamWait::ALONE;
+        there = before;
+    }
+    return done < (uint32_t)there ? TeamWait::GO_ON : TeamWait::END;
+}
+
+}  // namespace swarm
