@@ -29,8 +29,8 @@ constexpr uint32_t REDUCE_WORDS = 8;              // words a thread of a reducin
 constexpr uint32_t COPIES = 8;                    // of a step's totals, read by every eighth workgroup each: all of them ask for the same lines
 constexpr unsigned long long START_TICKS = 200000000ull;    // 2 s of the 100 MHz wall clock
 
-// Of a team.  tag: number of the next launch's first step.  claim: first number of the launch << 32 | steps whose totals are known to be
-// out, set by the workgroup that ends the team's part of the launch.  started: workgroups of the launch that have begun.
+// Of a team.  tag: number of the next launch's first step.  claim: TeamClaim, by the workgroup that ends the team's part of the launch,
+// one that holds columns.  started: workgroups of the launch that have begun.
 struct LsqTeamHead {
     unsigned long long claim;
     uint32_t tag, started;
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     uint32_t first_tag = 0, tag = 0;
     unsigned long long patience = sa.patience;
     bool alone = false;
-    // A wave that has waited long enough for the step's words; false: it waits on.
+    // A wave that has waited long enough for the step's totals; false: it waits on.
     auto give_up = [&](uint32_t with) {
         uint32_t then = 0;
         if ((threadIdx.x & 63u) == 0) {
@@ -198,7 +198,10 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
 #pragma unroll
                 for (uint32_t i = 0; i < REDUCE_WORDS; ++i) there = there && (uint32_t)(word[i] >> 32) == with;
                 if (__all(there)) break;
-                if (wall_clock64() - t0 > patience && give_up(with)) break;
+                if (wall_clock64() - t0 > patience) {
+                    quit = with;                  // and makes no claim
+                    break;
+                }
                 __builtin_amdgcn_s_sleep(1);
             }
 #pragma unroll
@@ -264,9 +267,10 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     if (member >= G) {
         if (!enter()) return;
         do {
-            if (!reduce(member - G, offered(tag & 1u), summed(tag & 1u), tag, tag & 1u)) { alone = true; break; }
+            if (!reduce(member - G, offered(tag & 1u), summed(tag & 1u), tag, tag & 1u)) break;
             ++tag;
         } while (advance(it));
+        return;
     } else {
         f4 a[ROWS][COLS], w[COLS];
         float b_of_row;
@@ -298,7 +302,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             begin(rows);
         }
     }
-    // The end of the team's part: by its first workgroup, all others having published the last step, or by the one that took the rest.
+    // The end of the team's part: by its first workgroup, all totals being out, or by the one that took the rest.
     if (alone ? took == 0 : member != 0) return;
     if (!alone) {
         if (threadIdx.x == 0) {

@@ -17,9 +17,11 @@ typedef unsigned long long TeamClaim;
 
 enum class TeamWait { GO_ON, END, ALONE };
 
-// At the launch's step `done`, all steps before it being known to come to their end.  load and swap (compare and exchange, which
-// returns what was there) reach the claim; it is another launch's until one of this launch is made.  So that no step falls between two workgroups, leaving and
-// claiming are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.
+// At the launch's step `done`, for a workgroup that holds columns: it has had the whole totals of every step before, so that these
+// are there for all others too.  (One that adds some of the rows knows of its own totals only: it ends without a claim, and a
+// workgroup that misses its next totals makes one.)  load and swap (compare and exchange, which returns what was there) reach the
+// claim; it is another launch's until one of this launch is made.  So that no step falls between two workgroups, leaving and claiming
+// are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.
 template <class Load, class Swap>
 SWARM_TEAM_FN TeamWait out_of_patience(uint32_t first, uint32_t done, Load load, Swap swap) {
     TeamClaim there = load();

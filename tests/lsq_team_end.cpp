@@ -55,8 +55,8 @@ struct Team {
                                           return before;
                                       });
     }
-    // Until all the words carry the number.
-    TeamWait wait(const std::vector<uint32_t> &words, uint32_t first, uint32_t with) {
+    // Until all the words carry the number; whoever makes no claim ends when it has waited long enough.
+    TeamWait wait(const std::vector<uint32_t> &words, uint32_t first, uint32_t with, bool claims) {
         while (true) {
             bool there = true;
             for (const uint32_t &w : words) {
@@ -65,6 +65,7 @@ struct Team {
             }
             if (there) return TeamWait::GO_ON;
             if (tired()) {
+                if (!claims) return TeamWait::END;
                 const TeamWait then = give_up(first, with - first);
                 if (then != TeamWait::GO_ON) return then;
             }
@@ -89,7 +90,7 @@ struct Team {
             const uint32_t tag = first + k;
             yield();
             part[tag & 1u][c] = tag;
-            const TeamWait then = wait(total[tag & 1u], first, tag);
+            const TeamWait then = wait(total[tag & 1u], first, tag, true);
             if (then == TeamWait::ALONE) return alone(k);
             if (then == TeamWait::END) return;
             if (k % steps_each == steps_each - 1) {
@@ -108,9 +109,7 @@ struct Team {
         if (claimed(first)) return;
         for (uint32_t k = 0; k < steps; ++k) {
             const uint32_t tag = first + k;
-            const TeamWait then = wait(part[tag & 1u], first, tag);
-            if (then == TeamWait::ALONE) return alone(k);
-            if (then == TeamWait::END) return;
+            if (wait(part[tag & 1u], first, tag, false) == TeamWait::END) return;
             yield();
             total[tag & 1u][j] = tag;
         }
@@ -131,8 +130,8 @@ struct Team {
             fibers.push_back(std::move(f));
         }
         size_t left = fibers.size();
-        for (uint32_t turns = 0; left; ++turns) {
-            if (turns == 20000) return false;
+        for (size_t turns = 0; left; ++turns) {
+            if (turns == 10000 * fibers.size()) return false;
             running = fibers[gen() % fibers.size()].get();
             if (running->ended) continue;
             const uint32_t some = 1 + gen() % 8;          // accesses in a row
