@@ -27,7 +27,7 @@ constexpr int TEAM_WAVES = 4;
 constexpr int TEAM_THREADS = 64 * TEAM_WAVES;
 constexpr uint32_t REDUCE_WORDS = 8;              // words a thread of a reducing workgroup asks for at a time
 constexpr uint32_t COPIES = 8;                    // of a step's totals, read by every eighth workgroup each: all of them ask for the same lines
-constexpr unsigned long long START_TICKS = 200000000ull;    // 2 s of the 100 MHz wall clock
+constexpr unsigned long long WAIT_TICKS = 200000000ull;     // 2 s of the 100 MHz wall clock: no wait lasts longer past its patience
 
 // Of a team.  tag: number of the next launch's first step.  claim: TeamClaim, by the workgroup that ends the team's part of the launch,
 // one that holds columns.  started: workgroups of the launch that have begun.
@@ -106,15 +106,16 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     unsigned long long patience = sa.patience;
     bool alone = false;
     // A wave that has waited long enough for the step's totals; false: it waits on.
-    auto give_up = [&](uint32_t with) {
+    auto give_up = [&](uint32_t with, bool overdue) {
         uint32_t then = 0;
         if ((threadIdx.x & 63u) == 0) {
             then = (uint32_t)out_of_patience(
-                first_tag, with - first_tag,
+                first_tag, with - first_tag, overdue,
                 [&] { return __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
                 [&](TeamClaim there, TeamClaim mine) { return (TeamClaim)atomicCAS(&head->claim, there, mine); });
             if (then != (uint32_t)TeamWait::GO_ON) quit = with;
             if (then == (uint32_t)TeamWait::ALONE) took = 1;
+            if (then == (uint32_t)TeamWait::LOST) atomicOr(&sa.counters->barrier_timeouts, 1u);
         }
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)then) != (uint32_t)TeamWait::GO_ON;
     };
@@ -179,7 +180,8 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
         while (true) {
             word = load_word(at_bytes(uniform(from), 8u * min(lane, batch - 1u)));
             if (__all((uint32_t)(word >> 32) == with)) break;
-            if (wall_clock64() - t0 > patience && give_up(with)) break;
+            const unsigned long long waited = wall_clock64() - t0;
+            if (waited > patience && give_up(with, waited - patience > WAIT_TICKS)) break;
             __builtin_amdgcn_s_sleep(1);
         }
         resid[parity][lane] = __uint_as_float((uint32_t)word) - b_of_row;
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
         if (!head_tag) return;
     }
     if (alone) {
-        patience = START_TICKS;                   // what it waits for it has stored itself
+        patience = WAIT_TICKS;                   // what it waits for it has stored itself
         it.q = 0;
         ++tag;                                    // `quit` holds the one that was given up
         uint32_t parity = 0;
@@ -330,8 +332,8 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
                 fetch(it, g, rows, a);
                 publish(a, w, g, offered(2), tag);
             }
-            for (uint32_t j = 0; j < sa.reducers; ++j, parity ^= 1u) (void)reduce(j, offered(2), summed(2), tag, parity);
-            if (wave == 0) wait_total(summed(2), b_of_row, tag, 0);
+            for (uint32_t j = 0; j < sa.reducers && reduce(j, offered(2), summed(2), tag, parity); ++j) parity ^= 1u;
+            if (wave == 0 && quit != tag) wait_total(summed(2), b_of_row, tag, 0);
             __syncthreads();
             if (quit == tag) {
                 if (threadIdx.x == 0) atomicOr(&sa.counters->barrier_timeouts, 1u);
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
         if (threadIdx.x == 0) {                   // the number may go on once no workgroup of this launch has yet to read it
             const unsigned long long t0 = wall_clock64();
             while (__hip_atomic_load(&head->started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
-                if (wall_clock64() - t0 > START_TICKS) { atomicOr(&sa.counters->barrier_timeouts, 1u); break; }
+                if (wall_clock64() - t0 > WAIT_TICKS) { atomicOr(&sa.counters->barrier_timeouts, 1u); break; }
                 __builtin_amdgcn_s_sleep(64);
             }
         }

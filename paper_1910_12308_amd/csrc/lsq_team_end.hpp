@@ -15,22 +15,24 @@ namespace swarm {
 // claim is the first of the launch takes the others by itself.
 typedef unsigned long long TeamClaim;
 
-enum class TeamWait { GO_ON, END, ALONE };
+enum class TeamWait { GO_ON, END, ALONE, LOST };
 
 // At the launch's step `done`, for a workgroup that holds columns: it has had the whole totals of every step before, so that these
 // are there for all others too.  (One that adds some of the rows knows of its own totals only: it ends without a claim, and a
 // workgroup that misses its next totals makes one.)  load and swap (compare and exchange, which returns what was there) reach the
 // claim; it is another launch's until one of this launch is made.  So that no step falls between two workgroups, leaving and claiming
-// are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.
+// are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.  It finds the totals at its next look;
+// `overdue`, when it has not for long, ends the wait all the same, as an error.
 template <class Load, class Swap>
-SWARM_TEAM_FN TeamWait out_of_patience(uint32_t first, uint32_t done, Load load, Swap swap) {
+SWARM_TEAM_FN TeamWait out_of_patience(uint32_t first, uint32_t done, bool overdue, Load load, Swap swap) {
     TeamClaim there = load();
     if ((uint32_t)(there >> 32) != first) {
         const TeamClaim before = swap(there, (TeamClaim)first << 32 | done);
         if (before == there) return TeamWait::ALONE;
         there = before;
     }
-    return done < (uint32_t)there ? TeamWait::GO_ON : TeamWait::END;
+    if (done >= (uint32_t)there) return TeamWait::END;
+    return overdue ? TeamWait::LOST : TeamWait::GO_ON;
 }
 
 }  // namespace swarm

@@ -1,8 +1,9 @@
 // A model of a least-squares team (paper_1910_12308_amd/csrc/lsq_team.hip) on the host: its workgroups are fibers that a seeded
 // generator runs in any order, changing after every access to what they share, and every look for words that are not there may be the
 // last one that a workgroup has patience for.  What such a workgroup does then is the kernel's own code (lsq_team_end.hpp).
-//   lsq_team_end schedules reducers
-// runs so many random schedules and prints how many of them did not end, and in how many a slice of a node was not written.
+//   lsq_team_end schedules reducers [wrong]
+// runs so many random schedules and prints how many of them did not end, in how many a slice of a node was not written, and in how many
+// a workgroup gave up with an error.  wrong: a claim that nobody made lies on the way, so that workgroups wait for what does not come.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -44,10 +45,11 @@ struct Team {
     std::vector<std::vector<bool>> written;               // [node][column]
     std::mt19937_64 gen;
     double patience;                                      // chance that a workgroup waits on
+    bool wrong = false, lost = false;
 
     bool tired() { return std::generate_canonical<double, 32>(gen) > patience; }
-    TeamWait give_up(uint32_t first, uint32_t done) {
-        return swarm::out_of_patience(first, done, [&] { yield(); return claim; },
+    TeamWait give_up(uint32_t first, uint32_t done, bool overdue) {
+        return swarm::out_of_patience(first, done, overdue, [&] { yield(); return claim; },
                                       [&](TeamClaim expected, TeamClaim mine) {
                                           yield();
                                           const TeamClaim before = claim;
@@ -57,7 +59,7 @@ struct Team {
     }
     // Until all the words carry the number; whoever makes no claim ends when it has waited long enough.
     TeamWait wait(const std::vector<uint32_t> &words, uint32_t first, uint32_t with, bool claims) {
-        while (true) {
+        for (uint32_t looks = 0;; ++looks) {
             bool there = true;
             for (const uint32_t &w : words) {
                 yield();
@@ -66,7 +68,8 @@ struct Team {
             if (there) return TeamWait::GO_ON;
             if (tired()) {
                 if (!claims) return TeamWait::END;
-                const TeamWait then = give_up(first, with - first);
+                const TeamWait then = give_up(first, with - first, looks > 500);
+                lost = lost || then == TeamWait::LOST;
                 if (then != TeamWait::GO_ON) return then;
             }
         }
@@ -92,7 +95,7 @@ struct Team {
             part[tag & 1u][c] = tag;
             const TeamWait then = wait(total[tag & 1u], first, tag, true);
             if (then == TeamWait::ALONE) return alone(k);
-            if (then == TeamWait::END) return;
+            if (then != TeamWait::GO_ON) return;
             if (k % steps_each == steps_each - 1) {
                 yield();
                 written[k / steps_each][c] = true;
@@ -137,6 +140,7 @@ struct Team {
             const uint32_t some = 1 + gen() % 8;          // accesses in a row
             for (uint32_t k = 0; k < some && !running->ended; ++k) swapcontext(&scheduler, &running->context);
             left -= running->ended;
+            if (wrong && (uint32_t)(claim >> 32) != number && gen() % 16 == 0) claim = (TeamClaim)number << 32 | (1 + gen() % (nodes * steps_each));
         }
         number += nodes * steps_each;
         return true;
@@ -148,7 +152,7 @@ struct Team {
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const uint32_t schedules = (uint32_t)std::atoi(argv[1]), reducers = (uint32_t)std::atoi(argv[2]);
-    uint32_t endless = 0, unwritten = 0;
+    uint32_t endless = 0, unwritten = 0, lost = 0;
     for (uint32_t seed = 0; seed < schedules; ++seed) {
         Team t;
         t.gen.seed(seed);
@@ -156,6 +160,7 @@ int main(int argc, char **argv) {
         t.reducers = reducers;
         t.steps_each = 1 + seed / 2 % 3;
         t.nodes = 2;
+        t.wrong = argc > 3;
         t.patience = seed % 3 == 0 ? 0.5 : seed % 3 == 1 ? 0.9 : 0.98;
         for (auto &w : t.part) w.assign(t.columns, ~0u);
         for (auto &w : t.total) w.assign(t.reducers, ~0u);
@@ -167,7 +172,8 @@ int main(int argc, char **argv) {
         }
         endless += !ended;
         unwritten += ended && !whole;
+        lost += t.lost;
     }
-    std::printf("endless %u unwritten %u\n", endless, unwritten);
+    std::printf("endless %u unwritten %u lost %u\n", endless, unwritten, lost);
     return 0;
 }
