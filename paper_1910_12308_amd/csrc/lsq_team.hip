@@ -5,7 +5,8 @@
 // number of columns alone decides, and publish the totals.  While a workgroup waits for them the next step's rows are on
 // their way to it, and other teams' workgroups share its compute unit.
 // A word carries the number of the step it belongs to beside the value, so a reader simply waits until the word it needs is there.
-// A team's numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too).
+// The numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too), a copy for each workgroup
+// of a team, which it alone reads and moves on: whenever it gets to run, it finds the number of its launch.
 // Workgroups wait for one another, so a launch has no more than fit the chip at once, and such launches of several swarms on one GPU
 // take turns (device_turn).  Where other work keeps some of a team's workgroups from starting, the first of the others that has waited
 // long enough takes the rest of the team's nodes by itself, with the same sums, and the others end.
@@ -27,14 +28,13 @@ constexpr int TEAM_WAVES = 4;
 constexpr int TEAM_THREADS = 64 * TEAM_WAVES;
 constexpr uint32_t REDUCE_WORDS = 8;              // words a thread of a reducing workgroup asks for at a time
 constexpr uint32_t COPIES = 8;                    // of a step's totals, read by every eighth workgroup each: all of them ask for the same lines
-constexpr unsigned long long WAIT_TICKS = 200000000ull;     // 2 s of the 100 MHz wall clock: no wait lasts longer past its patience
+constexpr uint32_t WAIT_TICKS = 200000000u;       // 2 s of the 100 MHz wall clock: no wait lasts longer past its patience
+constexpr unsigned long long MOST_PATIENCE = 1ull << 31;    // both together less than 2^32
 
-// Of a team.  tag: number of the next launch's first step.  claim: TeamClaim, by the workgroup that ends the team's part of the launch,
-// one that holds columns.  started: workgroups of the launch that have begun.
+// Of a team: the claim of its last launch.
 struct LsqTeamHead {
-    unsigned long long claim;
-    uint32_t tag, started;
-    uint32_t pad[28];         // a line each
+    TeamClaim claim;
+    uint32_t pad[30];         // a line each
 };
 
 struct LsqTeamArgs {
@@ -42,11 +42,12 @@ struct LsqTeamArgs {
     float *W;
     LocalSlots slots;
     LsqTeamHead *heads;
+    uint32_t *numbers;        // [team][workgroup] of the next launch's first step
     Word *words, *totals;     // [team][parity; 2: of a workgroup by itself][slice][LSQ_MAX_BATCH], [team][..][COPIES][LSQ_MAX_BATCH]
     float *models;            // [team][d] model of a workgroup by itself between two steps
     DeviceCounters *counters;
     uint64_t d, seed;
-    unsigned long long patience;     // ticks of the 100 MHz clock
+    uint32_t patience;        // ticks of the 100 MHz clock
     uint32_t count, teams, slices, reducers, rows_each, H, m_rows, batch, event;
     float lr;
 };
@@ -73,16 +74,18 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     __shared__ float red[2][TEAM_WAVES][LSQ_MAX_BATCH];
     __shared__ float resid[2][LSQ_MAX_BATCH];
     __shared__ uint32_t rows_of[2][LSQ_MAX_BATCH];
-    __shared__ uint32_t quit;                      // the step that was given up
-    __shared__ uint32_t took;                      // this workgroup's claim was the first
-    __shared__ unsigned long long head_claim;
-    __shared__ uint32_t head_tag;
+    __shared__ uint32_t quit;                      // the step that was given up, or was not begun
+    __shared__ uint32_t ended;                     // and how: TeamWait
+    __shared__ TeamClaim head_claim;
+    __shared__ uint32_t number;                    // of the launch's first step
     constexpr uint32_t WIDTH = 256 * COLS;
     uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    auto thread = [&] { return 64u * wave + lane; };        // threadIdx.x has no register of its own beside the lane
+    auto first = [&] { return wave == 0 && lane == 0; };
     const uint32_t batch = sa.batch, first_row = ROWS * wave, G = sa.slices, all = G + sa.reducers;
     const uint64_t d = sa.d;
-    const float step = sa.lr * ((float)sa.m_rows / (float)batch);
+    const float step = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(sa.lr * ((float)sa.m_rows / (float)batch))));
     // neighbours of a team on one die: workgroups go round the eight dies
     const uint32_t die = blockIdx.x & 7u, spare = gridDim.x & 7u;
     const uint32_t id = die * (gridDim.x >> 3) + min(die, spare) + (blockIdx.x >> 3);
@@ -102,20 +105,18 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     TeamItem it{};
     if (!find(it, team)) return;
     LsqTeamHead *head = sa.heads + team;
-    uint32_t first_tag = 0, tag = 0;
-    unsigned long long patience = sa.patience;
-    bool alone = false;
     // A wave that has waited long enough for the step's totals; false: it waits on.
     auto give_up = [&](uint32_t with, bool overdue) {
         uint32_t then = 0;
-        if ((threadIdx.x & 63u) == 0) {
+        if (lane == 0) {
             then = (uint32_t)out_of_patience(
-                first_tag, with - first_tag, overdue,
+                number, with - number, overdue,
                 [&] { return __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
                 [&](TeamClaim there, TeamClaim mine) { return (TeamClaim)atomicCAS(&head->claim, there, mine); });
-            if (then != (uint32_t)TeamWait::GO_ON) quit = with;
-            if (then == (uint32_t)TeamWait::ALONE) took = 1;
-            if (then == (uint32_t)TeamWait::LOST) atomicOr(&sa.counters->barrier_timeouts, 1u);
+            if (then != (uint32_t)TeamWait::GO_ON) {
+                quit = with;
+                ended = then;
+            }
         }
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)then) != (uint32_t)TeamWait::GO_ON;
     };
@@ -174,24 +175,24 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
         }
     };
     // The residuals into local memory, by one wave.
-    auto wait_total = [&](const Word *from, float b_of_row, uint32_t with, uint32_t parity) {     // lane s: the batch's row s
-        const unsigned long long t0 = wall_clock64();
+    auto wait_total = [&](const Word *from, float b_of_row, uint32_t with, uint32_t parity, uint32_t patience) {     // lane s: the batch's row s
+        const uint32_t t0 = (uint32_t)wall_clock64();
         Word word;
         while (true) {
             word = load_word(at_bytes(uniform(from), 8u * min(lane, batch - 1u)));
             if (__all((uint32_t)(word >> 32) == with)) break;
-            const unsigned long long waited = wall_clock64() - t0;
+            const uint32_t waited = (uint32_t)wall_clock64() - t0;
             if (waited > patience && give_up(with, waited - patience > WAIT_TICKS)) break;
             __builtin_amdgcn_s_sleep(1);
         }
         resid[parity][lane] = __uint_as_float((uint32_t)word) - b_of_row;
     };
     // rows [j * rows_each, ...) of the batch summed over the slices: a thread takes every (256 / rows_each)-th slice of one row
-    auto reduce = [&](uint32_t j, const Word *from, Word *to, uint32_t with, uint32_t parity) {
-        const uint32_t R = sa.rows_each, row = j * R + (threadIdx.x & (R - 1u)), own = min(row, batch - 1u), stride = TEAM_THREADS / R;
-        const unsigned long long t0 = wall_clock64();
+    auto reduce = [&](uint32_t j, const Word *from, Word *to, uint32_t with, uint32_t parity, uint32_t patience) {
+        const uint32_t R = sa.rows_each, row = j * R + (thread() & (R - 1u)), own = min(row, batch - 1u), stride = TEAM_THREADS / R;
+        const uint32_t t0 = (uint32_t)wall_clock64();
         float t = 0.f;
-        for (uint32_t g0 = threadIdx.x / R; __any(g0 < G); g0 += REDUCE_WORDS * stride) {
+        for (uint32_t g0 = thread() / R; __any(g0 < G); g0 += REDUCE_WORDS * stride) {
             Word word[REDUCE_WORDS];
             while (true) {
                 bool there = true;
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
 #pragma unroll
                 for (uint32_t i = 0; i < REDUCE_WORDS; ++i) there = there && (uint32_t)(word[i] >> 32) == with;
                 if (__all(there)) break;
-                if (wall_clock64() - t0 > patience) {
+                if ((uint32_t)wall_clock64() - t0 > patience) {
                     quit = with;                  // and makes no claim
                     break;
                 }
@@ -215,11 +216,11 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
         __syncthreads();
         if (quit == with) return false;
         if (row < batch) {
-            const uint32_t r = threadIdx.x & (R - 1u);
+            const uint32_t r = thread() & (R - 1u);
             float sum = red[parity][0][r];
 #pragma unroll
             for (int w = 1; w < TEAM_WAVES; ++w) sum += red[parity][w][r];
-            for (uint32_t copy = threadIdx.x / R; copy < COPIES; copy += stride) store_word(at_bytes(uniform(to), 8u * (copy * LSQ_MAX_BATCH + row)), with, sum);
+            for (uint32_t copy = thread() / R; copy < COPIES; copy += stride) store_word(at_bytes(uniform(to), 8u * (copy * LSQ_MAX_BATCH + row)), with, sum);
         }
         return true;
     };
@@ -253,27 +254,37 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
     };
 
     auto base_of = [&](uint32_t node) { return sa.base + (uint64_t)node * d; };
-    auto enter = [&] {                            // the team's numbers; false: the launch's part of the team has ended
-        if (threadIdx.x == 0) {
-            head_tag = __hip_atomic_load(&head->tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            head_claim = __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            atomicAdd(&head->started, 1u);        // has read them
-            quit = head_tag - 1u;
-            took = 0;
+    if (first()) {
+        number = __hip_atomic_load(sa.numbers + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        head_claim = __hip_atomic_load(&head->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        quit = (uint32_t)(head_claim >> 32) == number ? number : number - 1u;
+        ended = (uint32_t)TeamWait::END;
+    }
+    __syncthreads();
+    uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)number);
+    auto move_on = [&] {
+        if (!first()) return;
+        const bool left = quit == tag;
+        uint32_t last = tag;                      // past the last step
+        if (left) {
+            TeamItem rest = it;
+            do ++last; while (advance(rest));
         }
-        __syncthreads();
-        tag = first_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)head_tag);
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(head_claim >> 32)) != first_tag;
+        __hip_atomic_store(sa.numbers + id, next_number(number, last - number), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // All steps are left to all: a claim in every launch, so that none is old enough for the numbers to have come round to it.
+        if (!left && member == 0) atomicCAS(&head->claim, head_claim, (TeamClaim)number << 32 | (last - number));
     };
-    if (member >= G) {
-        if (!enter()) return;
-        do {
-            if (!reduce(member - G, offered(tag & 1u), summed(tag & 1u), tag, tag & 1u)) break;
-            ++tag;
-        } while (advance(it));
+    const bool begun = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(head_claim >> 32)) != tag;     // else the rest has been taken
+    if (!begun || member >= G) {
+        if (begun)
+            do {
+                if (!reduce(member - G, offered(tag & 1u), summed(tag & 1u), tag, tag & 1u, sa.patience)) break;
+                ++tag;
+            } while (advance(it));
+        move_on();
         return;
-    } else {
+    }
+    {
         f4 a[ROWS][COLS], w[COLS];
         float b_of_row;
         auto begin = [&](uint32_t rows) {         // the step's rows on their way
@@ -281,8 +292,6 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             fetch(it, member, rows, a);
             b_of_row = sa.b[(uint64_t)it.node * sa.m_rows + rows];
         };
-        if (false) return;
-        if (!enter()) return;
         begin(drawn(it));
         while (true) {
             const uint32_t parity = tag & 1u;
@@ -290,13 +299,13 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             publish(a, w, member, offered(parity), tag);
             TeamItem then = it;
             const bool more = advance(then);
-            if (wave == 0) wait_total(summed(parity) + (member % COPIES) * LSQ_MAX_BATCH, b_of_row, tag, parity);
+            if (wave == 0) wait_total(summed(parity) + (member % COPIES) * LSQ_MAX_BATCH, b_of_row, tag, parity, sa.patience);
             if (wave == 1 && more) rows_of[parity][lane] = drawn(then);      // the next step's, meanwhile
             __syncthreads();
-            alone = quit == tag;
-            if (alone) break;
+            if (quit == tag) break;
             const uint32_t rows = rows_of[parity][lane];
             update(a, parity, parity, w);
+            asm volatile("" : "+v"(lane));
             if (it.q + 1 == it.H) store_model(sa.W + (uint64_t)it.node * d, member, w);
             ++tag;
             if (!more) break;
@@ -304,18 +313,9 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             begin(rows);
         }
     }
-    // The end of the team's part: by its first workgroup, all totals being out, or by the one that took the rest.
-    if (alone ? took == 0 : member != 0) return;
-    if (!alone) {
-        if (threadIdx.x == 0) {
-            const TeamClaim unclaimed = head_claim;
-            head_tag = atomicCAS(&head->claim, unclaimed, (TeamClaim)first_tag << 32 | (tag - first_tag)) == unclaimed;
-        }
-        __syncthreads();
-        if (!head_tag) return;
-    }
-    if (alone) {
-        patience = WAIT_TICKS;                   // what it waits for it has stored itself
+    move_on();
+    if (ended == (uint32_t)TeamWait::LOST && first()) atomicOr(&sa.counters->barrier_timeouts, 1u);
+    if (ended == (uint32_t)TeamWait::ALONE) {
         it.q = 0;
         ++tag;                                    // `quit` holds the one that was given up
         uint32_t parity = 0;
@@ -332,11 +332,11 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
                 fetch(it, g, rows, a);
                 publish(a, w, g, offered(2), tag);
             }
-            for (uint32_t j = 0; j < sa.reducers && reduce(j, offered(2), summed(2), tag, parity); ++j) parity ^= 1u;
-            if (wave == 0 && quit != tag) wait_total(summed(2), b_of_row, tag, 0);
+            for (uint32_t j = 0; j < sa.reducers && reduce(j, offered(2), summed(2), tag, parity, WAIT_TICKS); ++j) parity ^= 1u;
+            if (wave == 0 && quit != tag) wait_total(summed(2), b_of_row, tag, 0, WAIT_TICKS);
             __syncthreads();
             if (quit == tag) {
-                if (threadIdx.x == 0) atomicOr(&sa.counters->barrier_timeouts, 1u);
+                if (first()) atomicOr(&sa.counters->barrier_timeouts, 1u);
                 break;
             }
             for (uint32_t g = 0; g < G; ++g, parity ^= 1u) {
@@ -348,17 +348,6 @@ __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kern
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // the next step reads what other waves have written
             __syncthreads();
         }
-        if (threadIdx.x == 0) {                   // the number may go on once no workgroup of this launch has yet to read it
-            const unsigned long long t0 = wall_clock64();
-            while (__hip_atomic_load(&head->started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
-                if (wall_clock64() - t0 > WAIT_TICKS) { atomicOr(&sa.counters->barrier_timeouts, 1u); break; }
-                __builtin_amdgcn_s_sleep(64);
-            }
-        }
-    }
-    if (threadIdx.x == 0) {
-        atomicSub(&head->started, all);
-        __hip_atomic_store(&head->tag, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -391,6 +380,7 @@ struct LsqTeams {
     int device;
     uint32_t most, slices, reducers, rows_each;   // most: teams whose workgroups fit the chip together
     LsqTeamHead *heads;
+    uint32_t *numbers;
     Word *words, *totals;
     float *models;
 };
@@ -414,13 +404,14 @@ hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     LsqTeams t{};
     t.device = device; t.most = (uint32_t)most; t.slices = (uint32_t)slices; t.reducers = reducers; t.rows_each = rows_each;
     const uint64_t head_bytes = sizeof(LsqTeamHead) * most, words = most * 3 * slices * LSQ_MAX_BATCH, totals = most * 3 * COPIES * LSQ_MAX_BATCH;
-    const uint64_t exchange = head_bytes + sizeof(Word) * (words + totals);
-    if ((e = hipMalloc((void **)&t.heads, exchange + sizeof(float) * most * d)) != hipSuccess) return e;
+    const uint64_t exchange = head_bytes + sizeof(Word) * (words + totals), groups = most * (slices + reducers);
+    if ((e = hipMalloc((void **)&t.heads, exchange + sizeof(float) * most * d + sizeof(uint32_t) * groups)) != hipSuccess) return e;
     t.words = (Word *)(t.heads + most);
     t.totals = t.words + words;
     t.models = (float *)(t.totals + totals);
-    // numbers begin at 0; no word carries one that is used soon, no claim one at all
-    if ((e = hipMemset(t.heads, 0xFF, exchange)) != hipSuccess || (e = hipMemset2D(&t.heads->tag, sizeof(LsqTeamHead), 0, 2 * sizeof(uint32_t), most)) != hipSuccess) {
+    t.numbers = (uint32_t *)(t.models + most * d);
+    // numbers begin at 0 and stay even; no word carries one that is used soon, no claim one at all
+    if ((e = hipMemset(t.heads, 0xFF, exchange)) != hipSuccess || (e = hipMemset(t.numbers, 0, sizeof(uint32_t) * groups)) != hipSuccess) {
         (void)hipFree(t.heads);
         return e;
     }
@@ -453,7 +444,7 @@ hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, 
                             uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
     const LsqTeams &t = *o.teams;
     const uint32_t rounds = (count + t.most - 1) / t.most, teams = (count + rounds - 1) / rounds;
-    const LsqTeamArgs a{base, o.A, o.b, W, slots, t.heads, t.words, t.totals, t.models, counters, d, seed, o.patience,
+    const LsqTeamArgs a{base, o.A, o.b, W, slots, t.heads, t.numbers, t.words, t.totals, t.models, counters, d, seed, (uint32_t)std::min(o.patience, MOST_PATIENCE),
                         count, teams, t.slices, t.reducers, t.rows_each, H, o.m_rows, o.batch, event, lr};
     DeviceTurn &turn = device_turns[t.device];
     std::lock_guard<std::mutex> lock(turn.mutex);

@@ -35,4 +35,8 @@ SWARM_TEAM_FN TeamWait out_of_patience(uint32_t first, uint32_t done, bool overd
     return overdue ? TeamWait::LOST : TeamWait::GO_ON;
 }
 
+// Number of the next launch's first step, by the steps of this one.  A workgroup by itself numbers the steps of a node that was begun once
+// more, past the others': twice the steps are more than it needs, so that no word carries a number of the next launch.
+SWARM_TEAM_FN uint32_t next_number(uint32_t first, uint32_t steps) { return first + 2u * steps; }
+
 }  // namespace swarm

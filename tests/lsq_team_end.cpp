@@ -2,8 +2,9 @@
 // generator runs in any order, changing after every access to what they share, and every look for words that are not there may be the
 // last one that a workgroup has patience for.  What such a workgroup does then is the kernel's own code (lsq_team_end.hpp).
 //   lsq_team_end schedules reducers [wrong]
-// runs so many random schedules and prints how many of them did not end, in how many a slice of a node was not written, and in how many
-// a workgroup gave up with an error.  wrong: a claim that nobody made lies on the way, so that workgroups wait for what does not come.
+// runs so many random schedules and prints how many of them did not end, in how many a slice of a node was not written, in how many a
+// workgroup gave up with an error, and in how many the next launch's numbers were not the same for all, or had been used.  wrong: a claim that nobody made lies on the way, so that workgroups wait for what does not come.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -41,11 +42,12 @@ struct Team {
     uint32_t columns, reducers, steps_each, nodes;        // nodes: that the team takes one after the other in a launch
     std::vector<uint32_t> part[2], total[2];              // numbers of the words, by the parity of the number
     TeamClaim claim = ~0ull;
-    uint32_t number = 0;                                  // of the next launch's first step
+    std::vector<uint32_t> number;                         // of the next launch's first step, a copy for each workgroup
+    uint32_t highest = 0;                                 // number that a word has carried
     std::vector<std::vector<bool>> written;               // [node][column]
     std::mt19937_64 gen;
     double patience;                                      // chance that a workgroup waits on
-    bool wrong = false, lost = false;
+    bool wrong = false, lost = false, numbered = true;
 
     bool tired() { return std::generate_canonical<double, 32>(gen) > patience; }
     TeamWait give_up(uint32_t first, uint32_t done, bool overdue) {
@@ -74,48 +76,59 @@ struct Team {
             }
         }
     }
-    void alone(uint32_t step) {
-        for (uint32_t node = step / steps_each; node < nodes; ++node)
+    void carry(uint32_t tag) { highest = std::max(highest, tag); }
+    void alone(uint32_t step, uint32_t tag) {
+        for (uint32_t k = step / steps_each * steps_each; k < nodes * steps_each; ++k) {
+            carry(++tag);
             for (uint32_t c = 0; c < columns; ++c) {
                 yield();
-                written[node][c] = true;
+                if (k % steps_each == steps_each - 1) written[k / steps_each][c] = true;
             }
+        }
     }
     bool claimed(uint32_t first) {
         yield();
         return (uint32_t)(claim >> 32) == first;
     }
+    void move_on(uint32_t m, uint32_t first) {
+        yield();
+        number[m] = swarm::next_number(first, nodes * steps_each);
+    }
     void column(uint32_t c) {
         yield();
-        const uint32_t first = number, steps = nodes * steps_each;
-        if (claimed(first)) return;
-        for (uint32_t k = 0; k < steps; ++k) {
+        const uint32_t first = number[c], steps = nodes * steps_each;
+        TeamWait then = claimed(first) ? TeamWait::END : TeamWait::GO_ON;
+        uint32_t k = 0;
+        for (; k < steps && then == TeamWait::GO_ON; ++k) {
             const uint32_t tag = first + k;
             yield();
-            part[tag & 1u][c] = tag;
-            const TeamWait then = wait(total[tag & 1u], first, tag, true);
-            if (then == TeamWait::ALONE) return alone(k);
-            if (then != TeamWait::GO_ON) return;
+            carry(part[tag & 1u][c] = tag);
+            then = wait(total[tag & 1u], first, tag, true);
+            if (then != TeamWait::GO_ON) break;
             if (k % steps_each == steps_each - 1) {
                 yield();
                 written[k / steps_each][c] = true;
             }
         }
-        if (c == 0 && !claimed(first)) {                  // the kernel's is one compare and exchange
+        move_on(c, first);
+        if (then == TeamWait::ALONE) alone(k, first + k);
+        if (then == TeamWait::GO_ON && c == 0 && !claimed(first)) {           // the kernel's is one compare and exchange
             const TeamClaim mine = (TeamClaim)first << 32 | steps;
             if ((uint32_t)(claim >> 32) != first) claim = mine;
         }
     }
     void reducer(uint32_t j) {
         yield();
-        const uint32_t first = number, steps = nodes * steps_each;
-        if (claimed(first)) return;
-        for (uint32_t k = 0; k < steps; ++k) {
+        const uint32_t first = number[columns + j], steps = nodes * steps_each;
+        TeamWait then = claimed(first) ? TeamWait::END : TeamWait::GO_ON;
+        for (uint32_t k = 0; k < steps && then == TeamWait::GO_ON; ++k) {
             const uint32_t tag = first + k;
-            if (wait(part[tag & 1u], first, tag, false) == TeamWait::END) return;
+            then = wait(part[tag & 1u], first, tag, false);
+            if (then != TeamWait::GO_ON) break;
             yield();
-            total[tag & 1u][j] = tag;
+            carry(total[tag & 1u][j] = tag);
         }
+        move_on(columns + j, first);
     }
     // One launch; false: not all its workgroups end.
     bool launch() {
@@ -132,17 +145,21 @@ struct Team {
             makecontext(&f->context, enter_fiber, 0);
             fibers.push_back(std::move(f));
         }
-        size_t left = fibers.size();
+        size_t left = fibers.size(), late = gen() % 3 ? 0 : 1 + gen() % left;          // the last to be let in when all others have ended
+        const size_t order = gen() % left;
         for (size_t turns = 0; left; ++turns) {
             if (turns == 10000 * fibers.size()) return false;
-            running = fibers[gen() % fibers.size()].get();
+            const size_t some_one = gen() % fibers.size();
+            if (left > late && (some_one + order) % fibers.size() < late) continue;
+            if (left <= late) late = 0;
+            running = fibers[some_one].get();
             if (running->ended) continue;
             const uint32_t some = 1 + gen() % 8;          // accesses in a row
             for (uint32_t k = 0; k < some && !running->ended; ++k) swapcontext(&scheduler, &running->context);
             left -= running->ended;
-            if (wrong && (uint32_t)(claim >> 32) != number && gen() % 16 == 0) claim = (TeamClaim)number << 32 | (1 + gen() % (nodes * steps_each));
+            if (wrong && (uint32_t)(claim >> 32) != number[0] && gen() % 16 == 0) claim = (TeamClaim)number[0] << 32 | (1 + gen() % (nodes * steps_each));
         }
-        number += nodes * steps_each;
+        for (const uint32_t v : number) numbered = numbered && v == number[0] && v > highest;
         return true;
     }
 };
@@ -152,7 +169,7 @@ struct Team {
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const uint32_t schedules = (uint32_t)std::atoi(argv[1]), reducers = (uint32_t)std::atoi(argv[2]);
-    uint32_t endless = 0, unwritten = 0, lost = 0;
+    uint32_t endless = 0, unwritten = 0, lost = 0, misnumbered = 0;
     for (uint32_t seed = 0; seed < schedules; ++seed) {
         Team t;
         t.gen.seed(seed);
@@ -162,6 +179,7 @@ int main(int argc, char **argv) {
         t.nodes = 2;
         t.wrong = argc > 3;
         t.patience = seed % 3 == 0 ? 0.5 : seed % 3 == 1 ? 0.9 : 0.98;
+        t.number.assign(t.columns + reducers, 0);
         for (auto &w : t.part) w.assign(t.columns, ~0u);
         for (auto &w : t.total) w.assign(t.reducers, ~0u);
         bool ended = true, whole = true;
@@ -173,7 +191,8 @@ int main(int argc, char **argv) {
         endless += !ended;
         unwritten += ended && !whole;
         lost += t.lost;
+        misnumbered += !t.numbered;
     }
-    std::printf("endless %u unwritten %u lost %u\n", endless, unwritten, lost);
+    std::printf("endless %u unwritten %u lost %u misnumbered %u\n", endless, unwritten, lost, misnumbered);
     return 0;
 }

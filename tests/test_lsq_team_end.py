@@ -21,7 +21,7 @@ def model(tmp_path_factory):
 
 @pytest.mark.parametrize("reducers", [1, 2, 4, 16])
 def test_every_schedule_ends_and_every_slice_is_written(model, reducers):
-    assert model(4000 if reducers < 16 else 500, reducers) == ["endless", "0", "unwritten", "0", "lost", "0"]
+    assert model(4000 if reducers < 16 else 500, reducers) == ["endless", "0", "unwritten", "0", "lost", "0", "misnumbered", "0"]
 
 
 # The bound of a wait for totals that a claim says are there: it ends although they are not
