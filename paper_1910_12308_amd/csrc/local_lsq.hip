@@ -479,8 +479,9 @@ hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
         o.wide_slices = wide_slices(d, n);
         o.by_rows = o.wide_slices == 1 && lsq_by_rows(d, n, o.batch);
         o.wide_rows = (uint64_t)n * o.wide_slices;
-        if ((o.wide_slices > 1 || teams_pay(d, o.batch)) && (e = alloc_lsq_teams(o, d, n)) != hipSuccess) return e;
-        return hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH);
+        if ((e = hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH)) != hipSuccess) return e;
+        if (o.wide_slices > 1 || teams_pay(d, o.batch)) alloc_lsq_teams(o, d, n);
+        return hipSuccess;
     }
     const uint64_t slices = (d + SLICE - 1) / SLICE;
     o.part_bytes = sizeof(unsigned long long) * n * 2 * slices * LSQ_MAX_BATCH;

@@ -385,45 +385,44 @@ struct LsqTeams {
     float *models;
 };
 
-// o.teams stays null where not even one team fits, or where the runtime cannot tell.
-hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
+// o.teams stays null where not even one team fits, where memory is short, or where the runtime cannot tell: the wide form serves.
+void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     int device = 0, units = 0, each = 0;
     if (hipGetDevice(&device) != hipSuccess || device >= MAX_DEVICES ||
         hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&each, (const void *)team_kernel(o.batch), TEAM_THREADS, 0) != hipSuccess) {
         (void)hipGetLastError();
-        return hipSuccess;
+        return;
     }
-    hipError_t e;
     const uint64_t width = o.batch <= 8 ? 1024 : o.batch <= 32 ? 512 : 256, slices = (d + width - 1) / width;
     uint32_t rows_each = 4;                       // rows a reducing workgroup adds: REDUCE_WORDS words per thread where four rows have no more
     while (rows_each < o.batch && 2 * rows_each * slices <= REDUCE_WORDS * TEAM_THREADS) rows_each *= 2;
     const uint32_t reducers = (o.batch + rows_each - 1) / rows_each;
     const uint64_t most = std::min<uint64_t>((uint64_t)units * each / (slices + reducers), n);
-    if (most == 0) return hipSuccess;
+    if (most == 0) return;
     LsqTeams t{};
     t.device = device; t.most = (uint32_t)most; t.slices = (uint32_t)slices; t.reducers = reducers; t.rows_each = rows_each;
     const uint64_t head_bytes = sizeof(LsqTeamHead) * most, words = most * 3 * slices * LSQ_MAX_BATCH, totals = most * 3 * COPIES * LSQ_MAX_BATCH;
     const uint64_t exchange = head_bytes + sizeof(Word) * (words + totals), groups = most * (slices + reducers);
-    if ((e = hipMalloc((void **)&t.heads, exchange + sizeof(float) * most * d + sizeof(uint32_t) * groups)) != hipSuccess) return e;
+    if (hipMalloc((void **)&t.heads, exchange + sizeof(float) * most * d + sizeof(uint32_t) * groups) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
     t.words = (Word *)(t.heads + most);
     t.totals = t.words + words;
     t.models = (float *)(t.totals + totals);
     t.numbers = (uint32_t *)(t.models + most * d);
-    // numbers begin at 0 and stay even; no word carries one that is used soon, no claim one at all
-    if ((e = hipMemset(t.heads, 0xFF, exchange)) != hipSuccess || (e = hipMemset(t.numbers, 0, sizeof(uint32_t) * groups)) != hipSuccess) {
-        (void)hipFree(t.heads);
-        return e;
-    }
     DeviceTurn &turn = device_turns[device];
     std::lock_guard<std::mutex> lock(turn.mutex);
-    if (turn.swarms == 1 && (e = hipEventCreateWithFlags(&turn.last, hipEventDisableTiming)) != hipSuccess) {
+    // numbers begin at 0 and stay even; no word carries one that is used soon, no claim one at all
+    if (hipMemset(t.heads, 0xFF, exchange) != hipSuccess || hipMemset(t.numbers, 0, sizeof(uint32_t) * groups) != hipSuccess ||
+        (turn.swarms == 1 && hipEventCreateWithFlags(&turn.last, hipEventDisableTiming) != hipSuccess)) {
+        (void)hipGetLastError();
         (void)hipFree(t.heads);
-        return e;
+        return;
     }
     turn.swarms += 1;
     o.teams = new LsqTeams(t);
-    return hipSuccess;
 }
 
 void free_lsq_teams(LsqObjective &o) {

@@ -72,7 +72,7 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
 hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, const SeqDesc &one, uint32_t count,
                                LsqObjective &o, float lr, hipStream_t st);
 void free_lsq(LsqObjective &o);
-hipError_t alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n);
+void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n);
 void free_lsq_teams(LsqObjective &o);
 hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, const LocalSlots &slots, DeviceCounters *counters,
                             uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st);

@@ -9,6 +9,8 @@
 //   host_calls mlp_fp32 n in hid out batch H nodes         the same in float32
 //   host_calls mlp_room n in hid out batch H nodes room    as mlp, with `room` bytes of device memory left for the arithmetic; and
 //                                                          device memory with the objective, the arithmetic, and back in float32
+// In the environment, for the least-squares objective: GROUPS_PER_UNIT, workgroups that fit one of 256 compute units (else the
+// runtime cannot tell), and ROOM, bytes of device memory left for it.
 // graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
 #include <cxxabi.h>
 #include <cstdio>
@@ -26,6 +28,7 @@ struct Dim3 { uint32_t x, y, z; };
 bool logging = false;
 int launches = 0, fail_at = 0, last_error = 0;
 size_t in_use = 0, memory = ~(size_t)0;                            // device memory
+const char *setting(const char *name) { return std::getenv(name); }
 std::map<void *, size_t> &allocations() { static std::map<void *, size_t> a; return a; }
 struct Call { Dim3 grid, block; size_t shared; void *stream; } pushed;
 std::map<const void *, std::string> &kernels() { static std::map<const void *, std::string> k; return k; }
@@ -58,6 +61,12 @@ int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3 block, void **, size_t s
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int) { return "stand-in error"; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *value, int, int) { *value = 256; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *groups, const void *, int, size_t) {
+    if (!setting("GROUPS_PER_UNIT")) { last_error = 1; return 1; }
+    *groups = std::atoi(setting("GROUPS_PER_UNIT"));
+    return 0;
+}
 int hipHostMalloc(void **p, size_t n, unsigned) { *p = std::calloc(n ? n : 1, 1); return *p ? 0 : 2; }
 int hipHostFree(void *p) { std::free(p); return 0; }
 int hipMalloc(void **p, size_t n) {
@@ -168,8 +177,10 @@ int main(int argc, char **argv) {
     swarm_t h = nullptr;
     const float *data = reinterpret_cast<const float *>(64);        // objective data: the host never reads them
     if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
+    if (setting("ROOM")) memory = in_use + std::strtoull(setting("ROOM"), nullptr, 10);
     swarm_status rc = batch ? swarm_set_objective_lsq(h, data, data, 64, batch) : swarm_set_objective_diag(h, data, data, 0.1f);
     if (rc != SWARM_OK) { std::printf("objective: %s\n", swarm_last_error(h)); return 1; }
+    memory = ~(size_t)0;
     float *snapshots = nullptr;
     swarm_models_ptr(h, SWARM_MODELS_SNAP, &snapshots);              // created ahead of the log
     logging = true;

@@ -21,8 +21,9 @@ def host_calls(tmp_path_factory):
                     os.path.join(HERE, "host_calls.cpp"), "-o", exe, "-L", package, "-l:libswarm.so", "-Wl,-rpath," + package,
                     "-Wl,--allow-shlib-undefined"], check=True)
 
-    def call(*args):
-        out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True)
+    def call(*args, **settings):
+        out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True,
+                             env={**os.environ, **{k: str(v) for k, v in settings.items()}})
         assert out.returncode == 0, out.stdout + out.stderr
         return out.stdout.splitlines()
     return call
@@ -90,6 +91,13 @@ def test_wide_least_squares_steps(host_calls, n, d, batch, kernel, threads, grid
     slices = H + 1 if kernel.endswith("false>") else 1
     assert [ln for ln in out if ln.startswith("launch")] == [f"launch {kernel} grid {grid} block {threads} shared 0"] * slices
     assert out[-1] == "status 0"
+
+
+# The wide form's exchange takes 2 x 64 x 5 x 64 floats, that of one team with its model 4104 floats and more
+@pytest.mark.parametrize("room,teams", [(163840 + 10_000_000, True), (163840 + 4 * 4104, False), (163840, False)])
+def test_least_squares_where_memory_is_short_for_teams(host_calls, room, teams):
+    out = host_calls("steps", 64, 4104, 8, 3, 32, "ring", GROUPS_PER_UNIT=5, ROOM=room)
+    assert kernels(out) == (["lsq_team_kernel"] if teams else ["lsq_wide_kernel"] * 4) and out[-1] == "status 0"
 
 
 @pytest.mark.parametrize("fail", [0, 1, 2, 3, 4])
