@@ -8,7 +8,7 @@
 // The numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too), a copy for each workgroup
 // of a team, which it alone reads and moves on: whenever it gets to run, it finds the number of its launch.
 // Workgroups wait for one another, so a launch has no more than fit the chip at once, and such launches of several swarms on one GPU
-// take turns (device_turn).  Where other work keeps some of a team's workgroups from starting, the first of the others that has waited
+// take turns (DeviceTurn).  Where other work keeps some of a team's workgroups from starting, the first of the others that has waited
 // long enough takes the rest of the team's nodes by itself, with the same sums, and the others end.
 #include <algorithm>
 #include <mutex>
@@ -364,7 +364,9 @@ static TeamKernel team_kernel(uint32_t batch) {
     }
 }
 
-// Launches of several swarms on one GPU one after the other: each waits for the last one, where there are several such swarms.
+// Launches of several swarms on one GPU one after the other: each waits for the last one, where there are several such swarms.  With one
+// swarm no launch is recorded, so the GPU is waited for when a second one joins.  Launches captured into a graph take no turns:
+// two that run at once may each hold a part of the chip until one of a team's workgroups has waited long enough and takes the rest.
 namespace {
 struct DeviceTurn {
     std::mutex mutex;
@@ -416,7 +418,8 @@ void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     std::lock_guard<std::mutex> lock(turn.mutex);
     // numbers begin at 0 and stay even; no word carries one that is used soon, no claim one at all
     if (hipMemset(t.heads, 0xFF, exchange) != hipSuccess || hipMemset(t.numbers, 0, sizeof(uint32_t) * groups) != hipSuccess ||
-        (turn.swarms == 1 && hipEventCreateWithFlags(&turn.last, hipEventDisableTiming) != hipSuccess)) {
+        (turn.swarms == 1 &&
+         (hipDeviceSynchronize() != hipSuccess || hipEventCreateWithFlags(&turn.last, hipEventDisableTiming) != hipSuccess))) {
         (void)hipGetLastError();
         (void)hipFree(t.heads);
         return;

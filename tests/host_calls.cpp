@@ -5,6 +5,7 @@
 //   host_calls interact n d bits H batch graph             swarm_interact(0, a neighbour)
 //   host_calls steps    n d bits H batch graph             swarm_local_steps(all)
 //   host_calls rounds   n d bits H fail count              `count` rounds of one pair; the launch numbered `fail` fails (0: none)
+//   host_calls two      n d bits H batch graph             the same of one swarm, then of a second one that is set up after it
 //   host_calls mlp      n in hid out batch H nodes         swarm_local_steps(0 .. nodes - 1) of perceptrons, bf16x3 arithmetic
 //   host_calls mlp_fp32 n in hid out batch H nodes         the same in float32
 //   host_calls mlp_room n in hid out batch H nodes room    as mlp, with `room` bytes of device memory left for the arithmetic; and
@@ -97,6 +98,9 @@ int hipEventCreate(void **e) { return hipEventCreateWithFlags(e, 0); }
 int hipEventDestroy(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0.f; return 0; }
 int hipEventRecord(void *e, void *) { if (logging) std::printf("record %d\n", event_number(e)); return 0; }
+int hipDeviceSynchronize() { if (logging) std::printf("wait for all\n"); return 0; }
+int hipStreamIsCapturing(void *, int *capturing) { *capturing = 0; return 0; }
+int hipStreamWaitEvent(void *, void *e, unsigned) { if (logging) std::printf("stream waits %d\n", event_number(e)); return 0; }
 int hipEventSynchronize(void *e) { if (logging) std::printf("wait %d\n", event_number(e)); return 0; }
 }
 
@@ -192,6 +196,15 @@ int main(int argc, char **argv) {
         rc = swarm_interact(h, edges[0], edges[1]);
     } else if (call == "steps") {
         rc = swarm_local_steps(h, nullptr, 0);
+    } else if (call == "two") {
+        swarm_t second = nullptr;
+        rc = swarm_local_steps(h, nullptr, 0);
+        if (rc == SWARM_OK) rc = swarm_init(&c, nullptr, nullptr, &second);
+        if (rc == SWARM_OK) rc = swarm_set_objective_lsq(second, data, data, 64, batch);
+        if (rc == SWARM_OK) rc = swarm_local_steps(second, nullptr, 0);
+        if (rc == SWARM_OK) rc = swarm_local_steps(h, nullptr, 0);
+        swarm_destroy(second);
+        if (rc == SWARM_OK) rc = swarm_local_steps(h, nullptr, 0);
     } else if (call == "rounds") {
         fail_at = std::atoi(argv[6]);
         const uint32_t pair[2] = {0, 1};

@@ -100,6 +100,17 @@ def test_least_squares_where_memory_is_short_for_teams(host_calls, room, teams):
     assert kernels(out) == (["lsq_team_kernel"] if teams else ["lsq_wide_kernel"] * 4) and out[-1] == "status 0"
 
 
+def test_teams_of_several_swarms_take_turns(host_calls):
+    """One swarm alone is not held up; when a second joins, what the first has launched is waited for; from then on a launch waits
+    for the one before, whoever made that."""
+    out = host_calls("two", 64, 4104, 8, 3, 32, "ring", GROUPS_PER_UNIT=5)
+    team, event = "launch lsq_team_kernel<8, 2, true>", next(ln.split()[2] for ln in out if ln.startswith("stream waits"))
+    calls = [ln.split(" grid")[0] for ln in out
+             if ln.startswith(("launch", "stream waits")) or ln in (f"record {event}", "wait for all")]
+    assert calls == [team, "wait for all", team, f"record {event}", f"stream waits {event}", team, f"record {event}", team]
+    assert out[-1] == "status 0"
+
+
 @pytest.mark.parametrize("fail", [0, 1, 2, 3, 4])
 def test_staging_slot_is_guarded_until_its_readers_are_done(host_calls, fail):
     """Small rounds are described in a staging slot that their kernels read: the event that frees the slot is recorded behind
