@@ -29,6 +29,11 @@ constexpr int TEAM_THREADS = 64 * TEAM_WAVES;
 constexpr uint32_t REDUCE_WORDS = 8;              // words a thread of a reducing workgroup asks for at a time
 constexpr uint32_t COPIES = 8;                    // of a step's totals, read by every eighth workgroup each: all of them ask for the same lines
 constexpr uint32_t WAIT_TICKS = 200000000u;       // 2 s of the 100 MHz wall clock: no wait lasts longer past its patience
+// Workgroups that run on a compute unit at once, at most.  The runtime counts vector registers and local memory (seven at a batch of
+// 16), not the 800 scalar registers of a SIMD, of which a wave of this kernel takes 112 and 16 for the trap handler: six.  With seven,
+// 64 nodes x 131072 columns, batch 16, one step took 24.4 ms, until a workgroup of every team had waited long enough, with six
+// 141 us; 100 x 65536 166 and 102, 200 x 16392 52 and 44.
+constexpr int TEAM_GROUPS_PER_UNIT = 6;
 constexpr unsigned long long MOST_PATIENCE = 1ull << 31;    // both together less than 2^32
 
 // Of a team: the claim of its last launch.
@@ -400,7 +405,7 @@ void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     uint32_t rows_each = 4;                       // rows a reducing workgroup adds: REDUCE_WORDS words per thread where four rows have no more
     while (rows_each < o.batch && 2 * rows_each * slices <= REDUCE_WORDS * TEAM_THREADS) rows_each *= 2;
     const uint32_t reducers = (o.batch + rows_each - 1) / rows_each;
-    const uint64_t most = std::min<uint64_t>((uint64_t)units * each / (slices + reducers), n);
+    const uint64_t most = std::min<uint64_t>((uint64_t)units * std::min(each, TEAM_GROUPS_PER_UNIT) / (slices + reducers), n);
     if (most == 0) return;
     LsqTeams t{};
     t.device = device; t.most = (uint32_t)most; t.slices = (uint32_t)slices; t.reducers = reducers; t.rows_each = rows_each;

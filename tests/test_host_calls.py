@@ -100,6 +100,13 @@ def test_least_squares_where_memory_is_short_for_teams(host_calls, room, teams):
     assert kernels(out) == (["lsq_team_kernel"] if teams else ["lsq_wide_kernel"] * 4) and out[-1] == "status 0"
 
 
+# Whatever the runtime counts, no more workgroups than run at once: six on each of 256 compute units
+@pytest.mark.parametrize("counted,grid", [(5, 1161), (6, 1290), (7, 1290), (8, 1290)])
+def test_workgroups_of_teams_run_at_once(host_calls, counted, grid):
+    out = host_calls("steps", 100, 65536, 8, 1, 16, "ring", GROUPS_PER_UNIT=counted)
+    assert [ln for ln in out if ln.startswith("launch")] == [f"launch lsq_team_kernel<4, 2, true> grid {grid} 1 block 256 shared 0"]
+
+
 def test_teams_of_several_swarms_take_turns(host_calls):
     """One swarm alone is not held up; when a second joins, what the first has launched is waited for; from then on a launch waits
     for the one before, whoever made that."""
