@@ -473,14 +473,24 @@ static bool teams_pay(uint64_t d, uint32_t batch) {
     return batch >= 64 ? d >= 2048 : batch >= 32 ? d >= 4096 : batch >= 16 && d >= 16384;
 }
 
-hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs) {
+// Of the swarms whose columns are cut, those with few rows in all whose workgroups of the wide form run at once, four per compute
+// unit: teams have to take all their nodes at once there, too, for with their reducing workgroups in a second round they lose more by
+// the exchange than they gain by reading rows once.  us, the wide form and teams in two rounds:
+//   124 x 8192, batch 4, H = 1     8.7   12.0    100 x 9304, batch 8, H = 1    10.7   13.0    70 x 14336, batch 4, H = 3    25.7   27.3
+//   64 x 16384, batch 4, H = 1     9.2   12.0    40 x 25600, batch 8, H = 1    12.7   13.5    16 x 65536, batch 4, H = 1    12.0   12.3
+//   64 x 16384, batch 4, H = 2    17.8   19.7    64 x 16384, batch 8, H = 2    26.4   23.8     8 x 131072, batch 4, H = 1   15.7   13.0
+static bool one_round_only(uint32_t n, uint32_t slices, uint32_t batch, uint32_t H) {
+    return batch <= 8 && batch * H < 16 && slices > 1 && slices <= 32 && n * slices <= 1024;
+}
+
+hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, uint32_t H, bool merge_runs) {
     hipError_t e;
     if (!lsq_split_fits(d, n)) {
         o.wide_slices = wide_slices(d, n);
         o.by_rows = o.wide_slices == 1 && lsq_by_rows(d, n, o.batch);
         o.wide_rows = (uint64_t)n * o.wide_slices;
         if ((e = hipMalloc((void **)&o.wide_part, sizeof(float) * 2 * o.wide_rows * LSQ_MAX_BATCH)) != hipSuccess) return e;
-        if (o.wide_slices > 1 || teams_pay(d, o.batch)) alloc_lsq_teams(o, d, n);
+        if (o.wide_slices > 1 || teams_pay(d, o.batch)) alloc_lsq_teams(o, d, n, one_round_only(n, o.wide_slices, o.batch, H));
         return hipSuccess;
     }
     const uint64_t slices = (d + SLICE - 1) / SLICE;

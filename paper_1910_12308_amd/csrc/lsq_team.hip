@@ -392,8 +392,8 @@ struct LsqTeams {
     float *models;
 };
 
-// o.teams stays null where not even one team fits, where memory is short, or where the runtime cannot tell: the wide form serves.
-void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
+// o.teams stays null where not even one team fits (at_once: where the chip has no room for all nodes at once), where memory is short, or where the runtime cannot tell: the wide form serves.
+void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n, bool at_once) {
     int device = 0, units = 0, each = 0;
     if (hipGetDevice(&device) != hipSuccess || device >= MAX_DEVICES ||
         hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
@@ -406,7 +406,7 @@ void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n) {
     while (rows_each < o.batch && 2 * rows_each * slices <= REDUCE_WORDS * TEAM_THREADS) rows_each *= 2;
     const uint32_t reducers = (o.batch + rows_each - 1) / rows_each;
     const uint64_t most = std::min<uint64_t>((uint64_t)units * std::min(each, TEAM_GROUPS_PER_UNIT) / (slices + reducers), n);
-    if (most == 0) return;
+    if (most == 0 || (at_once && most < n)) return;
     LsqTeams t{};
     t.device = device; t.most = (uint32_t)most; t.slices = (uint32_t)slices; t.reducers = reducers; t.rows_each = rows_each;
     const uint64_t head_bytes = sizeof(LsqTeamHead) * most, words = most * 3 * slices * LSQ_MAX_BATCH, totals = most * 3 * COPIES * LSQ_MAX_BATCH;

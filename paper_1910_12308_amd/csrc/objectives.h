@@ -62,7 +62,7 @@ struct SeqDesc;
 // Allocates the exchange buffers of the split form when ceil(d / 512) * n workgroups are few enough to be
 // resident together (they wait for one another inside the kernel), and with merge_runs also those of the form that takes
 // a run of Algorithm 1 in one launch (lsq_run_fits).
-hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, bool merge_runs);
+hipError_t alloc_lsq(LsqObjective &o, uint64_t d, uint32_t n, uint32_t H, bool merge_runs);
 hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const LocalSlots &slots,
                             DeviceCounters *counters, uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed,
                             uint32_t event, hipStream_t st);
@@ -72,7 +72,7 @@ hipError_t launch_local_lsq(const float *base, float *W, LsqObjective &o, const 
 hipError_t launch_lsq_interact(const GossipArgs &g, uint32_t bits, const SeqDesc *descs_dev, const SeqDesc &one, uint32_t count,
                                LsqObjective &o, float lr, hipStream_t st);
 void free_lsq(LsqObjective &o);
-void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n);
+void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n, bool at_once);
 void free_lsq_teams(LsqObjective &o);
 hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, const LocalSlots &slots, DeviceCounters *counters,
                             uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st);

@@ -473,7 +473,7 @@ swarm_status swarm_set_objective_lsq(swarm_t h, const float *A_dev, const float 
     h->lsq = LsqObjective{};
     h->lsq.A = A_dev; h->lsq.b = b_dev; h->lsq.m_rows = m_rows; h->lsq.batch = batch;
     const bool merge_runs = lsq_run_fits(h->cfg.d, h->cfg.n, batch) && interactions_side_by_side(h) <= LSQ_RUN_WIDTH;
-    const hipError_t e = alloc_lsq(h->lsq, h->cfg.d, h->cfg.n, merge_runs);
+    const hipError_t e = alloc_lsq(h->lsq, h->cfg.d, h->cfg.n, h->cfg.H, merge_runs);
     if (e != hipSuccess) return fail(h, e == hipErrorOutOfMemory ? SWARM_ENOMEM : SWARM_EDEVICE,
                                      std::string("least-squares exchange buffers: ") + hipGetErrorString(e));
     h->kind = OBJ_LSQ;

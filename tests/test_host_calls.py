@@ -107,6 +107,19 @@ def test_workgroups_of_teams_run_at_once(host_calls, counted, grid):
     assert [ln for ln in out if ln.startswith("launch")] == [f"launch lsq_team_kernel<4, 2, true> grid {grid} 1 block 256 shared 0"]
 
 
+# Few rows in all, and a swarm whose workgroups run at once in the wide form but not with reducing workgroups beside them
+@pytest.mark.parametrize("n,d,batch,H,teams", [
+    (64, 16384, 8, 1, 0), (64, 16384, 4, 3, 0), (64, 16384, 8, 2, 32), (64, 16384, 12, 1, 32), (60, 16384, 4, 1, 60), (65, 16384, 4, 1, 33),
+    (124, 8192, 4, 1, 0), (32, 32768, 8, 1, 0), (31, 33000, 4, 1, 16)])
+def test_teams_of_few_rows_take_all_nodes_at_once(host_calls, n, d, batch, H, teams):
+    out = [ln for ln in host_calls("steps", n, d, 8, H, batch, "ring", GROUPS_PER_UNIT=4 if batch <= 8 else 6) if ln.startswith("launch")]
+    if teams:
+        groups = -(-d // (1024 if batch <= 8 else 512)) + 1
+        assert len(out) == 1 and out[0].startswith("launch lsq_team_kernel") and f" grid {teams * groups} " in out[0]
+    else:
+        assert out == [f"launch lsq_wide_kernel<256, false> grid {-(-d // 1024)} {n} block 256 shared 0"] * (H + 1)
+
+
 def test_teams_of_several_swarms_take_turns(host_calls):
     """One swarm alone is not held up; when a second joins, what the first has launched is waited for; from then on a launch waits
     for the one before, whoever made that."""
