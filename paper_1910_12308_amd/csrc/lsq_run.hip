@@ -132,7 +132,46 @@ __global__ __launch_bounds__(RUN_WAVES * 64, 1) void lsq_run_kernel(const LsqRun
     if (threadIdx.x < TEAMS) arrived[threadIdx.x][0] = arrived[threadIdx.x][1] = stepped[threadIdx.x] = 0;
     if (threadIdx.x == 0) finished = bail = 0;
     const bool single = !ra.descs;                // a single interaction touches two nodes
-    for (uint32_t u = wave; u < (single ? 2u : n); u += RUN_WAVES) {
+    const uint32_t team = wave / CREW, mate = wave % CREW;
+    uint64_t row_at = 0;                          // rows of A and their right-hand sides, as drawn
+    float rhs_at = 0.f;
+    // A wave's rows are every second of the batch's: row mate + 2 i, of the steps q + lane / R
+    auto draw = [&](const RunDesc &rd, uint32_t q) {
+        const uint32_t i = lane % R, word = mate + 2u * (i & 1u), node = rd.nodes & 0xFFFFu;
+        const Words4 r = stream(here(seed), TAG_BATCH, q + lane / R, node, rd.event, i >> 1);
+        const uint64_t row = (uint64_t)node * ra.m_rows + scaled_index(word == 0 ? r.w0 : word == 1 ? r.w1 : word == 2 ? r.w2 : r.w3, ra.m_rows);
+        row_at = (uint64_t)ra.A + 4u * row * d;
+        rhs_at = ra.b[row];
+    };
+    // the lane's columns of the step's rows (past the batch of rows that no sum takes)
+    auto request = [&](uint32_t q, f2v (&rows)[R]) {
+        const uint32_t from = R * (q % EACH);
+        uint32_t offset = 4u * at_col;
+        asm("" : "+v"(offset));                   // a 32-bit offset to a scalar base, not a 64-bit one made ahead of the loop
+        constexpr int B = 4;                      // addresses side by side: a scalar that a lane was read into may address a load five instructions later
+#pragma unroll
+        for (int i = 0; i < R; i += B) {
+            uint64_t at[B];
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)row_at, from + i + j);
+                const uint32_t high = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(row_at >> 32), from + i + j);
+                at[j] = (uint64_t)high << 32 | low;
+            }
+            asm volatile("" : "+s"(at[0]), "+s"(at[1]), "+s"(at[2]), "+s"(at[3]));
+#pragma unroll
+            for (int j = 0; j < B; ++j) rows[i + j] = *(SWARM_GLOBAL const f2v *)at_bytes((SWARM_GLOBAL const float *)at[j], offset);
+        }
+    };
+    f2v rows[R] = {}, rows_ahead[R] = {};         // of this step and the next
+    // Its rows come with the models, which other waves fetch, not after them (us of a call among others: 8 nodes x 1024, batch 16,
+    // H = 1 5.8 -> 5.4, 32 x 512, batch 16, H = 2 7.1 -> 6.4); of a run the first wait for its descriptors.
+    if (single && team == 0) {
+        draw(ra.one, 0);
+        request(0, rows);
+        if (((ra.one.flags >> 8) & 0xFFu) > 1) request(1, rows_ahead);
+    }
+    for (uint32_t u = (wave + RUN_WAVES - CREW) % RUN_WAVES; u < (single ? 2u : n); u += RUN_WAVES) {
         const uint32_t node = single ? (u ? ra.one.nodes >> 16 : ra.one.nodes & 0xFFFFu) : u;
         const f2v x = *(const f2v *)(a.X + (uint64_t)node * d + at_col), h = *(const f2v *)(a.Xhat + (uint64_t)node * d + at_col);
         X[node * 64u + lane] = in ? x : zero;
@@ -141,7 +180,7 @@ __global__ __launch_bounds__(RUN_WAVES * 64, 1) void lsq_run_kernel(const LsqRun
     __syncthreads();
 
     if (wave < TEAMS * CREW) {
-        const uint32_t team = wave / CREW, mate = wave % CREW, own = ra.batch / CREW;      // the batch is a multiple of 4
+        const uint32_t own = ra.batch / CREW;     // the batch is a multiple of 4
         const uint32_t slots = slots_of(groups, NB);
         const auto part = __builtin_amdgcn_make_buffer_rsrc((void *)ra.part, 0, (int)(TEAMS * CREW * 2 * R * 8u * slots), 0x00020000);
         // Cycles from a wave's words to its first request.  us for 200 interactions (89 in the last column) at 0 / 400 / 800 / 1200 /
@@ -155,49 +194,21 @@ __global__ __launch_bounds__(RUN_WAVES * 64, 1) void lsq_run_kernel(const LsqRun
             const u4 v = ((SWARM_GLOBAL const u4 *)ra.descs)[min(k, ra.count - 1)];
             after = RunDesc{v.x, v.y, v.z, v.w};
         };
-        uint64_t row_at = 0;                      // rows of A and their right-hand sides, as drawn
-        float rhs_at = 0.f;
-        // A wave's rows are every second of the batch's: row mate + 2 i, of the steps q + lane / R
-        auto draw = [&](const RunDesc &rd, uint32_t q) {
-            const uint32_t i = lane % R, word = mate + 2u * (i & 1u), node = rd.nodes & 0xFFFFu;
-            const Words4 r = stream(here(seed), TAG_BATCH, q + lane / R, node, rd.event, i >> 1);
-            const uint64_t row = (uint64_t)node * ra.m_rows + scaled_index(word == 0 ? r.w0 : word == 1 ? r.w1 : word == 2 ? r.w2 : r.w3, ra.m_rows);
-            row_at = (uint64_t)ra.A + 4u * row * d;
-            rhs_at = ra.b[row];
-        };
-        // the lane's columns of the step's rows (past the batch of rows that no sum takes)
-        auto request = [&](uint32_t q, f2v (&rows)[R]) {
-            const uint32_t from = R * (q % EACH);
-            uint32_t offset = 4u * at_col;
-            asm("" : "+v"(offset));               // a 32-bit offset to a scalar base, not a 64-bit one made ahead of the loop
-            constexpr int B = 4;                  // addresses side by side: a scalar that a lane was read into may address a load five instructions later
-#pragma unroll
-            for (int i = 0; i < R; i += B) {
-                uint64_t at[B];
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
-                    const uint32_t low = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)row_at, from + i + j);
-                    const uint32_t high = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(row_at >> 32), from + i + j);
-                    at[j] = (uint64_t)high << 32 | low;
-                }
-                asm volatile("" : "+s"(at[0]), "+s"(at[1]), "+s"(at[2]), "+s"(at[3]));
-#pragma unroll
-                for (int j = 0; j < B; ++j) rows[i + j] = *(SWARM_GLOBAL const f2v *)at_bytes((SWARM_GLOBAL const float *)at[j], offset);
-            }
-        };
-        f2v rows[R] = {}, rows_ahead[R] = {};     // of this step and the next
         uint32_t turn = 0;                        // steps this team has taken: numbers the exchanged words
-        if (ra.descs) fetch_after(team);
-        for (uint32_t k = team, through = 0; k < ra.count; k += TEAMS, ++through) {
-            RunDesc rd = ra.one;
-            if (ra.descs) {
-                rd = RunDesc{first_lane(after.nodes), first_lane(after.event), first_lane(after.flags), first_lane(after.turn)};
-                fetch_after(k + TEAMS);
-            }
-            const uint32_t node = rd.nodes & 0xFFFFu, H = (rd.flags >> 8) & 0xFFu;
+        RunDesc rd = ra.one;
+        auto begin = [&](uint32_t k) {            // interaction k of a run: its rows on their way
+            rd = RunDesc{first_lane(after.nodes), first_lane(after.event), first_lane(after.flags), first_lane(after.turn)};
+            fetch_after(k + TEAMS);
             draw(rd, 0);
             request(0, rows);
-            if (H > 1) request(1, rows_ahead);
+            if (((rd.flags >> 8) & 0xFFu) > 1) request(1, rows_ahead);
+        };
+        if (!single && team < ra.count) {
+            fetch_after(team);
+            begin(team);
+        }
+        for (uint32_t k = team, through = 0; k < ra.count; k += TEAMS, ++through) {
+            const uint32_t node = rd.nodes & 0xFFFFu, H = (rd.flags >> 8) & 0xFFu;
             wait_for(&finished, rd.turn);         // the initiator's snapshot
             if (lost) break;
             __builtin_amdgcn_s_setprio(2);        // ahead of the teams that wait
@@ -297,6 +308,7 @@ __global__ __launch_bounds__(RUN_WAVES * 64, 1) void lsq_run_kernel(const LsqRun
                 if ((rd.flags & RUN_LAST_LED) && in) *(f2v *)(ra.W + (uint64_t)node * d + col) = w;
             }
             __builtin_amdgcn_s_setprio(0);
+            if (k + TEAMS < ra.count) begin(k + TEAMS);
         }
     } else {
         __builtin_amdgcn_s_setprio(3);            // everyone waits for this wave
