@@ -11,7 +11,7 @@
 //   host_calls mlp_room n in hid out batch H nodes room    as mlp, with `room` bytes of device memory left for the arithmetic; and
 //                                                          device memory with the objective, the arithmetic, and back in float32
 // In the environment, for the least-squares objective: GROUPS_PER_UNIT, workgroups that fit one of 256 compute units (else the
-// runtime cannot tell), and ROOM, bytes of device memory left for it.
+// runtime cannot tell), ROOM, bytes of device memory left for it, and INPLACE, where the steps update the models themselves.
 // graph: complete, ring (two neighbours), path, star, or hubsK (nodes 0..K-1 joined to all others).
 #include <cxxabi.h>
 #include <cstdio>
@@ -178,6 +178,7 @@ int main(int argc, char **argv) {
     c.eps = 0.5f;
     c.lr = 0.1f;
     c.seed = 1;
+    c.apply_mode = setting("INPLACE") ? SWARM_APPLY_INPLACE : SWARM_APPLY_DEFERRED;
     swarm_t h = nullptr;
     const float *data = reinterpret_cast<const float *>(64);        // objective data: the host never reads them
     if (swarm_init(&c, nullptr, nullptr, &h) != SWARM_OK) { std::printf("init: %s\n", swarm_last_error(nullptr)); return 1; }
@@ -186,7 +187,7 @@ int main(int argc, char **argv) {
     if (rc != SWARM_OK) { std::printf("objective: %s\n", swarm_last_error(h)); return 1; }
     memory = ~(size_t)0;
     float *snapshots = nullptr;
-    swarm_models_ptr(h, SWARM_MODELS_SNAP, &snapshots);              // created ahead of the log
+    if (c.apply_mode == SWARM_APPLY_DEFERRED) swarm_models_ptr(h, SWARM_MODELS_SNAP, &snapshots);      // created ahead of the log
     logging = true;
     if (call == "run") {
         uint32_t reported = 0;

@@ -10,10 +10,10 @@ from helpers import ALGORITHM1_RUNS, TOL_GEMM, assert_close, make_both
 pytestmark = pytest.mark.gpu
 
 
-def lsq_swarm(gpu, n, d, m, batch, H, geometric, seed):
+def lsq_swarm(gpu, n, d, m, batch, H, geometric, seed, inplace=False):
     A, b, _ = wl.least_squares_data(n, d, m, seed)
     edges = wl.complete_graph(n) if n < 16 else wl.random_regular_graph(n, 4, 0)
-    g, c = make_both(gpu, n, d, edges, 8, 2.0 ** -6, H, 0.05, 0, seed=seed, geometric=geometric)
+    g, c = make_both(gpu, n, d, edges, 8, 2.0 ** -6, H, 0.05, 0, seed=seed, geometric=geometric, inplace=inplace)
     c.objective = LeastSquares(A, b, batch)
     g.set_objective_lsq(torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(), m, batch)
     gen = np.random.Generator(np.random.PCG64(seed))
@@ -22,9 +22,9 @@ def lsq_swarm(gpu, n, d, m, batch, H, geometric, seed):
     return g, c
 
 
-# n x ceil(d / 512) > 256: several workgroups share a node (blocks of 1024 columns, one or more per slice, ragged or a whole
-# number) or one takes a node alone: from 256 nodes on, from 128 up to 16384 columns, from 65 up to 2048 and from 3080 to
-# 4096 columns (256, 512 or 1024 threads, or a wave per row)
+# n x ceil(d / 512) > 256: one workgroup takes a node alone, from 256 nodes on, from 128 up to 16384 columns, from 65 up to 2048 and
+# from 3080 to 4096 columns (256, 512 or 1024 threads, or a wave per row), or teams of workgroups take one node after the other: all
+# others, and of these 64 rows from 2048 columns on, 32 from 4096 and 16 from 16384
 @pytest.mark.parametrize("n,d,m,batch,H,geometric", [
     (129, 1024, 8, 4, 2, False), (129, 1032, 8, 20, 3, False), (40, 4096, 40, 64, 1, False), (9, 8 * 2051, 33, 16, 2, True),
     (2, 8 * 33001, 17, 12, 2, False), (255, 8 * 1300, 6, 32, 2, False),
@@ -44,6 +44,35 @@ def test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric):
     g.write_models(gpu.COMM, c.X)                          # clears the pending marks, same round: same draws
     g.local_steps()
     assert np.array_equal(g.read_models(gpu.LIVE)[nodes], some)        # the same sums whatever the launch carries
+
+
+# The wide form with several workgroups per node (blocks of 1024 columns, one or more per slice, ragged or a whole number) and a launch
+# per step: where not one team fits the chip, where teams would need a second round for a few rows, and where the steps update the
+# models themselves; so also the forms of one workgroup per node that teams take otherwise.  One workgroup beyond 16384 columns
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", [
+    (2, 8 * 41001, 5, 64, 2, False), (2, 8 * 131080, 4, 4, 3, True), (64, 16384, 4, 8, 1, False), (70, 14000, 4, 4, 3, False),
+    (260, 16392, 4, 12, 2, False)])
+def test_wide_least_squares_steps_beside_teams(gpu, n, d, m, batch, H, geometric):
+    test_wide_least_squares_steps(gpu, n, d, m, batch, H, geometric)
+
+
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", [
+    (9, 8 * 2051, 33, 16, 2, True), (64, 8200, 5, 64, 3, False), (2, 8 * 33001, 17, 12, 2, False), (255, 8 * 1300, 6, 32, 2, False),
+    (300, 4096, 5, 64, 2, False), (80, 4096, 5, 60, 2, True), (260, 16392, 5, 16, 2, False)])
+def test_least_squares_steps_that_update_the_models_themselves(gpu, n, d, m, batch, H, geometric):
+    g, c = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n, inplace=True)
+    nodes = sorted({n - 1, 0, n // 2}, reverse=True)
+    start = c.X.copy()
+    for node in nodes:
+        c.local_steps([node])
+    g.local_steps(nodes)
+    some = g.read_models(gpu.COMM)
+    assert_close(some[nodes], c.X[nodes], TOL_GEMM, "steps of a few nodes")
+    others = np.setdiff1d(np.arange(n), nodes)
+    assert np.array_equal(some[others], start[others])
+    g.write_models(gpu.COMM, start)
+    g.local_steps()
+    assert np.array_equal(g.read_models(gpu.COMM)[nodes], some[nodes])         # the same sums whatever the launch carries
 
 
 # n x ceil(d / 512) <= 256: a workgroup per slice of 512 columns.  One, four or sixteen rows per wave and one, two or more requests
@@ -68,8 +97,9 @@ def test_least_squares_steps_by_teams(gpu, n, d, m, batch, H, geometric):
 
 
 # Workgroups that do not wait: one takes what is left of a team's nodes by itself, the sums are the same bits, and the next launch
-# starts from the numbers this one has left
-@pytest.mark.parametrize("n,d,m,batch,H,geometric", [(34, 8200, 5, 64, 3, False), (40, 8200, 6, 20, 2, True), (33, 4104, 5, 12, 2, False)])
+# starts from the numbers this one has left.  One, two and sixteen workgroups that add rows
+@pytest.mark.parametrize("n,d,m,batch,H,geometric", [
+    (34, 8200, 5, 64, 3, False), (40, 8200, 6, 20, 2, True), (33, 4104, 5, 12, 2, False), (2, 8 * 9001, 6, 64, 3, False)])
 def test_least_squares_steps_by_teams_whose_workgroups_do_not_wait(gpu, n, d, m, batch, H, geometric):
     g, _ = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)
     h, _ = lsq_swarm(gpu, n, d, m, batch, H, geometric, seed=n)

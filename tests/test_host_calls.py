@@ -33,8 +33,8 @@ def kernels(lines):
     return [re.match(r"launch (\w+)", ln).group(1) for ln in lines if ln.startswith("launch")]
 
 
-# Least squares, runs of Algorithm 1: one launch on graphs where at most seven interactions run side by side (the kernel has
-# room for four), a launch per level otherwise and beyond 64 nodes, a batch of 32, 2048 words and 64 groups of 128 columns
+# Least squares, runs of Algorithm 1: one launch on graphs where at most seven interactions run side by side, a launch per level
+# otherwise and beyond 64 nodes, a batch of 32, 2048 words and 64 groups of 128 columns
 @pytest.mark.parametrize("n,d,batch,graph,merged", [
     (8, 4096, 32, "complete", True), (16, 8192, 32, "complete", True), (32, 4096, 32, "complete", True),
     (48, 2048, 32, "complete", False), (64, 2048, 16, "complete", False), (64, 512, 32, "ring", False),
@@ -72,8 +72,9 @@ def test_diagonal_runs(host_calls, n, d, H, graph, count, merged):
     assert levels > 1 and run[-1] == "status 0"
 
 
-# Least-squares local steps of swarms too wide for the exchanging form: several workgroups per node and a launch more than
-# steps, or one workgroup per node and one launch
+# Least-squares local steps of swarms too wide for the exchanging form, in the wide form: several workgroups per node and a launch
+# more than steps, or one workgroup per node and one launch.  All of them take it where the runtime cannot tell how many workgroups
+# of a team fit the chip, and where the steps update the models themselves; else the next test says which are taken by teams.
 @pytest.mark.parametrize("n,d,batch,kernel,threads,grid", [
     (64, 4104, 32, "lsq_wide_kernel<256, false>", 256, "5 64"), (65, 2048, 16, "lsq_wide_kernel<512, true>", 512, "1 65"),
     (65, 2056, 16, "lsq_wide_kernel<256, false>", 256, "3 65"), (100, 3080, 64, "lsq_wide_kernel<512, true>", 512, "1 100"),
@@ -87,10 +88,34 @@ def test_diagonal_runs(host_calls, n, d, H, graph, count, merged):
     (256, 8192, 16, "lsq_wide_kernel<512, true>", 512, "1 256")])
 def test_wide_least_squares_steps(host_calls, n, d, batch, kernel, threads, grid):
     H = 3
-    out = host_calls("steps", n, d, 8, H, batch, "ring")
     slices = H + 1 if kernel.endswith("false>") else 1
-    assert [ln for ln in out if ln.startswith("launch")] == [f"launch {kernel} grid {grid} block {threads} shared 0"] * slices
-    assert out[-1] == "status 0"
+    for settings in ({}, dict(GROUPS_PER_UNIT=5, INPLACE=1)):
+        out = host_calls("steps", n, d, 8, H, batch, "ring", **settings)
+        assert [ln for ln in out if ln.startswith("launch")] == [f"launch {kernel} grid {grid} block {threads} shared 0"] * slices
+        assert out[-1] == "status 0"
+
+
+# The same by teams, with five workgroups per compute unit, four at batches up to 8 and six at batches of 12 and 16: teams at
+# once (all nodes, or as many as fit, evenly over the rounds), workgroups of a team that hold columns and that add rows
+@pytest.mark.parametrize("n,d,batch,kernel,teams,columns,adding", [
+    (64, 4104, 32, "8, 2, true", 64, 9, 1), (64, 4104, 28, "8, 2, false", 64, 9, 1), (16, 65544, 64, "16, 1, true", 4, 257, 16),
+    (16, 65544, 60, "16, 1, false", 4, 257, 15), (9, 131072, 32, "8, 2, true", 3, 256, 4), (80, 4096, 64, "16, 1, true", 40, 16, 1),
+    (255, 2048, 64, "16, 1, true", 128, 8, 1), (255, 2040, 64, None, 0, 0, 0), (100, 4096, 32, "8, 2, true", 100, 8, 1),
+    (100, 4088, 32, None, 0, 0, 0), (128, 16384, 16, "4, 2, true", 43, 32, 1), (128, 16376, 16, None, 0, 0, 0),
+    (300, 16384, 20, "8, 2, false", 38, 32, 1), (300, 16384, 12, None, 0, 0, 0), (300, 4096, 64, "16, 1, true", 75, 16, 1),
+    (65, 2056, 16, "4, 2, true", 65, 5, 1), (33, 4104, 12, "4, 2, false", 33, 9, 1), (64, 8200, 8, "2, 4, true", 64, 9, 1),
+    (35, 4104, 4, "2, 4, false", 35, 5, 1), (2, 264008, 64, "16, 1, true", 1, 1032, 16), (2, 330000, 64, None, 0, 0, 0),
+    (8, 66000, 16, "4, 2, true", 8, 129, 2)])
+def test_least_squares_steps_by_teams(host_calls, n, d, batch, kernel, teams, columns, adding):
+    groups = 4 if batch <= 8 else 6 if batch <= 16 else 5
+    out = [ln for ln in host_calls("steps", n, d, 8, 3, batch, "ring", GROUPS_PER_UNIT=groups) if ln.startswith("launch")]
+    if kernel:
+        assert out == [f"launch lsq_team_kernel<{kernel}> grid {teams * (columns + adding)} 1 block 256 shared 0"]
+    else:
+        assert not any("team" in ln for ln in out)
+    # the steps of one node: one team
+    one = [ln for ln in host_calls("interact", n, d, 8, 3, batch, "ring", GROUPS_PER_UNIT=groups) if ln.startswith("launch")]
+    assert kernel is None or one[0] == f"launch lsq_team_kernel<{kernel}> grid {columns + adding} 1 block 256 shared 0"
 
 
 # The wide form's exchange takes 2 x 64 x 5 x 64 floats, that of one team with its model 4104 floats and more
