@@ -20,7 +20,7 @@ enum class TeamWait { GO_ON, END, ALONE, LOST };
 // At the launch's step `done`, for a workgroup that holds columns: it has had the whole totals of every step before, so that these
 // are there for all others too.  (One that adds some of the rows knows of its own totals only: it ends without a claim, and a
 // workgroup that misses its next totals makes one.)  load and swap (compare and exchange, which returns what was there) reach the
-// claim; it is another launch's until one of this launch is made.  So that no step falls between two workgroups, leaving and claiming
+// claim; it is another launch's until one of this launch is made (load may be late: swap says what holds).  So that no step falls between two workgroups, leaving and claiming
 // are one: a workgroup that finds a claim goes on with every step that the claim leaves to all.  It finds the totals at its next look;
 // `overdue`, when it has not for long, ends the wait all the same, as an error.
 template <class Load, class Swap>

@@ -41,7 +41,7 @@ void enter_fiber() {
 struct Team {
     uint32_t columns, reducers, steps_each, nodes;        // nodes: that the team takes one after the other in a launch
     std::vector<uint32_t> part[2], total[2];              // numbers of the words, by the parity of the number
-    TeamClaim claim = ~0ull;
+    TeamClaim claim = ~0ull, claim_before = ~0ull;        // and what a load that is late still finds
     std::vector<uint32_t> number;                         // of the next launch's first step, a copy for each workgroup
     uint32_t highest = 0;                                 // number that a word has carried
     std::vector<std::vector<bool>> written;               // [node][column]
@@ -51,13 +51,18 @@ struct Team {
 
     bool tired() { return std::generate_canonical<double, 32>(gen) > patience; }
     TeamWait give_up(uint32_t first, uint32_t done, bool overdue) {
-        return swarm::out_of_patience(first, done, overdue, [&] { yield(); return claim; },
-                                      [&](TeamClaim expected, TeamClaim mine) {
-                                          yield();
-                                          const TeamClaim before = claim;
-                                          if (before == expected) claim = mine;
-                                          return before;
-                                      });
+        return swarm::out_of_patience(first, done, overdue, [&] { return seen(); },
+                                      [&](TeamClaim expected, TeamClaim mine) { return swap(expected, mine); });
+    }
+    TeamClaim seen() {
+        yield();
+        return gen() % 4 ? claim : claim_before;
+    }
+    TeamClaim swap(TeamClaim expected, TeamClaim mine) {
+        yield();
+        const TeamClaim before = claim;
+        if (before == expected) { claim_before = claim; claim = mine; }
+        return before;
     }
     // Until all the words carry the number; whoever makes no claim ends when it has waited long enough.
     TeamWait wait(const std::vector<uint32_t> &words, uint32_t first, uint32_t with, bool claims) {
@@ -86,10 +91,6 @@ struct Team {
             }
         }
     }
-    bool claimed(uint32_t first) {
-        yield();
-        return (uint32_t)(claim >> 32) == first;
-    }
     void move_on(uint32_t m, uint32_t first) {
         yield();
         number[m] = swarm::next_number(first, nodes * steps_each);
@@ -97,7 +98,8 @@ struct Team {
     void column(uint32_t c) {
         yield();
         const uint32_t first = number[c], steps = nodes * steps_each;
-        TeamWait then = claimed(first) ? TeamWait::END : TeamWait::GO_ON;
+        const TeamClaim there = seen();
+        TeamWait then = (uint32_t)(there >> 32) == first ? TeamWait::END : TeamWait::GO_ON;
         uint32_t k = 0;
         for (; k < steps && then == TeamWait::GO_ON; ++k) {
             const uint32_t tag = first + k;
@@ -112,15 +114,13 @@ struct Team {
         }
         move_on(c, first);
         if (then == TeamWait::ALONE) alone(k, first + k);
-        if (then == TeamWait::GO_ON && c == 0 && !claimed(first)) {           // the kernel's is one compare and exchange
-            const TeamClaim mine = (TeamClaim)first << 32 | steps;
-            if ((uint32_t)(claim >> 32) != first) claim = mine;
-        }
+        if (then == TeamWait::GO_ON && c == 0) swap(there, (TeamClaim)first << 32 | steps);
     }
     void reducer(uint32_t j) {
         yield();
         const uint32_t first = number[columns + j], steps = nodes * steps_each;
-        TeamWait then = claimed(first) ? TeamWait::END : TeamWait::GO_ON;
+        const TeamClaim there = seen();
+        TeamWait then = (uint32_t)(there >> 32) == first ? TeamWait::END : TeamWait::GO_ON;
         for (uint32_t k = 0; k < steps && then == TeamWait::GO_ON; ++k) {
             const uint32_t tag = first + k;
             then = wait(part[tag & 1u], first, tag, false);
@@ -159,6 +159,7 @@ struct Team {
             left -= running->ended;
             if (wrong && (uint32_t)(claim >> 32) != number[0] && gen() % 16 == 0) claim = (TeamClaim)number[0] << 32 | (1 + gen() % (nodes * steps_each));
         }
+        claim_before = claim;                             // a launch finds what the ones before it have left
         for (const uint32_t v : number) numbered = numbered && v == number[0] && v > highest;
         return true;
     }
