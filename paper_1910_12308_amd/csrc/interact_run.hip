@@ -9,7 +9,7 @@
 // An interaction reads what is not in local memory -- a_i, c_i and, unless the initiator's last interaction was its
 // own, the snapshot -- and writes the snapshot unless the next interaction of the node writes it again.  Where tiles are few
 // (AHEAD), snapshots are held in local memory too, and the noise of the first four steps is drawn ahead of the wait.
-// Bound by vector instructions (408 counted per interaction and 256 coordinates at H = 3) and, with few tiles, by the chain of
+// Bound by vector instructions (405 counted per interaction and 256 coordinates at H = 3) and, with few tiles, by the chain of
 // dependent interactions.  On complete graphs with 8-bit codes, steps that waited for both nodes and steps that wait for the
 // snapshot: 64 nodes x 2^20, H = 3, 256 interactions 784 and 759 us (1636 in 28 launches that moved 34 B per
 // interaction-coordinate at 5.6 TB/s), 31 x 2 000 000, H = 5, 100 interactions 745 and 693; and with few tiles 8 x 8888, H = 3,

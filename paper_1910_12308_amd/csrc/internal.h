@@ -12,7 +12,7 @@ void set_global_error(const char *message);
 struct DeviceCounters {
     unsigned long long decode_failures;
     unsigned int range_clamped;
-    unsigned int barrier_timeouts;   // a workgroup gave up waiting for the others of its node (least-squares split form)
+    unsigned int barrier_timeouts;   // a workgroup gave up waiting for the others of its node, team or run (least squares)
 };
 
 // Multi-resolution registers: tiles read beyond the first plane (to 8 bits, to 16 bits), the coordinates

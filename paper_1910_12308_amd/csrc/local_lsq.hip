@@ -10,8 +10,8 @@
 // simply waits until the word it needs carries the right tag (no counters, no fences, nothing to reset).  In a
 // batch of Algorithm 1 steps the workgroup then runs the interaction on its slice, which is exactly one gossip tile.
 // Of all other swarms, many nodes with few rows take the wide form (lsq_wide_kernel) with one workgroup per node, the rest steps by
-// teams of workgroups (lsq_team.hip) or, where not even one node's workgroups fit the chip or the steps update the models themselves, the wide
-// form with several per node, which exchange their residuals between launches.
+// teams of workgroups (lsq_team.hip) or, where not even one node's workgroups fit the chip, the steps update the models themselves
+// or their rows are few (one_round_only), the wide form with several per node, which exchange their residuals between launches.
 #include <algorithm>
 #include <type_traits>
 
@@ -32,7 +32,7 @@ namespace swarm {
 // steps.  With one slice per node (WHOLE) nothing leaves the workgroup and one launch runs all steps, in blocks of 1024
 // to 4096 columns.
 // Bound by memory: the rows of a step are read twice, once for the residuals and, when these are known, once for the
-// update, and are too many for a workgroup to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
+// update, as they are too many for a workgroup to hold (16 MiB per node at 64 rows of 65536 columns).  16 rows (256 bytes) are in flight
 // per thread.  16 nodes x 65544 columns, batch 64, 2 steps: 190 us = 1.07 GB of rows at 5.6 TB/s, against 1.96 ms for
 // one workgroup of 1024 threads per node, which left 240 of 256 compute units idle.  Measured without effect: groups
 // of nodes whose rows fit the last-level cache (more launches cost more than the hits give), non-temporal loads

@@ -9,8 +9,9 @@
 //   -> dlogits = (softmax - onehot)/batch -> dpre = (dlogits W2) * [hid > 0]
 //   -> W2 -= eta dlogits^T hid, b2 -= eta colsum(dlogits), W1 -= eta dpre^T x, b1 -= eta colsum(dpre).
 // The weight updates ride in the two weight-gradient products, so the gradients never reach memory: up to 128 samples
-// in mlp_float_update_kernel, which streams down the weight matrix and takes the biases along (at 128 samples the hidden bias goes
-// with the epilogue of the backward GEMM, one tile of which holds the whole batch), beyond in the epilogue of mlp_gemm_kernel.  Where the logits' product has few tiles it is cut along the hidden units, and the softmax adds the parts.
+// in mlp_float_update_kernel, which streams down the weight matrix and takes the biases along (at 128 samples the hidden
+// bias goes with the epilogue of the backward GEMM, one tile of which holds the whole batch), beyond in the epilogue of
+// mlp_gemm_kernel.  Where the logits' product has few tiles it is cut along the hidden units, and the softmax adds the parts.
 //
 // Tiling: 4 waves per workgroup, each wave a quarter of the tile (64x64 = 2x2 MFMA blocks of 128x128), or 2 waves of a 32x32 block
 // each; K is consumed in slabs of 16 staged through LDS (double buffered, the next slab, of small tiles the next four, prefetched
@@ -740,7 +741,7 @@ hipError_t launch_local_mlp(const float *base, float *W, const MlpObjective &o, 
         g.C = o.dhid; g.strideC = (uint64_t)Bt * Hd; g.ldc = Hd;
         g.aux = o.hid; g.strideAux = (uint64_t)Bt * Hd; g.aux_by_node = 0; g.ldaux = Hd;
         g.M = Bt; g.N = Hd; g.K = O;
-        if (Bt == STREAMED_SAMPLES && !biases_inside) { g.colsum_src = src + off_b1; g.colsum_dst = W + off_b1; g.strideColsum = d; }
+        if (Bt == STREAMED_SAMPLES) { g.colsum_src = src + off_b1; g.colsum_dst = W + off_b1; g.strideColsum = d; }
         gemm<true, false, EPI_RELU_MASK>(g, count, st);
         g.colsum_src = nullptr; g.colsum_dst = nullptr;
         // W2 <- W2 - eta dlogits^T hid,  W1 <- W1 - eta dpre^T x;  all operands stored [sample][row]

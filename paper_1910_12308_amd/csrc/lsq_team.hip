@@ -2,14 +2,15 @@
 // teams: the workgroups of a team take one node after the other, each on its own columns, and keep a step's rows of A in
 // registers from the residuals to the update, so that these are read once.  Between the two the team's partial residuals are
 // added: a workgroup publishes one word per row of the batch, the team's reducing workgroups add these up, in an order that the
-// number of columns alone decides, and publish the totals.  While a workgroup waits for them the next step's rows are on
-// their way to it, and other teams' workgroups share its compute unit.
+// number of columns alone decides, and publish the totals.  While a workgroup waits for them, other teams' workgroups share its
+// compute unit; the next step's rows are drawn meanwhile and requested after the update, whose registers they take.
 // A word carries the number of the step it belongs to beside the value, so a reader simply waits until the word it needs is there.
-// The numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too), a copy for each workgroup
-// of a team, which it alone reads and moves on: whenever it gets to run, it finds the number of its launch.
-// Workgroups wait for one another, so a launch has no more than fit the chip at once, and such launches of several swarms on one GPU
-// take turns (DeviceTurn).  Where other work keeps some of a team's workgroups from starting, the first of the others that has waited
-// long enough takes the rest of the team's nodes by itself, with the same sums, and the others end.
+// The numbers go on from launch to launch in device memory (a launch in a replayed graph finds fresh ones, too), a copy for each
+// workgroup of a team, which it alone reads and moves on: whenever it gets to run, it finds the number of its launch.
+// Workgroups wait for one another, so a launch has no more than run at once, and such launches of several swarms on one GPU take
+// turns (DeviceTurn).  Where other work keeps some of a team's workgroups from starting all the same, the others' patience ends, 20 ms
+// after they began to wait: one of those that hold columns then takes by itself, with the same sums, the nodes whose steps not
+// all can finish, and the others end when they have finished theirs (lsq_team_end.hpp).  No wait lasts longer than its patience and two seconds.
 #include <algorithm>
 #include <mutex>
 
@@ -68,11 +69,17 @@ __device__ __forceinline__ Word load_word(SWARM_GLOBAL const Word *p) { return _
 // 4 ROWS rows.
 // Bound by the exchange and memory together: a step of one team is its loads and then about 5 us until the totals are back, hidden
 // behind the loads of the other teams on the chip.  Hence as few registers as five workgroups per compute unit take (with four 16 nodes
-// x 65544 columns, batch 64, two steps take 140 us, with two buffers of rows and three workgroups 154), the first rows asked for
-// after the team's number (before, they delay it: 134), totals in copies (one for all: 190).  us for the steps of all nodes, before (rows
-// read twice, a launch per step) and now: 16 x 65544, batch 64, H = 2: 189 and 126 (4.3 TB/s of rows read once); 64 x 131072, 64, 1: 709
-// and 513; 9 x 131072, 64, 4: 432 and 285; 8 x 32768, 64, 2: 46.3 and 28.7; 31 x 16384, 32, 3: 68.5 and 34.7; 100 x 12288, 64, 2: 158 and 82;
-// 64 x 4104, 16, 1: 9.0 and 8.8; 16 x 16384, 16, 1: 8.8 and 7.7.  Error against 64 bits as before (3.6e-8).
+// x 65544 columns, batch 64, two steps take 140 us instead of 126, with two buffers of rows and three workgroups 154), the first rows
+// asked for after the team's number (before, they delay it: 134), totals in copies (one for all: 190).  us for the steps of all nodes
+// with 256 rows each, in the wide form (rows read twice, a launch per step or one workgroup per node) and by teams:
+//   16 x 65544, batch 64, H = 2    188   122    31 x 16384, batch 32, H = 3   65.9   33.5    64 x 8200, batch 8, H = 2      16.9   13.3
+//   64 x 131072, batch 64, H = 1   707   504    64 x 131072, batch 16, H = 1   213    149    16 x 65544, batch 8, H = 2     44.6   25.7
+//   9 x 131072, batch 64, H = 4    426   266    64 x 4104, batch 16, H = 1     8.6    8.0    100 x 40000, batch 4, H = 1    32.6   29.9
+//   8 x 32768, batch 64, H = 2    46.0  26.5    16 x 16384, batch 16, H = 1    8.1    7.4    40 x 12296, batch 4, H = 2     14.2   11.3
+//   100 x 12288, batch 64, H = 2   193   119    33 x 4104, batch 12, H = 2    12.5   10.7    128 x 16392, batch 4, H = 1    17.4   18.1
+//   300 x 16384, batch 64, H = 2   993   457                                                 64 x 131072, batch 4, H = 1    59.4   62.8
+// (4.4 TB/s of rows read once in the first).  One step of four rows in three rounds or more is the one that loses a little.  Error
+// against 64 bits as in the wide form (3.6e-8).
 template <int ROWS, int COLS, bool FULL>
 __global__ __launch_bounds__(TEAM_THREADS, ROWS <= 4 ? 6 : 5) void lsq_team_kernel(const LsqTeamArgs sa) {
     __shared__ f4 gsum[2][TEAM_WAVES][64 * COLS];
@@ -394,7 +401,8 @@ struct LsqTeams {
     float *models;
 };
 
-// o.teams stays null where not even one team fits (at_once: where the chip has no room for all nodes at once), where memory is short, or where the runtime cannot tell: the wide form serves.
+// o.teams stays null where not even one team fits (at_once: where the chip has no room for all nodes at once), where memory is
+// short, or where the runtime cannot tell: the wide form serves.
 void alloc_lsq_teams(LsqObjective &o, uint64_t d, uint32_t n, bool at_once) {
     int device = 0, units = 0, each = 0;
     if (hipGetDevice(&device) != hipSuccess || device >= MAX_DEVICES ||
@@ -453,8 +461,8 @@ hipError_t launch_lsq_teams(const float *base, float *W, const LsqObjective &o, 
                             uint32_t count, uint64_t d, uint32_t H, float lr, uint64_t seed, uint32_t event, hipStream_t st) {
     const LsqTeams &t = *o.teams;
     const uint32_t rounds = (count + t.most - 1) / t.most, teams = (count + rounds - 1) / rounds;
-    const LsqTeamArgs a{base, o.A, o.b, W, slots, t.heads, t.numbers, t.words, t.totals, t.models, counters, d, seed, (uint32_t)std::min(o.patience, MOST_PATIENCE),
-                        count, teams, t.slices, t.reducers, t.rows_each, H, o.m_rows, o.batch, event, lr};
+    const LsqTeamArgs a{base, o.A, o.b, W, slots, t.heads, t.numbers, t.words, t.totals, t.models, counters, d, seed,
+                        (uint32_t)std::min(o.patience, MOST_PATIENCE), count, teams, t.slices, t.reducers, t.rows_each, H, o.m_rows, o.batch, event, lr};
     DeviceTurn &turn = device_turns[t.device];
     std::lock_guard<std::mutex> lock(turn.mutex);
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;

@@ -29,7 +29,7 @@ struct LsqObjective {
     uint64_t wide_rows = 0;
     uint32_t wide_slices = 0;
     bool by_rows = false;           // wide form with a wave per row of the batch instead
-    // teams of workgroups (lsq_team.hip), where the wide form would cut a node's columns and its models and live copies differ
+    // teams of workgroups (lsq_team.hip), where these are the better form; not for steps that update the models themselves
     LsqTeams *teams = nullptr;
     unsigned long long patience = 2000000;        // 100 MHz ticks a workgroup waits for the others of its team: 20 ms
 };

@@ -39,8 +39,8 @@ constexpr uint32_t HOST_MATCH_EDGES = 128;
 // Least-squares runs of Algorithm 1 are merged into one launch (lsq_run_kernel) on graphs where at most so many
 // interactions run side by side, as many as the kernel has teams that take steps.  us per run of 256 interactions, by levels and
 // merged, at 9 to 12 side by side: 48 nodes x 2048, batch 32, H = 2: 516 and 270; 64 x 512: 399 and 242; 64 x 2048, batch 16, H = 5:
-// 631 and 452.  So merging would pay there as well now; when the line was drawn the kernel had room for four (409 and 422, 342
-// and 375, 574 and 689), and the tests of the host's choice hold it.
+// 631 and 452.  So merging pays there as well: the line was drawn when the kernel had room for four (409 and 422, 342 and 375, 574
+// and 689) and has not been drawn again since.
 constexpr double LSQ_RUN_WIDTH = 7.0;
 constexpr uint32_t SEQ_CHUNK = 1u << 15;                              // interactions of Algorithm 1 staged per upload
 constexpr size_t SEQ_ENTRY_BYTES = sizeof(swarm::SeqDesc) + 3 * sizeof(uint32_t);
